@@ -55,6 +55,25 @@ __device__ __forceinline__ T group_sum(T v) {
   return v;
 }
 
+// Sum over a wave with DPP moves (row shifts within rows of 16 lanes, then
+// row broadcasts): the total lands in lane 63, in a fixed order.
+template <int C, int RM>
+__device__ __forceinline__ double dpp64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, C, RM, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, RM, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v += dpp64<0x111, 0xf>(v);   // row_shr:1
+  v += dpp64<0x112, 0xf>(v);   // row_shr:2
+  v += dpp64<0x114, 0xf>(v);   // row_shr:4
+  v += dpp64<0x118, 0xf>(v);   // row_shr:8
+  v += dpp64<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp64<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Deterministic sum over the workgroup (blockDim.x a multiple of 64, at
 // most 1024).  Every thread receives the result.
 template <typename T>
@@ -223,101 +242,101 @@ __device__ __forceinline__ int lattice_col(const RowBox& b, int k, int n1) {
   return (b.lo[0] + kx) + n1 * ((b.lo[1] + ky) + n1 * (b.lo[2] + kz));
 }
 
-// The cells holding lattice index g along one direction (at most two, in
-// ascending order) and the function's local index on each: a vertex index
-// (g a multiple of p) is local 1 (right end) of cell g/p - 1 and local 0 of
-// cell g/p; any other index is local g % p + 1 of cell g/p alone.
-struct CellsOf {
-  int cnt;
-  int cell[2], loc[2];
+// Where the outputs of the cells holding lattice index g along one direction
+// lie in the block outputs (cells are the blocks, in order; cs and ls are the
+// distances of a cell step and of a local-index step along this direction).
+// A vertex index (g a multiple of p) is local 1 (right end) of the cell to its
+// left, slot 0, and local 0 of the cell to its right, slot 1; any other index
+// is local g % p + 1 of its cell, slot 1.  An absent slot repeats the present
+// one's offset, so both can be loaded without a branch.
+struct PullDir {
+  int off0, off1;
+  bool on0, on1;
 };
 
-__device__ __forceinline__ CellsOf cells_of(int g, int n, int p, const FastDiv dp) {
-  CellsOf c;
-  c.cnt = 0;
-  const int e = (int)fdiv((uint32_t)g, dp), rem = g - e * p;
-  if (rem == 0) {
-    if (e >= 1) {
-      c.cell[c.cnt] = e - 1;
-      c.loc[c.cnt] = 1;
-      ++c.cnt;
-    }
-    if (e < n) {
-      c.cell[c.cnt] = e;
-      c.loc[c.cnt] = 0;
-      ++c.cnt;
-    }
-  } else {
-    c.cell[0] = e;
-    c.loc[0] = rem + 1;
-    c.cnt = 1;
-  }
-  return c;
+__device__ __forceinline__ PullDir pull_dir(uint32_t g, const PullLattice& L, int cs, int ls) {
+  const uint32_t e = fdiv(g, L.dp), rem = g - e * (uint32_t)L.p;
+  PullDir d;
+  d.on0 = rem == 0 && e > 0;
+  d.on1 = rem != 0 || e < (uint32_t)L.n;
+  const int left = ((int)e - 1) * cs + ls;
+  const int own = (int)e * cs + (rem == 0 ? 0 : (int)rem + 1) * ls;
+  d.off0 = d.on0 ? left : own;
+  d.off1 = d.on1 ? own : left;
+  return d;
 }
 
-// Node tiles of the lattice pull: 16 x 4 x 4 nodes (3-D) or 32 x 8 (2-D)
-// per 256-thread workgroup, so the cells whose block outputs a workgroup
-// sums are mostly summed by that workgroup alone.  The tile counts along the
-// first two directions are the divisors of L.dtx and L.dty.
-__host__ __device__ __forceinline__ int64_t pull_num_tiles(const PullLattice L) {
-  const int64_t ntz = L.dim == 3 ? (L.n1 + 3) / 4 : 1;
-  return (int64_t)L.dtx.d * L.dty.d * ntz;
-}
-
-// Node of slot `slot` (0 .. 255) of tile `tile` (one unknown per node: the
-// lattice pull serves scalar problems): a tile's nodes are taken row by row
-// (TX consecutive nodes), which keeps the vector accesses of consecutive
-// lanes contiguous.  The tile sizes are powers of two and the tile counts
-// are divided by multiply-shift.  False when the node lies outside the
-// lattice.
-__device__ __forceinline__ bool pull_node(const PullLattice L, int64_t tile, int slot, int* gx,
-                                          int* gy, int* gz) {
-  const uint32_t t = (uint32_t)tile;   // fewer than 2^31 tiles
-  const uint32_t tyz = fdiv(t, L.dtx), bz = fdiv(tyz, L.dty);
-  const int bx = (int)(t - tyz * L.dtx.d), by = (int)(tyz - bz * L.dty.d);
-  const int sx = L.dim == 3 ? 4 : 5, sy = L.dim == 3 ? 2 : 3;   // log2 TX, log2 TY
-  const int row = slot >> sx;
-  *gx = (bx << sx) + (slot & ((1 << sx) - 1));
-  *gy = (by << sy) + (row & ((1 << sy) - 1));
-  *gz = L.dim == 3 ? (int)(bz << 2) + (row >> sy) : (int)bz + (row >> sy);
-  return *gx < L.n1 && *gy < L.n1 && (L.dim < 3 ? *gz == 0 : *gz < L.n1);
-}
-
-// Sum of the block outputs y_B holding node (gx, gy, gz), in ascending
-// block (= cell) order, as the node-to-block map lists them.  All (at most
-// eight) loads are issued before the ordered sum.
-__device__ __forceinline__ double pull_lattice_sum(const double* __restrict__ y,
-                                                   const PullLattice L, int m, int gx, int gy,
-                                                   int gz) {
-  const CellsOf cx = cells_of(gx, L.n, L.p, L.dp);
-  CellsOf cy{1, {0, 0}, {0, 0}}, cz{1, {0, 0}, {0, 0}};
-  if (L.dim >= 2) cy = cells_of(gy, L.n, L.p, L.dp);
-  if (L.dim >= 3) cz = cells_of(gz, L.n, L.p, L.dp);
+// Block outputs holding component c of node `node`, in ascending block
+// (= cell) order, zero where a cell is absent: at most eight loads, all
+// independent.  Consecutive lanes take consecutive unknowns, so whether a
+// second cell exists along the second and third directions is mostly the same
+// for a whole wave: a wave without one skips its loads.
+__device__ __forceinline__ void pull_lattice_load(const double* __restrict__ y,
+                                                  const PullLattice& L, int m, int bd,
+                                                  uint32_t node, int c, double v[8]) {
+  const uint32_t n1 = (uint32_t)L.n1;
+  const uint32_t row = fdiv(node, L.dn1), gx = node - row * n1;
   const int p1 = L.p + 1;
-  double v[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int ix = k & 1, iy = (k >> 1) & 1, iz = k >> 2;
-    const bool on = ix < cx.cnt && iy < cy.cnt && iz < cz.cnt;
-    v[k] = 0.0;
-    if (on) {
-      const int64_t e =
-          cx.cell[ix] + (int64_t)L.n * (cy.cell[iy] + (int64_t)L.n * cz.cell[iz]);
-      const int loc = cx.loc[ix] + p1 * (cy.loc[iy] + p1 * cz.loc[iz]);
-      v[k] = y[e * m + loc];
-    }
+  const PullDir dx = pull_dir(gx, L, m, bd);
+  PullDir dy{0, 0, false, true}, dz{0, 0, false, true};
+  if (L.dim == 3) {
+    const uint32_t gz = fdiv(row, L.dn1), gy = row - gz * n1;
+    dy = pull_dir(gy, L, m * L.n, bd * p1);
+    dz = pull_dir(gz, L, m * L.n * L.n, bd * p1 * p1);
+  } else {
+    dy = pull_dir(row, L, m * L.n, bd * p1);
   }
+  const double* yc = y + c;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = 0.0;
+  auto pair = [&](int o, bool on, double& v0, double& v1) {
+    const double t0 = yc[dx.off0 + o], t1 = yc[dx.off1 + o];
+    v0 = on && dx.on0 ? t0 : 0.0;
+    v1 = on && dx.on1 ? t1 : 0.0;
+  };
+  const bool two_y = __any(dy.on0 && dy.on1), two_z = __any(dz.on0 && dz.on1);
+  // a single slot: whichever of the two is present
+  pair(dy.off0 + dz.off0, (!two_y || dy.on0) && (!two_z || dz.on0), v[0], v[1]);
+  if (two_y) pair(dy.off1 + dz.off0, dy.on1 && (!two_z || dz.on0), v[2], v[3]);
+  if (two_z) {
+    pair(dy.off0 + dz.off1, (!two_y || dy.on0) && dz.on1, v[4], v[5]);
+    if (two_y) pair(dy.off1 + dz.off1, dy.on1 && dz.on1, v[6], v[7]);
+  }
+}
+
+// The ordered sum of pull_lattice_load's terms (adding an absent term's zero
+// changes no bit: the sum starts from +0 and never becomes -0).
+__device__ __forceinline__ double pull_sum8(const double v[8]) {
   double s = 0.0;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int ix = k & 1, iy = (k >> 1) & 1, iz = k >> 2;
-    if (ix < cx.cnt && iy < cy.cnt && iz < cz.cnt) s += v[k];
+  for (int k = 0; k < 8; ++k) s += v[k];
+  return s;
+}
+
+// Sum of the block outputs listed for a node in the node-to-block map (block
+// order): four entries per round, their loads in flight together.
+__device__ __forceinline__ double pull_mapped_sum(const double* __restrict__ y,
+                                                  const int32_t* __restrict__ inv_ptr,
+                                                  const int32_t* __restrict__ inv_idx,
+                                                  uint32_t node, int c) {
+  const int32_t lo = inv_ptr[node], hi = inv_ptr[node + 1];
+  double s = 0.0;
+  for (int32_t e = lo; e < hi; e += 4) {
+    int32_t idx[4];
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) idx[u] = inv_idx[min(e + u, hi - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = y[(int64_t)idx[u] + c];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e + u < hi) s += v[u];
   }
   return s;
 }
 
 // Node of local function loc of cell e on a lattice whose cells are the
-// blocks, in order (the inverse of cells_of: local index 0 is a cell's
+// blocks, in order (the inverse of pull_dir: local index 0 is a cell's
 // left vertex, 1 its right vertex, 2 .. p its interior indices, tensor
 // order with the first direction fastest).
 __device__ __forceinline__ int64_t lattice_cell_node(const PullLattice L, int e, int loc) {

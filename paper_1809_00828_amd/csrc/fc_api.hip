@@ -581,16 +581,14 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   FC_HIP(hipMemcpyAsync(drop.data(), d_drop, drop.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   FC_HIP(hipStreamSynchronize(s));
   pc->n_fallback = (int64_t)cnt;
-  // scalar lattice problem with every cell a block, in cell order (checked
-  // row by row on the device): the block products find a row's unknown and
-  // the pull a node's blocks from lattice indices (FC_PULL_LATTICE=0 keeps
-  // the node lists and the node-to-block map).  With three components per
-  // node the mapped pull is faster (46 against 57 us at 32^3 cells, p = 3),
-  // so it stays there.
+  // lattice problem with every cell a block, in cell order (checked row by
+  // row on the device): the pull finds a node's blocks from its lattice
+  // indices, and the block products of scalar problems a row's unknown
+  // (FC_PULL_LATTICE=0 keeps the node lists and the node-to-block map).
   {
     const char* env = std::getenv("FC_PULL_LATTICE");
     const bool allowed = !(env && std::atoi(env) == 0);
-    if (allowed && !patch && pb->bdim == 1 && pb->dim >= 2 && pb->dim <= 3 && pb->n > 0 &&
+    if (allowed && !patch && pb->dim >= 2 && pb->dim <= 3 && pb->n > 0 &&
         pb->p > 0 && nb == pb->n_el &&
         nb == std::pow((double)pb->n, pb->dim) && pb->nn == (int)std::pow(pb->p + 1.0, pb->dim)) {
       const PullLattice L = make_pull_lattice(pb->dim, pb->n, pb->p);

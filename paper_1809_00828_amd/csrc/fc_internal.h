@@ -88,9 +88,7 @@ inline LatticeInfo make_lattice_info(int32_t dim, int32_t n1, int32_t p) {
 // node-to-block map.
 struct PullLattice {
   int32_t dim = 0, n = 0, p = 0, n1 = 0;
-  // division by n, p and p + 1, and by the node-tile counts along the
-  // first two directions (16 x 4 x 4 node tiles in 3-D, 32 x 8 in 2-D)
-  FastDiv dn, dp, dp1, dtx, dty;
+  FastDiv dn, dp, dp1, dn1;   // division by n, p, p + 1 and n1
 };
 
 inline PullLattice make_pull_lattice(int32_t dim, int32_t n, int32_t p) {
@@ -102,9 +100,7 @@ inline PullLattice make_pull_lattice(int32_t dim, int32_t n, int32_t p) {
   l.dn = make_fastdiv((uint32_t)n);
   l.dp = make_fastdiv((uint32_t)p);
   l.dp1 = make_fastdiv((uint32_t)(p + 1));
-  const int tx = dim == 3 ? 16 : 32, ty = dim == 3 ? 4 : 8;
-  l.dtx = make_fastdiv((uint32_t)((l.n1 + tx - 1) / tx));
-  l.dty = make_fastdiv((uint32_t)((l.n1 + ty - 1) / ty));
+  l.dn1 = make_fastdiv((uint32_t)l.n1);
   return l;
 }
 

@@ -86,6 +86,7 @@ void solver_ws_destroy(SolverWs* w) {
 
 // -------------------------------------------------------------- kernels
 constexpr int kVecThreads = 256;
+constexpr int kPullElems = 2;   // unknowns per thread and round of the pull
 
 // Three dots of the starting vectors: (r,z), (z,z), (r,r); the last
 // workgroup initialises the scalars.
@@ -176,91 +177,78 @@ __global__ __launch_bounds__(256) void k_cg_pq(const double* __restrict__ p,
 }
 
 // Pull of the Schwarz apply fused with x += alpha p, r -= alpha q and the
-// reductions of the new r and z (one partial triple per workgroup; the
-// grid loops over the unknowns).  kFlex adds a fourth partial, (z, q),
-// for the flexible beta.
-template <bool kFlex>
+// reductions of the new r and z (one partial triple per workgroup).  kFlex
+// adds a fourth partial, (z, q), for the flexible beta.  kLat: every cell is a
+// block, and a node's blocks follow from its lattice indices; else the
+// node-to-block map lists them.  Both sum in block order, so z is the same bit
+// for bit.  A workgroup takes `rounds` runs of 512 consecutive unknowns, two
+// per thread, whose loads are all issued before the first is used; runs are
+// dealt so that one XCD walks a contiguous range and the outputs of cells that
+// neighbouring runs share stay in its L2.  fb may be null (no unknown needs
+// the diagonal scaling).
+// Bound by load latency below about 1M unknowns and by HBM above.  Measured
+// against node tiles whose per-direction cell lists were indexed arrays (the
+// compiler kept them in LDS, and the loads waited on it): 18.8 -> 4.4 us at
+// 110^2 cells, p = 3; 7.2 -> 3.7 us at 16^2, p = 2; 66 -> 53 us (0.21 GB, 4.0
+// TB/s) at 64^3, p = 2; against the map with three components per node 11.3 ->
+// 7.5 us at 16^3, p = 3.
+template <bool kFlex, bool kLat>
 __global__ __launch_bounds__(256) void k_cg_pull(
     const double* __restrict__ y, const int32_t* __restrict__ inv_ptr,
-    const int32_t* __restrict__ inv_idx, const double* __restrict__ fb, int bd, int64_t n,
-    double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-    const double* __restrict__ q, double* __restrict__ z, double* __restrict__ partial,
-    const CgScalars* __restrict__ sc) {
-  __shared__ double lds[16];
-  if (sc->done) return;
-  const double alpha = sc->alpha;
-  double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t node = i / bd;
-    const int cc = (int)(i - node * bd);
-    double s = 0.0;
-    for (int32_t e = inv_ptr[node]; e < inv_ptr[node + 1]; ++e) s += y[(int64_t)inv_idx[e] + cc];
-    const double qi = q[i];
-    const double ri = fma(-alpha, qi, r[i]);
-    x[i] = fma(alpha, p[i], x[i]);
-    r[i] = ri;
-    const double zi = fma(fb[i], ri, s);
-    z[i] = zi;
-    a = fma(ri, zi, a);
-    b = fma(zi, zi, b);
-    c = fma(ri, ri, c);
-    if (kFlex) d = fma(zi, qi, d);
-  }
-  a = block_sum(a, lds);
-  b = block_sum(b, lds);
-  c = block_sum(c, lds);
-  if (kFlex) d = block_sum(d, lds);
-  if (threadIdx.x == 0) {
-    partial[blockIdx.x] = a;
-    partial[gridDim.x + blockIdx.x] = b;
-    partial[2 * gridDim.x + blockIdx.x] = c;
-    if (kFlex) partial[3 * gridDim.x + blockIdx.x] = d;
-  }
-}
-
-// The same pull where every cell is a block (scalar problems): the
-// workgroups walk node tiles of the lattice and find each node's blocks
-// from its lattice indices (no node-to-block map is read), summing them in
-// the same ascending order, so z is bitwise the mapped pull's.  fb may be
-// null (no unknown needs the diagonal scaling).  The partial sums of a
-// workgroup are reduced together, with one barrier.
-template <bool kFlex>
-__global__ __launch_bounds__(256) void k_cg_pull_lat(
-    const double* __restrict__ y, const PullLattice L, int m, const double* __restrict__ fb,
-    double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-    const double* __restrict__ q, double* __restrict__ z, double* __restrict__ partial,
-    const CgScalars* __restrict__ sc) {
+    const int32_t* __restrict__ inv_idx, const double* __restrict__ fb, int bd, const FastDiv dbd,
+    int m, const PullLattice L, uint32_t n, int rounds, double* __restrict__ x,
+    double* __restrict__ r, const double* __restrict__ p, const double* __restrict__ q,
+    double* __restrict__ z, double* __restrict__ partial, const CgScalars* __restrict__ sc) {
   constexpr int kN = kFlex ? 4 : 3;
+  constexpr int kE = kPullElems;
   __shared__ double lds[4][kN];
   if (sc->done) return;
   const double alpha = sc->alpha;
-  const int64_t ntiles = pull_num_tiles(L);
-  double v[kN] = {};
-  // XCD-contiguous tile ranges: the block outputs of the cells on a tile's
-  // faces, which the neighbouring tiles read too, stay in one XCD's L2
-  const XcdRange xr = xcd_range(blockIdx.x, gridDim.x, ntiles);
-  for (int64_t tile = xr.t0 + xr.j; tile < xr.t1; tile += xr.per) {
-    int gx, gy, gz;
-    if (!pull_node(L, tile, threadIdx.x, &gx, &gy, &gz)) continue;
-    const double sv = pull_lattice_sum(y, L, m, gx, gy, gz);
-    const int64_t i = gx + (int64_t)L.n1 * (gy + (int64_t)L.n1 * gz);
-    const double qi = q[i];
-    const double ri = fma(-alpha, qi, r[i]);
-    x[i] = fma(alpha, p[i], x[i]);
-    r[i] = ri;
-    const double zi = fb ? fma(fb[i], ri, sv) : sv;
-    z[i] = zi;
-    v[0] = fma(ri, zi, v[0]);
-    v[1] = fma(zi, zi, v[1]);
-    v[2] = fma(ri, ri, v[2]);
-    if constexpr (kFlex) v[3] = fma(zi, qi, v[3]);
+  const uint32_t first = xcd_remap(blockIdx.x, gridDim.x) * (uint32_t)rounds;
+  double acc[kN] = {};
+  for (int t = 0; t < rounds; ++t) {
+    const uint32_t i0 = (first + t) * (256 * kE) + threadIdx.x;
+    if (i0 >= n) break;
+    uint32_t i[kE];
+    double qi[kE], ri[kE], pi[kE], xi[kE], fi[kE], v[kE][8], s[kE];
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      i[e] = min(i0 + 256u * e, n - 1);
+      qi[e] = q[i[e]];
+      ri[e] = r[i[e]];
+      pi[e] = p[i[e]];
+      xi[e] = x[i[e]];
+      fi[e] = fb ? fb[i[e]] : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      const uint32_t node = fdiv(i[e], dbd);
+      const int c = (int)(i[e] - node * (uint32_t)bd);
+      if constexpr (kLat)
+        pull_lattice_load(y, L, m, bd, node, c, v[e]);
+      else
+        s[e] = pull_mapped_sum(y, inv_ptr, inv_idx, node, c);
+    }
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      if (i0 + 256u * e >= n) break;
+      if constexpr (kLat) s[e] = pull_sum8(v[e]);
+      const double rn = fma(-alpha, qi[e], ri[e]);
+      x[i[e]] = fma(alpha, pi[e], xi[e]);
+      r[i[e]] = rn;
+      const double zn = fb ? fma(fi[e], rn, s[e]) : s[e];
+      z[i[e]] = zn;
+      acc[0] = fma(rn, zn, acc[0]);
+      acc[1] = fma(zn, zn, acc[1]);
+      acc[2] = fma(rn, rn, acc[2]);
+      if constexpr (kFlex) acc[3] = fma(zn, qi[e], acc[3]);
+    }
   }
   const int w = threadIdx.x / kWave;
 #pragma unroll
   for (int k = 0; k < kN; ++k) {
-    v[k] = group_sum<kWave>(v[k]);
-    if (threadIdx.x % kWave == 0) lds[w][k] = v[k];
+    acc[k] = wave_sum_last(acc[k]);
+    if (threadIdx.x % kWave == kWave - 1) lds[w][k] = acc[k];
   }
   __syncthreads();
   if (threadIdx.x < kN) {
@@ -566,40 +554,34 @@ __global__ __launch_bounds__(256) void k_resid(const double* __restrict__ b,
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kVecThreads - 1) / kVecThreads); }
 static constexpr unsigned kRedBlocks = 1024;
-// grid of the fused pull: enough workgroups to fill the chip, few partials
-static inline unsigned pull_grid(int64_t n) { return std::min<unsigned>(nblk(n), 2048u); }
-// grid of the pull actually launched for this preconditioner (the lattice
-// pull walks node tiles, one workgroup per tile up to 16,384 workgroups,
-// which at 64^3 cells, p = 2 is 6 % faster than 4,096; never more
-// workgroups than partial slots)
-static inline unsigned pull_grid_for(const fc_precond_s& pc, int64_t n, int64_t partial_len) {
-  if (pc.lat.dim == 0) return pull_grid(n);
-  static const int cap = [] {
-    const char* e = std::getenv("FC_PULL_GRID");
-    return e ? std::max(64, std::atoi(e)) : 16384;
-  }();
-  const int64_t nt = pull_num_tiles(pc.lat);
-  // at most one partial set (four values) per workgroup fits in `partial`
-  return (unsigned)std::min<int64_t>({nt, (int64_t)cap, (partial_len - 8) / 4});
+// Workgroups of the fused pull: one round each up to 4,096 of them, then more
+// rounds (each leaves one partial set, which the next kernel sums).
+static inline int pull_rounds(int64_t n) {
+  const int64_t runs = (n + 256 * kPullElems - 1) / (256 * kPullElems);
+  return (int)((runs + 4095) / 4096);
+}
+static inline unsigned pull_grid(int64_t n) {
+  const int64_t per = (int64_t)256 * kPullElems * pull_rounds(n);
+  return (unsigned)((n + per - 1) / per);
 }
 
 // Schwarz pull fused with the CG updates and the (r,z), (z,z), (r,r)
-// [, (z,q)] partials, one partial set per workgroup of the grid pg.
+// [, (z,q)] partials, one partial set per workgroup of pull_grid(n).
 template <bool kFlex>
-static hipError_t launch_cg_pull(const fc_precond_s& pc, unsigned pg, double* x, double* r,
-                                 const double* p, const double* q, double* z, double* partial,
-                                 const CgScalars* sc, hipStream_t s) {
+static hipError_t launch_cg_pull(const fc_precond_s& pc, double* x, double* r, const double* p,
+                                 const double* q, double* z, double* partial, const CgScalars* sc,
+                                 hipStream_t s) {
   const int64_t n = pc.pb->n_dofs;
-  if (pc.lat.dim == 0) {
-    hipLaunchKernelGGL(k_cg_pull<kFlex>, dim3(pg), dim3(kVecThreads), 0, s, pc.y, pc.inv_ptr,
-                       pc.inv_idx, pc.fallback, pc.bdim, n, x, r, p, q, z, partial, sc);
-    return hipGetLastError();
-  }
-  // the lattice is set for scalar problems only
-  if (pc.bdim != 1) return hipErrorInvalidValue;
   const double* fb = pc.n_fallback ? pc.fallback : nullptr;
-  hipLaunchKernelGGL(k_cg_pull_lat<kFlex>, dim3(pg), dim3(256), 0, s, pc.y, pc.lat, pc.m, fb, x,
-                     r, p, q, z, partial, sc);
+  const FastDiv dbd = make_fastdiv((uint32_t)pc.bdim);
+  const dim3 g(pull_grid(n)), b(256);
+  const int rounds = pull_rounds(n);
+  if (pc.lat.dim > 0)
+    hipLaunchKernelGGL((k_cg_pull<kFlex, true>), g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, fb,
+                       pc.bdim, dbd, pc.m, pc.lat, (uint32_t)n, rounds, x, r, p, q, z, partial, sc);
+  else
+    hipLaunchKernelGGL((k_cg_pull<kFlex, false>), g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, fb,
+                       pc.bdim, dbd, pc.m, pc.lat, (uint32_t)n, rounds, x, r, p, q, z, partial, sc);
   return hipGetLastError();
 }
 
@@ -686,7 +668,7 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
       // row-mixed matrix: rows touching cut or fictitious cells in FP64,
       // the others from the FP32 copy, which gather p rounded to FP32 (half
       // the gathered bytes; those products round p to FP32 anyway)
-      hipLaunchKernelGGL(k_round_f32, dim3(pull_grid(n)), dim3(kVecThreads), 0, s, w.p, w.p32,
+      hipLaunchKernelGGL(k_round_f32, dim3(std::min<unsigned>(nblk(n), 2048u)), dim3(kVecThreads), 0, s, w.p, w.p32,
                          n, w.sc);
       e = launch_spmv_mixed(pb.A, w.p, w.p32, w.q, w.sc, s);
       if (e != hipSuccess) return e;
@@ -715,12 +697,12 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
     e = launch_schwarz_phase1(pc, precS, w.r, w.q, w.sc, s);
     if (e != hipSuccess) return e;
     if (tev_it && (e = hipEventRecord(tev[4 * it + 3], s)) != hipSuccess) return e;
-    const unsigned pg = pull_grid_for(pc, n, w.partial_len);
+    const unsigned pg = pull_grid(n);
     const bool ring = learn && fcg_m > 1;
     if (ring) {
       // FCG(m): Schwarz pull, correction, then the new direction made
       // A-orthogonal to the m kept ones
-      if ((e = launch_cg_pull<false>(pc, pg, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
+      if ((e = launch_cg_pull<false>(pc, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
           hipSuccess)
         return e;
       if ((e = coarse_correct(*learn, w.r, w.z, nullptr, w.sc, s)) != hipSuccess) return e;
@@ -732,14 +714,14 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
       hipLaunchKernelGGL(k_fcg_dir, dim3(pg), dim3(kVecThreads), 0, s, w.z, w.p, w.ring, n, fcg_m,
                          w.fr, w.sc);
     } else if (learn) {
-      if ((e = launch_cg_pull<true>(pc, pg, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
+      if ((e = launch_cg_pull<true>(pc, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
           hipSuccess)
         return e;
       if ((e = coarse_correct(*learn, w.r, w.z, w.q, w.sc, s)) != hipSuccess) return e;
       hipLaunchKernelGGL(k_cg_beta_flex, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc,
                          learn->ls);
     } else {
-      if ((e = launch_cg_pull<false>(pc, pg, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
+      if ((e = launch_cg_pull<false>(pc, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
           hipSuccess)
         return e;
       hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc);

@@ -361,18 +361,28 @@ static hipError_t phase1_chol(const fc_precond_s& pc, const T* L, const double* 
   return hipGetLastError();
 }
 
-// Phase 2: z_i = sum over blocks containing i of y_B[slot] + fb_i * r_i.
+// Phase 2: z_i = sum over blocks containing i of y_B[slot] + fb_i * r_i.  kLat:
+// every cell is a block, and a node's blocks follow from its lattice indices.
+// fb may be null (no unknown needs the diagonal scaling).
+template <bool kLat>
 __global__ __launch_bounds__(256) void k_schwarz_pull(
     const double* __restrict__ y, const int32_t* __restrict__ inv_ptr,
-    const int32_t* __restrict__ inv_idx, const double* __restrict__ fb, int bd,
-    int64_t n_dofs, const double* __restrict__ r, double* __restrict__ z) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t* __restrict__ inv_idx, const double* __restrict__ fb, int bd, const FastDiv dbd,
+    int m, const PullLattice L, uint32_t n_dofs, const double* __restrict__ r,
+    double* __restrict__ z) {
+  const uint32_t i = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= n_dofs) return;
-  const int64_t node = i / bd;
-  const int c = (int)(i - node * bd);
-  double s = 0.0;
-  for (int32_t e = inv_ptr[node]; e < inv_ptr[node + 1]; ++e) s += y[(int64_t)inv_idx[e] + c];
-  z[i] = fma(fb[i], r[i], s);
+  const uint32_t node = fdiv(i, dbd);
+  const int c = (int)(i - node * (uint32_t)bd);
+  double s;
+  if constexpr (kLat) {
+    double v[8];
+    pull_lattice_load(y, L, m, bd, node, c, v);
+    s = pull_sum8(v);
+  } else {
+    s = pull_mapped_sum(y, inv_ptr, inv_idx, node, c);
+  }
+  z[i] = fb ? fma(fb[i], r[i], s) : s;
 }
 
 // Wrapped-diagonal copy: entry (k, i) of block blk, P[blk][i][(i+k) mod m]
@@ -539,7 +549,7 @@ static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, co
     const int64_t nwg = (pc.n_blocks + per_wg - 1) / per_wg;
     // the block sizes of scalar and vector problems at p = 1..3 (2-D and
     // 3-D) have their own compiled kernels
-    const bool lat = pc.lat.dim > 0;
+    const bool lat = pc.lat.dim > 0 && pc.bdim == 1;
 #define FC_SMALL_LAUNCH(KM)                                                                    \
   do {                                                                                         \
     if (lat && KM > 0)                                                                         \
@@ -619,36 +629,19 @@ hipError_t launch_schwarz_phase1(const fc_precond_s& pc, int precision, const do
   return hipErrorInvalidValue;
 }
 
-// The same where every cell is a block (lattice pull, see k_cg_pull_lat;
-// scalar problems only).
-__global__ __launch_bounds__(256) void k_schwarz_pull_lat(const double* __restrict__ y,
-                                                          const PullLattice L, int m,
-                                                          const double* __restrict__ fb,
-                                                          const double* __restrict__ r,
-                                                          double* __restrict__ z) {
-  const int64_t ntiles = pull_num_tiles(L);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    int gx, gy, gz;
-    if (!pull_node(L, tile, threadIdx.x, &gx, &gy, &gz)) continue;
-    const double sv = pull_lattice_sum(y, L, m, gx, gy, gz);
-    const int64_t i = gx + (int64_t)L.n1 * (gy + (int64_t)L.n1 * gz);
-    z[i] = fb ? fma(fb[i], r[i], sv) : sv;
-  }
-}
-
 hipError_t launch_schwarz_pull(const fc_precond_s& pc, const double* r, double* z,
                                hipStream_t s) {
   const int64_t n = pc.pb->n_dofs;
   if (n == 0) return hipSuccess;
-  if (pc.lat.dim > 0) {
-    if (pc.bdim != 1) return hipErrorInvalidValue;
-    const dim3 g((unsigned)std::min<int64_t>(pull_num_tiles(pc.lat), 4096)), b(256);
-    const double* fb = pc.n_fallback ? pc.fallback : nullptr;
-    hipLaunchKernelGGL(k_schwarz_pull_lat, g, b, 0, s, pc.y, pc.lat, pc.m, fb, r, z);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_schwarz_pull, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pc.y,
-                     pc.inv_ptr, pc.inv_idx, pc.fallback, pc.bdim, n, r, z);
+  const dim3 g((unsigned)((n + 255) / 256)), b(256);
+  const double* fb = pc.n_fallback ? pc.fallback : nullptr;
+  const FastDiv dbd = make_fastdiv((uint32_t)pc.bdim);
+  if (pc.lat.dim > 0)
+    hipLaunchKernelGGL(k_schwarz_pull<true>, g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, fb, pc.bdim,
+                       dbd, pc.m, pc.lat, (uint32_t)n, r, z);
+  else
+    hipLaunchKernelGGL(k_schwarz_pull<false>, g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, fb,
+                       pc.bdim, dbd, pc.m, pc.lat, (uint32_t)n, r, z);
   return hipGetLastError();
 }
 
