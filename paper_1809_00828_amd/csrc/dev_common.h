@@ -90,6 +90,33 @@ __device__ __forceinline__ T block_sum(T v, T* lds /* >= 16 */) {
   return t;
 }
 
+// Step length alpha = (r, z) / (p, q) from the (p, q) partials, by every
+// workgroup on its own (a fixed order, so all agree); the first one also
+// counts the step and stores the scalars.  False: breakdown, the step is not
+// taken.  red: LDS of at least 16 doubles.
+__device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double* red,
+                                         double* alpha) {
+  const double rz = sc->rzn;
+  double t = 0.0;
+  for (int i = threadIdx.x; i < ai.np; i += blockDim.x) t += ai.partial[i];
+  t = wave_sum_last(t);
+  const int w = threadIdx.x / kWave;
+  if (threadIdx.x % kWave == kWave - 1) red[w] = t;
+  __syncthreads();
+  double pq = red[0];
+  for (int i = 1; i < (int)(blockDim.x / kWave); ++i) pq += red[i];
+  const bool ok = pq > 0.0 && rz > 0.0;
+  *alpha = rz / pq;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->pq = pq;
+    sc->rz = rz;
+    sc->iter += 1;
+    if (ok) sc->alpha = *alpha;
+    else sc->done = (pq != pq || rz != rz) ? 4 : 3;
+  }
+  return ok;
+}
+
 __device__ __forceinline__ double load_relaxed(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -22,11 +22,12 @@ void set_error(const std::string& msg);
   } while (0)
 
 // Scalars of one PCG run kept on the device so the iteration never waits on
-// the host.  Dots are reduced per workgroup into `partial`, and the last
-// workgroup to finish (found with `ticket`) sums the partials in a fixed
-// order, so every run is bitwise reproducible.
+// the host.  Dots are reduced per workgroup into `partial`, which a later
+// kernel sums in a fixed order, so every run is bitwise reproducible.  Kernels
+// of many workgroups derive alpha and beta from the partials themselves; only
+// their first workgroup writes scalars, and none that the same kernel reads.
 struct CgScalars {
-  double rz;        // (r, z) of the current iterate
+  double rz;        // (r, z) of the iterate the step starts from
   double pq;        // (p, A p)
   double alpha, beta;
   double zz;        // (z, z) of the newest z
@@ -38,8 +39,7 @@ struct CgScalars {
   int64_t maxit;
   int32_t done;     // 0 running, 1 converged, 2 maxit, 3 breakdown, 4 non-finite
   int32_t stop;     // FC_STOP_*
-  uint32_t ticket;  // last-workgroup counter (reset by the last workgroup)
-  uint32_t pad;
+  double rzn;       // (r, z) of the newest iterate (rz of the next step)
   double zn0, rn0;  // ||z_0||, ||r_0||
   double* history;  // optional per-iteration criterion
 };
@@ -127,14 +127,20 @@ struct DeviceBsr {
   // entries 2j and 2j + 1 of lane l at sell_val[sell_off[s] + 128 j + 2 l]
   // and the next word, an odd last entry alone at sell_off[s] + 128 j + l
   // (zero for lanes past the class's end).
-  // The boundary vertex rows (x = 0 and x = n1 - 1) are listed in sell_rest
-  // and use the row layout.
+  // The n_rest boundary vertex rows (x = 0 and x = n1 - 1 of every line) use
+  // the row layout.
   double* sell_val = nullptr;
   int64_t* sell_off = nullptr;   // [n_slices + 1]
   int64_t n_slices = 0;
   int32_t sell_cv = 0, sell_nv = 0, sell_nn = 0;   // vertex slices per line, rows per class
-  int32_t* sell_rest = nullptr;
   int64_t n_rest = 0;
+};
+
+// Per-workgroup (p, q) partials a kernel derives the step length from; np = 0:
+// the step length is in CgScalars already.
+struct AlphaIn {
+  const double* partial = nullptr;
+  int np = 0;
 };
 
 struct SolverWs;

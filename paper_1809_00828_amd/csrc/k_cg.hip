@@ -4,18 +4,24 @@
 // Recurrences (x_0 = 0):  r_0 = b, z_0 = S r_0, p_0 = z_0, then per step
 //   q = A p;  alpha = (r,z)/(p,q);  x += alpha p;  r -= alpha q;
 //   z = S r;  beta = (r,z)_new/(r,z);  p = z + beta p.
-// One step is seven kernels, all reading their scalars from device memory:
-//   1. SpMV q = A p (k_spmv.hip)
-//   2. (p, q) by workgroup partials in a separate pass over p and q, then
-//      one workgroup sums them in a fixed order: alpha, step count.
-//      Fusing the dot into the SpMV costs more than this extra pass: the
+// One step is four or five kernels up to 1,024 pull workgroups (0.5M
+// unknowns) and six above, all reading their scalars from device memory:
+//   1. SpMV q = A p (k_spmv.hip), with the (p, q) partials of its workgroups
+//      where they are few
+//   2. else (p, q) by workgroup partials in a separate pass over p and q.
+//      Fusing the dot into a large SpMV costs more than this extra pass: the
 //      SpMV's end-of-workgroup reduction holds its four waves until the
 //      slowest one finishes.
-//   3. Schwarz phase 1 on the gathered r - alpha q (k_schwarz.hip)
+//   3. Schwarz phase 1 on the gathered r - alpha q (k_schwarz.hip); every
+//      workgroup sums the (p, q) partials to alpha itself, behind its first
+//      loads of the local inverses
 //   4. pull z = sum_B R_B^T y_B + fallback, fused with the x and r updates
 //      and per-workgroup (r,z), (z,z), (r,r) partials
-//   5. one workgroup: stop test and beta
-//   6. p = z + beta p
+//   5. p = z + beta p, every workgroup summing the pull's partials to beta, the
+//      first one also testing for the stop (above 1,024 partials one
+//      workgroup's own launch before it)
+// A launch costs 2.5 to 5 us at any size, and one-workgroup kernels for alpha
+// and beta were two of eight.
 // The reductions stay atomic-free: a same-address atomic per workgroup
 // serialises in L2 and costs more than the SpMV itself at this size.
 // Every kernel returns at once when the stop flag is set, so a captured
@@ -88,19 +94,42 @@ void solver_ws_destroy(SolverWs* w) {
 constexpr int kVecThreads = 256;
 constexpr int kPullElems = 2;   // unknowns per thread and round of the pull
 
-// Three dots of the starting vectors: (r,z), (z,z), (r,r); the last
-// workgroup initialises the scalars.
-__global__ __launch_bounds__(256) void k_cg_start(const double* __restrict__ r,
-                                                  const double* __restrict__ z, int64_t n,
-                                                  double* __restrict__ partial, CgScalars* sc) {
+// x = 0, r = b and the scalars of a new run.
+__global__ __launch_bounds__(256) void k_cg_init(const double* __restrict__ b,
+                                                 double* __restrict__ x, double* __restrict__ r,
+                                                 int64_t n, CgScalars* sc, double tol,
+                                                 int64_t maxit, int32_t stop, double* history) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    x[i] = 0.0;
+    r[i] = b[i];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    CgScalars v{};
+    v.tol = tol;
+    v.maxit = maxit;
+    v.stop = stop;
+    v.history = history;
+    *sc = v;
+  }
+}
+
+// p = z and the partials of three dots of the starting vectors: (r,z), (z,z),
+// (r,r).  One workgroup sums them next (k_cg_start_fin): the ticket atomic of a
+// last-workgroup sum costs 37 ns per workgroup, 38 us for 1,024 of them.
+__global__ __launch_bounds__(1024) void k_cg_start(const double* __restrict__ r,
+                                                   const double* __restrict__ z,
+                                                   double* __restrict__ p, int64_t n,
+                                                   double* __restrict__ partial) {
   __shared__ double lds[16];
-  __shared__ int flag;
   double a = 0.0, b = 0.0, c = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    a = fma(r[i], z[i], a);
-    b = fma(z[i], z[i], b);
-    c = fma(r[i], r[i], c);
+    const double ri = r[i], zi = z[i];
+    p[i] = zi;
+    a = fma(ri, zi, a);
+    b = fma(zi, zi, b);
+    c = fma(ri, ri, c);
   }
   a = block_sum(a, lds);
   b = block_sum(b, lds);
@@ -110,12 +139,18 @@ __global__ __launch_bounds__(256) void k_cg_start(const double* __restrict__ r,
     partial[gridDim.x + blockIdx.x] = b;
     partial[2 * gridDim.x + blockIdx.x] = c;
   }
-  if (!last_block(&sc->ticket, gridDim.x, &flag)) return;
-  const double rz = sum_partials(partial, gridDim.x, lds);
-  const double zz = sum_partials(partial + gridDim.x, gridDim.x, lds);
-  const double rr = sum_partials(partial + 2 * gridDim.x, gridDim.x, lds);
-  if (threadIdx.x == 0) {
+}
+
+__global__ __launch_bounds__(256) void k_cg_start_fin(const double* __restrict__ partial, int np,
+                                                      CgScalars* sc) {
+  __shared__ double lds[16];
+  const int t = threadIdx.x;
+  const double rz = block_sum(t < np ? partial[t] : 0.0, lds);
+  const double zz = block_sum(t < np ? partial[np + t] : 0.0, lds);
+  const double rr = block_sum(t < np ? partial[2 * np + t] : 0.0, lds);
+  if (t == 0) {
     sc->rz = rz;
+    sc->rzn = rz;
     sc->zz = zz;
     sc->rr = rr;
     sc->iter = 0;
@@ -131,49 +166,35 @@ __global__ __launch_bounds__(256) void k_cg_start(const double* __restrict__ r,
   }
 }
 
-// Step length: sum the per-workgroup (p, A p) partials of the SpMV in a
-// fixed order (one workgroup), count the step and check for breakdown.
-__global__ __launch_bounds__(1024) void k_cg_alpha(const double* __restrict__ partial, int np,
-                                                   CgScalars* sc) {
+// Step length where the next kernel does not derive it itself (no block, BF16
+// inverses, the learned modes).
+__global__ __launch_bounds__(1024) void k_cg_alpha(const AlphaIn ai, CgScalars* sc) {
   __shared__ double lds[16];
   if (sc->done) return;
-  double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-  int i = threadIdx.x;
-  for (; i + 3 * (int)blockDim.x < np; i += 4 * blockDim.x) {
-    t0 += partial[i];
-    t1 += partial[i + blockDim.x];
-    t2 += partial[i + 2 * blockDim.x];
-    t3 += partial[i + 3 * blockDim.x];
-  }
-  for (; i < np; i += blockDim.x) t0 += partial[i];
-  const double pq = block_sum((t0 + t1) + (t2 + t3), lds);
-  if (threadIdx.x == 0) {
-    sc->pq = pq;
-    sc->iter += 1;
-    const double rz = sc->rz;
-    if (!(pq > 0.0) || !(rz > 0.0)) {
-      sc->done = (pq != pq || rz != rz) ? 4 : 3;
-    } else {
-      sc->alpha = rz / pq;
-    }
-  }
+  double alpha;
+  (void)cg_alpha(sc, ai, lds, &alpha);
 }
 
-// (p, q) partials of a separate pass over p and q, one per workgroup; the
-// one-workgroup k_cg_alpha sums them in a fixed order.  (A last-workgroup
-// ticket here would serialise thousands of same-address atomics in L2.)
-__global__ __launch_bounds__(256) void k_cg_pq(const double* __restrict__ p,
-                                               const double* __restrict__ q, int64_t n,
-                                               double* __restrict__ partial,
-                                               const CgScalars* __restrict__ sc) {
+// (p, q) partials of a separate pass over p and q, one per workgroup of a grid
+// of at most 256: every workgroup of the next kernel sums them all.
+constexpr unsigned kPqBlocks = 256;
+__global__ __launch_bounds__(1024) void k_cg_pq(const double* __restrict__ p,
+                                                const double* __restrict__ q, int64_t n,
+                                                double* __restrict__ partial,
+                                                const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
   if (sc->done) return;
-  double a = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    a = fma(p[i], q[i], a);
-  a = block_sum(a, lds);
-  if (threadIdx.x == 0) partial[blockIdx.x] = a;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (; i + 3 * step < n; i += 4 * step)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[u] = fma(p[i + u * step], q[i + u * step], a[u]);
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (i + u * step < n) a[u] = fma(p[i + u * step], q[i + u * step], a[u]);
+  const double t = block_sum((a[0] + a[1]) + (a[2] + a[3]), lds);
+  if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
 // Pull of the Schwarz apply fused with x += alpha p, r -= alpha q and the
@@ -257,37 +278,86 @@ __global__ __launch_bounds__(256) void k_cg_pull(
   }
 }
 
-// Stop test (Eq. 12 or the plain residual) and beta from the pull's
-// partials, summed in a fixed order by one workgroup.
+// Stop test (Eq. 12 or the plain residual) and the scalars of the next step,
+// by one thread.  sc->rz stays: the workgroups of k_cg_beta_p divide by it.
+__device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double zz, double rr) {
+  const double crit = (sc->stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / sc->crit0;
+  sc->zz = zz;
+  sc->rr = rr;
+  sc->crit = crit;
+  if (sc->history) sc->history[sc->iter] = crit;
+  sc->beta = rz / sc->rz;
+  sc->rzn = rz;
+  if (!(crit == crit) || !(rz == rz) || isinf(rz)) {
+    sc->done = 4;
+  } else if (crit <= sc->tol) {
+    sc->done = 1;
+  } else if (sc->iter >= sc->maxit) {
+    sc->done = 2;
+  }
+}
+
+// The pull's partials summed in a fixed order by one workgroup (more than
+// kBetaSets of them), four sets per thread in flight.
+constexpr int kBetaSets = 1024;
 __global__ __launch_bounds__(1024) void k_cg_beta(const double* __restrict__ partial, int np,
                                                   CgScalars* sc) {
   __shared__ double lds[16];
   if (sc->done) return;
-  double ta = 0.0, tb = 0.0, tc = 0.0;
-  for (int i = threadIdx.x; i < np; i += blockDim.x) {
-    ta += partial[i];
-    tb += partial[np + i];
-    tc += partial[2 * np + i];
+  double t[3] = {0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < np; i += 4 * blockDim.x) {
+    double v[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = i + u * (int)blockDim.x;
+        v[k][u] = j < np ? partial[k * np + j] : 0.0;
+      }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
   }
-  const double rz = block_sum(ta, lds);
-  const double zz = block_sum(tb, lds);
-  const double rr = block_sum(tc, lds);
-  if (threadIdx.x == 0) {
-    const double crit = (sc->stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / sc->crit0;
-    sc->zz = zz;
-    sc->rr = rr;
-    sc->crit = crit;
-    if (sc->history) sc->history[sc->iter] = crit;
-    if (!(crit == crit) || !(rz == rz) || isinf(rz)) {
-      sc->done = 4;
-    } else if (crit <= sc->tol) {
-      sc->done = 1;
-    } else if (sc->iter >= sc->maxit) {
-      sc->done = 2;
+  const double rz = block_sum(t[0], lds);
+  const double zz = block_sum(t[1], lds);
+  const double rr = block_sum(t[2], lds);
+  if (threadIdx.x == 0) cg_beta_store(sc, rz, zz, rr);
+}
+
+// p = z + beta p with beta from the pull's np <= kBetaSets partials, summed by
+// every workgroup in the same order; the first one also sums (z,z) and (r,r),
+// tests for the stop and stores the scalars.  Two unknowns per thread, loaded
+// before the sums.  (A workgroup that still updates p after the first one set
+// the stop flag changes nothing: p is not read again.)
+__global__ __launch_bounds__(256) void k_cg_beta_p(const double* __restrict__ partial, int np,
+                                                   const double* __restrict__ z,
+                                                   double* __restrict__ p, int64_t n,
+                                                   CgScalars* sc) {
+  __shared__ double red[3][4];
+  if (sc->done) return;
+  const double rz_old = sc->rz;
+  const int64_t i0 = (int64_t)blockIdx.x * 512 + threadIdx.x, i1 = i0 + 256;
+  const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p[i0] : 0.0;
+  const double z1 = i1 < n ? z[i1] : 0.0, p1 = i1 < n ? p[i1] : 0.0;
+  const int nk = blockIdx.x == 0 ? 3 : 1;
+  const int w = threadIdx.x / kWave;
+  for (int k = 0; k < nk; ++k) {
+    double v[kBetaSets / 256];
+#pragma unroll
+    for (int u = 0; u < kBetaSets / 256; ++u) {
+      const int j = threadIdx.x + 256 * u;
+      v[u] = j < np ? partial[k * np + j] : 0.0;
     }
-    sc->beta = rz / sc->rz;
-    sc->rz = rz;
+    const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
+    if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
   }
+  __syncthreads();
+  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+  const double beta = rz / rz_old;
+  if (i0 < n) p[i0] = fma(beta, p0, z0);
+  if (i1 < n) p[i1] = fma(beta, p1, z1);
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    cg_beta_store(sc, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
+                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
 }
 
 // Flexible variant (FCG(1)) for the learned correction z = S r + gamma w:
@@ -329,7 +399,7 @@ __global__ __launch_bounds__(1024) void k_cg_beta_flex(const double* __restrict_
       sc->done = 2;
     }
     sc->beta = -zq / sc->pq;
-    sc->rz = rz;
+    sc->rzn = rz;
   }
 }
 
@@ -464,7 +534,7 @@ __global__ __launch_bounds__(1024) void k_fcg_beta(const double* __restrict__ pa
     } else if (sc->iter >= sc->maxit) {
       sc->done = 2;
     }
-    sc->rz = rz;
+    sc->rzn = rz;
   }
 }
 
@@ -523,13 +593,12 @@ __global__ void k_fill(double* __restrict__ a, double v, int64_t n) {
     a[i] = v;
 }
 
-// ||b - t||^2 and ||b||^2 into sc->rr and sc->zz (final true residual).
-__global__ __launch_bounds__(256) void k_resid(const double* __restrict__ b,
-                                               const double* __restrict__ t, int64_t n,
-                                               double* __restrict__ partial, CgScalars* sc,
-                                               double* out /* [2] */) {
+// Partials of ||b - t||^2 and ||b||^2 (final true residual), then their sums
+// by one workgroup of 256.
+__global__ __launch_bounds__(1024) void k_resid(const double* __restrict__ b,
+                                                const double* __restrict__ t, int64_t n,
+                                                double* __restrict__ partial) {
   __shared__ double lds[16];
-  __shared__ int flag;
   double a = 0.0, c = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -543,17 +612,34 @@ __global__ __launch_bounds__(256) void k_resid(const double* __restrict__ b,
     partial[blockIdx.x] = a;
     partial[gridDim.x + blockIdx.x] = c;
   }
-  if (!last_block(&sc->ticket, gridDim.x, &flag)) return;
-  const double ra = sum_partials(partial, gridDim.x, lds);
-  const double rc = sum_partials(partial + gridDim.x, gridDim.x, lds);
-  if (threadIdx.x == 0) {
-    out[0] = ra;
-    out[1] = rc;
+}
+
+__global__ __launch_bounds__(256) void k_resid_fin(const double* __restrict__ partial, int np,
+                                                   double* out /* [2] */) {
+  __shared__ double lds[16];
+  const int t = threadIdx.x;
+  const double a = block_sum(t < np ? partial[t] : 0.0, lds);
+  const double c = block_sum(t < np ? partial[np + t] : 0.0, lds);
+  if (t == 0) {
+    out[0] = a;
+    out[1] = c;
   }
 }
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kVecThreads - 1) / kVecThreads); }
-static constexpr unsigned kRedBlocks = 1024;
+// grid and workgroup of the vector reductions: at most 256 workgroups (their
+// partials are summed by one workgroup, or by every workgroup of the next
+// kernel), of 1,024 threads where 256 of 256 would leave over eight elements
+// to a thread
+static inline unsigned red_threads(int64_t n) { return n > 256 * 256 * 8 ? 1024u : 256u; }
+static inline unsigned red_grid(int64_t n) {
+  const int64_t t = red_threads(n);
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + t - 1) / t, kPqBlocks));
+}
+// partial sums of one kernel: four sets per pull workgroup, three per
+// reduction workgroup, or one per SpMV workgroup; two doubles at the end
+// receive the final residual
+constexpr int64_t kPartials = 4 * 4096 + 8;
 // Workgroups of the fused pull: one round each up to 4,096 of them, then more
 // rounds (each leaves one partial set, which the next kernel sums).
 static inline int pull_rounds(int64_t n) {
@@ -585,10 +671,6 @@ static hipError_t launch_cg_pull(const fc_precond_s& pc, double* x, double* r, c
   return hipGetLastError();
 }
 
-// grid of a two-vector dot: a few elements per lane keep enough loads in
-// flight (1024 workgroups left ten dependent iterations per lane at 2.7M)
-static inline unsigned dot_grid(int64_t n) { return std::min<unsigned>(nblk(n), 4096u); }
-
 // ----------------------------------------------------------- host side
 static fc_status ensure_ws(fc_precond_s& pc, SolverWs** out) {
   fc_problem_s& pb = *pc.pb;
@@ -603,9 +685,7 @@ static fc_status ensure_ws(fc_precond_s& pc, SolverWs** out) {
     FC_HIP(hipMalloc(&w->p, n * sizeof(double)));
     FC_HIP(hipMalloc(&w->q, n * sizeof(double)));
     FC_HIP(hipMalloc(&w->t, n * sizeof(double)));
-    int64_t np = std::max<int64_t>({(int64_t)spmv_num_blocks(pb.A), (int64_t)nblk(n),
-                                    (int64_t)kRedBlocks});
-    w->partial_len = 4 * np + 8;
+    w->partial_len = kPartials;
     FC_HIP(hipMalloc(&w->partial, w->partial_len * sizeof(double)));
     FC_HIP(hipMalloc(&w->sc, sizeof(CgScalars)));
     FC_HIP(hipMemset(w->sc, 0, sizeof(CgScalars)));
@@ -642,14 +722,36 @@ static fc_status ensure_ring(SolverWs& w, int m) {
   return FC_OK;
 }
 
-// FC_CG_SPLIT_DOT=0 fuses (p, A p) into the SpMV (one partial per SpMV
-// workgroup); the default computes it in a separate pass over p and q.
-static bool split_dot() {
-  static const bool v = [] {
-    const char* e = std::getenv("FC_CG_SPLIT_DOT");
-    return !(e && e[0] == '0');
-  }();
-  return v;
+// Start of a run from x = 0: r = b, z = S r, p = z and the scalars (learn: with
+// the learned correction).
+static hipError_t enqueue_start(fc_precond_s& pc, SolverWs& w, const double* b, double* x,
+                                double tol, int64_t maxit, int stop, double* history, int precS,
+                                hipStream_t s, CoarseCtx* learn = nullptr, int fcg_m = 1) {
+  const int64_t n = pc.pb->n_dofs;
+  const unsigned g = red_grid(n), t = red_threads(n);
+  hipLaunchKernelGGL(k_cg_init, dim3(std::min<unsigned>(nblk(n), 2048u)), dim3(256), 0, s, b, x,
+                     w.r, n, w.sc, tol, maxit, stop, history);
+  hipError_t e;
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_schwarz_phase1(pc, precS, w.r, nullptr, nullptr, AlphaIn{}, s)) != hipSuccess)
+    return e;
+  if ((e = launch_schwarz_pull(pc, w.r, w.z, s)) != hipSuccess) return e;
+  if (learn) {
+    if ((e = coarse_correct(*learn, w.r, w.z, nullptr, w.sc, s)) != hipSuccess) return e;
+    if (fcg_m > 1) hipLaunchKernelGGL(k_fcg_reset, dim3(1), dim3(1), 0, s, w.fr);
+  }
+  hipLaunchKernelGGL(k_cg_start, dim3(g), dim3(t), 0, s, w.r, w.z, w.p, n, w.partial);
+  hipLaunchKernelGGL(k_cg_start_fin, dim3(1), dim3(256), 0, s, w.partial, (int)g, w.sc);
+  return hipGetLastError();
+}
+
+// ||b - t||^2 and ||b||^2 into the last two doubles of the partials.
+static hipError_t enqueue_resid(SolverWs& w, const double* b, const double* t, hipStream_t s) {
+  const unsigned g = red_grid(w.n);
+  hipLaunchKernelGGL(k_resid, dim3(g), dim3(red_threads(w.n)), 0, s, b, t, w.n, w.partial);
+  hipLaunchKernelGGL(k_resid_fin, dim3(1), dim3(256), 0, s, w.partial, (int)g,
+                     w.partial + w.partial_len - 2);
+  return hipGetLastError();
 }
 
 // Enqueue `chunk` PCG steps on stream s (with timing events when tev).
@@ -660,6 +762,7 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
                                 CoarseCtx* learn = nullptr, int every = 1, int fcg_m = 1) {
   fc_problem_s& pb = *pc.pb;
   const int64_t n = pb.n_dofs;
+  const int np_spmv = precA == 1 ? 0 : spmv_dot_blocks(pb.A);
   for (int it = 0; it < chunk; ++it) {
     hipError_t e;
     hipEvent_t* tev_it = (tev && it % every == 0) ? tev : nullptr;
@@ -668,33 +771,26 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
       // row-mixed matrix: rows touching cut or fictitious cells in FP64,
       // the others from the FP32 copy, which gather p rounded to FP32 (half
       // the gathered bytes; those products round p to FP32 anyway)
-      hipLaunchKernelGGL(k_round_f32, dim3(std::min<unsigned>(nblk(n), 2048u)), dim3(kVecThreads), 0, s, w.p, w.p32,
-                         n, w.sc);
+      hipLaunchKernelGGL(k_round_f32, dim3(std::min<unsigned>(nblk(n), 2048u)),
+                         dim3(kVecThreads), 0, s, w.p, w.p32, n, w.sc);
       e = launch_spmv_mixed(pb.A, w.p, w.p32, w.q, w.sc, s);
-      if (e != hipSuccess) return e;
-      if (tev_it && (e = hipEventRecord(tev[4 * it + 1], s)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_cg_pq, dim3(dot_grid(n)), dim3(256), 0, s, w.p, w.q, n, w.partial,
-                         w.sc);
-      hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(1024), 0, s, w.partial, (int)dot_grid(n),
-                         w.sc);
-    } else if (split_dot()) {
-      // SpMV without its fused dot, then (p, q) and alpha in one reduction
-      e = launch_spmv_pq(pb.A, w.p, w.q, w.sc, nullptr, s);
-      if (e != hipSuccess) return e;
-      if (tev_it && (e = hipEventRecord(tev[4 * it + 1], s)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_cg_pq, dim3(dot_grid(n)), dim3(256), 0, s, w.p, w.q, n, w.partial,
-                         w.sc);
-      hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(1024), 0, s, w.partial, (int)dot_grid(n),
-                         w.sc);
     } else {
-      e = launch_spmv_pq(pb.A, w.p, w.q, w.sc, w.partial, s);
-      if (e != hipSuccess) return e;
-      if (tev_it && (e = hipEventRecord(tev[4 * it + 1], s)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(1024), 0, s, w.partial,
-                         spmv_num_blocks(pb.A), w.sc);
+      e = launch_spmv_pq(pb.A, w.p, w.q, w.sc, np_spmv ? w.partial : nullptr, s);
+    }
+    if (e != hipSuccess) return e;
+    if (tev_it && (e = hipEventRecord(tev[4 * it + 1], s)) != hipSuccess) return e;
+    AlphaIn ai{w.partial, np_spmv};
+    if (!np_spmv) {
+      ai.np = (int)red_grid(n);
+      hipLaunchKernelGGL(k_cg_pq, dim3(red_grid(n)), dim3(red_threads(n)), 0, s, w.p, w.q, n,
+                         w.partial, w.sc);
+    }
+    if (learn || !schwarz_takes_alpha(pc, precS)) {
+      hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(1024), 0, s, ai, w.sc);
+      ai.np = 0;
     }
     if (tev_it && (e = hipEventRecord(tev[4 * it + 2], s)) != hipSuccess) return e;
-    e = launch_schwarz_phase1(pc, precS, w.r, w.q, w.sc, s);
+    e = launch_schwarz_phase1(pc, precS, w.r, w.q, w.sc, ai, s);
     if (e != hipSuccess) return e;
     if (tev_it && (e = hipEventRecord(tev[4 * it + 3], s)) != hipSuccess) return e;
     const unsigned pg = pull_grid(n);
@@ -724,9 +820,13 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
       if ((e = launch_cg_pull<false>(pc, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
           hipSuccess)
         return e;
-      hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc);
+      if (pg > (unsigned)kBetaSets)
+        hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc);
+      else
+        hipLaunchKernelGGL(k_cg_beta_p, dim3((unsigned)((n + 511) / 512)), dim3(256), 0, s,
+                           w.partial, (int)pg, w.z, w.p, n, w.sc);
     }
-    if (!ring)
+    if (learn ? !ring : pg > (unsigned)kBetaSets)
       hipLaunchKernelGGL(k_cg_p, dim3(nblk(n)), dim3(kVecThreads), 0, s, w.z, w.p, n, w.sc);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -803,24 +903,8 @@ static fc_status pcg_core(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, Core
                           hipStream_t s) {
   fc_problem_s& pb = *pc.pb;
   const int64_t n = pb.n_dofs;
-  CgScalars init{};
-  init.tol = a.tol;
-  init.maxit = a.maxit;
-  init.stop = a.stop;
-  init.history = a.history;
-  FC_HIP(hipMemcpyAsync(w.sc, &init, sizeof(CgScalars), hipMemcpyHostToDevice, s));
-  // x = 0, r = b, z = S r, p = z
-  hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, s, a.x, 0.0, n);
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, a.b, w.r, n);
-  FC_HIP(hipGetLastError());
-  FC_HIP(launch_schwarz_phase1(pc, a.precS, w.r, nullptr, nullptr, s));
-  FC_HIP(launch_schwarz_pull(pc, w.r, w.z, s));
-  if (a.learn) FC_HIP(coarse_correct(*a.learn, w.r, w.z, nullptr, w.sc, s));
-  if (a.learn && a.fcg_m > 1) hipLaunchKernelGGL(k_fcg_reset, dim3(1), dim3(1), 0, s, w.fr);
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, w.z, w.p, n);
-  hipLaunchKernelGGL(k_cg_start, dim3(kRedBlocks), dim3(256), 0, s, w.r, w.z, n, w.partial,
-                     w.sc);
-  FC_HIP(hipGetLastError());
+  FC_HIP(enqueue_start(pc, w, a.b, a.x, a.tol, a.maxit, a.stop, a.history, a.precS, s, a.learn,
+                       a.fcg_m));
   const int chunk = a.chunk > 0 ? a.chunk : 16;
   const int64_t max_chunks = (a.maxit + chunk - 1) / chunk + 1;
   int64_t launched = 0;
@@ -876,8 +960,7 @@ static fc_status true_residual(fc_precond_s& pc, SolverWs& w, const double* b, c
   FC_HIP(launch_spmv(pb.A, x, t, s));
   if (out_r) hipLaunchKernelGGL(k_sub, dim3(1024), dim3(256), 0, s, b, t, out_r, n);
   double* out2 = w.partial + w.partial_len - 2;
-  hipLaunchKernelGGL(k_resid, dim3(kRedBlocks), dim3(256), 0, s, b, t, n, w.partial, w.sc, out2);
-  FC_HIP(hipGetLastError());
+  FC_HIP(enqueue_resid(w, b, t, s));
   FC_HIP(hipMemcpyAsync(w.host, out2, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
   FC_HIP(hipStreamSynchronize(s));
   const double* v = reinterpret_cast<const double*>(w.host);
@@ -1061,9 +1144,8 @@ fc_status pcg_solve(fc_precond_s& pc, const double* b, double* x, const fc_solve
 // code reaches it only through the address hipGetSymbolAddress returns for
 // the current device.
 constexpr int64_t kNoAllocMaxDofs = int64_t(1) << 19;
-constexpr int64_t kNoAllocPartials = 4 * 4096 + 8;
 constexpr int64_t kNoAllocScalars = (sizeof(CgScalars) + sizeof(double) - 1) / sizeof(double);
-constexpr int64_t kNoAllocDoubles = 5 * kNoAllocMaxDofs + kNoAllocPartials + kNoAllocScalars;
+constexpr int64_t kNoAllocDoubles = 5 * kNoAllocMaxDofs + kPartials + kNoAllocScalars;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 
 constexpr int kMaxDevices = 64;
@@ -1091,18 +1173,6 @@ static fc_status scratch_for(int dev, double** out) {
   return FC_OK;
 }
 
-// The scalars start from a kernel, not a copy from host memory, so the
-// ticket of the last-workgroup reductions starts at zero on every call.
-__global__ void k_sc_init(CgScalars* sc, double tol, int64_t maxit, int32_t stop,
-                          double* history) {
-  CgScalars v{};
-  v.tol = tol;
-  v.maxit = maxit;
-  v.stop = stop;
-  v.history = history;
-  *sc = v;
-}
-
 fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x, const fc_solve_opts& o,
                             fc_solve_info* info, hipStream_t s) {
   fc_problem_s& pb = *pc.pb;
@@ -1122,12 +1192,6 @@ fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x, const 
     set_error("fc_pcg_solve_noalloc: the current device is not the problem's");
     return FC_E_ARG;
   }
-  // the SpMV with its fused dot (FC_CG_SPLIT_DOT=0) leaves one partial per
-  // workgroup, which must fit the scratch's partial sums
-  if (!split_dot() && (int64_t)spmv_num_blocks(pb.A) > (kNoAllocPartials - 8) / 4) {
-    set_error("fc_pcg_solve_noalloc: too many SpMV partials for the fused dot");
-    return FC_E_UNSUPPORTED;
-  }
   double* base = nullptr;
   FC_TRY_ST(scratch_for(dev, &base));
   // a workspace view of the scratch: only the members the FP64 steps use
@@ -1139,19 +1203,9 @@ fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x, const 
   w.q = base + 3 * kNoAllocMaxDofs;
   w.t = base + 4 * kNoAllocMaxDofs;
   w.partial = base + 5 * kNoAllocMaxDofs;
-  w.partial_len = kNoAllocPartials;
-  w.sc = reinterpret_cast<CgScalars*>(w.partial + kNoAllocPartials);
-  hipLaunchKernelGGL(k_sc_init, dim3(1), dim3(1), 0, s, w.sc, o.tol, o.maxit, o.stop,
-                     o.history_dev);
-  hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, s, x, 0.0, n);
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, b, w.r, n);
-  FC_HIP(hipGetLastError());
-  FC_HIP(launch_schwarz_phase1(pc, 0, w.r, nullptr, nullptr, s));
-  FC_HIP(launch_schwarz_pull(pc, w.r, w.z, s));
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, w.z, w.p, n);
-  hipLaunchKernelGGL(k_cg_start, dim3(kRedBlocks), dim3(256), 0, s, w.r, w.z, n, w.partial,
-                     w.sc);
-  FC_HIP(hipGetLastError());
+  w.partial_len = kPartials;
+  w.sc = reinterpret_cast<CgScalars*>(w.partial + kPartials);
+  FC_HIP(enqueue_start(pc, w, b, x, o.tol, o.maxit, o.stop, o.history_dev, 0, s));
   const int chunk = o.check_every > 0 ? o.check_every : 16;
   const int64_t max_chunks = (o.maxit + chunk - 1) / chunk + 1;
   CgScalars h{};
@@ -1165,9 +1219,7 @@ fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x, const 
   // ||b - A x|| / ||b|| with the FP64 matrix
   FC_HIP(launch_spmv(pb.A, x, w.t, s));
   double* out2 = w.partial + w.partial_len - 2;
-  hipLaunchKernelGGL(k_resid, dim3(kRedBlocks), dim3(256), 0, s, b, w.t, n, w.partial, w.sc,
-                     out2);
-  FC_HIP(hipGetLastError());
+  FC_HIP(enqueue_resid(w, b, w.t, s));
   double v[2] = {0.0, 0.0};
   FC_HIP(hipMemcpyAsync(v, out2, sizeof(v), hipMemcpyDeviceToHost, s));
   FC_HIP(hipStreamSynchronize(s));
@@ -1225,20 +1277,8 @@ extern "C" fc_status fc_learned_snapshots(fc_precond pc, const double* b, const 
   hipStream_t s = w.stream;
   FC_HIP(hipEventRecord(w.ev[0], user));
   FC_HIP(hipStreamWaitEvent(s, w.ev[0], 0));
-  CgScalars init{};
-  init.tol = tol;
-  init.maxit = (int64_t)iters[n_snap - 1] + 1;
-  init.stop = FC_STOP_RESIDUAL;
-  FC_HIP(hipMemcpyAsync(w.sc, &init, sizeof(CgScalars), hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, s, x, 0.0, n);
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, b, w.r, n);
-  FC_HIP(hipGetLastError());
-  FC_HIP(launch_schwarz_phase1(*pc, 0, w.r, nullptr, nullptr, s));
-  FC_HIP(launch_schwarz_pull(*pc, w.r, w.z, s));
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, w.z, w.p, n);
-  hipLaunchKernelGGL(k_cg_start, dim3(kRedBlocks), dim3(256), 0, s, w.r, w.z, n, w.partial,
-                     w.sc);
-  FC_HIP(hipGetLastError());
+  FC_HIP(enqueue_start(*pc, w, b, x, tol, (int64_t)iters[n_snap - 1] + 1, FC_STOP_RESIDUAL,
+                       nullptr, 0, s));
   const int64_t nv = c.nvox;
   int j = 0;
   int64_t it = 0;

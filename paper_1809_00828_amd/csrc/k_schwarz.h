@@ -5,9 +5,13 @@
 namespace fc {
 // Phase 1 only: y_B = P_B R_B (r - alpha q) for every block (q may be NULL,
 // then r is gathered as is).  precision 0 = FP64, 1 = FP32, 2 = BF16 copy of
-// the local inverses.  Skipped when sc->done is set (sc may be NULL).
+// the local inverses.  Skipped when sc->done is set (sc may be NULL).  With
+// ai.np > 0 (schwarz_takes_alpha) every workgroup derives alpha from the (p, q)
+// partials, and the first one stores it.
 hipError_t launch_schwarz_phase1(const fc_precond_s& pc, int precision, const double* r,
-                                 const double* q, const CgScalars* sc, hipStream_t s);
+                                 const double* q, CgScalars* sc, const AlphaIn ai, hipStream_t s);
+// Whether the block products of this precision can derive alpha themselves.
+bool schwarz_takes_alpha(const fc_precond_s& pc, int precision);
 // Phase 2 only: z = sum_B R_B^T y_B + fallback * r.
 hipError_t launch_schwarz_pull(const fc_precond_s& pc, const double* r, double* z,
                                hipStream_t s);

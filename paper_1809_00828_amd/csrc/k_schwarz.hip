@@ -48,12 +48,12 @@ __global__ __launch_bounds__(256) void k_schwarz_large(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
     const int32_t* __restrict__ block_elem, int nn, int bd, int m,
     const double* __restrict__ r, const double* __restrict__ q, const double* __restrict__ isd,
-    const CgScalars* __restrict__ sc, double* __restrict__ y, int64_t n_blocks) {
-  __shared__ double rB[256];
+    CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks) {
+  __shared__ double rB[256], red[16];
   if (sc && sc->done) return;
   const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-  if (blk >= n_blocks) return;
-  const double alpha = (sc && q) ? sc->alpha : 0.0;
+  double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
+  if (ai.np && !cg_alpha(sc, ai, red, &alpha)) return;
   const int i = threadIdx.x;
   const int64_t e = block_elem[blk];
   int64_t dof = -1;
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
     const int32_t* __restrict__ block_elem, int nn, int bd, int m,
     const double* __restrict__ r, const double* __restrict__ q, const double* __restrict__ isd,
-    const CgScalars* __restrict__ sc, double* __restrict__ y, int64_t n_blocks,
+    CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks,
     const int32_t* __restrict__ list, const int32_t* __restrict__ skip) {
   using A = typename Acc<T>::type;
   constexpr int kStageRows = StageRows<T>::value;
@@ -85,25 +85,37 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
   // LDS traffic of the rotated reads
   __shared__ A rB[256];
   __shared__ __align__(16) T tile[kStageRows * 256];
+  __shared__ double red[16];
   if (sc && sc->done) return;
   // list: the workgroups handle only the listed blocks; skip: blocks
   // flagged there are left to another launch
   const int64_t blk = list ? (int64_t)list[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x);
-  if (blk >= n_blocks) return;
-  if (skip && skip[blk]) return;
-  const double alpha = (sc && q) ? sc->alpha : 0.0;
   const int i = threadIdx.x;
   const bool act = i < m;
-  const int64_t e = block_elem[blk];
   int64_t dof = -1;
-  if (act) {
-    dof = block_dof(elem_nodes, e, nn, bd, i);
-    rB[i] = dof >= 0 ? (A)(gather_r(r, q, alpha, dof) * (isd ? isd[dof] : 1.0)) : A(0);
-  }
+  bool stop = false;
+  const bool skipped = skip && skip[blk];
+  if (skipped && blockIdx.x != 0) return;   // the first workgroup stores alpha
+  // the right-hand side, gathered behind the first loads of the inverse
+  auto gather = [&] {
+    double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
+    const int64_t e = block_elem[blk];
+    double gr = 0.0, gq = 0.0, gs = 1.0;
+    if (act) {
+      dof = block_dof(elem_nodes, e, nn, bd, i);
+      if (dof >= 0) {
+        gr = r[dof];
+        if (q) gq = q[dof];
+        if (isd) gs = isd[dof];
+      }
+    }
+    if (ai.np) stop = !cg_alpha(sc, ai, red, &alpha);
+    if (act) rB[i] = dof >= 0 ? (A)((q ? fma(-alpha, gq, gr) : gr) * gs) : A(0);
+  };
   const T* Qb = P + blk * block_stride;
-  const double v = kRuns ? sym_block_staged_runs<T, A>(Qb, rB, m, i, tile)
-                         : sym_block_staged_rows<T, A>(Qb, rB, m, i, tile);
-  if (act) y[blk * m + i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
+  const double v = kRuns ? sym_block_staged_runs<T, A>(Qb, rB, m, i, tile, gather)
+                         : sym_block_staged_rows<T, A>(Qb, rB, m, i, tile, gather);
+  if (act && !stop && !skipped) y[blk * m + i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
 }
 
 // m <= 64: each wave handles floor(64/m) blocks, one lane per output row.
@@ -122,12 +134,12 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
     const int32_t* __restrict__ block_elem, int nn, int bd, int m_arg,
     const double* __restrict__ r, const double* __restrict__ q, const double* __restrict__ isd,
-    const CgScalars* __restrict__ sc, double* __restrict__ y, int64_t n_blocks,
+    CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks,
     const PullLattice lat) {
-  __shared__ double rB[4][64];
+  __shared__ double rB[4][64], red[16];
   if (sc && sc->done) return;
   const int m = kM > 0 ? kM : m_arg;
-  const double alpha = (sc && q) ? sc->alpha : 0.0;
+  double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
   const int bpw = 64 / m;
   const int w = threadIdx.x / 64, l = threadIdx.x % 64;
   const int lb = l / m, i = l % m;
@@ -140,7 +152,6 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
   constexpr int kH = kM / 2;
   T v[kH + 1];
   int64_t dof = -1;
-  double rv = 0.0;
   double g_r = 0.0, g_q = 0.0, g_s = 1.0;
   if constexpr (kLat) {
     // the gathered entries are loaded first and the stored rows next, all
@@ -164,14 +175,18 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
     }
     if constexpr (kNP < kH + 1) v[kH] = Pb[kH * kM + i];
   }
-  if constexpr (kLat) {
-    rv = (q ? fma(-alpha, g_q, g_r) : g_r) * (isd ? g_s : 1.0);
-  } else {
+  if constexpr (!kLat) {
     if (active) {
       dof = block_dof(elem_nodes, block_elem[blk], nn, bd, i);
-      rv = dof >= 0 ? gather_r(r, q, alpha, dof) * (isd ? isd[dof] : 1.0) : 0.0;
+      if (dof >= 0) {
+        g_r = r[dof];
+        if (q) g_q = q[dof];
+        if (isd) g_s = isd[dof];
+      }
     }
   }
+  if (ai.np && !cg_alpha(sc, ai, red, &alpha)) return;
+  const double rv = (q ? fma(-alpha, g_q, g_r) : g_r) * (isd ? g_s : 1.0);
   if (active) rB[w][l] = rv;
   __syncthreads();
   double out;
@@ -510,22 +525,22 @@ inline bool staged_runs(int m) { return m > 128; }
 template <typename T>
 static void launch_staged(const fc_precond_s& pc, const T* Q, int64_t n_launch,
                           const double* r, const double* q, const double* isd,
-                          const CgScalars* sc, const int32_t* list, const int32_t* skip,
-                          hipStream_t s) {
+                          CgScalars* sc, const AlphaIn ai, const int32_t* list,
+                          const int32_t* skip, hipStream_t s) {
   const dim3 g((unsigned)n_launch), b(64 * ((pc.m + 63) / 64));
   if (staged_runs(pc.m))
     hipLaunchKernelGGL((k_schwarz_sym_staged<T, true>), g, b, 0, s, Q, sym_block_stride(pc.m),
-                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, pc.y,
+                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, ai, pc.y,
                        pc.n_blocks, list, skip);
   else
     hipLaunchKernelGGL((k_schwarz_sym_staged<T, false>), g, b, 0, s, Q, sym_block_stride(pc.m),
-                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, pc.y,
+                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, ai, pc.y,
                        pc.n_blocks, list, skip);
 }
 
 template <typename T, bool kSym>
 static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, const double* q,
-                         const CgScalars* sc, hipStream_t s) {
+                         CgScalars* sc, const AlphaIn ai, hipStream_t s) {
   const double* isd = sizeof(T) == 8 ? nullptr : pc.isd;
   const fc_problem_s& pb = *pc.pb;
   if (pc.n_blocks == 0) return hipSuccess;
@@ -537,12 +552,12 @@ static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, co
   if (pc.m > 64) {
     const int threads = 64 * ((pc.m + 63) / 64);
     if (kSym && variant)
-      launch_staged<T>(pc, P, pc.n_blocks, r, q, isd, sc, nullptr,
+      launch_staged<T>(pc, P, pc.n_blocks, r, q, isd, sc, ai, nullptr,
                        sizeof(T) == 4 ? pc.unsafe_flag32 : nullptr, s);
     else
       hipLaunchKernelGGL((k_schwarz_large<T, kSym>), dim3((unsigned)pc.n_blocks), dim3(threads),
                          0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r,
-                         q, isd, sc, pc.y, pc.n_blocks);
+                         q, isd, sc, ai, pc.y, pc.n_blocks);
   } else {
     const int bpw = 64 / pc.m;
     const int64_t per_wg = 4 * (int64_t)bpw;
@@ -555,11 +570,11 @@ static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, co
     if (lat && KM > 0)                                                                         \
       hipLaunchKernelGGL((k_schwarz_small<T, kSym, KM, true>), dim3((unsigned)nwg), dim3(256), \
                          0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, \
-                         r, q, isd, sc, pc.y, pc.n_blocks, pc.lat);                            \
+                         r, q, isd, sc, ai, pc.y, pc.n_blocks, pc.lat);                        \
     else                                                                                       \
       hipLaunchKernelGGL((k_schwarz_small<T, kSym, KM, false>), dim3((unsigned)nwg),           \
                          dim3(256), 0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn,    \
-                         pc.bdim, pc.m, r, q, isd, sc, pc.y, pc.n_blocks, pc.lat);             \
+                         pc.bdim, pc.m, r, q, isd, sc, ai, pc.y, pc.n_blocks, pc.lat);         \
   } while (0)
     switch (kSym ? pc.m : 0) {
       case 8: FC_SMALL_LAUNCH(8); break;
@@ -602,19 +617,25 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_list(
   if (i < m) y[blk * m + i] = sym_row<double>(Q + blk * stride, rB, m, i);
 }
 
+bool schwarz_takes_alpha(const fc_precond_s& pc, int precision) {
+  return pc.n_blocks > 0 && precision != 2;
+}
+
 hipError_t launch_schwarz_phase1(const fc_precond_s& pc, int precision, const double* r,
-                                 const double* q, const CgScalars* sc, hipStream_t s) {
+                                 const double* q, CgScalars* sc, const AlphaIn ai,
+                                 hipStream_t s) {
   switch (precision) {
     case 0:
-      if (pc.Q) return phase1<double, true>(pc, pc.Q, r, q, sc, s);
-      return phase1<double, false>(pc, pc.P, r, q, sc, s);
+      if (pc.Q) return phase1<double, true>(pc, pc.Q, r, q, sc, ai, s);
+      return phase1<double, false>(pc, pc.P, r, q, sc, ai, s);
     case 1: {
       if (!pc.Q32 || !pc.Q) return hipErrorInvalidValue;
-      hipError_t e = phase1<float, true>(pc, pc.Q32, r, q, sc, s);
+      hipError_t e = phase1<float, true>(pc, pc.Q32, r, q, sc, ai, s);
       if (e != hipSuccess || pc.n_unsafe32 == 0) return e;
-      const fc_problem_s& pb = *pc.pb;
+      // the first launch has stored alpha
       if (pc.m > 64)
-        launch_staged<double>(pc, pc.Q, pc.n_unsafe32, r, q, nullptr, sc, pc.unsafe32, nullptr, s);
+        launch_staged<double>(pc, pc.Q, pc.n_unsafe32, r, q, nullptr, sc, AlphaIn{}, pc.unsafe32,
+                              nullptr, s);
       else
         hipLaunchKernelGGL(k_schwarz_sym_list, dim3((unsigned)pc.n_unsafe32),
                            dim3(64 * ((pc.m + 63) / 64)), 0, s, pc.Q, sym_block_stride(pc.m),
@@ -647,7 +668,7 @@ hipError_t launch_schwarz_pull(const fc_precond_s& pc, const double* r, double* 
 
 hipError_t launch_schwarz_apply(const fc_precond_s& pc, const double* r, double* z,
                                 hipStream_t s) {
-  hipError_t e = launch_schwarz_phase1(pc, 0, r, nullptr, nullptr, s);
+  hipError_t e = launch_schwarz_phase1(pc, 0, r, nullptr, nullptr, AlphaIn{}, s);
   if (e != hipSuccess) return e;
   return launch_schwarz_pull(pc, r, z, s);
 }

@@ -3,10 +3,11 @@
 #include "fc_internal.h"
 
 namespace fc {
-// Number of workgroups (and so of dot partials) of the fused SpMV.
-int spmv_num_blocks(const DeviceBsr& A);
-// q = A p leaving one partial (p, q) per workgroup in partial[0..nb)
-// (skipped when sc->done is set)
+// (p, q) partials the product can leave, one per workgroup; 0: it has too many
+// workgroups, and the dot is a pass of its own.
+int spmv_dot_blocks(const DeviceBsr& A);
+// q = A p, with one partial (p, q) per workgroup in partial[0 ..
+// spmv_dot_blocks(A)) unless partial is null (skipped when sc->done is set)
 hipError_t launch_spmv_pq(const DeviceBsr& A, const double* p, double* q, CgScalars* sc,
                           double* partial, hipStream_t s);
 // q = A p with the rows A.rows_hi from the FP64 values and p, and the rows

@@ -374,42 +374,98 @@ __device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, in
   return acc;
 }
 
+// Product of one scalar lattice row with x by eight lanes (lane = 0 .. 7), eight
+// entries per lane and round, from the row layout: the order k_spmv_bsr<1, 8>
+// takes.  Every lane receives the sum.
+__device__ __forceinline__ double lattice_row8(const double* __restrict__ v, int L,
+                                               const RowBox& box, int n1,
+                                               const double* __restrict__ x, int lane) {
+  double acc = 0.0;
+  for (int k = lane; k < L; k += 64) {
+    double a[8], xv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int ku = k + 8 * u;
+      const bool on = ku < L;
+      a[u] = on ? v[ku] : 0.0;
+      xv[u] = on ? x[lattice_col(box, ku, n1)] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = fma(a[u], xv[u], acc);
+  }
+  return group_sum<8>(acc);
+}
+
+// The first rest_blocks workgroups take the boundary vertex rows (x = 0 and x
+// = n1 - 1 of every line, 32 rows each) from the row layout, the others the
+// slices: launched apart, the 1.6 % of the rows at 64^3 cells, p = 2 cost 11
+// us of load latency after the slices' 217 us.  partial (may be null): (x, y)
+// per workgroup.
 template <int P, bool kNT>
-__global__ __launch_bounds__(256) void k_spmv_sell(const double* __restrict__ sv,
-                                                   const int64_t* __restrict__ off,
-                                                   int64_t n_slices, int cv, const FastDiv dspl,
-                                                   int nv, int nn, const double* __restrict__ x,
-                                                   double* __restrict__ y,
-                                                   const CgScalars* __restrict__ sc,
-                                                   const LatticeInfo lat) {
+__global__ __launch_bounds__(256) void k_spmv_sell(
+    const double* __restrict__ sv, const int64_t* __restrict__ off, int64_t n_slices, int cv,
+    const FastDiv dspl, int nv, int nn, const double* __restrict__ val, int rest_blocks,
+    int64_t n_rest, const double* __restrict__ x, double* __restrict__ y,
+    double* __restrict__ partial, const CgScalars* __restrict__ sc, const LatticeInfo lat) {
+  __shared__ double lds[16];
   if (sc && sc->done) return;
-  // the slice of this wave (wave-uniform, so everything derived from it
-  // stays in scalar registers; no division by a run-time value)
-  const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 +
-                    __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  if (s >= n_slices) return;
   const int l = threadIdx.x % 64;
-  const SellSlice sl = sell_slice_fast((uint32_t)s, cv, dspl);
   const int n1 = lat.n1;
-  const uint32_t lz = fdiv((uint32_t)sl.line, lat.dn1);
-  const int y0 = lat.dim >= 2 ? (int)((uint32_t)sl.line - lz * (uint32_t)n1) : 0;
-  const int z0 = lat.dim == 3 ? (int)lz : 0;
-  int lo1 = 0, len1 = 1, lo2 = 0, len2 = 1;
-  if (lat.dim >= 2) dir_box_p<P>(y0, n1, &lo1, &len1);
-  if (lat.dim == 3) dir_box_p<P>(z0, n1, &lo2, &len2);
-  const int count = sl.vertex ? nv : nn;
-  const int i = sl.chunk * 64 + l;
-  const bool valid = i < count;
-  const int xr = sell_x_p<P>(sl.vertex, valid ? i : count - 1);
-  const int lo0 = sl.vertex ? xr - P : (xr / P) * P;
-  const double* vs = sv + off[s];
-  const double* xb = x + lo0 + (int64_t)n1 * (lo1 + (int64_t)n1 * lo2);
-  const int npen = len1 * len2;
-  // two pencils per round: 1 % faster than four and 3 % faster than eight
-  // at 64^3 cells, p = 2
-  const double acc = sl.vertex ? sell_pencils<2 * P + 1, kNT>(vs, l, xb, len1, npen, n1)
-                               : sell_pencils<P + 1, kNT>(vs, l, xb, len1, npen, n1);
-  if (valid) y[xr + (int64_t)n1 * (y0 + (int64_t)n1 * z0)] = acc;
+  double dot = 0.0;
+  if ((int)blockIdx.x < rest_blocks) {
+    const int64_t rr = (int64_t)blockIdx.x * 32 + threadIdx.x / 8;
+    if (rr < n_rest) {
+      const uint32_t line = (uint32_t)(rr >> 1);
+      const uint32_t lz = fdiv(line, lat.dn1);
+      const int c[3] = {(rr & 1) ? n1 - 1 : 0, lat.dim == 3 ? (int)(line - lz * n1) : (int)line,
+                        lat.dim == 3 ? (int)lz : 0};
+      const RowBox box = row_box_at(c, lat);
+      const double acc = lattice_row8(val + lattice_row_start_at(c, box, lat),
+                                      box.len[0] * box.len[1] * box.len[2], box, n1, x,
+                                      threadIdx.x % 8);
+      if (threadIdx.x % 8 == 0) {
+        const int64_t row = c[0] + (int64_t)n1 * (c[1] + (int64_t)n1 * c[2]);
+        y[row] = acc;
+        if (partial) dot = x[row] * acc;
+      }
+    }
+  } else {
+    // the slice of this wave (wave-uniform, so everything derived from it
+    // stays in scalar registers; no division by a run-time value)
+    const int64_t s = xcd_remap(blockIdx.x - rest_blocks, gridDim.x - rest_blocks) * 4 +
+                      __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    if (s < n_slices) {
+      const SellSlice sl = sell_slice_fast((uint32_t)s, cv, dspl);
+      const uint32_t lz = fdiv((uint32_t)sl.line, lat.dn1);
+      const int y0 = lat.dim == 3 ? (int)((uint32_t)sl.line - lz * (uint32_t)n1) : (int)sl.line;
+      const int z0 = lat.dim == 3 ? (int)lz : 0;
+      int lo1 = 0, len1 = 1, lo2 = 0, len2 = 1;
+      dir_box_p<P>(y0, n1, &lo1, &len1);
+      if (lat.dim == 3) dir_box_p<P>(z0, n1, &lo2, &len2);
+      const int count = sl.vertex ? nv : nn;
+      const int i = sl.chunk * 64 + l;
+      const bool valid = i < count;
+      const int xr = sell_x_p<P>(sl.vertex, valid ? i : count - 1);
+      const int lo0 = sl.vertex ? xr - P : (xr / P) * P;
+      const double* vs = sv + off[s];
+      const double* xb = x + lo0 + (int64_t)n1 * (lo1 + (int64_t)n1 * lo2);
+      const int npen = len1 * len2;
+      // two pencils per round: 1 % faster than four and 3 % faster than eight
+      // at 64^3 cells, p = 2
+      const double acc = sl.vertex ? sell_pencils<2 * P + 1, kNT>(vs, l, xb, len1, npen, n1)
+                                   : sell_pencils<P + 1, kNT>(vs, l, xb, len1, npen, n1);
+      const int64_t row = xr + (int64_t)n1 * (y0 + (int64_t)n1 * z0);
+      if (valid) {
+        y[row] = acc;
+        if (partial) dot = x[row] * acc;
+      }
+    }
+  }
+  if (!partial) return;
+  dot = wave_sum_last(dot);
+  if (l == 63) lds[threadIdx.x / 64] = dot;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[blockIdx.x] = ((lds[0] + lds[1]) + lds[2]) + lds[3];
 }
 
 // Launch shape.  G lanes per block row: enough lanes that one pass of U
@@ -417,9 +473,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell(const double* __restrict__ sv
 // rounded up to 8, 16, 32 or 64 (FC_SPMV_GROUP overrides it).  Measured on
 // MI355X this picks the fastest width for both FP64 workloads: 64 for the
 // 3x3 rows of 32^3-cell p = 3 elasticity (about 122 blocks), 8 for the
-// scalar rows of 64^3-cell p = 2 Poisson (about 63).  The PCG variant uses
-// one tile per workgroup unless FC_SPMV_FUSED_GRID caps the grid (then
-// workgroups loop over tiles).
+// scalar rows of 64^3-cell p = 2 Poisson (about 63).
 static int env_int(const char* name, int dflt) {
   const char* e = std::getenv(name);
   return e ? std::atoi(e) : dflt;
@@ -446,10 +500,21 @@ static int64_t num_tiles(const DeviceBsr& A) {
   return (A.n_rows + rpw - 1) / rpw;
 }
 
-static int64_t fused_grid(const DeviceBsr& A) {
-  static const int cap = env_int("FC_SPMV_FUSED_GRID", 0);
-  const int64_t nt = num_tiles(A);
-  return cap > 0 ? std::min<int64_t>(nt, cap) : nt;
+static bool lattice_allowed() {
+  static const bool v = env_int("FC_SPMV_LATTICE", 1) != 0;
+  return v;
+}
+
+static bool use_sell(const DeviceBsr& A) {
+  return lattice_allowed() && A.lat.dim > 0 && A.bdim == 1 && A.sell_val;
+}
+
+// workgroups of the sliced product: boundary rows, then slices
+static int sell_rest_blocks(const DeviceBsr& A) { return (int)((A.n_rest + 31) / 32); }
+
+// Workgroups of the whole-matrix product (one (x, y) partial each when asked).
+static int64_t spmv_blocks(const DeviceBsr& A) {
+  return use_sell(A) ? sell_rest_blocks(A) + (A.n_slices + 3) / 4 : num_tiles(A);
 }
 
 template <int B, typename T, typename XT>
@@ -460,16 +525,13 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
   const int64_t n_rows = rows ? n_list : A.n_rows;
   const int64_t nt = (n_rows + 256 / G - 1) / (256 / G);
   if (nt == 0) return hipSuccess;
-  const int64_t nb = (partial && !rows) ? fused_grid(A) : nt;
-  static const bool lat_allowed = env_int("FC_SPMV_LATTICE", 1) != 0;
-  const bool lat = lat_allowed && A.lat.dim > 0;
-  // the whole scalar matrix with its sliced copy, no fused dot: the sliced
-  // rows, then the boundary vertex rows from the row layout
+  const bool lat = lattice_allowed() && A.lat.dim > 0;
+  // the whole scalar matrix with its sliced copy
   if constexpr (B == 1 && sizeof(T) == 8 && sizeof(XT) == 8) {
-    if (lat && A.sell_val && !rows && !partial) {
+    if (use_sell(A) && !rows) {
       const int cn = A.sell_nn > 0 ? (A.sell_nn + 63) / 64 : 0;
       const FastDiv dspl = make_fastdiv((uint32_t)(A.sell_cv + cn));
-      dim3 g((unsigned)((A.n_slices + 3) / 4)), b(256);
+      dim3 g((unsigned)spmv_blocks(A)), b(256);
       // values streamed non-temporally (3 % faster at 64^3 cells, p = 2;
       // FC_SPMV_SELL_NT=0 reads them through the caches)
       static const bool sell_nt = env_int("FC_SPMV_SELL_NT", 1) != 0;
@@ -477,12 +539,14 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
   do {                                                                                        \
     if (sell_nt)                                                                              \
       hipLaunchKernelGGL((k_spmv_sell<PP, true>), g, b, 0, s, A.sell_val, A.sell_off,         \
-                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, (const double*)x, y, \
-                         sc, A.lat);                                                          \
+                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, val,              \
+                         sell_rest_blocks(A), A.n_rest, (const double*)x, y, partial, sc,     \
+                         A.lat);                                                              \
     else                                                                                      \
       hipLaunchKernelGGL((k_spmv_sell<PP, false>), g, b, 0, s, A.sell_val, A.sell_off,        \
-                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, (const double*)x, y, \
-                         sc, A.lat);                                                          \
+                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, val,              \
+                         sell_rest_blocks(A), A.n_rest, (const double*)x, y, partial, sc,     \
+                         A.lat);                                                              \
   } while (0)
       switch (A.lat.p) {
         case 1: FC_SELL(1); break;
@@ -491,12 +555,10 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
         default: FC_SELL(4); break;
       }
 #undef FC_SELL
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess || A.n_rest == 0) return e;
-      return spmv_dispatch<B, T, XT>(A, val, x, y, s, sc, nullptr, A.sell_rest, A.n_rest);
+      return hipGetLastError();
     }
   }
-  dim3 grid((unsigned)nb), block(256);
+  dim3 grid((unsigned)nt), block(256);
   // 3x3 blocks: two per lane per pass (nine values each), FP64 values
   // non-temporal; scalar rows: eight per lane per pass through the caches
   constexpr bool kNT = B != 1 && sizeof(T) == 8;
@@ -536,10 +598,19 @@ hipError_t launch_spmv(const DeviceBsr& A, const double* x, double* y, hipStream
   return spmv_any<double>(A, A.val, x, y, s, nullptr, nullptr);
 }
 
-int spmv_num_blocks(const DeviceBsr& A) { return (int)fused_grid(A); }
+// Up to 1,024 workgroups the product leaves one (x, y) partial per workgroup
+// (every workgroup of the next kernel sums them, four loads a thread at most);
+// more, and the reduction at the end of a workgroup costs more than a pass
+// over both vectors: it holds the workgroup's waves until the slowest row is
+// done (11 % of the product at 32^3 cells, p = 3 elasticity).
+int spmv_dot_blocks(const DeviceBsr& A) {
+  const int64_t nb = spmv_blocks(A);
+  return nb <= 1024 ? (int)nb : 0;
+}
 
 // Host side of the sliced copy: slice offsets (each slice holds 64 lanes of
-// its box size), the boundary vertex rows, then the copy on the device.
+// its box size), then the copy on the device; the two boundary vertex rows of
+// every line stay in the row layout.
 static hipError_t spmv_build_sell(DeviceBsr& A, hipStream_t s) {
   const LatticeInfo lat = A.lat;
   const int n1 = lat.n1, p = lat.p, n = (n1 - 1) / p;
@@ -554,38 +625,29 @@ static hipError_t spmv_build_sell(DeviceBsr& A, hipStream_t s) {
   std::vector<int64_t> off;
   off.reserve((size_t)(lines * (cv + cn) + 1));
   off.push_back(0);
-  std::vector<int32_t> rest;
   for (int64_t line = 0; line < lines; ++line) {
     const int y0 = (int)(line % n1), z0 = lat.dim == 3 ? (int)(line / n1) : 0;
     const int64_t yz = (int64_t)len(y0) * (lat.dim == 3 ? len(z0) : 1);
     for (int k = 0; k < cv; ++k) off.push_back(off.back() + 64 * yz * (2 * p + 1));
     for (int k = 0; k < cn; ++k) off.push_back(off.back() + 64 * yz * (p + 1));
-    const int64_t r0 = (int64_t)n1 * (y0 + (int64_t)n1 * z0);
-    rest.push_back((int32_t)r0);
-    if (n1 > 1) rest.push_back((int32_t)(r0 + n1 - 1));
   }
   const int64_t ns = (int64_t)off.size() - 1;
   hipError_t e = hipMalloc(&A.sell_val, (size_t)off.back() * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&A.sell_off, off.size() * sizeof(int64_t));
-  if (e == hipSuccess) e = hipMalloc(&A.sell_rest, rest.size() * sizeof(int32_t));
   if (e == hipSuccess)
     e = hipMemcpyAsync(A.sell_off, off.data(), off.size() * sizeof(int64_t),
-                       hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(A.sell_rest, rest.data(), rest.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_sell_build, dim3(4096), dim3(256), 0, s, A.val, A.sell_off, ns, cv, cn,
                        nv, nn, lat, A.sell_val);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(s);   // the host vectors die here
+  if (e == hipSuccess) e = hipStreamSynchronize(s);   // the host vector dies here
   if (e != hipSuccess) {
-    for (void* q : {(void*)A.sell_val, (void*)A.sell_off, (void*)A.sell_rest})
+    for (void* q : {(void*)A.sell_val, (void*)A.sell_off})
       if (q) (void)hipFree(q);
     A.sell_val = nullptr;
     A.sell_off = nullptr;
-    A.sell_rest = nullptr;
     // without room for the copy the row layout serves every product
     if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
@@ -597,7 +659,7 @@ static hipError_t spmv_build_sell(DeviceBsr& A, hipStream_t s) {
   A.sell_cv = cv;
   A.sell_nv = nv;
   A.sell_nn = nn;
-  A.n_rest = (int64_t)rest.size();
+  A.n_rest = 2 * lines;
   return hipSuccess;
 }
 

@@ -79,12 +79,12 @@ struct StageRows {
 // non-temporally, into LDS, and each thread then reads its own entry and
 // the rotated one back from LDS, so HBM and L2 see each stored entry exactly
 // once.  The next chunk's loads are issued before the current chunk is
-// summed.  rB holds the block's gathered right-hand side (m entries, in
-// LDS).  tile (16-byte aligned) holds kStageRows * m <= kStageRows * 256 entries,
+// summed.  gather() writes the block's right-hand side to rB (m entries, in
+// LDS) once the first chunk's loads are in flight.  tile (16-byte aligned) holds kStageRows * m <= kStageRows * 256 entries,
 // as tile[kk * m + j] for stored row k0 + kk.
-template <typename T, typename RB>
+template <typename T, typename RB, typename F>
 __device__ __forceinline__ double sym_block_staged_runs(const T* __restrict__ Qb, const RB* rB,
-                                                   int m, int i, T* tile) {
+                                                        int m, int i, T* tile, F&& gather) {
   using A = typename Acc<T>::type;
   constexpr int kStageRows = StageRows<T>::value;
   constexpr int V = 16 / sizeof(T);                // entries per 16-byte piece
@@ -114,6 +114,7 @@ __device__ __forceinline__ double sym_block_staged_runs(const T* __restrict__ Qb
   };
   tv v[kPer];
   load_chunk(0, v);
+  gather();
   for (int k0 = 0; k0 <= h; k0 += kStageRows) {
     const int cnt = min(kStageRows, h + 1 - k0) * m;   // entries of this chunk
     __syncthreads();   // previous chunk's reads are done
@@ -147,9 +148,9 @@ __device__ __forceinline__ double sym_block_staged_runs(const T* __restrict__ Qb
 // The same with every thread loading its own entry of each stored row of
 // the chunk (8-byte loads) and keeping it in a register; only the rotated
 // entries are read back from LDS (tile[kk * 256 + j]).
-template <typename T, typename RB>
+template <typename T, typename RB, typename F>
 __device__ __forceinline__ double sym_block_staged_rows(const T* __restrict__ Qb, const RB* rB,
-                                                        int m, int i, T* tile) {
+                                                        int m, int i, T* tile, F&& gather) {
   using A = typename Acc<T>::type;
   constexpr int kStageRows = StageRows<T>::value;
   const bool act = i < m;
@@ -165,6 +166,7 @@ __device__ __forceinline__ double sym_block_staged_rows(const T* __restrict__ Qb
       const T* src = Qb + (int64_t)k * m + i;
       v[kk] = (act && k <= h) ? __builtin_nontemporal_load(src) : T(0);
     }
+    if (k0 == 0) gather();
     __syncthreads();   // previous chunk's rotated reads are done
 #pragma unroll
     for (int kk = 0; kk < kStageRows; ++kk) tile[kk * 256 + i] = v[kk];
