@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -111,8 +112,39 @@ static fc_status upload_system_body(const HostSystem& S, hipStream_t stream, fc_
   FC_HIP(launch_diag(*pb, stream));
   if (S.dim > 0) FC_HIP(spmv_enable_lattice(pb->A, S.dim, S.p * S.n + 1, S.p, stream));
   pb->A.group = spmv_group_for(pb->A);
+  if (S.dim >= 2 && S.dim <= 3 && S.n > 0 && S.p > 0 &&
+      S.n_el == (int64_t)std::pow((double)S.n, S.dim) &&
+      S.nn == (int)std::pow(S.p + 1.0, S.dim)) {
+    const PullLattice L = make_pull_lattice(S.dim, S.n, S.p);
+    bool ok = false;
+    FC_HIP(schwarz_check_cells(*pb, L, &ok, stream));
+    if (ok) pb->cells = L;
+  }
   FC_HIP(hipStreamSynchronize(stream));
   *out = pb.release();
+  return FC_OK;
+}
+
+fc_status precond_ensure_map(fc_precond_s& pc, hipStream_t s) {
+  static std::mutex mu;   // a batch may ask for the map of a shared handle
+  std::lock_guard<std::mutex> lock(mu);
+  if (pc.inv_ptr) return FC_OK;
+  const int64_t n = pc.pb->n_nodes + 1;
+  struct Tmp {
+    int32_t *work = nullptr, *sums = nullptr, *ptr = nullptr, *idx = nullptr;
+    ~Tmp() {
+      for (int32_t* q : {work, sums, ptr, idx})
+        if (q) (void)hipFree(q);
+    }
+  } t;
+  FC_TRY(dev_alloc(&t.work, (size_t)n));
+  FC_TRY(dev_alloc(&t.sums, (size_t)map_scan_blocks(n)));
+  FC_TRY(dev_alloc(&t.ptr, (size_t)n));
+  FC_TRY(dev_alloc(&t.idx, (size_t)std::max<int64_t>(1, pc.n_blocks * pc.nn)));
+  FC_HIP(launch_build_map(pc, pc.pb->n_nodes, t.ptr, t.idx, t.work, t.sums, s));
+  FC_HIP(hipStreamSynchronize(s));
+  std::swap(pc.inv_ptr, t.ptr);
+  std::swap(pc.inv_idx, t.idx);
   return FC_OK;
 }
 
@@ -426,38 +458,23 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
       blocks.push_back((int32_t)(blocks.size()));
     }
   }
-  const std::vector<int32_t>& bn = patch ? pnodes : pb->elem_nodes_host;
   pc->n_blocks = (int64_t)blocks.size();
   const int64_t nb = pc->n_blocks;
   if (nb * (int64_t)m >= (int64_t(1) << 31)) {
     set_error("fc_precond_build: too many block entries for int32 indices");
     return FC_E_UNSUPPORTED;
   }
-  // node -> (block, local node) map, blocks in increasing order
-  std::vector<int32_t> ptr(pb->n_nodes + 1, 0), idx((size_t)nb * nn);
-  int64_t n_entries = 0;
-  for (int64_t k = 0; k < nb; ++k)
-    for (int a = 0; a < nn; ++a) {
-      const int32_t node = bn[(int64_t)blocks[k] * nn + a];
-      if (node >= 0) {
-        ptr[node + 1]++;
-        ++n_entries;
-      }
-    }
-  for (int64_t i = 0; i < pb->n_nodes; ++i) ptr[i + 1] += ptr[i];
-  idx.resize((size_t)n_entries);
-  {
-    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
-    for (int64_t k = 0; k < nb; ++k)
-      for (int a = 0; a < nn; ++a) {
-        const int32_t node = bn[(int64_t)blocks[k] * nn + a];
-        if (node >= 0) idx[fill[node]++] = (int32_t)(k * m + a * bd);
-      }
-  }
   if (patch) FC_TRY(upload(&pc->bnodes, pnodes.data(), pnodes.size()));
   FC_TRY(upload(&pc->block_elem, blocks.data(), blocks.size()));
-  FC_TRY(upload(&pc->inv_ptr, ptr.data(), ptr.size()));
-  FC_TRY(upload(&pc->inv_idx, idx.data(), idx.size()));
+  // lattice problem with every cell a block: the pull finds a node's blocks
+  // from its lattice indices, and the block products of scalar problems a row's
+  // unknown (FC_PULL_LATTICE=0 keeps the node lists and the node-to-block map)
+  {
+    const char* env = std::getenv("FC_PULL_LATTICE");
+    const bool allowed = !(env && std::atoi(env) == 0);
+    if (allowed && !patch && nb == pb->n_el) pc->lat = pb->cells;
+  }
+  if (pc->lat.dim == 0) FC_TRY(precond_ensure_map(*pc, s));
   FC_TRY(dev_alloc(&pc->P, (size_t)nb * m * m));
   FC_TRY(dev_alloc(&pc->y, (size_t)nb * m));
   FC_TRY(dev_alloc(&pc->fallback, (size_t)pb->n_dofs));
@@ -581,22 +598,6 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   FC_HIP(hipMemcpyAsync(drop.data(), d_drop, drop.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   FC_HIP(hipStreamSynchronize(s));
   pc->n_fallback = (int64_t)cnt;
-  // lattice problem with every cell a block, in cell order (checked row by
-  // row on the device): the pull finds a node's blocks from its lattice
-  // indices, and the block products of scalar problems a row's unknown
-  // (FC_PULL_LATTICE=0 keeps the node lists and the node-to-block map).
-  {
-    const char* env = std::getenv("FC_PULL_LATTICE");
-    const bool allowed = !(env && std::atoi(env) == 0);
-    if (allowed && !patch && pb->dim >= 2 && pb->dim <= 3 && pb->n > 0 &&
-        pb->p > 0 && nb == pb->n_el &&
-        nb == std::pow((double)pb->n, pb->dim) && pb->nn == (int)std::pow(pb->p + 1.0, pb->dim)) {
-      const PullLattice L = make_pull_lattice(pb->dim, pb->n, pb->p);
-      bool ok = false;
-      FC_HIP(schwarz_check_lattice(*pc, L, &ok, s));
-      if (ok) pc->lat = L;
-    }
-  }
   int64_t nd = 0;
   for (int64_t k = 0; k < nb; ++k) nd += drop[k];
   pc->n_dropped = nd;

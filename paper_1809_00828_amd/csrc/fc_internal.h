@@ -161,6 +161,7 @@ struct fc_problem_s {
   std::vector<double> eta;         // host copy [n_el]
   std::vector<int32_t> elem_nodes_host;
   double* diag = nullptr;          // A_ll [n_dofs]
+  fc::PullLattice cells;           // set when the elements are a lattice's cells, in order
 };
 
 struct fc_precond_s {
@@ -178,8 +179,8 @@ struct fc_precond_s {
   int64_t n_unsafe32 = 0;          //   (applied from the FP64 copy instead)
   uint16_t* Lbf = nullptr;         // optional BF16 scaled Cholesky factors
   double* isd = nullptr;           // [n_dofs] 1/sqrt(A_ll), scaling of Q32/Lbf
-  int32_t* inv_ptr = nullptr;      // [n_nodes+1] node -> (block, local node)
-  int32_t* inv_idx = nullptr;      // entries: block*m + local_node*bdim
+  int32_t* inv_ptr = nullptr;      // [n_nodes+1] node -> (block, local node); null where
+  int32_t* inv_idx = nullptr;      // `lat` is set; entries: block*m + local_node*bdim
   double* fallback = nullptr;      // [n_dofs] 1/A_ll where S_ll = 0, else 0
   fc::PullLattice lat;             // set when every cell is a block (lattice pull)
   double* y = nullptr;             // [n_blocks*m] block outputs (workspace)
@@ -216,6 +217,9 @@ hipError_t launch_block_extract(const fc_problem_s& pb, const fc_precond_s& pc,
 // z = S r
 hipError_t launch_schwarz_apply(const fc_precond_s& pc, const double* r,
                                 double* z, hipStream_t s);
+
+// Build the node-to-block map of pc on the device unless it is there.
+fc_status precond_ensure_map(fc_precond_s& pc, hipStream_t s);
 
 // drop the captured solver chunk (its kernels hold buffers about to change)
 void solver_invalidate_graph(fc_precond_s& pc);

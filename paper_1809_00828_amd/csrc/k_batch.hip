@@ -583,6 +583,7 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
       set_error("fc_batch_create: vertex-patch preconditioners are not batched");
       return FC_E_UNSUPPORTED;
     }
+    FC_TRY_B(precond_ensure_map(*pc, user));
     BProb& P = B.host[k];
     std::memset(&P, 0, sizeof(P));
     P.rowptr = pb->A.rowptr;

@@ -468,33 +468,28 @@ hipError_t launch_pack_sym(const fc_precond_s& pc, void* Q, int precision, hipSt
   return hipGetLastError();
 }
 
-// rows whose unknown differs from the lattice's (counted with an atomic only
+// element nodes that differ from the lattice's (counted with an atomic only
 // where one occurs)
-__global__ void k_check_cell_lattice(const int32_t* __restrict__ nodes,
-                                     const int32_t* __restrict__ block_elem, int nn, int bd,
-                                     int m, int64_t n_blocks, const PullLattice L,
-                                     unsigned long long* __restrict__ bad) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_blocks * m;
+__global__ void k_check_cells(const int32_t* __restrict__ nodes, int nn, int64_t n_el,
+                              const PullLattice L, unsigned long long* __restrict__ bad) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_el * nn;
        t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b = t / m;
-    const int i = (int)(t - b * m);
-    const int64_t want = lattice_cell_node(L, (int)b, i / bd) * bd + i % bd;
-    if (block_elem[b] != b || block_dof(nodes, b, nn, bd, i) != want) atomicAdd(bad, 1ull);
+    const int64_t e = t / nn;
+    if (nodes[t] != lattice_cell_node(L, (int)e, (int)(t - e * nn))) atomicAdd(bad, 1ull);
   }
 }
 
-hipError_t schwarz_check_lattice(const fc_precond_s& pc, const PullLattice L, bool* ok,
-                                 hipStream_t s) {
+hipError_t schwarz_check_cells(const fc_problem_s& pb, const PullLattice L, bool* ok,
+                               hipStream_t s) {
   *ok = false;
-  if (pc.n_blocks == 0) return hipSuccess;
   unsigned long long* bad = nullptr;
   hipError_t e = hipMalloc(&bad, sizeof(*bad));
   if (e != hipSuccess) return e;
   unsigned long long hbad = 1;
   e = hipMemsetAsync(bad, 0, sizeof(*bad), s);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_check_cell_lattice, dim3(2048), dim3(256), 0, s, block_nodes(pc),
-                       pc.block_elem, pc.nn, pc.bdim, pc.m, pc.n_blocks, L, bad);
+    hipLaunchKernelGGL(k_check_cells, dim3(2048), dim3(256), 0, s, pb.elem_nodes, pb.nn, pb.n_el,
+                       L, bad);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(hbad), hipMemcpyDeviceToHost, s);

@@ -15,6 +15,13 @@ hipError_t launch_sweep_small(fc_precond_s& pc, int32_t* need_eig, hipStream_t s
 // scaled inverse is not safely positive definite
 hipError_t launch_chol_pack(fc_precond_s& pc, hipStream_t s, int32_t* unsafe = nullptr);
 hipError_t launch_diag(const fc_problem_s& pb, hipStream_t s);
+// The node-to-block map: ptr [n_nodes + 1] and idx (room for n_blocks * nn
+// entries), the entries of a node in block order.  work: [n_nodes + 1] and the
+// sums of map_scan_blocks(n_nodes + 1) runs.
+int64_t map_scan_blocks(int64_t n);
+hipError_t launch_build_map(const fc_precond_s& pc, int64_t n_nodes, int32_t* ptr, int32_t* idx,
+                            int32_t* work, int32_t* sums, hipStream_t s);
+// Algorithm 1's diagonal scaling (uses pc.y for the blocks' diagonals)
 hipError_t launch_fallback(const fc_problem_s& pb, fc_precond_s& pc,
                            unsigned long long* d_count, hipStream_t s);
 // A.val32 = FP32 copy of A.val (same layout)

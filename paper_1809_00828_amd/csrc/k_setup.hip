@@ -21,6 +21,8 @@
 //    certificate, and for every block of the unstabilised inverse when
 //    m <= 64.  The block and its eigenvectors stay in LDS when they fit,
 //    else in global memory.
+#include <algorithm>
+
 #include "dev_common.h"
 #include "k_setup.h"
 
@@ -575,26 +577,166 @@ __global__ void k_diag(const int32_t* __restrict__ rowptr, const int32_t* __rest
         found >= 0 ? val[(int64_t)lo * bd * bd + (int64_t)(c * bd + c) * L + (found - lo)] : 0.0;
 }
 
+// Diagonals of the local inverses in the layout of the block outputs.
+__global__ __launch_bounds__(256) void k_block_diag(const double* __restrict__ P, int m,
+                                                    int64_t total, double* __restrict__ d) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= total) return;
+  const int64_t blk = t / m;
+  const int i = (int)(t - blk * m);
+  d[t] = P[blk * (int64_t)m * m + (int64_t)i * m + i];
+}
+
 // Algorithm 1 diagonal scaling: S_ll == 0 -> 1/A_ll (only where A_ll > 0).
-__global__ void k_fallback(const double* __restrict__ P, const int32_t* __restrict__ inv_ptr,
-                           const int32_t* __restrict__ inv_idx, const double* __restrict__ diag,
-                           int m, int bd, int64_t n_dofs, double* __restrict__ fb,
-                           unsigned long long* __restrict__ count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// S_ll is the pull of the blocks' diagonals d.
+template <bool kLat>
+__global__ __launch_bounds__(256) void k_fallback(
+    const double* __restrict__ d, const int32_t* __restrict__ inv_ptr,
+    const int32_t* __restrict__ inv_idx, const double* __restrict__ diag, int m, int bd,
+    const FastDiv dbd, const PullLattice L, uint32_t n_dofs, double* __restrict__ fb,
+    unsigned long long* __restrict__ count) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n_dofs) return;
-  const int64_t node = i / bd;
-  const int c = (int)(i % bd);
-  double s = 0.0;
-  for (int32_t e = inv_ptr[node]; e < inv_ptr[node + 1]; ++e) {
-    const int64_t idx = inv_idx[e];
-    const int64_t blk = idx / m;
-    const int slot = (int)(idx - blk * m) + c;
-    s += P[blk * (int64_t)m * m + (int64_t)slot * m + slot];
+  const uint32_t node = fdiv(i, dbd);
+  const int c = (int)(i - node * (uint32_t)bd);
+  double s;
+  if constexpr (kLat) {
+    double v[8];
+    pull_lattice_load(d, L, m, bd, node, c, v);
+    s = pull_sum8(v);
+  } else {
+    s = pull_mapped_sum(d, inv_ptr, inv_idx, node, c);
   }
   const double a = diag[i];
   const bool fall = (s == 0.0) && (a > 0.0);
   fb[i] = fall ? 1.0 / a : 0.0;
   if (fall) atomicAdd(count, 1ull);
+}
+
+// ------------------------------------------------------ node-to-block map
+// Counted, scanned and filled on the device: on the host the two passes over
+// (block, node) pairs and the upload took 4 ms at 48^3 cells, p = 2 (3.0M
+// pairs), as long as all kernels of the build.  Entries land in the order of
+// the atomics and are then sorted per node, so the map does not depend on it.
+__global__ void k_map_count(const int32_t* __restrict__ nodes,
+                            const int32_t* __restrict__ block_elem, int nn, int64_t total,
+                            int32_t* __restrict__ count) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t b = t / nn;
+    const int32_t node = nodes[(int64_t)block_elem[b] * nn + (t - b * nn)];
+    if (node >= 0) atomicAdd(count + node, 1);
+  }
+}
+
+// Exclusive scan of runs of 1,024 entries: pass 0 leaves the runs' sums, one
+// workgroup scans those (pass 1), pass 2 writes the offsets (and zeroes the
+// counts, which become fill positions).
+__device__ __forceinline__ int32_t scan256(int32_t v, int32_t* lds /* 4 */) {
+  const int l = threadIdx.x % 64, w = threadIdx.x / 64;
+  int32_t x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(x, o, 64);
+    if (l >= o) x += y;
+  }
+  __syncthreads();
+  if (l == 63) lds[w] = x;
+  __syncthreads();
+  for (int k = 0; k < w; ++k) x += lds[k];
+  return x;   // inclusive
+}
+
+template <int kPass>
+__global__ __launch_bounds__(256) void k_map_scan(int32_t* __restrict__ count, int64_t n,
+                                                  int32_t* __restrict__ sums, int nruns,
+                                                  int32_t* __restrict__ ptr) {
+  __shared__ int32_t lds[4];
+  if constexpr (kPass == 1) {
+    int32_t carry = 0;
+    for (int r0 = 0; r0 < nruns; r0 += 256) {
+      const int r = r0 + threadIdx.x;
+      const int32_t v = r < nruns ? sums[r] : 0;
+      const int32_t x = scan256(v, lds);
+      if (r < nruns) sums[r] = carry + x - v;
+      carry += lds[0] + lds[1] + lds[2] + lds[3];
+      __syncthreads();
+    }
+  } else {
+    const int64_t i0 = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
+    int32_t v[4], t = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v[u] = i0 + u < n ? count[i0 + u] : 0;
+      t += v[u];
+    }
+    const int32_t x = scan256(t, lds);
+    if constexpr (kPass == 0) {
+      if (threadIdx.x == 255) sums[blockIdx.x] = x;
+    } else {
+      int32_t o = sums[blockIdx.x] + x - t;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i0 + u < n) {
+          ptr[i0 + u] = o;
+          count[i0 + u] = 0;
+        }
+        o += v[u];
+      }
+    }
+  }
+}
+
+__global__ void k_map_fill(const int32_t* __restrict__ nodes,
+                           const int32_t* __restrict__ block_elem, int nn, int m, int bd,
+                           int64_t total, const int32_t* __restrict__ ptr,
+                           int32_t* __restrict__ fill, int32_t* __restrict__ idx) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t b = t / nn;
+    const int a = (int)(t - b * nn);
+    const int32_t node = nodes[(int64_t)block_elem[b] * nn + a];
+    if (node >= 0) idx[ptr[node] + atomicAdd(fill + node, 1)] = (int32_t)(b * m + a * bd);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_map_sort(const int32_t* __restrict__ ptr, int64_t n_nodes,
+                                                  int32_t* __restrict__ idx) {
+  const int64_t node = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (node >= n_nodes) return;
+  const int32_t lo = ptr[node], hi = ptr[node + 1];
+  for (int32_t e = lo + 1; e < hi; ++e) {
+    const int32_t v = idx[e];
+    int32_t k = e;
+    for (; k > lo && idx[k - 1] > v; --k) idx[k] = idx[k - 1];
+    idx[k] = v;
+  }
+}
+
+__global__ void k_zero_i32(int32_t* __restrict__ a, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    a[i] = 0;
+}
+
+int64_t map_scan_blocks(int64_t n) { return (n + 1023) / 1024; }
+
+hipError_t launch_build_map(const fc_precond_s& pc, int64_t n_nodes, int32_t* ptr, int32_t* idx,
+                            int32_t* work, int32_t* sums, hipStream_t s) {
+  const int64_t n = n_nodes + 1, total = pc.n_blocks * pc.nn;
+  const int nruns = (int)map_scan_blocks(n);
+  const dim3 b(256), runs((unsigned)nruns);
+  const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 8192)));
+  hipLaunchKernelGGL(k_zero_i32, dim3(1024), b, 0, s, work, n);
+  hipLaunchKernelGGL(k_map_count, g, b, 0, s, block_nodes(pc), pc.block_elem, pc.nn, total, work);
+  hipLaunchKernelGGL(k_map_scan<0>, runs, b, 0, s, work, n, sums, nruns, ptr);
+  hipLaunchKernelGGL(k_map_scan<1>, dim3(1), b, 0, s, work, n, sums, nruns, ptr);
+  hipLaunchKernelGGL(k_map_scan<2>, runs, b, 0, s, work, n, sums, nruns, ptr);
+  hipLaunchKernelGGL(k_map_fill, g, b, 0, s, block_nodes(pc), pc.block_elem, pc.nn, pc.m, pc.bdim,
+                     total, ptr, work, idx);
+  hipLaunchKernelGGL(k_map_sort, dim3((unsigned)((n_nodes + 255) / 256)), b, 0, s, ptr, n_nodes,
+                     idx);
+  return hipGetLastError();
 }
 
 __global__ void k_cast_f32(const double* __restrict__ in, float* __restrict__ out, int64_t n) {
@@ -685,10 +827,19 @@ hipError_t launch_diag(const fc_problem_s& pb, hipStream_t s) {
 
 hipError_t launch_fallback(const fc_problem_s& pb, fc_precond_s& pc,
                            unsigned long long* d_count, hipStream_t s) {
-  const int64_t n = pb.n_dofs;
-  hipLaunchKernelGGL(k_fallback, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     pc.P, pc.inv_ptr, pc.inv_idx, pb.diag, pc.m, pc.bdim, n,
-                     pc.fallback, d_count);
+  const uint32_t n = (uint32_t)pb.n_dofs;
+  const int64_t total = pc.n_blocks * pc.m;
+  const dim3 g((n + 255) / 256), b(256);
+  const FastDiv dbd = make_fastdiv((uint32_t)pc.bdim);
+  if (total > 0)
+    hipLaunchKernelGGL(k_block_diag, dim3((unsigned)((total + 255) / 256)), b, 0, s, pc.P, pc.m,
+                       total, pc.y);
+  if (pc.lat.dim > 0)
+    hipLaunchKernelGGL(k_fallback<true>, g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, pb.diag, pc.m,
+                       pc.bdim, dbd, pc.lat, n, pc.fallback, d_count);
+  else
+    hipLaunchKernelGGL(k_fallback<false>, g, b, 0, s, pc.y, pc.inv_ptr, pc.inv_idx, pb.diag, pc.m,
+                       pc.bdim, dbd, pc.lat, n, pc.fallback, d_count);
   return hipGetLastError();
 }
 
