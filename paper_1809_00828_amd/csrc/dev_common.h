@@ -64,11 +64,16 @@ __device__ __forceinline__ double dpp64(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, RM, 0xf, false);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
-__device__ __forceinline__ double wave_sum_last(double v) {
+// (over every 16 lanes: in the last of them)
+__device__ __forceinline__ double row16_sum_last(double v) {
   v += dpp64<0x111, 0xf>(v);   // row_shr:1
   v += dpp64<0x112, 0xf>(v);   // row_shr:2
   v += dpp64<0x114, 0xf>(v);   // row_shr:4
   v += dpp64<0x118, 0xf>(v);   // row_shr:8
+  return v;
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v = row16_sum_last(v);
   v += dpp64<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
   v += dpp64<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
   return v;

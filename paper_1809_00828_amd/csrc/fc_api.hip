@@ -16,6 +16,7 @@
 #include "host_assemble.h"
 #include "k_schwarz.h"
 #include "k_setup.h"
+#include "schwarz_dev.h"
 
 struct fc_host_system_s {
   fc::HostSystem sys;
@@ -53,6 +54,14 @@ static fc_status upload(T** p, const T* src, size_t count) {
   return FC_OK;
 }
 
+// Device scratch of one call, freed at its end.
+struct Scratch {
+  double* p = nullptr;
+  ~Scratch() {
+    if (p) (void)hipFree(p);
+  }
+};
+
 #define FC_TRY(x)                  \
   do {                             \
     fc_status s_ = (x);            \
@@ -73,7 +82,7 @@ static void free_precond(fc_precond_s* pc) {
   if (!pc) return;
   solver_ws_destroy(pc->ws);
   coarse_destroy(pc->coarse);
-  for (void* p : {(void*)pc->block_elem, (void*)pc->bnodes, (void*)pc->P, (void*)pc->Q,
+  for (void* p : {(void*)pc->block_elem, (void*)pc->bnodes, (void*)pc->Q,
                   (void*)pc->Q32,
                   (void*)pc->unsafe32, (void*)pc->unsafe_flag32, (void*)pc->Lbf, (void*)pc->isd,
                   (void*)pc->inv_ptr, (void*)pc->inv_idx, (void*)pc->fallback, (void*)pc->y})
@@ -475,7 +484,7 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     if (allowed && !patch && nb == pb->n_el) pc->lat = pb->cells;
   }
   if (pc->lat.dim == 0) FC_TRY(precond_ensure_map(*pc, s));
-  FC_TRY(dev_alloc(&pc->P, (size_t)nb * m * m));
+  FC_TRY(dev_alloc(&pc->Q, (size_t)nb * sym_block_stride(m)));
   FC_TRY(dev_alloc(&pc->y, (size_t)nb * m));
   FC_TRY(dev_alloc(&pc->fallback, (size_t)pb->n_dofs));
 
@@ -498,72 +507,49 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   FC_HIP(hipMemsetAsync(d_drop, 0, std::max<int64_t>(nb, 1) * sizeof(int32_t), s));
   FC_HIP(hipMemsetAsync(d_count, 0, sizeof(unsigned long long), s));
 
-  if (nb > 0) {
-    FC_HIP(launch_block_extract(*pb, *pc, s));
-    if (m <= 64 && !pc->stabilize) {
-      // the plain inverse (S*): every block by the eigen-decomposition with
-      // every nonzero eigenvalue inverted; in LDS when it fits
-      const int64_t chunk = jacobi_needs_work(m) ? 16384 : nb;
-      double* work = nullptr;
-      if (jacobi_needs_work(m)) FC_TRY(dev_alloc(&work, (size_t)std::min(chunk, nb) * 2 * m * m));
-      std::vector<int32_t> all(nb);
-      for (int64_t k = 0; k < nb; ++k) all[k] = (int32_t)k;
-      int32_t* d_all = nullptr;
-      fc_status st = upload(&d_all, all.data(), all.size());
-      hipError_t e = hipSuccess;
-      for (int64_t s0 = 0; st == FC_OK && s0 < nb && e == hipSuccess; s0 += chunk)
-        e = launch_jacobi(*pc, d_all + s0, std::min(chunk, nb - s0), work, d_drop, s);
-      hipError_t e2 = hipStreamSynchronize(s);
-      if (d_all) (void)hipFree(d_all);
-      if (work) (void)hipFree(work);
-      FC_TRY(st);
-      FC_HIP(e);
-      FC_HIP(e2);
-      pc->n_eig = nb;
-    } else {
-      // certified direct inverses; the blocks whose certificate fails (some
-      // eigenvalue may be near the threshold of Eq. 11) keep A_B and are
-      // eigen-decomposed below
-      if (m <= 64)
-        FC_HIP(launch_sweep_small(*pc, d_flag, s));
-      else
-        FC_HIP(launch_sweep(*pc, d_flag, s));
-      std::vector<int32_t> flag(nb);
-      FC_HIP(hipMemcpyAsync(flag.data(), d_flag, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      FC_HIP(hipStreamSynchronize(s));
-      std::vector<int32_t> sel;
-      for (int64_t k = 0; k < nb; ++k)
-        if (flag[k]) sel.push_back((int32_t)k);
-      pc->n_eig = (int64_t)sel.size();
-      if (!sel.empty()) {
-        // blocks whose certificate failed still hold A_B: eigen-decompose
-        const int64_t chunk = 2048;
-        int32_t* d_sel = nullptr;
-        double* work = nullptr;
-        FC_TRY(upload(&d_sel, sel.data(), sel.size()));
-        fc_status st = dev_alloc(&work, (size_t)std::min<int64_t>(chunk, sel.size()) * 2 * m * m);
-        if (st != FC_OK) {
-          (void)hipFree(d_sel);
-          return st;
-        }
-        hipError_t e = hipSuccess;
-        for (int64_t s0 = 0; s0 < (int64_t)sel.size() && e == hipSuccess; s0 += chunk) {
-          const int64_t cnt = std::min<int64_t>(chunk, sel.size() - s0);
-          e = launch_jacobi(*pc, d_sel + s0, cnt, work, d_drop, s);
-        }
-        hipError_t e2 = hipStreamSynchronize(s);
-        (void)hipFree(d_sel);
-        (void)hipFree(work);
-        FC_HIP(e);
-        FC_HIP(e2);
-      }
+  // Blocks that take the eigen-decomposition: every block of the plain inverse
+  // (S*) at m <= 64 (every nonzero eigenvalue inverted); else those whose
+  // certificate fails (some eigenvalue may be near the threshold of Eq. 11).
+  std::vector<int32_t> sel;
+  if (nb > 0 && m <= 64 && !pc->stabilize) {
+    sel.resize(nb);
+    for (int64_t k = 0; k < nb; ++k) sel[k] = (int32_t)k;
+  } else if (nb > 0) {
+    // certified direct inverses; without the lattice the blocks are extracted
+    // into 256 MB of scratch at a time
+    Scratch dense;
+    int64_t chunk = nb;
+    if (!sweep_reads_lattice(*pc)) {
+      chunk = std::min<int64_t>(nb, std::max<int64_t>(1, (int64_t(1) << 25) / ((int64_t)m * m)));
+      FC_TRY(dev_alloc(&dense.p, (size_t)chunk * m * m));
     }
+    for (int64_t b0 = 0; b0 < nb; b0 += chunk)
+      FC_HIP(launch_sweep(*pc, b0, std::min(chunk, nb - b0), dense.p, d_flag, s));
+    std::vector<int32_t> flag(nb);
+    FC_HIP(hipMemcpyAsync(flag.data(), d_flag, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    FC_HIP(hipStreamSynchronize(s));
+    for (int64_t k = 0; k < nb; ++k)
+      if (flag[k]) sel.push_back((int32_t)k);
+  }
+  pc->n_eig = (int64_t)sel.size();
+  if (!sel.empty()) {
+    const int64_t chunk = std::min<int64_t>(2048, (int64_t)sel.size());
+    Scratch dense, work;
+    int32_t* d_sel = nullptr;
+    FC_TRY(upload(&d_sel, sel.data(), sel.size()));
+    fc_status st = dev_alloc(&dense.p, (size_t)chunk * m * m);
+    if (st == FC_OK && jacobi_needs_work(m)) st = dev_alloc(&work.p, (size_t)chunk * 2 * m * m);
+    hipError_t e = hipSuccess;
+    for (int64_t s0 = 0; st == FC_OK && s0 < (int64_t)sel.size() && e == hipSuccess; s0 += chunk)
+      e = launch_jacobi(*pc, d_sel + s0, std::min<int64_t>(chunk, sel.size() - s0), dense.p,
+                        work.p, d_drop, s);
+    const hipError_t e2 = hipStreamSynchronize(s);
+    (void)hipFree(d_sel);
+    FC_TRY(st);
+    FC_HIP(e);
+    FC_HIP(e2);
   }
   FC_HIP(launch_fallback(*pb, *pc, d_count, s));
-  // wrapped-diagonal symmetric copies streamed by the block products
-  const size_t qn = (size_t)nb * sym_block_stride(m);
-  FC_TRY(dev_alloc(&pc->Q, qn));
-  FC_HIP(launch_pack_sym(*pc, pc->Q, 0, s));
   if (o.store_mask & (FC_STORE_F32 | FC_STORE_BF16)) {
     FC_TRY(dev_alloc(&pc->isd, (size_t)pb->n_dofs));
     FC_HIP(launch_inv_sqrt_diag(*pb, pc->isd, s));
@@ -574,8 +560,8 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   // a Cholesky factorisation of the rounded matrix shows otherwise are
   // listed and applied from the FP64 copy.
   if (o.store_mask & FC_STORE_F32) {
-    FC_TRY(dev_alloc(&pc->Q32, qn));
-    FC_HIP(launch_pack_sym(*pc, pc->Q32, 1, s));
+    FC_TRY(dev_alloc(&pc->Q32, (size_t)nb * sym_block_stride(m)));
+    FC_HIP(launch_pack_f32(*pc, s));
     FC_TRY(dev_alloc(&pc->unsafe_flag32, (size_t)std::max<int64_t>(nb, 1)));
     FC_HIP(launch_chol_pack(*pc, s, pc->unsafe_flag32));
     std::vector<int32_t> hf(std::max<int64_t>(nb, 1), 0);
@@ -664,8 +650,17 @@ fc_status fc_get_block_inverse(fc_precond pc, int64_t k, double* out_host) {
     set_error("fc_get_block_inverse: invalid arguments");
     return FC_E_ARG;
   }
-  const size_t mm = (size_t)pc->m * pc->m;
-  FC_HIP(hipMemcpy(out_host, pc->P + k * mm, mm * sizeof(double), hipMemcpyDeviceToHost));
+  const int m = pc->m;
+  const int64_t per = sym_block_stride(m);
+  try {
+    std::vector<double> q((size_t)per);
+    FC_HIP(hipMemcpy(q.data(), pc->Q + k * per, per * sizeof(double), hipMemcpyDeviceToHost));
+    for (int i = 0; i < m; ++i)
+      for (int j = 0; j < m; ++j) out_host[(int64_t)i * m + j] = q[sym_entry(i, j, m)];
+  } catch (const std::bad_alloc&) {
+    set_error("fc_get_block_inverse: out of host memory");
+    return FC_E_NOMEM;
+  }
   return FC_OK;
 }
 

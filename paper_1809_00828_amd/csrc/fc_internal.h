@@ -171,9 +171,8 @@ struct fc_precond_s {
   int32_t block_kind = FC_BLOCK_ELEMENT;
   int32_t* block_elem = nullptr;   // [n_blocks] element of each block (patch: its index)
   int32_t* bnodes = nullptr;       // vertex patches: [n_blocks][nn] node lists, -1 padding
-  double* P = nullptr;             // [n_blocks*m*m] FP64 local inverses (dense)
-  double* Q = nullptr;             // wrapped-diagonal symmetric copy, FP64
-  float* Q32 = nullptr;            // optional FP32 wrapped-diagonal copy of D^1/2 P D^1/2
+  double* Q = nullptr;             // FP64 local inverses, wrapped-diagonal symmetric storage
+  float* Q32 = nullptr;            // optional FP32 copy of D^1/2 P D^1/2, same storage
   int32_t* unsafe32 = nullptr;     // blocks whose FP32 copy is not safely positive
   int32_t* unsafe_flag32 = nullptr; // the same as one flag per block
   int64_t n_unsafe32 = 0;          //   (applied from the FP64 copy instead)
@@ -210,9 +209,6 @@ int spmv_group_for(const DeviceBsr& A);
 // p); if so record it in A.lat, so the SpMV computes columns instead of
 // reading them
 hipError_t spmv_enable_lattice(DeviceBsr& A, int dim, int n1, int p, hipStream_t s);
-
-hipError_t launch_block_extract(const fc_problem_s& pb, const fc_precond_s& pc,
-                                hipStream_t s);
 
 // z = S r
 hipError_t launch_schwarz_apply(const fc_precond_s& pc, const double* r,

@@ -8,9 +8,8 @@
 //
 // Shape classes and their launch variants are fixed at batch creation by a
 // small autotuner: for every SpMV class (block dimension, mean row length)
-// it times the group widths 8/16/32/64 on that class's own work items, and
-// for every Schwarz class (block size m) it times the available block-
-// product variants, keeping the fastest.
+// it times the group widths 8/16/32/64 on that class's own work items, keeping
+// the fastest.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -40,7 +39,6 @@ struct BProb {
   const int32_t* elem_nodes;
   const int32_t* block_elem;
   const double* Q;         // wrapped-diagonal symmetric local inverses
-  const double* P;         // dense local inverses
   const int32_t* inv_ptr;
   const int32_t* inv_idx;
   const double* fallback;
@@ -210,50 +208,6 @@ __global__ __launch_bounds__(256) void kb_schwarz(const BProb* __restrict__ prob
   }
 }
 
-// Dense variant of the same product (autotuner candidate).
-template <bool kSmall>
-__global__ __launch_bounds__(256) void kb_schwarz_dense(const BProb* __restrict__ probs,
-                                                        const WorkItem* __restrict__ items,
-                                                        const CgScalars* __restrict__ sc,
-                                                        const double* __restrict__ rvec,
-                                                        const double* __restrict__ qvec, int m,
-                                                        int bpw) {
-  __shared__ double rB[256];
-  const WorkItem it = items[blockIdx.x];
-  const CgScalars& S = sc[it.prob];
-  if (S.done) return;
-  const BProb& P = probs[it.prob];
-  const double alpha = qvec ? S.alpha : 0.0;
-  const double* r = rvec + P.voff;
-  const double* q = qvec ? qvec + P.voff : nullptr;
-  const int64_t stride = (int64_t)m * m;
-  if constexpr (kSmall) {
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int lb = l / m, i = l % m;
-    const int64_t blk = ((int64_t)it.tile * 4 + w) * bpw + lb;
-    const bool active = lb < bpw && blk < P.n_blocks;
-    if (active) {
-      const int64_t e = P.block_elem[blk];
-      const int64_t dof = (int64_t)P.elem_nodes[e * P.nn + i / P.bdim] * P.bdim + (i % P.bdim);
-      rB[threadIdx.x] = gather_r(r, q, alpha, dof);
-    }
-    __syncthreads();
-    if (!active) return;
-    P.y[blk * m + i] = dense_row<double>(P.P + blk * stride, &rB[w * 64 + lb * m], m, i);
-  } else {
-    const int64_t blk = it.tile;
-    const int i = threadIdx.x;
-    if (i < m) {
-      const int64_t e = P.block_elem[blk];
-      const int64_t dof = (int64_t)P.elem_nodes[e * P.nn + i / P.bdim] * P.bdim + (i % P.bdim);
-      rB[i] = gather_r(r, q, alpha, dof);
-    }
-    __syncthreads();
-    if (i >= m) return;
-    P.y[blk * m + i] = dense_row<double>(P.P + blk * stride, rB, m, i);
-  }
-}
-
 // Pull + x, r updates + partial dots (mode 1), or the start (mode 0: z = S r
 // only, dots of r and z).
 template <int kMode>
@@ -386,7 +340,7 @@ struct SpmvClass {
 };
 
 struct SchwarzClass {
-  int m, bpw, variant;   // variant: 0 symmetric, 1 dense
+  int m, bpw;
   bool small;
   std::vector<WorkItem> items;
   WorkItem* d_items = nullptr;
@@ -474,17 +428,10 @@ static hipError_t launch_schwarz_class(fc_batch_s& bt, const SchwarzClass& c, co
   if (n == 0) return hipSuccess;
   const int threads = c.small ? 256 : 64 * ((c.m + 63) / 64);
   dim3 g((unsigned)n), b((unsigned)threads);
-  if (c.variant == 0) {
-    if (c.small)
-      hipLaunchKernelGGL(kb_schwarz<true>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
-    else
-      hipLaunchKernelGGL(kb_schwarz<false>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
-  } else {
-    if (c.small)
-      hipLaunchKernelGGL(kb_schwarz_dense<true>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
-    else
-      hipLaunchKernelGGL(kb_schwarz_dense<false>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
-  }
+  if (c.small)
+    hipLaunchKernelGGL(kb_schwarz<true>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
+  else
+    hipLaunchKernelGGL(kb_schwarz<false>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
   return hipGetLastError();
 }
 
@@ -593,7 +540,6 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
     P.elem_nodes = pb->elem_nodes;
     P.block_elem = pc->block_elem;
     P.Q = pc->Q;
-    P.P = pc->P;
     P.inv_ptr = pc->inv_ptr;
     P.inv_idx = pc->inv_idx;
     P.fallback = pc->fallback;
@@ -621,7 +567,6 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
       c.m = P.m;
       c.small = P.m <= 64;
       c.bpw = c.small ? 64 / P.m : 1;
-      c.variant = 0;
       B.schw.push_back(c);
     }
   }
@@ -737,22 +682,6 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
       c.G = bestG;
       build_spmv_items(c, (int)ci);
     }
-    for (auto& c : B.schw) {
-      float best = 1e30f;
-      int bestv = 0;
-      for (int v : {0, 1}) {
-        c.variant = v;
-        float ms = time_launches(s, B.ev[1], B.ev[2], 3, [&]() {
-          (void)launch_schwarz_class(B, c, c.d_items, (int)c.items.size(), nullptr, s);
-        });
-        rep << "schwarz m=" << c.m << " " << (v ? "dense" : "symmetric") << ": " << ms << " ms\n";
-        if (ms < best) {
-          best = ms;
-          bestv = v;
-        }
-      }
-      c.variant = bestv;
-    }
     FC_HIP(hipGetLastError());
     finalize_spmv_ranges();
     for (auto& c : B.spmv) FC_TRY_B(upload_items(c.items, &c.d_items));
@@ -761,8 +690,7 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
   for (auto& c : B.spmv)
     rep << "chosen spmv B=" << c.B << " G=" << c.G << " items=" << c.items.size() << "\n";
   for (auto& c : B.schw)
-    rep << "chosen schwarz m=" << c.m << " " << (c.variant ? "dense" : "symmetric")
-        << " items=" << c.items.size() << "\n";
+    rep << "schwarz m=" << c.m << " items=" << c.items.size() << "\n";
   B.report = rep.str();
   for (auto& c : B.spmv)
     if (!c.items.empty()) FC_HIP(hipMalloc(&c.d_act, c.items.size() * sizeof(WorkItem)));

@@ -17,9 +17,8 @@ hipError_t launch_schwarz_pull(const fc_precond_s& pc, const double* r, double* 
                                hipStream_t s);
 // Elements per block of the wrapped-diagonal symmetric layout, (m/2+1)*m.
 int64_t sym_block_stride(int m);
-// Q = wrapped-diagonal copy of the dense FP64 local inverses pc.P in FP64
-// (0), or diagonally scaled in FP32 (1) or BF16 (2) (needs pc.isd).
-hipError_t launch_pack_sym(const fc_precond_s& pc, void* Q, int precision, hipStream_t s);
+// pc.Q32 = FP32 copy of pc.Q, diagonally scaled (needs pc.isd).
+hipError_t launch_pack_f32(const fc_precond_s& pc, hipStream_t s);
 // Whether the elements of pb are the cells of the lattice L, in order, with
 // their nodes in the cells' local tensor order; synchronises s.
 hipError_t schwarz_check_cells(const fc_problem_s& pb, const PullLattice L, bool* ok,

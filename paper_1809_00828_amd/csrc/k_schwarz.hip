@@ -7,7 +7,7 @@
 //
 // Phase 1 (one pass over the local inverses): per block, gather
 // r_B = R_B r into LDS and write y_B = P_B r_B.
-//   * Symmetric (default) layout.  P_B is symmetric, so only its m(m+1)/2
+//   * FP64.  P_B is symmetric, so only its m(m+1)/2
 //     distinct entries are stored, as "wrapped diagonals":
 //         Q_B[k][i] = P_B[i][(i + k) mod m],   k = 0 .. floor(m/2).
 //     Thread i then needs, for every k, Q_B[k][i] (the entry P[i][i+k]) and
@@ -20,8 +20,6 @@
 //     m <= 64 (one lane per column) the stored rows are kept in pairs,
 //     rows 2j and 2j + 1 interleaved column by column, so a lane reads two
 //     of its entries with one load (sym_offset).
-//   * Dense layout: lane i accumulates sum_j P_B[j][i] r_B[j] (row j of a
-//     symmetric matrix is its column j) reading P_B row by row.
 //   * FP32: the same wrapped diagonals of the diagonally scaled inverse
 //     D^{1/2} P_B D^{1/2} rounded to FP32 (FP32 accumulation), applied as
 //     D^{-1/2} (.) D^{-1/2}; blocks whose rounded copy is not certified
@@ -41,32 +39,6 @@
 #include "schwarz_dev.h"
 
 namespace fc {
-
-// m > 64: one workgroup of 64*ceil(m/64) threads per block.
-template <typename T, bool kSym>
-__global__ __launch_bounds__(256) void k_schwarz_large(
-    const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
-    const int32_t* __restrict__ block_elem, int nn, int bd, int m,
-    const double* __restrict__ r, const double* __restrict__ q, const double* __restrict__ isd,
-    CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks) {
-  __shared__ double rB[256], red[16];
-  if (sc && sc->done) return;
-  const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-  double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
-  if (ai.np && !cg_alpha(sc, ai, red, &alpha)) return;
-  const int i = threadIdx.x;
-  const int64_t e = block_elem[blk];
-  int64_t dof = -1;
-  if (i < m) {
-    dof = block_dof(elem_nodes, e, nn, bd, i);
-    rB[i] = dof >= 0 ? gather_r(r, q, alpha, dof) * (isd ? isd[dof] : 1.0) : 0.0;
-  }
-  __syncthreads();
-  if (i >= m) return;
-  const T* Pb = P + blk * block_stride;
-  const double v = kSym ? sym_row<T>(Pb, rB, m, i) : dense_row<T>(Pb, rB, m, i);
-  y[blk * m + i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
-}
 
 // m > 64, symmetric layout staged through LDS.  kRuns: 16-byte runs of the
 // chunk per thread (sym_block_staged_runs), else every thread's own entry of
@@ -119,17 +91,17 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
 }
 
 // m <= 64: each wave handles floor(64/m) blocks, one lane per output row.
-// kM > 0 (symmetric layout, m = kM known at compile time): lane i loads its
+// kM > 0 (m = kM known at compile time): lane i loads its
 // column of the stored rows (Q_B[k][i] = P_B[i][(i + k) mod m], k = 0 ..
 // m/2; two rows per load, as sym_offset pairs them) into registers before
 // it gathers r_B, so the block's stream is in
 // flight during the gather; the entries P_B[i][(i - k) mod m] =
 // Q_B[k][(i - k) mod m] are then read from the lane that loaded them (a
 // cross-lane read within the wave).  kM = 0: any m, the stored rows read
-// after the gather (sym_row / dense_row).  kLat: the blocks are the cells of
+// after the gather (sym_row).  kLat: the blocks are the cells of
 // a lattice in order, so a row's unknown follows from the block and row
 // indices and the gather of r_B is issued together with the stored rows.
-template <typename T, bool kSym, int kM, bool kLat>
+template <typename T, int kM, bool kLat>
 __global__ __launch_bounds__(256) void k_schwarz_small(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
     const int32_t* __restrict__ block_elem, int nn, int bd, int m_arg,
@@ -163,7 +135,7 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
     g_q = (q ? q : r)[dof];
     g_s = (isd ? isd : r)[dof];
   }
-  if constexpr (kSym && kM > 0) {
+  if constexpr (kM > 0) {
     // stored rows in pairs (sym_offset, m <= 64): one two-wide load each
     constexpr int kNP = (kH + 1) & ~1;
     typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
@@ -190,7 +162,7 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
   if (active) rB[w][l] = rv;
   __syncthreads();
   double out;
-  if constexpr (kSym && kM > 0) {
+  if constexpr (kM > 0) {
     // every lane takes part in the cross-lane reads; a lane without a block
     // reads its own group's entries and discards the result
     const int g0 = (active ? lb : 0) * kM;
@@ -208,7 +180,7 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
   } else {
     if (!active) return;
     const double* rb = &rB[w][lb * m];
-    out = kSym ? sym_row<T>(Pb, rb, m, i) : dense_row<T>(Pb, rb, m, i);
+    out = sym_row<T>(Pb, rb, m, i);
   }
   if (!active) return;
   y[blk * m + i] = dof < 0 ? 0.0 : isd ? out * isd[dof] : out;
@@ -400,19 +372,15 @@ __global__ __launch_bounds__(256) void k_schwarz_pull(
   z[i] = fb ? fma(fb[i], r[i], s) : s;
 }
 
-// Wrapped-diagonal copy: entry (k, i) of block blk, P[blk][i][(i+k) mod m]
-// for k <= m/2, at Q[blk * (m/2 + 1) m + sym_offset(k, i, m)].
-// With isd (low-precision copies) the stored block is the diagonally
-// scaled D^{1/2} P_B D^{1/2} (D = diag(A) on the block's unknowns, isd =
-// D^{-1/2}), which removes the 1/alpha dynamic range of fictitious
-// functions before rounding; the apply undoes the scaling in FP64.
-template <typename T>
-__global__ void k_pack_sym(const double* __restrict__ P, T* __restrict__ Q, int m,
+// FP32 copy of the local inverses in the same storage: the diagonally scaled
+// D^{1/2} P_B D^{1/2} (D = diag(A) on the block's unknowns, isd = D^{-1/2}),
+// which removes the 1/alpha dynamic range of fictitious functions before
+// rounding; the apply undoes the scaling in FP64.
+__global__ void k_pack_f32(const double* __restrict__ Q, float* __restrict__ Q32, int m,
                            int64_t n_blocks, const double* __restrict__ isd,
                            const int32_t* __restrict__ elem_nodes,
                            const int32_t* __restrict__ block_elem, int nn, int bd) {
-  const int h = m / 2;
-  const int64_t per = (int64_t)(h + 1) * m;
+  const int64_t per = sym_block_stride_dev(m);
   const int64_t total = per * n_blocks;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * blockDim.x) {
@@ -421,50 +389,20 @@ __global__ void k_pack_sym(const double* __restrict__ P, T* __restrict__ Q, int 
     const int k = (int)(rem / m), i = (int)(rem - (int64_t)k * m);
     int j = i + k;
     if (j >= m) j -= m;
-    double v = P[blk * (int64_t)m * m + (int64_t)i * m + j];
-    if (isd) {
-      const int64_t e = block_elem[blk];
-      const int64_t di = block_dof(elem_nodes, e, nn, bd, i);
-      const int64_t dj = block_dof(elem_nodes, e, nn, bd, j);
-      v = (di < 0 || dj < 0) ? 0.0 : v / (isd[di] * isd[dj]);
-    }
     const int64_t dst = blk * per + sym_offset(k, i, m);
-    if constexpr (sizeof(T) == 8) {
-      Q[dst] = v;
-    } else if constexpr (sizeof(T) == 4) {
-      Q[dst] = (float)v;
-    } else {
-      // FP64 -> BF16 through FP32, round to nearest even
-      uint32_t u = __float_as_uint((float)v);
-      u += 0x7fffu + ((u >> 16) & 1u);
-      Q[dst] = (T)(u >> 16);
-    }
+    const int64_t e = block_elem[blk];
+    const int64_t di = block_dof(elem_nodes, e, nn, bd, i);
+    const int64_t dj = block_dof(elem_nodes, e, nn, bd, j);
+    Q32[dst] = (di < 0 || dj < 0) ? 0.0f : (float)(Q[dst] / (isd[di] * isd[dj]));
   }
 }
 
-int64_t sym_block_stride(int m) { return (int64_t)(m / 2 + 1) * m; }
+int64_t sym_block_stride(int m) { return sym_block_stride_dev(m); }
 
-hipError_t launch_pack_sym(const fc_precond_s& pc, void* Q, int precision, hipStream_t s) {
-  const int64_t nb = pc.n_blocks;
-  const int m = pc.m;
-  if (nb == 0) return hipSuccess;
-  dim3 g(8192), b(256);
-  const int32_t* en = block_nodes(pc);
-  switch (precision) {
-    case 0:
-      hipLaunchKernelGGL(k_pack_sym<double>, g, b, 0, s, pc.P, (double*)Q, m, nb, nullptr, en,
-                         pc.block_elem, pc.nn, pc.bdim);
-      break;
-    case 1:
-      hipLaunchKernelGGL(k_pack_sym<float>, g, b, 0, s, pc.P, (float*)Q, m, nb, pc.isd, en,
-                         pc.block_elem, pc.nn, pc.bdim);
-      break;
-    case 2:
-      hipLaunchKernelGGL(k_pack_sym<uint16_t>, g, b, 0, s, pc.P, (uint16_t*)Q, m, nb, pc.isd, en,
-                         pc.block_elem, pc.nn, pc.bdim);
-      break;
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_pack_f32(const fc_precond_s& pc, hipStream_t s) {
+  if (pc.n_blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_pack_f32, dim3(8192), dim3(256), 0, s, pc.Q, pc.Q32, pc.m, pc.n_blocks,
+                     pc.isd, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim);
   return hipGetLastError();
 }
 
@@ -533,26 +471,15 @@ static void launch_staged(const fc_precond_s& pc, const T* Q, int64_t n_launch,
                        pc.n_blocks, list, skip);
 }
 
-template <typename T, bool kSym>
-static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, const double* q,
+template <typename T>
+static hipError_t phase1(const fc_precond_s& pc, const T* Q, const double* r, const double* q,
                          CgScalars* sc, const AlphaIn ai, hipStream_t s) {
   const double* isd = sizeof(T) == 8 ? nullptr : pc.isd;
-  const fc_problem_s& pb = *pc.pb;
   if (pc.n_blocks == 0) return hipSuccess;
-  const int64_t stride = kSym ? sym_block_stride(pc.m) : (int64_t)pc.m * pc.m;
-  static const int variant = [] {
-    const char* v = std::getenv("FC_SCHWARZ_STAGED");
-    return v ? std::atoi(v) : 1;
-  }();
+  const int64_t stride = sym_block_stride(pc.m);
   if (pc.m > 64) {
-    const int threads = 64 * ((pc.m + 63) / 64);
-    if (kSym && variant)
-      launch_staged<T>(pc, P, pc.n_blocks, r, q, isd, sc, ai, nullptr,
-                       sizeof(T) == 4 ? pc.unsafe_flag32 : nullptr, s);
-    else
-      hipLaunchKernelGGL((k_schwarz_large<T, kSym>), dim3((unsigned)pc.n_blocks), dim3(threads),
-                         0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r,
-                         q, isd, sc, ai, pc.y, pc.n_blocks);
+    launch_staged<T>(pc, Q, pc.n_blocks, r, q, isd, sc, ai, nullptr,
+                     sizeof(T) == 4 ? pc.unsafe_flag32 : nullptr, s);
   } else {
     const int bpw = 64 / pc.m;
     const int64_t per_wg = 4 * (int64_t)bpw;
@@ -563,15 +490,15 @@ static hipError_t phase1(const fc_precond_s& pc, const T* P, const double* r, co
 #define FC_SMALL_LAUNCH(KM)                                                                    \
   do {                                                                                         \
     if (lat && KM > 0)                                                                         \
-      hipLaunchKernelGGL((k_schwarz_small<T, kSym, KM, true>), dim3((unsigned)nwg), dim3(256), \
-                         0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, \
+      hipLaunchKernelGGL((k_schwarz_small<T, KM, true>), dim3((unsigned)nwg), dim3(256),       \
+                         0, s, Q, stride, block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, \
                          r, q, isd, sc, ai, pc.y, pc.n_blocks, pc.lat);                        \
     else                                                                                       \
-      hipLaunchKernelGGL((k_schwarz_small<T, kSym, KM, false>), dim3((unsigned)nwg),           \
-                         dim3(256), 0, s, P, stride, block_nodes(pc), pc.block_elem, pc.nn,    \
+      hipLaunchKernelGGL((k_schwarz_small<T, KM, false>), dim3((unsigned)nwg),                 \
+                         dim3(256), 0, s, Q, stride, block_nodes(pc), pc.block_elem, pc.nn,    \
                          pc.bdim, pc.m, r, q, isd, sc, ai, pc.y, pc.n_blocks, pc.lat);         \
   } while (0)
-    switch (kSym ? pc.m : 0) {
+    switch (pc.m) {
       case 8: FC_SMALL_LAUNCH(8); break;
       case 9: FC_SMALL_LAUNCH(9); break;
       case 16: FC_SMALL_LAUNCH(16); break;
@@ -621,11 +548,10 @@ hipError_t launch_schwarz_phase1(const fc_precond_s& pc, int precision, const do
                                  hipStream_t s) {
   switch (precision) {
     case 0:
-      if (pc.Q) return phase1<double, true>(pc, pc.Q, r, q, sc, ai, s);
-      return phase1<double, false>(pc, pc.P, r, q, sc, ai, s);
+      return phase1<double>(pc, pc.Q, r, q, sc, ai, s);
     case 1: {
       if (!pc.Q32 || !pc.Q) return hipErrorInvalidValue;
-      hipError_t e = phase1<float, true>(pc, pc.Q32, r, q, sc, ai, s);
+      hipError_t e = phase1<float>(pc, pc.Q32, r, q, sc, ai, s);
       if (e != hipSuccess || pc.n_unsafe32 == 0) return e;
       // the first launch has stored alpha
       if (pc.m > 64)

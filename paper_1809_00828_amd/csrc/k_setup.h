@@ -3,13 +3,21 @@
 #include "fc_internal.h"
 
 namespace fc {
-hipError_t launch_jacobi(fc_precond_s& pc, const int32_t* sel, int64_t count,
+// A_B of `count` blocks, listed or b0, b0 + 1, .., into dense [count][m][m]
+hipError_t launch_block_extract(const fc_precond_s& pc, const int32_t* list, int64_t b0,
+                                int64_t count, double* dense, hipStream_t s);
+// Pseudo-inverses of the listed blocks by eigen-decomposition into pc.Q; dense:
+// [count][m][m] scratch, work: [count][2][m][m] where jacobi_needs_work
+hipError_t launch_jacobi(fc_precond_s& pc, const int32_t* sel, int64_t count, double* dense,
                          double* work, int32_t* dropped, hipStream_t s);
 // true when the Jacobi eigen path keeps its blocks in global memory
 bool jacobi_needs_work(int m);
-hipError_t launch_sweep(fc_precond_s& pc, int32_t* need_eig, hipStream_t s);
-// the same certified sweep for m <= 64 (one wave per block)
-hipError_t launch_sweep_small(fc_precond_s& pc, int32_t* need_eig, hipStream_t s);
+// Certified direct inverses of blocks b0 .. b0 + count - 1 into pc.Q; blocks
+// that fail are flagged.  dense: [count][m][m] scratch unless
+// sweep_reads_lattice(pc)
+hipError_t launch_sweep(fc_precond_s& pc, int64_t b0, int64_t count, double* dense,
+                        int32_t* need_eig, hipStream_t s);
+bool sweep_reads_lattice(const fc_precond_s& pc);
 // Scaled Cholesky factors of the local inverses in BF16 into pc.Lbf (needs
 // pc.isd); with `unsafe` instead only flag the blocks whose FP32-rounded
 // scaled inverse is not safely positive definite

@@ -21,6 +21,12 @@ __host__ __device__ __forceinline__ int64_t sym_offset(int k, int i, int m) {
   return k < npair ? (int64_t)(k & ~1) * m + 2 * i + (k & 1) : (int64_t)k * m + i;
 }
 
+// Offset of the stored entry that stands for P_B[i][j].
+__host__ __device__ __forceinline__ int64_t sym_entry(int i, int j, int m) {
+  const int k = j >= i ? j - i : j - i + m;
+  return k <= m / 2 ? sym_offset(k, i, m) : sym_offset(m - k, j, m);
+}
+
 template <typename T>
 __device__ __forceinline__ double to_f64(T v);
 template <>
@@ -208,22 +214,6 @@ __device__ __forceinline__ double sym_row(const T* __restrict__ Qb, const double
     acc0 = madd<A>(Qb[sym_offset(k, i, m)], rb[ip], acc0);
     if (!(even && k == h)) acc1 = madd<A>(Qb[sym_offset(k, im, m)], rb[im], acc1);
   }
-  return (double)acc0 + (double)acc1;
-}
-
-// Dense product for one block row i.
-template <typename T>
-__device__ __forceinline__ double dense_row(const T* __restrict__ Pb, const double* rb, int m,
-                                            int i) {
-  using A = typename Acc<T>::type;
-  A acc0 = 0, acc1 = 0;
-  int j = 0;
-#pragma unroll 8
-  for (; j + 1 < m; j += 2) {
-    acc0 = madd<A>(__builtin_nontemporal_load(Pb + (int64_t)j * m + i), rb[j], acc0);
-    acc1 = madd<A>(__builtin_nontemporal_load(Pb + (int64_t)(j + 1) * m + i), rb[j + 1], acc1);
-  }
-  if (j < m) acc0 = madd<A>(__builtin_nontemporal_load(Pb + (int64_t)j * m + i), rb[j], acc0);
   return (double)acc0 + (double)acc1;
 }
 
