@@ -32,11 +32,12 @@ fc_status pcg_solve(fc_precond_s& pc, const double* b, double* x, const fc_solve
 fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x,
                             const fc_solve_opts& o, fc_solve_info* info, hipStream_t s);
 
-template <class T>
+// kPool: from the memory kept between preconditioners (dev_pool.hip)
+template <bool kPool = false, class T>
 static fc_status dev_alloc(T** p, size_t count) {
   *p = nullptr;
   if (count == 0) return FC_OK;
-  hipError_t e = hipMalloc(p, count * sizeof(T));
+  hipError_t e = kPool ? pool_malloc((void**)p, count * sizeof(T)) : hipMalloc(p, count * sizeof(T));
   if (e != hipSuccess) {
     set_error(std::string("hipMalloc of ") + std::to_string(count * sizeof(T)) +
               " bytes failed: " + hipGetErrorString(e));
@@ -54,11 +55,33 @@ static fc_status upload(T** p, const T* src, size_t count) {
   return FC_OK;
 }
 
-// Device scratch of one call, freed at its end.
+// The same from the kept memory, on the caller's stream: a copy on the legacy
+// stream would break the graph capture of a solve in another thread.
+template <class T>
+static fc_status upload(T** p, const T* src, size_t count, hipStream_t s) {
+  fc_status st = dev_alloc<true>(p, count);
+  if (st != FC_OK || count == 0) return st;
+  FC_HIP(hipMemcpyAsync(*p, src, count * sizeof(T), hipMemcpyHostToDevice, s));
+  FC_HIP(hipStreamSynchronize(s));
+  return FC_OK;
+}
+
+// Device scratch of one call, given back at its end, when the stream has done
+// its work on it.
 struct Scratch {
-  double* p = nullptr;
+  hipStream_t s;
+  void* p[4] = {nullptr, nullptr, nullptr, nullptr};
+  explicit Scratch(hipStream_t stream) : s(stream) {}
+  Scratch(const Scratch&) = delete;
+  template <class T>
+  fc_status get(int k, T** q, size_t count) {
+    const fc_status st = dev_alloc<true>(q, count);
+    p[k] = *q;
+    return st;
+  }
   ~Scratch() {
-    if (p) (void)hipFree(p);
+    (void)hipStreamSynchronize(s);
+    for (void* q : p) pool_free(q);
   }
 };
 
@@ -70,6 +93,7 @@ struct Scratch {
 
 static void free_problem(fc_problem_s* pb) {
   if (!pb) return;
+  pool_problem_destroyed();
   for (void* p : {(void*)pb->A.rowptr, (void*)pb->A.col, (void*)pb->A.val, (void*)pb->A.val32,
                   (void*)pb->A.rows_hi, (void*)pb->A.rows_lo, (void*)pb->A.sell_val,
                   (void*)pb->A.sell_off, (void*)pb->rhs,
@@ -80,13 +104,18 @@ static void free_problem(fc_problem_s* pb) {
 
 static void free_precond(fc_precond_s* pc) {
   if (!pc) return;
+  // buffers that are kept for reuse must be idle on every stream
+  int dev = 0;
+  const bool other = hipGetDevice(&dev) == hipSuccess && dev != pc->device;
+  if (other) (void)hipSetDevice(pc->device);
+  (void)device_idle();
   solver_ws_destroy(pc->ws);
   coarse_destroy(pc->coarse);
-  for (void* p : {(void*)pc->block_elem, (void*)pc->bnodes, (void*)pc->Q,
-                  (void*)pc->Q32,
+  for (void* p : {(void*)pc->block_elem, (void*)pc->bnodes, (void*)pc->Q, (void*)pc->Q32,
                   (void*)pc->unsafe32, (void*)pc->unsafe_flag32, (void*)pc->Lbf, (void*)pc->isd,
                   (void*)pc->inv_ptr, (void*)pc->inv_idx, (void*)pc->fallback, (void*)pc->y})
-    if (p) (void)hipFree(p);
+    pool_free(p);
+  if (other) (void)hipSetDevice(dev);
   delete pc;
 }
 
@@ -94,6 +123,7 @@ static fc_status upload_system_body(const HostSystem& S, hipStream_t stream, fc_
   std::unique_ptr<fc_problem_s, void (*)(fc_problem_s*)> pb(new (std::nothrow) fc_problem_s(),
                                                            free_problem);
   if (!pb) return FC_E_NOMEM;
+  pool_problem_created();
   FC_HIP(hipGetDevice(&pb->device));
   pb->dim = S.dim;
   pb->p = S.p;
@@ -139,21 +169,16 @@ fc_status precond_ensure_map(fc_precond_s& pc, hipStream_t s) {
   std::lock_guard<std::mutex> lock(mu);
   if (pc.inv_ptr) return FC_OK;
   const int64_t n = pc.pb->n_nodes + 1;
-  struct Tmp {
-    int32_t *work = nullptr, *sums = nullptr, *ptr = nullptr, *idx = nullptr;
-    ~Tmp() {
-      for (int32_t* q : {work, sums, ptr, idx})
-        if (q) (void)hipFree(q);
-    }
-  } t;
-  FC_TRY(dev_alloc(&t.work, (size_t)n));
-  FC_TRY(dev_alloc(&t.sums, (size_t)map_scan_blocks(n)));
-  FC_TRY(dev_alloc(&t.ptr, (size_t)n));
-  FC_TRY(dev_alloc(&t.idx, (size_t)std::max<int64_t>(1, pc.n_blocks * pc.nn)));
-  FC_HIP(launch_build_map(pc, pc.pb->n_nodes, t.ptr, t.idx, t.work, t.sums, s));
-  FC_HIP(hipStreamSynchronize(s));
-  std::swap(pc.inv_ptr, t.ptr);
-  std::swap(pc.inv_idx, t.idx);
+  int32_t *work = nullptr, *sums = nullptr, *ptr = nullptr, *idx = nullptr;
+  Scratch tmp(s);
+  FC_TRY(tmp.get(0, &work, (size_t)n));
+  FC_TRY(tmp.get(1, &sums, (size_t)map_scan_blocks(n)));
+  FC_TRY(tmp.get(2, &ptr, (size_t)n));
+  FC_TRY(tmp.get(3, &idx, (size_t)std::max<int64_t>(1, pc.n_blocks * pc.nn)));
+  FC_HIP(launch_build_map(pc, pc.pb->n_nodes, ptr, idx, work, sums, s));
+  tmp.p[2] = tmp.p[3] = nullptr;   // kept
+  pc.inv_idx = idx;
+  pc.inv_ptr = ptr;
   return FC_OK;
 }
 
@@ -416,6 +441,7 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
                                                            free_precond);
   if (!pc) return FC_E_NOMEM;
   pc->pb = pb;
+  pc->device = pb->device;
   pc->m = pm;
   pc->nn = pnn;
   pc->bdim = pb->bdim;
@@ -473,8 +499,8 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     set_error("fc_precond_build: too many block entries for int32 indices");
     return FC_E_UNSUPPORTED;
   }
-  if (patch) FC_TRY(upload(&pc->bnodes, pnodes.data(), pnodes.size()));
-  FC_TRY(upload(&pc->block_elem, blocks.data(), blocks.size()));
+  if (patch) FC_TRY(upload(&pc->bnodes, pnodes.data(), pnodes.size(), s));
+  FC_TRY(upload(&pc->block_elem, blocks.data(), blocks.size(), s));
   // lattice problem with every cell a block: the pull finds a node's blocks
   // from its lattice indices, and the block products of scalar problems a row's
   // unknown (FC_PULL_LATTICE=0 keeps the node lists and the node-to-block map)
@@ -484,26 +510,17 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     if (allowed && !patch && nb == pb->n_el) pc->lat = pb->cells;
   }
   if (pc->lat.dim == 0) FC_TRY(precond_ensure_map(*pc, s));
-  FC_TRY(dev_alloc(&pc->Q, (size_t)nb * sym_block_stride(m)));
-  FC_TRY(dev_alloc(&pc->y, (size_t)nb * m));
-  FC_TRY(dev_alloc(&pc->fallback, (size_t)pb->n_dofs));
+  FC_TRY(dev_alloc<true>(&pc->Q, (size_t)nb * sym_block_stride(m)));
+  FC_TRY(dev_alloc<true>(&pc->y, (size_t)nb * m));
+  FC_TRY(dev_alloc<true>(&pc->fallback, (size_t)pb->n_dofs));
 
   int32_t* d_flag = nullptr;
   int32_t* d_drop = nullptr;
   unsigned long long* d_count = nullptr;
-  struct Tmp {
-    void* p[3] = {nullptr, nullptr, nullptr};
-    ~Tmp() {
-      for (void* q : p)
-        if (q) (void)hipFree(q);
-    }
-  } tmp;
-  FC_TRY(dev_alloc(&d_flag, (size_t)std::max<int64_t>(nb, 1)));
-  tmp.p[0] = d_flag;
-  FC_TRY(dev_alloc(&d_drop, (size_t)std::max<int64_t>(nb, 1)));
-  tmp.p[1] = d_drop;
-  FC_TRY(dev_alloc(&d_count, 1));
-  tmp.p[2] = d_count;
+  Scratch tmp(s);
+  FC_TRY(tmp.get(0, &d_flag, (size_t)std::max<int64_t>(nb, 1)));
+  FC_TRY(tmp.get(1, &d_drop, (size_t)std::max<int64_t>(nb, 1)));
+  FC_TRY(tmp.get(2, &d_count, 1));
   FC_HIP(hipMemsetAsync(d_drop, 0, std::max<int64_t>(nb, 1) * sizeof(int32_t), s));
   FC_HIP(hipMemsetAsync(d_count, 0, sizeof(unsigned long long), s));
 
@@ -517,14 +534,15 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   } else if (nb > 0) {
     // certified direct inverses; without the lattice the blocks are extracted
     // into 256 MB of scratch at a time
-    Scratch dense;
+    Scratch scratch(s);
+    double* dense = nullptr;
     int64_t chunk = nb;
     if (!sweep_reads_lattice(*pc)) {
       chunk = std::min<int64_t>(nb, std::max<int64_t>(1, (int64_t(1) << 25) / ((int64_t)m * m)));
-      FC_TRY(dev_alloc(&dense.p, (size_t)chunk * m * m));
+      FC_TRY(scratch.get(0, &dense, (size_t)chunk * m * m));
     }
     for (int64_t b0 = 0; b0 < nb; b0 += chunk)
-      FC_HIP(launch_sweep(*pc, b0, std::min(chunk, nb - b0), dense.p, d_flag, s));
+      FC_HIP(launch_sweep(*pc, b0, std::min(chunk, nb - b0), dense, d_flag, s));
     std::vector<int32_t> flag(nb);
     FC_HIP(hipMemcpyAsync(flag.data(), d_flag, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     FC_HIP(hipStreamSynchronize(s));
@@ -534,24 +552,21 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   pc->n_eig = (int64_t)sel.size();
   if (!sel.empty()) {
     const int64_t chunk = std::min<int64_t>(2048, (int64_t)sel.size());
-    Scratch dense, work;
+    Scratch scratch(s);
+    double *dense = nullptr, *work = nullptr;
     int32_t* d_sel = nullptr;
-    FC_TRY(upload(&d_sel, sel.data(), sel.size()));
-    fc_status st = dev_alloc(&dense.p, (size_t)chunk * m * m);
-    if (st == FC_OK && jacobi_needs_work(m)) st = dev_alloc(&work.p, (size_t)chunk * 2 * m * m);
-    hipError_t e = hipSuccess;
-    for (int64_t s0 = 0; st == FC_OK && s0 < (int64_t)sel.size() && e == hipSuccess; s0 += chunk)
-      e = launch_jacobi(*pc, d_sel + s0, std::min<int64_t>(chunk, sel.size() - s0), dense.p,
-                        work.p, d_drop, s);
-    const hipError_t e2 = hipStreamSynchronize(s);
-    (void)hipFree(d_sel);
-    FC_TRY(st);
-    FC_HIP(e);
-    FC_HIP(e2);
+    FC_TRY(scratch.get(0, &d_sel, sel.size()));
+    FC_HIP(hipMemcpyAsync(d_sel, sel.data(), sel.size() * sizeof(int32_t), hipMemcpyHostToDevice,
+                          s));
+    FC_TRY(scratch.get(1, &dense, (size_t)chunk * m * m));
+    if (jacobi_needs_work(m)) FC_TRY(scratch.get(2, &work, (size_t)chunk * 2 * m * m));
+    for (int64_t s0 = 0; s0 < (int64_t)sel.size(); s0 += chunk)
+      FC_HIP(launch_jacobi(*pc, d_sel + s0, std::min<int64_t>(chunk, sel.size() - s0), dense, work,
+                           d_drop, s));
   }
   FC_HIP(launch_fallback(*pb, *pc, d_count, s));
   if (o.store_mask & (FC_STORE_F32 | FC_STORE_BF16)) {
-    FC_TRY(dev_alloc(&pc->isd, (size_t)pb->n_dofs));
+    FC_TRY(dev_alloc<true>(&pc->isd, (size_t)pb->n_dofs));
     FC_HIP(launch_inv_sqrt_diag(*pb, pc->isd, s));
   }
   // FP32: the rounded, diagonally scaled inverse D^1/2 P_B D^1/2 in
@@ -560,9 +575,9 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   // a Cholesky factorisation of the rounded matrix shows otherwise are
   // listed and applied from the FP64 copy.
   if (o.store_mask & FC_STORE_F32) {
-    FC_TRY(dev_alloc(&pc->Q32, (size_t)nb * sym_block_stride(m)));
+    FC_TRY(dev_alloc<true>(&pc->Q32, (size_t)nb * sym_block_stride(m)));
     FC_HIP(launch_pack_f32(*pc, s));
-    FC_TRY(dev_alloc(&pc->unsafe_flag32, (size_t)std::max<int64_t>(nb, 1)));
+    FC_TRY(dev_alloc<true>(&pc->unsafe_flag32, (size_t)std::max<int64_t>(nb, 1)));
     FC_HIP(launch_chol_pack(*pc, s, pc->unsafe_flag32));
     std::vector<int32_t> hf(std::max<int64_t>(nb, 1), 0);
     FC_HIP(hipMemcpyAsync(hf.data(), pc->unsafe_flag32, nb * sizeof(int32_t),
@@ -572,11 +587,11 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     for (int64_t k = 0; k < nb; ++k)
       if (hf[k]) list.push_back((int32_t)k);
     pc->n_unsafe32 = (int64_t)list.size();
-    if (!list.empty()) FC_TRY(upload(&pc->unsafe32, list.data(), list.size()));
+    if (!list.empty()) FC_TRY(upload(&pc->unsafe32, list.data(), list.size(), s));
   }
   // BF16: scaled Cholesky factors (positive semi-definite however rounded)
   const size_t ln = (size_t)nb * ((size_t)m * (m + 1) / 2);
-  if (o.store_mask & FC_STORE_BF16) FC_TRY(dev_alloc(&pc->Lbf, ln));
+  if (o.store_mask & FC_STORE_BF16) FC_TRY(dev_alloc<true>(&pc->Lbf, ln));
   if (pc->Lbf) FC_HIP(launch_chol_pack(*pc, s));
   unsigned long long cnt = 0;
   std::vector<int32_t> drop(std::max<int64_t>(nb, 1));

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -136,6 +137,18 @@ struct DeviceBsr {
   int64_t n_rest = 0;
 };
 
+// Device memory that outlives no problem but is reused from one preconditioner
+// to the next (dev_pool.hip).  pool_free: nothing on the device uses p any more.
+hipError_t pool_malloc(void** p, size_t bytes);
+void pool_free(void* p);
+void pool_problem_created();
+void pool_problem_destroyed();
+
+// A synchronisation of the device ends the graph capture of any other thread:
+// device_idle() waits for the captures of this library, which hold the mutex.
+std::mutex& capture_mutex();
+hipError_t device_idle();
+
 // Per-workgroup (p, q) partials a kernel derives the step length from; np = 0:
 // the step length is in CgScalars already.
 struct AlphaIn {
@@ -166,6 +179,7 @@ struct fc_problem_s {
 
 struct fc_precond_s {
   fc_problem pb = nullptr;
+  int device = 0;
   int32_t m = 0, nn = 0, bdim = 1;
   int64_t n_blocks = 0;
   int32_t block_kind = FC_BLOCK_ELEMENT;

@@ -78,11 +78,10 @@ void solver_ws_destroy(SolverWs* w) {
   if (!w) return;
   if (w->exec) (void)hipGraphExecDestroy(w->exec);
   if (w->graph) (void)hipGraphDestroy(w->graph);
-  for (auto* p : {w->r, w->z, w->p, w->q, w->t, w->d, w->ro, w->partial, w->ring, w->ring_part})
-    if (p) (void)hipFree(p);
-  if (w->p32) (void)hipFree(w->p32);
-  if (w->fr) (void)hipFree(w->fr);
-  if (w->sc) (void)hipFree(w->sc);
+  for (void* p : {(void*)w->r, (void*)w->z, (void*)w->p, (void*)w->q, (void*)w->t, (void*)w->d,
+                  (void*)w->ro, (void*)w->partial, (void*)w->ring, (void*)w->ring_part,
+                  (void*)w->p32, (void*)w->fr, (void*)w->sc})
+    pool_free(p);
   if (w->host) (void)hipHostFree(w->host);
   for (auto& e : w->ev) if (e) (void)hipEventDestroy(e);
   for (auto& e : w->tev) if (e) (void)hipEventDestroy(e);
@@ -680,17 +679,19 @@ static fc_status ensure_ws(fc_precond_s& pc, SolverWs** out) {
     w = new SolverWs();
     pc.ws = w;
     w->n = n;
-    FC_HIP(hipMalloc(&w->r, n * sizeof(double)));
-    FC_HIP(hipMalloc(&w->z, n * sizeof(double)));
-    FC_HIP(hipMalloc(&w->p, n * sizeof(double)));
-    FC_HIP(hipMalloc(&w->q, n * sizeof(double)));
-    FC_HIP(hipMalloc(&w->t, n * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->r, n * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->z, n * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->p, n * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->q, n * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->t, n * sizeof(double)));
     w->partial_len = kPartials;
-    FC_HIP(hipMalloc(&w->partial, w->partial_len * sizeof(double)));
-    FC_HIP(hipMalloc(&w->sc, sizeof(CgScalars)));
-    FC_HIP(hipMemset(w->sc, 0, sizeof(CgScalars)));
+    FC_HIP(pool_malloc((void**)&w->partial, w->partial_len * sizeof(double)));
+    FC_HIP(pool_malloc((void**)&w->sc, sizeof(CgScalars)));
     FC_HIP(hipHostMalloc(&w->host, sizeof(CgScalars), hipHostMallocDefault));
     FC_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
+    // not on the legacy stream, which would break a capture in another thread
+    FC_HIP(hipMemsetAsync(w->sc, 0, sizeof(CgScalars), w->stream));
+    FC_HIP(hipStreamSynchronize(w->stream));
     for (auto& e : w->ev) FC_HIP(hipEventCreate(&e));
   }
   *out = w;
@@ -710,14 +711,15 @@ static fc_status ensure_ring(SolverWs& w, int m) {
     w.graph = nullptr;
   }
   w.key_prec = -1;
-  if (w.ring) FC_HIP(hipFree(w.ring));
-  if (w.ring_part) FC_HIP(hipFree(w.ring_part));
+  FC_HIP(device_idle());
+  pool_free(w.ring);
+  pool_free(w.ring_part);
   w.ring = nullptr;
   w.ring_part = nullptr;
   w.ring_cap = 0;
-  FC_HIP(hipMalloc(&w.ring, (size_t)2 * m * w.n * sizeof(double)));
-  FC_HIP(hipMalloc(&w.ring_part, (size_t)m * ring_blocks(w.n) * sizeof(double)));
-  if (!w.fr) FC_HIP(hipMalloc(&w.fr, sizeof(FcgRing)));
+  FC_HIP(pool_malloc((void**)&w.ring, (size_t)2 * m * w.n * sizeof(double)));
+  FC_HIP(pool_malloc((void**)&w.ring_part, (size_t)m * ring_blocks(w.n) * sizeof(double)));
+  if (!w.fr) FC_HIP(pool_malloc((void**)&w.fr, sizeof(FcgRing)));
   w.ring_cap = m;
   return FC_OK;
 }
@@ -880,6 +882,7 @@ static fc_status ensure_graph(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, 
     w.graph = nullptr;
   }
   w.key_prec = -1;
+  std::lock_guard<std::mutex> lock(capture_mutex());
   FC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   hipError_t e = enqueue_steps(pc, w, a.x, chunk, a.precA, a.precS, s, nullptr, a.learn, 1,
                                a.fcg_m);
@@ -1074,9 +1077,9 @@ fc_status pcg_solve(fc_precond_s& pc, const double* b, double* x, const fc_solve
     // the stored matrix indefinite on the low-energy fictitious modes).
     int precA = 1;
     FC_TRY_ST(ensure_mixed_matrix(pb, s));
-    if (!w.p32) FC_HIP(hipMalloc(&w.p32, n * sizeof(float)));
-    if (!w.d) FC_HIP(hipMalloc(&w.d, n * sizeof(double)));
-    if (!w.ro) FC_HIP(hipMalloc(&w.ro, n * sizeof(double)));
+    if (!w.p32) FC_HIP(pool_malloc((void**)&w.p32, n * sizeof(float)));
+    if (!w.d) FC_HIP(pool_malloc((void**)&w.d, n * sizeof(double)));
+    if (!w.ro) FC_HIP(pool_malloc((void**)&w.ro, n * sizeof(double)));
     FC_HIP(hipEventRecord(w.ev[1], s));
     hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, s, x, 0.0, n);
     hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, b, w.ro, n);
@@ -1272,7 +1275,7 @@ extern "C" fc_status fc_learned_snapshots(fc_precond pc, const double* b, const 
   SolverWs& w = *wp;
   fc_problem_s& pb = *pc->pb;
   const int64_t n = pb.n_dofs;
-  if (!w.d) FC_HIP(hipMalloc(&w.d, n * sizeof(double)));
+  if (!w.d) FC_HIP(pool_malloc((void**)&w.d, n * sizeof(double)));
   double* x = w.d;
   hipStream_t s = w.stream;
   FC_HIP(hipEventRecord(w.ev[0], user));
