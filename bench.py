@@ -776,8 +776,7 @@ def main():
     # the counter traffic was taken on the elasticity workload
     on_bench_workload = not args.small and args.workload == "elastic32"
     if info.get("sliced"):
-        spmv_name = ("k_spmv_sell (SpMV q = A p: sliced scalar rows, then the boundary vertex "
-                     "rows with k_spmv_bsr)")
+        spmv_name = "k_spmv_sell (SpMV q = A p: sliced scalar rows)"
     else:
         spmv_name = (f"k_spmv_bsr<{info['bsr_dim']},{info['spmv_group']},double,"
                      f"{'lattice' if info.get('lattice_columns') else 'columns'}> (SpMV q = A p)")

@@ -96,7 +96,7 @@ static void free_problem(fc_problem_s* pb) {
   pool_problem_destroyed();
   for (void* p : {(void*)pb->A.rowptr, (void*)pb->A.col, (void*)pb->A.val, (void*)pb->A.val32,
                   (void*)pb->A.rows_hi, (void*)pb->A.rows_lo, (void*)pb->A.sell_val,
-                  (void*)pb->A.sell_off, (void*)pb->rhs,
+                  (void*)pb->A.sell_slices, (void*)pb->rhs,
                   (void*)pb->elem_nodes, (void*)pb->diag})
     if (p) (void)hipFree(p);
   delete pb;

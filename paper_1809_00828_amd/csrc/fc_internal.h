@@ -105,6 +105,24 @@ inline PullLattice make_pull_lattice(int32_t dim, int32_t n, int32_t p) {
   return l;
 }
 
+// A slice of the sliced copy: 64 rows of class cls (bit d: the indices along
+// direction d are interior vertices), rows 64 chunk .. of its enumeration.  Its
+// entries are stored in pairs: entries 2j and 2j + 1 of lane l at
+// val[off + 128 j + 2 l] and the next word, an odd last entry alone at
+// off + 128 j + l (zero for lanes past the class's end).
+struct SellSlice {
+  int64_t off;
+  int32_t cls, chunk;
+};
+
+struct SellView {
+  const double* val = nullptr;
+  const SellSlice* slices = nullptr;
+  int32_t n_slices = 0, dim = 0, n1 = 0;
+  uint32_t nv = 0, nn = 0;   // interior vertices and other indices per direction
+  FastDiv dv, dn;            // division by nv and nn
+};
+
 struct DeviceBsr {
   int32_t bdim = 1;
   int64_t n_rows = 0;      // block rows
@@ -121,21 +139,26 @@ struct DeviceBsr {
   int32_t* rows_hi = nullptr;
   int32_t* rows_lo = nullptr;
   int64_t n_hi = 0, n_lo = 0;
-  // Sliced copy of a scalar lattice matrix (degree p <= 4): the rows of one
-  // lattice line (fixed y, z) and one x class, interior vertex indices
-  // (x = p, 2p, ..) or the other interior indices, in slices of 64 rows
-  // whose boxes have equal shape.  A slice's entries are stored in pairs:
-  // entries 2j and 2j + 1 of lane l at sell_val[sell_off[s] + 128 j + 2 l]
-  // and the next word, an odd last entry alone at sell_off[s] + 128 j + l
-  // (zero for lanes past the class's end).
-  // The n_rest boundary vertex rows (x = 0 and x = n1 - 1 of every line) use
-  // the row layout.
+  // Sliced copy of a scalar lattice matrix (degree p <= 4; spmv_dev.h)
   double* sell_val = nullptr;
-  int64_t* sell_off = nullptr;   // [n_slices + 1]
+  SellSlice* sell_slices = nullptr;
   int64_t n_slices = 0;
-  int32_t sell_cv = 0, sell_nv = 0, sell_nn = 0;   // vertex slices per line, rows per class
-  int64_t n_rest = 0;
+  int32_t sell_nv = 0;     // interior vertices per direction
 };
+
+inline SellView sell_view(const DeviceBsr& A) {
+  SellView v;
+  v.val = A.sell_val;
+  v.slices = A.sell_slices;
+  v.n_slices = (int32_t)A.n_slices;
+  v.dim = A.lat.dim;
+  v.n1 = A.lat.n1;
+  v.nv = (uint32_t)A.sell_nv;
+  v.nn = (uint32_t)(A.lat.n1 - A.sell_nv);
+  v.dv = make_fastdiv(v.nv > 0 ? v.nv : 1);
+  v.dn = make_fastdiv(v.nn);
+  return v;
+}
 
 // Device memory that outlives no problem but is reused from one preconditioner
 // to the next (dev_pool.hip).  pool_free: nothing on the device uses p any more.

@@ -25,13 +25,15 @@
 // Matrices assembled from a problem description have lattice rows: the
 // columns and the start of each row follow from the row's lattice indices
 // and are computed, not read.  Scalar ones (degree p <= 4) also keep a
-// sliced copy, 64 rows of one lattice line with equal boxes per slice, for
+// sliced copy, 64 rows with boxes of equal shape per slice (spmv_dev.h), for
 // the whole-matrix product (k_spmv_sell below).
+#include <algorithm>
 #include <cstdlib>
 #include <vector>
 
 #include "dev_common.h"
 #include "k_spmv.h"
+#include "spmv_dev.h"
 
 namespace fc {
 
@@ -205,265 +207,47 @@ __global__ __launch_bounds__(256, 5) void k_spmv_bsr(
 }
 
 // ---------------------------------------------------------------- sliced
-// x index of lane row i of a class: interior vertices x = p (i + 1), other
-// interior indices in ascending order (p - 1 per cell; none when p = 1)
-__device__ __forceinline__ int sell_x(bool vertex, int i, int p) {
-  if (vertex || p == 1) return p * (i + 1);
-  return (i / (p - 1)) * p + 1 + i % (p - 1);
-}
-
-template <int P>
-__device__ __forceinline__ int sell_x_p(bool vertex, int i) {
-  if constexpr (P == 1) {
-    return i + 1;
-  } else {
-    return vertex ? P * (i + 1) : (i / (P - 1)) * P + 1 + i % (P - 1);
-  }
-}
-
-// Lattice range of the functions whose support meets that of index g along
-// one direction (as in row_box_at), for degree P.
-template <int P>
-__device__ __forceinline__ void dir_box_p(int g, int n1, int* lo, int* len) {
-  if (g % P == 0) {
-    const int a = max(0, g - P), b = min(n1 - 1, g + P);
-    *lo = a;
-    *len = b - a + 1;
-  } else {
-    *lo = (g / P) * P;
-    *len = P + 1;
-  }
-}
-
-struct SellSlice {
-  int64_t line;
-  bool vertex;
-  int chunk;
-};
-
-__device__ __forceinline__ SellSlice sell_slice(int64_t s, int cv, int cn) {
-  SellSlice r;
-  const int spl = cv + cn;
-  r.line = s / spl;
-  const int loc = (int)(s - r.line * spl);
-  r.vertex = loc < cv;
-  r.chunk = r.vertex ? loc : loc - cv;
-  return r;
-}
-
-// The same for the product kernel: fewer than 2^31 slices, and the slices
-// per line divided by multiply-shift.
-__device__ __forceinline__ SellSlice sell_slice_fast(uint32_t s, int cv, const FastDiv dspl) {
-  SellSlice r;
-  const uint32_t line = fdiv(s, dspl);
-  const int loc = (int)(s - line * dspl.d);
-  r.line = line;
-  r.vertex = loc < cv;
-  r.chunk = r.vertex ? loc : loc - cv;
-  return r;
-}
-
 // sell_val from the row layout, one workgroup per slice
+template <int P>
 __global__ __launch_bounds__(256) void k_sell_build(const double* __restrict__ val,
-                                                    const int64_t* __restrict__ off,
-                                                    int64_t n_slices, int cv, int cn, int nv,
-                                                    int nn, const LatticeInfo lat,
+                                                    const SellView A, const LatticeInfo lat,
                                                     double* __restrict__ sv) {
-  for (int64_t s = blockIdx.x; s < n_slices; s += gridDim.x) {
-    const SellSlice sl = sell_slice(s, cv, cn);
-    const int n1 = lat.n1;
-    const int y0 = lat.dim >= 2 ? (int)(sl.line % n1) : 0;
-    const int z0 = lat.dim == 3 ? (int)(sl.line / n1) : 0;
-    const int64_t len = (off[s + 1] - off[s]) / 64;
-    for (int64_t e = threadIdx.x; e < 64 * len; e += blockDim.x) {
-      const int k = (int)(e / 64), l = (int)(e % 64);
-      const int i = sl.chunk * 64 + l;
-      double v = 0.0;
-      if (i < (sl.vertex ? nv : nn)) {
-        const int c[3] = {sell_x(sl.vertex, i, lat.p), y0, z0};
-        v = val[lattice_row_start_at(c, row_box_at(c, lat), lat) + k];
-      }
+  for (int64_t s = blockIdx.x; s < A.n_slices; s += gridDim.x) {
+    const SellSlice sl = A.slices[s];
+    const int l = threadIdx.x % 64;
+    const SellRow r = sell_row<P>(sl, l, A);
+    int c[3];
+    lattice_coords(r.row, lat, c);
+    const RowBox box = row_box_at(c, lat);
+    const int len = box.len[0] * box.len[1] * box.len[2];
+    const double* v = val + lattice_row_start_at(c, box, lat);
+    for (int k = threadIdx.x / 64; k < len; k += 4) {
       // entries in pairs: lane l holds entries 2j, 2j + 1 at 128 j + 2 l + 0/1;
       // an odd last entry alone at 128 j + l
-      const int64_t dst = (k == len - 1 && (len & 1)) ? (int64_t)(k / 2) * 128 + l
-                                                      : (int64_t)(k / 2) * 128 + 2 * l + (k & 1);
-      sv[off[s] + dst] = v;
+      const int dst = (k == len - 1 && (len & 1)) ? (k / 2) * 128 + l
+                                                  : (k / 2) * 128 + 2 * l + (k & 1);
+      sv[sl.off + dst] = r.valid ? v[k] : 0.0;
     }
   }
 }
 
-// y = A x on the sliced rows: one wave per slice, one row per lane.  The
-// box entries run x-pencil by x-pencil (kx fastest); every lane of a slice
-// has the same pencil count and length, so the pencil's column offset in y
-// and z is the same for all lanes.  Pencils go two per round, all their
-// loads issued before the first FMA: a round's 2K entries are K paired
-// values per lane (one 16-byte load each, 1 KB contiguous per wave; 8 %
-// faster than one 8-byte load per entry at 64^3 cells, p = 2), and each
-// pencil's x run is read two entries per load.  A last round with one
-// pencil reads its odd last entry alone.  kNT: the values (read once) are
-// streamed non-temporally.  The pencil's (y, z) offsets are stepped, not
-// divided out of its index.
-template <int K, bool kNT>
-__device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, int l,
-                                               const double* __restrict__ xb, int len1,
-                                               int npen, int64_t n1) {
-  typedef double d2 __attribute__((ext_vector_type(2)));
-  typedef double d2a8 __attribute__((ext_vector_type(2), aligned(8)));
-  double acc = 0.0;
-  int qy = 0, qz = 0;   // offsets of pencil q
-  for (int q = 0; q < npen; q += 2) {
-    const double* vr = vs + (int64_t)128 * K * (q / 2) + 2 * l;
-    const double* xp0 = xb + n1 * (qy + n1 * qz);
-    if (++qy == len1) {
-      qy = 0;
-      ++qz;
-    }
-    if (q + 1 < npen) {
-      const double* xp1 = xb + n1 * (qy + n1 * qz);
-      if (++qy == len1) {
-        qy = 0;
-        ++qz;
-      }
-      double a[2 * K], b[2 * K];
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        const d2* p = reinterpret_cast<const d2*>(vr + 128 * j);
-        const d2 t = kNT ? __builtin_nontemporal_load(p) : *p;
-        a[2 * j] = t.x;
-        a[2 * j + 1] = t.y;
-      }
-#pragma unroll
-      for (int kx = 0; kx + 1 < K; kx += 2) {
-        const d2a8 t0 = *reinterpret_cast<const d2a8*>(xp0 + kx);
-        const d2a8 t1 = *reinterpret_cast<const d2a8*>(xp1 + kx);
-        b[kx] = t0.x;
-        b[kx + 1] = t0.y;
-        b[K + kx] = t1.x;
-        b[K + kx + 1] = t1.y;
-      }
-      if (K & 1) {
-        b[K - 1] = xp0[K - 1];
-        b[2 * K - 1] = xp1[K - 1];
-      }
-#pragma unroll
-      for (int e = 0; e < 2 * K; ++e) acc = fma(a[e], b[e], acc);
-    } else {
-      double a[K], b[K];
-#pragma unroll
-      for (int j = 0; j < K / 2; ++j) {
-        const d2* p = reinterpret_cast<const d2*>(vr + 128 * j);
-        const d2 t = kNT ? __builtin_nontemporal_load(p) : *p;
-        a[2 * j] = t.x;
-        a[2 * j + 1] = t.y;
-      }
-      if (K & 1) {
-        const double* p = vr - l + 128 * (K / 2);   // the odd last entry, alone
-        a[K - 1] = kNT ? __builtin_nontemporal_load(p) : *p;
-      }
-#pragma unroll
-      for (int kx = 0; kx + 1 < K; kx += 2) {
-        const d2a8 t0 = *reinterpret_cast<const d2a8*>(xp0 + kx);
-        b[kx] = t0.x;
-        b[kx + 1] = t0.y;
-      }
-      if (K & 1) b[K - 1] = xp0[K - 1];
-#pragma unroll
-      for (int e = 0; e < K; ++e) acc = fma(a[e], b[e], acc);
-    }
-  }
-  return acc;
-}
-
-// Product of one scalar lattice row with x by eight lanes (lane = 0 .. 7), eight
-// entries per lane and round, from the row layout: the order k_spmv_bsr<1, 8>
-// takes.  Every lane receives the sum.
-__device__ __forceinline__ double lattice_row8(const double* __restrict__ v, int L,
-                                               const RowBox& box, int n1,
-                                               const double* __restrict__ x, int lane) {
-  double acc = 0.0;
-  for (int k = lane; k < L; k += 64) {
-    double a[8], xv[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int ku = k + 8 * u;
-      const bool on = ku < L;
-      a[u] = on ? v[ku] : 0.0;
-      xv[u] = on ? x[lattice_col(box, ku, n1)] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc = fma(a[u], xv[u], acc);
-  }
-  return group_sum<8>(acc);
-}
-
-// The first rest_blocks workgroups take the boundary vertex rows (x = 0 and x
-// = n1 - 1 of every line, 32 rows each) from the row layout, the others the
-// slices: launched apart, the 1.6 % of the rows at 64^3 cells, p = 2 cost 11
-// us of load latency after the slices' 217 us.  partial (may be null): (x, y)
-// per workgroup.
+// y = A x, one wave per slice.  partial (may be null): (x, y) per workgroup.
 template <int P, bool kNT>
-__global__ __launch_bounds__(256) void k_spmv_sell(
-    const double* __restrict__ sv, const int64_t* __restrict__ off, int64_t n_slices, int cv,
-    const FastDiv dspl, int nv, int nn, const double* __restrict__ val, int rest_blocks,
-    int64_t n_rest, const double* __restrict__ x, double* __restrict__ y,
-    double* __restrict__ partial, const CgScalars* __restrict__ sc, const LatticeInfo lat) {
-  __shared__ double lds[16];
+__global__ __launch_bounds__(256) void k_spmv_sell(const SellView A, const double* __restrict__ x,
+                                                   double* __restrict__ y,
+                                                   double* __restrict__ partial,
+                                                   const CgScalars* __restrict__ sc) {
+  __shared__ double lds[4];
   if (sc && sc->done) return;
-  const int l = threadIdx.x % 64;
-  const int n1 = lat.n1;
+  // the slice is wave-uniform, and what depends on it alone stays in scalar
+  // registers
+  const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   double dot = 0.0;
-  if ((int)blockIdx.x < rest_blocks) {
-    const int64_t rr = (int64_t)blockIdx.x * 32 + threadIdx.x / 8;
-    if (rr < n_rest) {
-      const uint32_t line = (uint32_t)(rr >> 1);
-      const uint32_t lz = fdiv(line, lat.dn1);
-      const int c[3] = {(rr & 1) ? n1 - 1 : 0, lat.dim == 3 ? (int)(line - lz * n1) : (int)line,
-                        lat.dim == 3 ? (int)lz : 0};
-      const RowBox box = row_box_at(c, lat);
-      const double acc = lattice_row8(val + lattice_row_start_at(c, box, lat),
-                                      box.len[0] * box.len[1] * box.len[2], box, n1, x,
-                                      threadIdx.x % 8);
-      if (threadIdx.x % 8 == 0) {
-        const int64_t row = c[0] + (int64_t)n1 * (c[1] + (int64_t)n1 * c[2]);
-        y[row] = acc;
-        if (partial) dot = x[row] * acc;
-      }
-    }
-  } else {
-    // the slice of this wave (wave-uniform, so everything derived from it
-    // stays in scalar registers; no division by a run-time value)
-    const int64_t s = xcd_remap(blockIdx.x - rest_blocks, gridDim.x - rest_blocks) * 4 +
-                      __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    if (s < n_slices) {
-      const SellSlice sl = sell_slice_fast((uint32_t)s, cv, dspl);
-      const uint32_t lz = fdiv((uint32_t)sl.line, lat.dn1);
-      const int y0 = lat.dim == 3 ? (int)((uint32_t)sl.line - lz * (uint32_t)n1) : (int)sl.line;
-      const int z0 = lat.dim == 3 ? (int)lz : 0;
-      int lo1 = 0, len1 = 1, lo2 = 0, len2 = 1;
-      dir_box_p<P>(y0, n1, &lo1, &len1);
-      if (lat.dim == 3) dir_box_p<P>(z0, n1, &lo2, &len2);
-      const int count = sl.vertex ? nv : nn;
-      const int i = sl.chunk * 64 + l;
-      const bool valid = i < count;
-      const int xr = sell_x_p<P>(sl.vertex, valid ? i : count - 1);
-      const int lo0 = sl.vertex ? xr - P : (xr / P) * P;
-      const double* vs = sv + off[s];
-      const double* xb = x + lo0 + (int64_t)n1 * (lo1 + (int64_t)n1 * lo2);
-      const int npen = len1 * len2;
-      // two pencils per round: 1 % faster than four and 3 % faster than eight
-      // at 64^3 cells, p = 2
-      const double acc = sl.vertex ? sell_pencils<2 * P + 1, kNT>(vs, l, xb, len1, npen, n1)
-                                   : sell_pencils<P + 1, kNT>(vs, l, xb, len1, npen, n1);
-      const int64_t row = xr + (int64_t)n1 * (y0 + (int64_t)n1 * z0);
-      if (valid) {
-        y[row] = acc;
-        if (partial) dot = x[row] * acc;
-      }
-    }
-  }
+  if (s < A.n_slices) dot = sell_slice_product<P, kNT>(A, s, l, x, y);
   if (!partial) return;
   dot = wave_sum_last(dot);
-  if (l == 63) lds[threadIdx.x / 64] = dot;
+  if (l == 63) lds[w] = dot;
   __syncthreads();
   if (threadIdx.x == 0) partial[blockIdx.x] = ((lds[0] + lds[1]) + lds[2]) + lds[3];
 }
@@ -509,12 +293,9 @@ static bool use_sell(const DeviceBsr& A) {
   return lattice_allowed() && A.lat.dim > 0 && A.bdim == 1 && A.sell_val;
 }
 
-// workgroups of the sliced product: boundary rows, then slices
-static int sell_rest_blocks(const DeviceBsr& A) { return (int)((A.n_rest + 31) / 32); }
-
 // Workgroups of the whole-matrix product (one (x, y) partial each when asked).
 static int64_t spmv_blocks(const DeviceBsr& A) {
-  return use_sell(A) ? sell_rest_blocks(A) + (A.n_slices + 3) / 4 : num_tiles(A);
+  return use_sell(A) ? (A.n_slices + 3) / 4 : num_tiles(A);
 }
 
 template <int B, typename T, typename XT>
@@ -529,24 +310,19 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
   // the whole scalar matrix with its sliced copy
   if constexpr (B == 1 && sizeof(T) == 8 && sizeof(XT) == 8) {
     if (use_sell(A) && !rows) {
-      const int cn = A.sell_nn > 0 ? (A.sell_nn + 63) / 64 : 0;
-      const FastDiv dspl = make_fastdiv((uint32_t)(A.sell_cv + cn));
+      const SellView v = sell_view(A);
       dim3 g((unsigned)spmv_blocks(A)), b(256);
       // values streamed non-temporally (3 % faster at 64^3 cells, p = 2;
       // FC_SPMV_SELL_NT=0 reads them through the caches)
       static const bool sell_nt = env_int("FC_SPMV_SELL_NT", 1) != 0;
-#define FC_SELL(PP)                                                                           \
-  do {                                                                                        \
-    if (sell_nt)                                                                              \
-      hipLaunchKernelGGL((k_spmv_sell<PP, true>), g, b, 0, s, A.sell_val, A.sell_off,         \
-                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, val,              \
-                         sell_rest_blocks(A), A.n_rest, (const double*)x, y, partial, sc,     \
-                         A.lat);                                                              \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_spmv_sell<PP, false>), g, b, 0, s, A.sell_val, A.sell_off,        \
-                         A.n_slices, A.sell_cv, dspl, A.sell_nv, A.sell_nn, val,              \
-                         sell_rest_blocks(A), A.n_rest, (const double*)x, y, partial, sc,     \
-                         A.lat);                                                              \
+#define FC_SELL(PP)                                                                          \
+  do {                                                                                       \
+    if (sell_nt)                                                                             \
+      hipLaunchKernelGGL((k_spmv_sell<PP, true>), g, b, 0, s, v, (const double*)x, y, partial, \
+                         sc);                                                                \
+    else                                                                                     \
+      hipLaunchKernelGGL((k_spmv_sell<PP, false>), g, b, 0, s, v, (const double*)x, y,       \
+                         partial, sc);                                                       \
   } while (0)
       switch (A.lat.p) {
         case 1: FC_SELL(1); break;
@@ -608,59 +384,75 @@ int spmv_dot_blocks(const DeviceBsr& A) {
   return nb <= 1024 ? (int)nb : 0;
 }
 
-// Host side of the sliced copy: slice offsets (each slice holds 64 lanes of
-// its box size), then the copy on the device; the two boundary vertex rows of
-// every line stay in the row layout.
+// Host side of the sliced copy: the slices of every class in the order of their
+// first rows, then the copy on the device.
 static hipError_t spmv_build_sell(DeviceBsr& A, hipStream_t s) {
   const LatticeInfo lat = A.lat;
-  const int n1 = lat.n1, p = lat.p, n = (n1 - 1) / p;
-  const int nv = n - 1, nn = n * (p - 1);
-  const int cv = nv > 0 ? (nv + 63) / 64 : 0, cn = nn > 0 ? (nn + 63) / 64 : 0;
-  const int64_t lines = lat.dim == 3 ? (int64_t)n1 * n1 : n1;
-  if (cv + cn == 0) return hipSuccess;
-  auto len = [&](int g) {
-    if (g % p != 0) return p + 1;
-    return std::min(n1 - 1, g + p) - std::max(0, g - p) + 1;
+  const int64_t n1 = lat.n1;
+  const int p = lat.p, n = (lat.n1 - 1) / p;
+  const int64_t nv = n - 1, nn = n1 - nv;
+  struct Entry {
+    int64_t first;   // line of the slice's first row
+    SellSlice sl;
   };
-  std::vector<int64_t> off;
-  off.reserve((size_t)(lines * (cv + cn) + 1));
-  off.push_back(0);
-  for (int64_t line = 0; line < lines; ++line) {
-    const int y0 = (int)(line % n1), z0 = lat.dim == 3 ? (int)(line / n1) : 0;
-    const int64_t yz = (int64_t)len(y0) * (lat.dim == 3 ? len(z0) : 1);
-    for (int k = 0; k < cv; ++k) off.push_back(off.back() + 64 * yz * (2 * p + 1));
-    for (int k = 0; k < cn; ++k) off.push_back(off.back() + 64 * yz * (p + 1));
+  std::vector<Entry> list;
+  auto index = [&](bool vertex, int64_t i) -> int64_t {
+    if (vertex) return p * (i + 1);
+    if (i == 0 || p == 1) return i == 0 ? 0 : n1 - 1;
+    return std::min<int64_t>(n1 - 1, ((i - 1) / (p - 1)) * p + 1 + (i - 1) % (p - 1));
+  };
+  for (int cls = 0; cls < (lat.dim == 3 ? 8 : 4); ++cls) {
+    const bool vy = cls & 2, vz = cls & 4;
+    const int64_t cx = cls & 1 ? nv : nn, cy = vy ? nv : nn, cz = lat.dim < 3 ? 1 : vz ? nv : nn;
+    for (int64_t t = 0; t < cx * cy * cz; t += 64) {
+      const int64_t line = t / cx;
+      const int64_t y = index(vy, line % cy), z = lat.dim == 3 ? index(vz, line / cy) : 0;
+      list.push_back({z * n1 + y, {0, cls, (int32_t)(t / 64)}});
+    }
   }
-  const int64_t ns = (int64_t)off.size() - 1;
-  hipError_t e = hipMalloc(&A.sell_val, (size_t)off.back() * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&A.sell_off, off.size() * sizeof(int64_t));
+  std::stable_sort(list.begin(), list.end(),
+                   [](const Entry& a, const Entry& b) { return a.first < b.first; });
+  std::vector<SellSlice> slices;
+  slices.reserve(list.size());
+  int64_t off = 0;
+  for (Entry& e : list) {
+    e.sl.off = off;
+    slices.push_back(e.sl);
+    int64_t len = 64;
+    for (int d = 0; d < lat.dim; ++d) len *= e.sl.cls >> d & 1 ? 2 * p + 1 : p + 1;
+    off += len;
+  }
+  hipError_t e = hipMalloc(&A.sell_val, (size_t)off * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc(&A.sell_slices, slices.size() * sizeof(SellSlice));
   if (e == hipSuccess)
-    e = hipMemcpyAsync(A.sell_off, off.data(), off.size() * sizeof(int64_t),
+    e = hipMemcpyAsync(A.sell_slices, slices.data(), slices.size() * sizeof(SellSlice),
                        hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_sell_build, dim3(4096), dim3(256), 0, s, A.val, A.sell_off, ns, cv, cn,
-                       nv, nn, lat, A.sell_val);
+    A.n_slices = (int64_t)slices.size();
+    A.sell_nv = (int32_t)nv;
+    const SellView v = sell_view(A);
+    const dim3 g((unsigned)std::min<int64_t>(A.n_slices, 65536)), b(256);
+    switch (p) {
+      case 1: hipLaunchKernelGGL(k_sell_build<1>, g, b, 0, s, A.val, v, lat, A.sell_val); break;
+      case 2: hipLaunchKernelGGL(k_sell_build<2>, g, b, 0, s, A.val, v, lat, A.sell_val); break;
+      case 3: hipLaunchKernelGGL(k_sell_build<3>, g, b, 0, s, A.val, v, lat, A.sell_val); break;
+      default: hipLaunchKernelGGL(k_sell_build<4>, g, b, 0, s, A.val, v, lat, A.sell_val); break;
+    }
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);   // the host vector dies here
   if (e != hipSuccess) {
-    for (void* q : {(void*)A.sell_val, (void*)A.sell_off})
+    for (void* q : {(void*)A.sell_val, (void*)A.sell_slices})
       if (q) (void)hipFree(q);
     A.sell_val = nullptr;
-    A.sell_off = nullptr;
+    A.sell_slices = nullptr;
     // without room for the copy the row layout serves every product
     if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
       return hipSuccess;
     }
-    return e;
   }
-  A.n_slices = ns;
-  A.sell_cv = cv;
-  A.sell_nv = nv;
-  A.sell_nn = nn;
-  A.n_rest = 2 * lines;
-  return hipSuccess;
+  return e;
 }
 
 // mismatches between stored rows and lattice boxes: length, start and
