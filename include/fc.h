@@ -347,9 +347,10 @@ fc_status fc_pcg_solve_noalloc(fc_problem pb, fc_precond pc, const double* b_dev
  * fc_batch_create groups nprob problems with their preconditioners (built
  * by fc_precond_build, FP64) into one batch: shape classes, segmented work
  * lists of (problem, tile), per-problem CG scalars.  With autotune != 0 it
- * times the SpMV group widths and the block-product variants of every
- * shape class on the batch's own data and keeps the fastest (the choices
- * and timings are in the report of fc_batch_info).  The handles must
+ * times the group widths of the row-layout products of every shape class
+ * on the batch's own data and keeps the fastest (the choices and timings
+ * are in the report of fc_batch_info; members with a sliced copy need
+ * none).  The handles must
  * outlive the batch.  Errors: FC_E_ARG, FC_E_NOMEM, FC_E_DEVICE.
  * fc_pcg_solve_batch runs FP64 PCG (Sec. 5 with S of Eq. 6) on every
  * problem from x = 0; b_dev and x_dev are host arrays of nprob device

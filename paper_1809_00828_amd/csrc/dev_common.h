@@ -100,7 +100,7 @@ __device__ __forceinline__ T block_sum(T v, T* lds /* >= 16 */) {
 // counts the step and stores the scalars.  False: breakdown, the step is not
 // taken.  red: LDS of at least 16 doubles.
 __device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double* red,
-                                         double* alpha) {
+                                         double* alpha, bool first) {
   const double rz = sc->rzn;
   double t = 0.0;
   for (int i = threadIdx.x; i < ai.np; i += blockDim.x) t += ai.partial[i];
@@ -112,7 +112,7 @@ __device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double
   for (int i = 1; i < (int)(blockDim.x / kWave); ++i) pq += red[i];
   const bool ok = pq > 0.0 && rz > 0.0;
   *alpha = rz / pq;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (first && threadIdx.x == 0) {
     sc->pq = pq;
     sc->rz = rz;
     sc->iter += 1;
@@ -120,6 +120,25 @@ __device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double
     else sc->done = (pq != pq || rz != rz) ? 4 : 3;
   }
   return ok;
+}
+
+// Stop test (Eq. 12 or the plain residual) and the scalars of the next step,
+// by one thread.  sc->rz stays: the workgroups that update p divide by it.
+__device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double zz, double rr) {
+  const double crit = (sc->stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / sc->crit0;
+  sc->zz = zz;
+  sc->rr = rr;
+  sc->crit = crit;
+  if (sc->history) sc->history[sc->iter] = crit;
+  sc->beta = rz / sc->rz;
+  sc->rzn = rz;
+  if (!(crit == crit) || !(rz == rz) || isinf(rz)) {
+    sc->done = 4;
+  } else if (crit <= sc->tol) {
+    sc->done = 1;
+  } else if (sc->iter >= sc->maxit) {
+    sc->done = 2;
+  }
 }
 
 __device__ __forceinline__ double load_relaxed(const double* p) {

@@ -164,10 +164,8 @@ static fc_status upload_system_body(const HostSystem& S, hipStream_t stream, fc_
   return FC_OK;
 }
 
-fc_status precond_ensure_map(fc_precond_s& pc, hipStream_t s) {
-  static std::mutex mu;   // a batch may ask for the map of a shared handle
-  std::lock_guard<std::mutex> lock(mu);
-  if (pc.inv_ptr) return FC_OK;
+// Node-to-block map of pc, on the device.
+static fc_status precond_map(fc_precond_s& pc, hipStream_t s) {
   const int64_t n = pc.pb->n_nodes + 1;
   int32_t *work = nullptr, *sums = nullptr, *ptr = nullptr, *idx = nullptr;
   Scratch tmp(s);
@@ -509,7 +507,7 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     const bool allowed = !(env && std::atoi(env) == 0);
     if (allowed && !patch && nb == pb->n_el) pc->lat = pb->cells;
   }
-  if (pc->lat.dim == 0) FC_TRY(precond_ensure_map(*pc, s));
+  if (pc->lat.dim == 0) FC_TRY(precond_map(*pc, s));
   FC_TRY(dev_alloc<true>(&pc->Q, (size_t)nb * sym_block_stride(m)));
   FC_TRY(dev_alloc<true>(&pc->y, (size_t)nb * m));
   FC_TRY(dev_alloc<true>(&pc->fallback, (size_t)pb->n_dofs));

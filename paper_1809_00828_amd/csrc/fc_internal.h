@@ -251,9 +251,6 @@ hipError_t spmv_enable_lattice(DeviceBsr& A, int dim, int n1, int p, hipStream_t
 hipError_t launch_schwarz_apply(const fc_precond_s& pc, const double* r,
                                 double* z, hipStream_t s);
 
-// Build the node-to-block map of pc on the device unless it is there.
-fc_status precond_ensure_map(fc_precond_s& pc, hipStream_t s);
-
 // drop the captured solver chunk (its kernels hold buffers about to change)
 void solver_invalidate_graph(fc_precond_s& pc);
 

@@ -6,10 +6,14 @@
 // work items of a converged problem return at once.  A chunk of steps is
 // captured into one hipGraph and replayed until every problem has stopped.
 //
-// Shape classes and their launch variants are fixed at batch creation by a
-// small autotuner: for every SpMV class (block dimension, mean row length)
-// it times the group widths 8/16/32/64 on that class's own work items, keeping
-// the fastest.
+// The kernels are the single problem's, over tiles of many problems: sliced
+// products for scalar lattice members (a class per degree), block products with
+// the block size compiled in (a class per size), the pull from the lattice
+// indices, and the step length and beta summed where they are used.  Members
+// without a sliced copy take the row layout; for each such class (block
+// dimension, mean row length) an autotuner at batch creation times the group
+// widths 8/16/32/64 on the class's own work items and keeps the fastest.
+// Lists of equal tiles are dealt so that one XCD walks a contiguous run.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -20,14 +24,18 @@
 #include <cstring>
 #include <map>
 #include <memory>
+#include <new>
+#include <numeric>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "dev_common.h"
 #include "k_schwarz.h"
 #include "k_spmv.h"
 #include "schwarz_dev.h"
+#include "spmv_dev.h"
 
 namespace fc {
 
@@ -46,15 +54,35 @@ struct BProb {
   const double* b;
   double* x;
   int64_t n_blocks, n_dofs, voff;
-  int32_t nn, m, bdim, pad;
-  int32_t spmv_item0, spmv_items, pull_item0, pull_items;
+  int32_t nn, m, bdim;
+  FastDiv dbd;
+  SellView sell;           // n_slices = 0: row layout
+  PullLattice lat;         // dim = 0: node-to-block map
+  // tiles of pull_rounds x 512 and of wide_rounds x 2048 unknowns, at most
+  // kPullTiles and kWideTiles of them: every workgroup of a later kernel sums
+  // their partials
+  int32_t pull_item0, pull_items, pull_rounds;
+  int32_t wide_item0, wide_items, wide_rounds;
 };
+
+constexpr int kPullTiles = 1024, kWideTiles = 256;
+
+__device__ __forceinline__ AlphaIn batch_alpha(const BProb& P, const double* partial,
+                                               int n_items) {
+  return AlphaIn{partial + 3 * (int64_t)n_items + P.wide_item0, P.wide_items};
+}
 
 // One tile of one problem.  slot is the item's fixed position in the
 // partial-sum array, so a compacted list of the still-running problems'
 // items writes where the per-problem reductions read.
 struct WorkItem {
   int32_t prob, tile, slot;
+};
+
+// One slice of one sliced problem of degree p.
+struct SellItem {
+  SellSlice sl;
+  int32_t prob, p;
 };
 
 // ------------------------------------------------------------ kernels
@@ -116,9 +144,35 @@ __global__ __launch_bounds__(256) void kb_spmv(const BProb* __restrict__ probs,
   }
 }
 
-// (p, q) per pull tile into partial[3 n_items + slot]: the step length's
-// dot runs as its own pass rather than at the end of every SpMV workgroup
-// (which would hold a workgroup's waves until the slowest row finishes).
+// The sliced product, one slice per wave, all degrees in one launch, the slice's
+// place in its item rather than behind it, and no contiguous run per XCD (the
+// members' rows differ in length, and an XCD with the long ones works alone).
+// 16 members of 50k - 200k unknowns (0.58 GB): 112 us, 5.2 TB/s; a launch per
+// degree, slices found through their problem 203 us; with runs per XCD 225 us;
+// the row layout 290 us.
+__global__ __launch_bounds__(256) void kb_spmv_sell(const BProb* __restrict__ probs,
+                                                    const SellItem* __restrict__ items,
+                                                    int n_items, const CgScalars* __restrict__ sc,
+                                                    const double* __restrict__ pvec,
+                                                    double* __restrict__ qvec) {
+  const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t s = (int64_t)blockIdx.x * 4 + w;
+  if (s >= n_items) return;
+  const SellItem it = items[s];
+  const BProb& B = probs[it.prob];
+  if (sc[it.prob].done) return;
+  const double* x = pvec + B.voff;
+  double* y = qvec + B.voff;
+  switch (it.p) {
+    case 1: (void)sell_slice_product<1, true>(B.sell, it.sl, l, x, y); break;
+    case 2: (void)sell_slice_product<2, true>(B.sell, it.sl, l, x, y); break;
+    case 3: (void)sell_slice_product<3, true>(B.sell, it.sl, l, x, y); break;
+    default: (void)sell_slice_product<4, true>(B.sell, it.sl, l, x, y); break;
+  }
+}
+
+// (p, q) per wide tile into partial[3 n_items + slot].  In the SpMV it would
+// hold a workgroup's waves until the slowest row finishes.
 __global__ __launch_bounds__(256) void kb_pq(const BProb* __restrict__ probs,
                                              const WorkItem* __restrict__ items, int n_items,
                                              const CgScalars* __restrict__ sc,
@@ -126,204 +180,269 @@ __global__ __launch_bounds__(256) void kb_pq(const BProb* __restrict__ probs,
                                              const double* __restrict__ qvec,
                                              double* __restrict__ partial) {
   __shared__ double lds[16];
-  const WorkItem it = items[blockIdx.x];
-  const BProb& P = probs[it.prob];
+  const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   if (sc[it.prob].done) return;
-  const int64_t i = (int64_t)it.tile * 256 + threadIdx.x;
-  double a = 0.0;
-  if (i < P.n_dofs) a = pvec[P.voff + i] * qvec[P.voff + i];
-  a = block_sum(a, lds);
-  if (threadIdx.x == 0) partial[3 * (int64_t)n_items + it.slot] = a;
-}
-
-// alpha per problem from its (p, q) partials (one workgroup per problem).
-__global__ __launch_bounds__(256) void kb_alpha(const BProb* __restrict__ probs, CgScalars* sc,
-                                                const double* __restrict__ partial, int n_items,
-                                                const int32_t* __restrict__ active) {
-  __shared__ double lds[16];
-  const int k = active ? active[blockIdx.x] : (int)blockIdx.x;
-  CgScalars& S = sc[k];
-  if (S.done) return;
-  const BProb& P = probs[k];
-  const double* pp = partial + 3 * (int64_t)n_items + P.pull_item0;
-  double t = 0.0;
-  for (int i = threadIdx.x; i < P.pull_items; i += blockDim.x) t += pp[i];
-  const double pq = block_sum(t, lds);
-  if (threadIdx.x == 0) {
-    S.pq = pq;
-    S.iter += 1;
-    if (!(pq > 0.0) || !(S.rz > 0.0))
-      S.done = (pq != pq || S.rz != S.rz) ? 4 : 3;
-    else
-      S.alpha = S.rz / pq;
-  }
-}
-
-// Schwarz phase 1 for a class of blocks of size m <= 64 (BPW blocks per
-// wave) or m > 64 (one block per workgroup of 64*ceil(m/64) threads).
-// Gathers r - alpha q (q may be null for the start).
-template <bool kSmall>
-__global__ __launch_bounds__(256) void kb_schwarz(const BProb* __restrict__ probs,
-                                                  const WorkItem* __restrict__ items,
-                                                  const CgScalars* __restrict__ sc,
-                                                  const double* __restrict__ rvec,
-                                                  const double* __restrict__ qvec, int m, int bpw) {
-  __shared__ double rB[256];
-  const WorkItem it = items[blockIdx.x];
-  const CgScalars& S = sc[it.prob];
-  if (S.done) return;
   const BProb& P = probs[it.prob];
-  const double alpha = qvec ? S.alpha : 0.0;
-  const double* r = rvec + P.voff;
-  const double* q = qvec ? qvec + P.voff : nullptr;
-  const int64_t stride = sym_block_stride_dev(m);
-  if constexpr (kSmall) {
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int lb = l / m, i = l % m;
-    const int64_t blk = ((int64_t)it.tile * 4 + w) * bpw + lb;
-    const bool active = lb < bpw && blk < P.n_blocks;
-    if (active) {
-      const int64_t e = P.block_elem[blk];
-      const int64_t dof = (int64_t)P.elem_nodes[e * P.nn + i / P.bdim] * P.bdim + (i % P.bdim);
-      rB[threadIdx.x] = gather_r(r, q, alpha, dof);
+  const double *p = pvec + P.voff, *q = qvec + P.voff;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int t = 0; t < P.wide_rounds; ++t) {
+    const int64_t i0 = ((int64_t)it.tile * P.wide_rounds + t) * 2048 + threadIdx.x;
+    double pv[8], qv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t i = i0 + 256 * u;
+      pv[u] = i < P.n_dofs ? p[i] : 0.0;
+      qv[u] = i < P.n_dofs ? q[i] : 0.0;
     }
-    __syncthreads();
-    if (!active) return;
-    P.y[blk * m + i] = sym_row<double>(P.Q + blk * stride, &rB[w * 64 + lb * m], m, i);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u & 3] = fma(pv[u], qv[u], a[u & 3]);
+  }
+  const double t = block_sum((a[0] + a[1]) + (a[2] + a[3]), lds);
+  if (threadIdx.x == 0) partial[3 * (int64_t)n_items + it.slot] = t;
+}
+
+// Schwarz phase 1 on r - alpha q (q null for the start), blocks of up to 64
+// rows: the workgroup of a member's first tile stores the step length.  kM: one
+// block size per launch, compiled in (0: any); kMixed: every size up to 27 that
+// has a kernel of its own in one launch, since each of them fills the chip for
+// a few microseconds only (56 us for the 0.23 GB of 16 members' blocks of 9 to
+// 27 rows, 71 us with a launch per size; the larger ones would cost it the
+// waves in flight: 80 registers at m = 27, 180 at m = 64).
+constexpr int kMixed = -1;
+#define FC_MIXED_SIZES(X) X(8) X(9) X(16) X(18) X(24) X(25) X(27)
+
+template <int kM, bool kLat>
+__device__ __forceinline__ void batch_small(const BProb& P, const WorkItem it, int n_items,
+                                            CgScalars* S, const double* rvec, const double* qvec,
+                                            const double* partial, double (*rB)[64],
+                                            double* red) {
+  schwarz_small_tile<double, kM, kLat>(
+      P.Q, sym_block_stride_dev(P.m), P.m, rvec + P.voff, qvec ? qvec + P.voff : nullptr, nullptr,
+      S, qvec ? batch_alpha(P, partial, n_items) : AlphaIn{}, it.tile == 0, P.y, P.n_blocks,
+      P.lat, it.tile, rB, red, [&](int64_t blk, int i) {
+        return block_dof(P.elem_nodes, P.block_elem[blk], P.nn, P.bdim, i);
+      });
+}
+
+template <int kM, bool kLat>
+__global__ __launch_bounds__(256) void kb_schwarz_small(
+    const BProb* __restrict__ probs, const WorkItem* __restrict__ items, int n_items,
+    CgScalars* __restrict__ sc, const double* __restrict__ rvec, const double* __restrict__ qvec,
+    const double* __restrict__ partial) {
+  __shared__ double rB[4][64], red[16];
+  const WorkItem it = items[kM == kMixed ? blockIdx.x
+                                         : xcd_remap(blockIdx.x, gridDim.x)];
+  CgScalars* S = sc + it.prob;
+  if (S->done) return;
+  const BProb& P = probs[it.prob];
+  if constexpr (kM != kMixed) {
+    batch_small<kM, kLat>(P, it, n_items, S, rvec, qvec, partial, rB, red);
   } else {
-    // one block per workgroup, its stored rows staged through LDS
-    __shared__ __align__(16) double tile[StageRows<double>::value * 256];
-    const int64_t blk = it.tile;
-    const int i = threadIdx.x;
-    auto gather = [&] {
-      if (i >= m) return;
-      const int64_t e = P.block_elem[blk];
-      const int64_t dof = (int64_t)P.elem_nodes[e * P.nn + i / P.bdim] * P.bdim + (i % P.bdim);
-      rB[i] = gather_r(r, q, alpha, dof);
-    };
-    // every thread's own entry of each stored row: for the batch's block
-    // sizes (m = 125 at p = 4 in 3-D) 4.5 % faster than 16-byte runs
-    const double v = sym_block_staged_rows<double>(P.Q + blk * stride, rB, m, i, tile, gather);
-    if (i < m) P.y[blk * m + i] = v;
+#define FC_MIXED(KM) \
+  case KM: batch_small<KM, kLat>(P, it, n_items, S, rvec, qvec, partial, rB, red); break;
+    switch (P.m) { FC_MIXED_SIZES(FC_MIXED) }
+#undef FC_MIXED
   }
 }
 
-// Pull + x, r updates + partial dots (mode 1), or the start (mode 0: z = S r
-// only, dots of r and z).
+// Blocks of more than 64 rows, one per workgroup (for the batch's m = 125 every
+// thread's own entry of each stored row is 4.5 % faster than 16-byte runs).
+__global__ __launch_bounds__(256) void kb_schwarz_staged(
+    const BProb* __restrict__ probs, const WorkItem* __restrict__ items, int n_items,
+    CgScalars* __restrict__ sc, const double* __restrict__ rvec, const double* __restrict__ qvec,
+    const double* __restrict__ partial) {
+  __shared__ double rB[256], red[16];
+  __shared__ __align__(16) double tile[StageRows<double>::value * 256];
+  const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
+  CgScalars* S = sc + it.prob;
+  if (S->done) return;
+  const BProb& P = probs[it.prob];
+  const AlphaIn ai = qvec ? batch_alpha(P, partial, n_items) : AlphaIn{};
+  const int64_t blk = it.tile;
+  schwarz_staged_block<double, false>(
+      P.Q + blk * sym_block_stride_dev(P.m), P.y + blk * P.m, P.m, rvec + P.voff,
+      qvec ? qvec + P.voff : nullptr, nullptr, S, ai, it.tile == 0, rB, tile, red,
+      [&](int i) { return block_dof(P.elem_nodes, P.block_elem[blk], P.nn, P.bdim, i); });
+}
+
+// Pull + x, r updates + partial dots (mode 1), or the start (mode 0: z = S r,
+// p = z and the dots of r and z).  Two unknowns per thread and round, whose
+// loads are all issued before the first is used.
 template <int kMode>
 __global__ __launch_bounds__(256) void kb_pull(const BProb* __restrict__ probs,
                                                const WorkItem* __restrict__ items, int n_items,
                                                const CgScalars* __restrict__ sc,
                                                double* __restrict__ rvec,
-                                               const double* __restrict__ pvec,
+                                               double* __restrict__ pvec,
                                                const double* __restrict__ qvec,
                                                double* __restrict__ zvec,
                                                double* __restrict__ partial) {
-  __shared__ double lds[16];
-  const WorkItem it = items[blockIdx.x];
+  __shared__ double lds[4][3];
+  const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
+  const CgScalars& S = sc[it.prob];
+  if (S.done) return;
   const BProb& P = probs[it.prob];
-  double a = 0.0, b = 0.0, c = 0.0;
-  if (!sc[it.prob].done) {
-    const int64_t i = (int64_t)it.tile * 256 + threadIdx.x;
-    if (i < P.n_dofs) {
-      const int bd = P.bdim;
-      const int64_t node = i / bd;
-      const int cc = (int)(i - node * bd);
-      double s = 0.0;
-      for (int32_t e = P.inv_ptr[node]; e < P.inv_ptr[node + 1]; ++e)
-        s += P.y[(int64_t)P.inv_idx[e] + cc];
-      const int64_t g = P.voff + i;
-      double ri = rvec[g];
+  const double alpha = kMode == 1 ? S.alpha : 0.0;
+  const uint32_t n = (uint32_t)P.n_dofs;
+  double* r = rvec + P.voff;
+  double* p = pvec + P.voff;
+  double* z = zvec + P.voff;
+  const double* q = qvec + P.voff;
+  double acc[3] = {0.0, 0.0, 0.0};
+  for (int t = 0; t < P.pull_rounds; ++t) {
+    const uint32_t i0 = ((uint32_t)it.tile * P.pull_rounds + t) * 512 + threadIdx.x;
+    if (i0 >= n) break;
+    uint32_t i[2];
+    double qi[2], ri[2], pi[2], xi[2], fi[2], v[2][8], s[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      i[e] = min(i0 + 256u * e, n - 1);
+      ri[e] = r[i[e]];
       if constexpr (kMode == 1) {
-        const double alpha = sc[it.prob].alpha;
-        ri = fma(-alpha, qvec[g], ri);
-        P.x[i] = fma(alpha, pvec[g], P.x[i]);
-        rvec[g] = ri;
+        qi[e] = q[i[e]];
+        pi[e] = p[i[e]];
+        xi[e] = P.x[i[e]];
       }
-      const double zi = fma(P.fallback[i], ri, s);
-      zvec[g] = zi;
-      a = ri * zi;
-      b = zi * zi;
-      c = ri * ri;
+      fi[e] = P.fallback ? P.fallback[i[e]] : 0.0;
+    }
+    uint32_t node[2];
+    int c[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      node[e] = fdiv(i[e], P.dbd);
+      c[e] = (int)(i[e] - node[e] * (uint32_t)P.bdim);
+    }
+    if (P.lat.dim > 0) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) pull_lattice_load(P.y, P.lat, P.m, P.bdim, node[e], c[e], v[e]);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) s[e] = pull_sum8(v[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) s[e] = pull_mapped_sum(P.y, P.inv_ptr, P.inv_idx, node[e], c[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      if (i0 + 256u * e >= n) break;
+      double rn = ri[e];
+      if constexpr (kMode == 1) {
+        rn = fma(-alpha, qi[e], rn);
+        P.x[i[e]] = fma(alpha, pi[e], xi[e]);
+        r[i[e]] = rn;
+      }
+      const double zn = P.fallback ? fma(fi[e], rn, s[e]) : s[e];
+      z[i[e]] = zn;
+      if constexpr (kMode == 0) p[i[e]] = zn;
+      acc[0] = fma(rn, zn, acc[0]);
+      acc[1] = fma(zn, zn, acc[1]);
+      acc[2] = fma(rn, rn, acc[2]);
     }
   }
-  a = block_sum(a, lds);
-  b = block_sum(b, lds);
-  c = block_sum(c, lds);
-  if (threadIdx.x == 0) {
-    partial[it.slot] = a;
-    partial[n_items + it.slot] = b;
-    partial[2 * n_items + it.slot] = c;
+  const int w = threadIdx.x / kWave;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    acc[k] = wave_sum_last(acc[k]);
+    if (threadIdx.x % kWave == kWave - 1) lds[w][k] = acc[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const int k = threadIdx.x;
+    partial[k * (int64_t)n_items + it.slot] = ((lds[0][k] + lds[1][k]) + lds[2][k]) + lds[3][k];
   }
 }
 
-// Per-problem stop test and beta (mode 1) or start (mode 0).
-template <int kMode>
-__global__ __launch_bounds__(256) void kb_beta(const BProb* __restrict__ probs, CgScalars* sc,
-                                               const double* __restrict__ partial, int n_items,
-                                               const int32_t* __restrict__ active) {
+// Scalars of the start, one workgroup per problem.
+__global__ __launch_bounds__(256) void kb_start(const BProb* __restrict__ probs, CgScalars* sc,
+                                                const double* __restrict__ partial, int n_items) {
   __shared__ double lds[16];
-  const int k = active ? active[blockIdx.x] : (int)blockIdx.x;
-  CgScalars& S = sc[k];
-  if (kMode == 1 && S.done) return;
-  const BProb& P = probs[k];
-  double ta = 0.0, tb = 0.0, tc = 0.0;
-  for (int i = threadIdx.x; i < P.pull_items; i += blockDim.x) {
-    ta += partial[P.pull_item0 + i];
-    tb += partial[n_items + P.pull_item0 + i];
-    tc += partial[2 * n_items + P.pull_item0 + i];
-  }
-  const double rz = block_sum(ta, lds);
-  const double zz = block_sum(tb, lds);
-  const double rr = block_sum(tc, lds);
+  CgScalars& S = sc[blockIdx.x];
+  const BProb& P = probs[blockIdx.x];
+  double t[3] = {0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < P.pull_items; i += blockDim.x)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] += partial[k * (int64_t)n_items + P.pull_item0 + i];
+  const double rz = block_sum(t[0], lds);
+  const double zz = block_sum(t[1], lds);
+  const double rr = block_sum(t[2], lds);
   if (threadIdx.x != 0) return;
-  if constexpr (kMode == 0) {
-    S.rz = rz;
-    S.zz = zz;
-    S.rr = rr;
-    S.iter = 0;
-    S.zn0 = sqrt(zz);
-    S.rn0 = sqrt(rr);
-    S.crit0 = S.stop == FC_STOP_PRECOND ? S.zn0 : S.rn0;
-    S.crit = S.crit0 > 0 ? 1.0 : 0.0;
-    S.done = !(S.crit0 == S.crit0) ? 4 : (S.crit0 == 0.0 ? 1 : 0);
-  } else {
-    const double crit = (S.stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / S.crit0;
-    S.zz = zz;
-    S.rr = rr;
-    S.crit = crit;
-    if (!(crit == crit) || !(rz == rz) || isinf(rz))
-      S.done = 4;
-    else if (crit <= S.tol)
-      S.done = 1;
-    else if (S.iter >= S.maxit)
-      S.done = 2;
-    S.beta = rz / S.rz;
-    S.rz = rz;
-  }
+  S.rz = rz;
+  S.rzn = rz;
+  S.zz = zz;
+  S.rr = rr;
+  S.iter = 0;
+  S.zn0 = sqrt(zz);
+  S.rn0 = sqrt(rr);
+  S.crit0 = S.stop == FC_STOP_PRECOND ? S.zn0 : S.rn0;
+  S.crit = S.crit0 > 0 ? 1.0 : 0.0;
+  S.done = !(S.crit0 == S.crit0) ? 4 : (S.crit0 == 0.0 ? 1 : 0);
 }
 
-// mode 0: r = b, x = 0;  mode 1: p = z + beta p;  mode 2: p = z
-template <int kMode>
-__global__ __launch_bounds__(256) void kb_vec(const BProb* __restrict__ probs,
-                                              const WorkItem* __restrict__ items,
-                                              const CgScalars* __restrict__ sc,
-                                              double* __restrict__ rvec,
-                                              double* __restrict__ pvec,
-                                              const double* __restrict__ zvec) {
+// p = z + beta p with beta from the pull's partials, summed by every workgroup
+// of a problem in the same order; its first one also tests for the stop and
+// stores the scalars (one that still updates p after that changes nothing: p is
+// not read again).
+__global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs,
+                                                 const WorkItem* __restrict__ items, int n_items,
+                                                 CgScalars* sc, const double* __restrict__ partial,
+                                                 const double* __restrict__ zvec,
+                                                 double* __restrict__ pvec) {
+  __shared__ double red[3][4];
+  const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
+  CgScalars* S = sc + it.prob;
+  if (S->done) return;
+  const BProb& P = probs[it.prob];
+  const double rz_old = S->rz;
+  const double* z = zvec + P.voff;
+  double* p = pvec + P.voff;
+  const int64_t i0 = (int64_t)it.tile * P.wide_rounds * 2048 + threadIdx.x;
+  double zv[8], pv[8];
+  auto load = [&](int64_t j0) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t i = j0 + 256 * u;
+      zv[u] = i < P.n_dofs ? z[i] : 0.0;
+      pv[u] = i < P.n_dofs ? p[i] : 0.0;
+    }
+  };
+  load(i0);   // the first round's unknowns, before the sums
+  const int nk = it.tile == 0 ? 3 : 1, w = threadIdx.x / kWave;
+  for (int k = 0; k < nk; ++k) {
+    const double* pp = partial + k * (int64_t)n_items + P.pull_item0;
+    double v[kPullTiles / 256];
+#pragma unroll
+    for (int u = 0; u < kPullTiles / 256; ++u) {
+      const int j = threadIdx.x + 256 * u;
+      v[u] = j < P.pull_items ? pp[j] : 0.0;
+    }
+    const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
+    if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
+  }
+  __syncthreads();
+  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+  const double beta = rz / rz_old;
+  for (int t = 0; t < P.wide_rounds; ++t) {
+    const int64_t j0 = i0 + 2048 * (int64_t)t;
+    if (t > 0) load(j0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j0 + 256 * u < P.n_dofs) p[j0 + 256 * u] = fma(beta, pv[u], zv[u]);
+  }
+  if (it.tile == 0 && threadIdx.x == 0)
+    cg_beta_store(S, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
+                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
+}
+
+// r = b, x = 0
+__global__ __launch_bounds__(256) void kb_init(const BProb* __restrict__ probs,
+                                               const WorkItem* __restrict__ items,
+                                               double* __restrict__ rvec) {
   const WorkItem it = items[blockIdx.x];
   const BProb& P = probs[it.prob];
-  if (kMode == 1 && sc[it.prob].done) return;
-  const int64_t i = (int64_t)it.tile * 256 + threadIdx.x;
-  if (i >= P.n_dofs) return;
-  const int64_t g = P.voff + i;
-  if constexpr (kMode == 0) {
-    rvec[g] = P.b[i];
+  const int64_t per = (int64_t)P.wide_rounds * 2048;
+  const int64_t end = min(P.n_dofs, ((int64_t)it.tile + 1) * per);
+  for (int64_t i = (int64_t)it.tile * per + threadIdx.x; i < end; i += 256) {
+    rvec[P.voff + i] = P.b[i];
     P.x[i] = 0.0;
-  } else if constexpr (kMode == 1) {
-    pvec[g] = fma(sc[it.prob].beta, pvec[g], zvec[g]);
-  } else {
-    pvec[g] = zvec[g];
   }
 }
 
@@ -334,14 +453,13 @@ struct SpmvClass {
   int B, G;
   std::vector<WorkItem> items;
   WorkItem* d_items = nullptr;
-  int item_base = 0;
   int n_act = 0;
   WorkItem* d_act = nullptr;
 };
 
 struct SchwarzClass {
-  int m, bpw;
-  bool small;
+  int m;       // kMixed: several
+  bool lat;    // gather from the lattice indices
   std::vector<WorkItem> items;
   WorkItem* d_items = nullptr;
   int n_act = 0;
@@ -357,15 +475,19 @@ struct fc_batch_s {
   std::vector<fc::BProb> host;
   fc::BProb* d_probs = nullptr;
   std::vector<fc::SpmvClass> spmv;
+  std::vector<fc::SellItem> sell;     // slices of the sliced members
+  int n_act_sell = 0;
+  fc::SellItem* d_act_sell = nullptr;
   std::vector<fc::SchwarzClass> schw;
   std::vector<fc::WorkItem> pull_items;
   fc::WorkItem* d_pull = nullptr;
   int n_act_pull = 0;                 // compacted pull items (see SpmvClass)
   fc::WorkItem* d_act_pull = nullptr;
-  int n_act_probs = 0;                // problems still running
-  int32_t* d_act_probs = nullptr;
+  std::vector<fc::WorkItem> wide_items;
+  fc::WorkItem* d_wide = nullptr;
+  int n_act_wide = 0;
+  fc::WorkItem* d_act_wide = nullptr;
   int64_t act_dofs = 0;               // unknowns of the problems in the lists
-  int spmv_total = 0;
   double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *partial = nullptr;
   fc::CgScalars* sc = nullptr;
   fc::CgScalars* host_sc = nullptr;
@@ -390,7 +512,7 @@ static void destroy_batch(fc_batch_s* b) {
   for (auto& c : b->schw)
     for (void* p : {(void*)c.d_items, (void*)c.d_act}) if (p) (void)hipFree(p);
   for (void* p : {(void*)b->d_probs, (void*)b->d_pull, (void*)b->d_act_pull,
-                  (void*)b->d_act_probs, (void*)b->r, (void*)b->z, (void*)b->p, (void*)b->q,
+                  (void*)b->d_wide, (void*)b->d_act_wide, (void*)b->d_act_sell, (void*)b->r, (void*)b->z, (void*)b->p, (void*)b->q,
                   (void*)b->partial, (void*)b->sc})
     if (p) (void)hipFree(p);
   if (b->host_sc) (void)hipHostFree(b->host_sc);
@@ -423,48 +545,58 @@ static hipError_t launch_spmv_class(fc_batch_s& bt, const SpmvClass& c, const Wo
   return hipGetLastError();
 }
 
+// q null: the start
 static hipError_t launch_schwarz_class(fc_batch_s& bt, const SchwarzClass& c, const WorkItem* items,
                                        int n, const double* q, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  const int threads = c.small ? 256 : 64 * ((c.m + 63) / 64);
-  dim3 g((unsigned)n), b((unsigned)threads);
-  if (c.small)
-    hipLaunchKernelGGL(kb_schwarz<true>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
-  else
-    hipLaunchKernelGGL(kb_schwarz<false>, g, b, 0, s, bt.d_probs, items, bt.sc, bt.r, q, c.m, c.bpw);
+  const int np = (int)bt.pull_items.size();
+  dim3 g((unsigned)n), b(c.m > 64 ? 64 * ((c.m + 63) / 64) : 256);
+  if (c.m > 64) {
+    hipLaunchKernelGGL(kb_schwarz_staged, g, b, 0, s, bt.d_probs, items, np, bt.sc, bt.r, q,
+                       bt.partial);
+    return hipGetLastError();
+  }
+#define FC_BSMALL(KM)                                                                         \
+  case KM:                                                                                    \
+    if (c.lat)                                                                                \
+      hipLaunchKernelGGL((kb_schwarz_small<KM, true>), g, b, 0, s, bt.d_probs, items, np,     \
+                         bt.sc, bt.r, q, bt.partial);                                         \
+    else                                                                                      \
+      hipLaunchKernelGGL((kb_schwarz_small<KM, false>), g, b, 0, s, bt.d_probs, items, np,    \
+                         bt.sc, bt.r, q, bt.partial);                                         \
+    break;
+  switch (c.m) {
+    FC_BSMALL(kMixed) FC_BSMALL(32) FC_BSMALL(36) FC_BSMALL(49) FC_BSMALL(50) FC_BSMALL(64)
+    default:
+      hipLaunchKernelGGL((kb_schwarz_small<0, false>), g, b, 0, s, bt.d_probs, items, np, bt.sc,
+                         bt.r, q, bt.partial);
+  }
+#undef FC_BSMALL
   return hipGetLastError();
 }
 
-// The steps launch the compacted lists: tiles and problems still running.
+// The steps launch the compacted lists: tiles of the problems still running.
 static hipError_t enqueue_batch_steps(fc_batch_s& bt, int chunk, hipStream_t s) {
   const int np = (int)bt.pull_items.size();
-  const int na = bt.n_act_pull;
-  if (bt.n_act_probs == 0) return hipSuccess;
+  if (bt.n_act_pull == 0) return hipSuccess;
   for (int it = 0; it < chunk; ++it) {
+    if (bt.n_act_sell > 0)
+      hipLaunchKernelGGL(kb_spmv_sell, dim3((bt.n_act_sell + 3) / 4), dim3(256), 0, s, bt.d_probs,
+                         bt.d_act_sell, bt.n_act_sell, bt.sc, bt.p, bt.q);
     for (auto& c : bt.spmv) {
       hipError_t e = launch_spmv_class(bt, c, c.d_act, c.n_act, s);
       if (e != hipSuccess) return e;
     }
-    if (na > 0) {
-      hipLaunchKernelGGL(kb_pq, dim3(na), dim3(256), 0, s, bt.d_probs, bt.d_act_pull, np, bt.sc,
-                         bt.p, bt.q, bt.partial);
-    }
-    hipLaunchKernelGGL(kb_alpha, dim3(bt.n_act_probs), dim3(256), 0, s, bt.d_probs, bt.sc,
-                       bt.partial, np, bt.d_act_probs);
+    hipLaunchKernelGGL(kb_pq, dim3(bt.n_act_wide), dim3(256), 0, s, bt.d_probs, bt.d_act_wide, np,
+                       bt.sc, bt.p, bt.q, bt.partial);
     for (auto& c : bt.schw) {
       hipError_t e = launch_schwarz_class(bt, c, c.d_act, c.n_act, bt.q, s);
       if (e != hipSuccess) return e;
     }
-    if (na > 0) {
-      hipLaunchKernelGGL(kb_pull<1>, dim3(na), dim3(256), 0, s, bt.d_probs, bt.d_act_pull, np,
-                         bt.sc, bt.r, bt.p, bt.q, bt.z, bt.partial);
-    }
-    hipLaunchKernelGGL(kb_beta<1>, dim3(bt.n_act_probs), dim3(256), 0, s, bt.d_probs, bt.sc,
-                       bt.partial, np, bt.d_act_probs);
-    if (na > 0) {
-      hipLaunchKernelGGL(kb_vec<1>, dim3(na), dim3(256), 0, s, bt.d_probs, bt.d_act_pull, bt.sc,
-                         bt.r, bt.p, bt.z);
-    }
+    hipLaunchKernelGGL(kb_pull<1>, dim3(bt.n_act_pull), dim3(256), 0, s, bt.d_probs, bt.d_act_pull,
+                       np, bt.sc, bt.r, bt.p, bt.q, bt.z, bt.partial);
+    hipLaunchKernelGGL(kb_beta_p, dim3(bt.n_act_wide), dim3(256), 0, s, bt.d_probs, bt.d_act_wide,
+                       np, bt.sc, bt.partial, bt.z, bt.p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -494,9 +626,9 @@ using namespace fc;
     if (s_ != FC_OK) return s_;     \
   } while (0)
 
-extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
-                                     const fc_precond* preconds, int32_t autotune, void* stream,
-                                     fc_batch* out) {
+static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
+                                   const fc_precond* preconds, int32_t autotune, void* stream,
+                                   fc_batch* out) {
   if (nprob <= 0 || !problems || !preconds || !out) {
     set_error("fc_batch_create: invalid arguments");
     return FC_E_ARG;
@@ -514,7 +646,8 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
   int64_t voff = 0;
   // shape classes
   std::map<std::pair<int, int>, int> spmv_key;   // (B, row-length bucket) -> class
-  std::map<int, int> schw_key;                   // m -> class
+  std::map<std::pair<int, bool>, int> schw_key;  // (m, lattice gather) -> class
+  std::vector<int> spmv_cls(nprob, -1), schw_cls(nprob);
   for (int k = 0; k < nprob; ++k) {
     fc_problem pb = problems[k];
     fc_precond pc = preconds[k];
@@ -530,9 +663,8 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
       set_error("fc_batch_create: vertex-patch preconditioners are not batched");
       return FC_E_UNSUPPORTED;
     }
-    FC_TRY_B(precond_ensure_map(*pc, user));
     BProb& P = B.host[k];
-    std::memset(&P, 0, sizeof(P));
+    P = BProb{};
     P.rowptr = pb->A.rowptr;
     P.col = pb->A.col;
     P.val = pb->A.val;
@@ -542,7 +674,7 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
     P.Q = pc->Q;
     P.inv_ptr = pc->inv_ptr;
     P.inv_idx = pc->inv_idx;
-    P.fallback = pc->fallback;
+    P.fallback = pc->n_fallback ? pc->fallback : nullptr;
     P.y = pc->y;
     P.n_blocks = pc->n_blocks;
     P.n_dofs = pb->n_dofs;
@@ -550,57 +682,88 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
     P.nn = pc->nn;
     P.m = pc->m;
     P.bdim = pb->bdim;
+    P.dbd = make_fastdiv((uint32_t)pb->bdim);
+    if (spmv_uses_sell(pb->A)) P.sell = sell_view(pb->A);
+    P.lat = pc->lat;
     voff += pb->n_dofs;
-    const double mean = pb->A.n_rows ? double(pb->A.nnzb) / double(pb->A.n_rows) : 1.0;
-    const int bucket = mean < 12 ? 0 : mean < 24 ? 1 : mean < 48 ? 2 : mean < 96 ? 3 : 4;
-    auto sk = std::make_pair(pb->bdim, bucket);
-    if (!spmv_key.count(sk)) {
-      spmv_key[sk] = (int)B.spmv.size();
-      SpmvClass c;
-      c.B = pb->bdim;
-      c.G = bucket == 0 ? 8 : bucket == 1 ? 16 : bucket == 2 ? 32 : 64;
-      B.spmv.push_back(c);
+    if (P.sell.n_slices == 0) {
+      const double mean = pb->A.n_rows ? double(pb->A.nnzb) / double(pb->A.n_rows) : 1.0;
+      const int bucket = mean < 12 ? 0 : mean < 24 ? 1 : mean < 48 ? 2 : mean < 96 ? 3 : 4;
+      const auto sk = std::make_pair((int)pb->bdim, bucket);
+      if (!spmv_key.count(sk)) {
+        spmv_key[sk] = (int)B.spmv.size();
+        SpmvClass c;
+        c.B = pb->bdim;
+        c.G = bucket == 0 ? 8 : bucket == 1 ? 16 : bucket == 2 ? 32 : 64;
+        B.spmv.push_back(c);
+      }
+      spmv_cls[k] = spmv_key[sk];
     }
-    if (!schw_key.count(P.m)) {
-      schw_key[P.m] = (int)B.schw.size();
+    int size = P.m;
+#define FC_MIXED(KM) \
+  case KM: size = kMixed; break;
+    switch (P.m) { FC_MIXED_SIZES(FC_MIXED) }
+#undef FC_MIXED
+    const auto hk = std::make_pair(size, P.m <= 64 && pc->lat.dim > 0 && pb->bdim == 1);
+    if (!schw_key.count(hk)) {
+      schw_key[hk] = (int)B.schw.size();
       SchwarzClass c;
-      c.m = P.m;
-      c.small = P.m <= 64;
-      c.bpw = c.small ? 64 / P.m : 1;
+      c.m = hk.first;
+      c.lat = hk.second;
       B.schw.push_back(c);
     }
+    schw_cls[k] = schw_key[hk];
   }
   B.total_dofs = voff;
   // items (SpMV tiles depend on G, rebuilt after tuning)
   auto build_spmv_items = [&](SpmvClass& c, int cls) {
     c.items.clear();
+    const int rpw = 256 / c.G;
     for (int k = 0; k < nprob; ++k) {
-      fc_problem pb = problems[k];
-      const double mean = pb->A.n_rows ? double(pb->A.nnzb) / double(pb->A.n_rows) : 1.0;
-      const int bucket = mean < 12 ? 0 : mean < 24 ? 1 : mean < 48 ? 2 : mean < 96 ? 3 : 4;
-      if (spmv_key[std::make_pair(pb->bdim, bucket)] != cls) continue;
-      const int rpw = 256 / c.G;
-      const int64_t nt = (pb->A.n_rows + rpw - 1) / rpw;
-      for (int64_t t = 0; t < nt; ++t)
-        c.items.push_back({k, (int32_t)t, (int32_t)c.items.size()});
+      if (spmv_cls[k] != cls) continue;
+      const int64_t nt = (B.host[k].n_rows + rpw - 1) / rpw;
+      for (int64_t t = 0; t < nt; ++t) c.items.push_back({k, (int32_t)t, 0});
     }
   };
+  // the members with the longest rows and the largest blocks first: the short
+  // ones fill the end of a launch
+  std::vector<int> order(nprob);
+  std::iota(order.begin(), order.end(), 0);
+  auto row_length = [&](int k) {
+    return double(problems[k]->A.nnzb) / double(std::max<int64_t>(1, problems[k]->A.n_rows));
+  };
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return row_length(a) > row_length(b); });
+  for (int k : order) {
+    const SellView& v = B.host[k].sell;
+    if (v.n_slices == 0) continue;
+    std::vector<SellSlice> sl(v.n_slices);
+    FC_HIP(hipMemcpy(sl.data(), v.slices, sl.size() * sizeof(SellSlice), hipMemcpyDeviceToHost));
+    for (const SellSlice& x : sl) B.sell.push_back({x, k, problems[k]->A.lat.p});
+  }
   for (size_t c = 0; c < B.spmv.size(); ++c) build_spmv_items(B.spmv[c], (int)c);
-  for (auto& c : B.schw) {
-    for (int k = 0; k < nprob; ++k) {
-      if (B.host[k].m != c.m) continue;
-      const int64_t per = c.small ? 4 * (int64_t)c.bpw : 1;
-      const int64_t nt = (B.host[k].n_blocks + per - 1) / per;
-      for (int64_t t = 0; t < nt; ++t)
-        c.items.push_back({k, (int32_t)t, (int32_t)c.items.size()});
+  for (size_t ci = 0; ci < B.schw.size(); ++ci) {
+    SchwarzClass& c = B.schw[ci];
+    for (int k : order) {
+      if (schw_cls[k] != (int)ci) continue;
+      const int m = B.host[k].m;
+      const int64_t per = m <= 64 ? 4 * (64 / m) : 1;
+      const int64_t nt = (B.host[k].n_blocks + per - 1) / per;   // at least one: Q is there
+      for (int64_t t = 0; t < nt; ++t) c.items.push_back({k, (int32_t)t, 0});
     }
   }
   for (int k = 0; k < nprob; ++k) {
-    const int64_t nt = (B.host[k].n_dofs + 255) / 256;
-    B.host[k].pull_item0 = (int32_t)B.pull_items.size();
-    B.host[k].pull_items = (int32_t)nt;
-    for (int64_t t = 0; t < nt; ++t)
-      B.pull_items.push_back({k, (int32_t)t, (int32_t)B.pull_items.size()});
+    BProb& P = B.host[k];
+    auto tiles = [&](int64_t unit, int most, int32_t* rounds, int32_t* first, int32_t* count,
+                     std::vector<WorkItem>& v) {
+      const int64_t units = (P.n_dofs + unit - 1) / unit;
+      *rounds = (int32_t)std::max<int64_t>(1, (units + most - 1) / most);
+      *count = (int32_t)((units + *rounds - 1) / *rounds);
+      *first = (int32_t)v.size();
+      for (int32_t t = 0; t < *count; ++t) v.push_back({k, t, (int32_t)v.size()});
+    };
+    tiles(512, kPullTiles, &P.pull_rounds, &P.pull_item0, &P.pull_items, B.pull_items);
+    tiles(2048, kWideTiles, &P.wide_rounds, &P.wide_item0, &P.wide_items, B.wide_items);
   }
   auto upload_items = [&](std::vector<WorkItem>& v, WorkItem** d) -> fc_status {
     if (*d) {
@@ -612,38 +775,18 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
     FC_HIP(hipMemcpy(*d, v.data(), v.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
     return FC_OK;
   };
-  auto finalize_spmv_ranges = [&]() {
-    int base = 0;
-    for (auto& c : B.spmv) {
-      c.item_base = base;
-      for (size_t i = 0; i < c.items.size(); ++i) {
-        c.items[i].slot = base + (int32_t)i;
-        BProb& P = B.host[c.items[i].prob];
-        if (i == 0 || c.items[i - 1].prob != c.items[i].prob) {
-          P.spmv_item0 = base + (int)i;
-          P.spmv_items = 0;
-        }
-        P.spmv_items++;
-      }
-      base += (int)c.items.size();
-    }
-    B.spmv_total = base;
-  };
-  finalize_spmv_ranges();
   for (auto& c : B.spmv) FC_TRY_B(upload_items(c.items, &c.d_items));
   for (auto& c : B.schw) FC_TRY_B(upload_items(c.items, &c.d_items));
   FC_TRY_B(upload_items(B.pull_items, &B.d_pull));
+  FC_TRY_B(upload_items(B.wide_items, &B.d_wide));
   const int64_t n = B.total_dofs;
   FC_HIP(hipMalloc(&B.r, n * sizeof(double)));
   FC_HIP(hipMalloc(&B.z, n * sizeof(double)));
   FC_HIP(hipMalloc(&B.p, n * sizeof(double)));
   FC_HIP(hipMalloc(&B.q, n * sizeof(double)));
-  // partials: SpMV items for every candidate width (<= 8 rows per item
-  // minimum) and 3 per pull item
-  int64_t max_spmv = 0;
-  for (int k = 0; k < nprob; ++k) max_spmv += (B.host[k].n_rows + 3) / 4 + 1;
-  const int64_t plen = std::max<int64_t>(max_spmv, 4 * (int64_t)B.pull_items.size()) + 8;
-  FC_HIP(hipMalloc(&B.partial, plen * sizeof(double)));
+  // three per pull tile, then (p, q) per wide tile
+  const int64_t plen = 3 * (int64_t)B.pull_items.size() + (int64_t)B.wide_items.size();
+  FC_HIP(hipMalloc(&B.partial, std::max<int64_t>(plen, 1) * sizeof(double)));
   FC_HIP(hipMalloc(&B.sc, nprob * sizeof(CgScalars)));
   FC_HIP(hipMemset(B.sc, 0, nprob * sizeof(CgScalars)));
   FC_HIP(hipHostMalloc(&B.host_sc, nprob * sizeof(CgScalars), hipHostMallocDefault));
@@ -668,7 +811,6 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
         build_spmv_items(trial, (int)ci);
         WorkItem* d = nullptr;
         FC_TRY_B(upload_items(trial.items, &d));
-        trial.item_base = 0;
         float ms = time_launches(s, B.ev[1], B.ev[2], 3, [&]() {
           (void)launch_spmv_class(B, trial, d, (int)trial.items.size(), s);
         });
@@ -683,32 +825,53 @@ extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
       build_spmv_items(c, (int)ci);
     }
     FC_HIP(hipGetLastError());
-    finalize_spmv_ranges();
     for (auto& c : B.spmv) FC_TRY_B(upload_items(c.items, &c.d_items));
-    FC_HIP(hipMemcpy(B.d_probs, B.host.data(), nprob * sizeof(BProb), hipMemcpyHostToDevice));
   }
+  if (!B.sell.empty()) rep << "sliced spmv items=" << B.sell.size() << "\n";
   for (auto& c : B.spmv)
     rep << "chosen spmv B=" << c.B << " G=" << c.G << " items=" << c.items.size() << "\n";
-  for (auto& c : B.schw)
-    rep << "schwarz m=" << c.m << " items=" << c.items.size() << "\n";
+  for (auto& c : B.schw) {
+    rep << "schwarz m=" << (c.m == kMixed ? "8..27" : std::to_string(c.m));
+    rep << " items=" << c.items.size() << "\n";
+  }
   B.report = rep.str();
   for (auto& c : B.spmv)
     if (!c.items.empty()) FC_HIP(hipMalloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
   for (auto& c : B.schw)
     if (!c.items.empty()) FC_HIP(hipMalloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
+  if (!B.sell.empty()) FC_HIP(hipMalloc(&B.d_act_sell, B.sell.size() * sizeof(SellItem)));
   FC_HIP(hipMalloc(&B.d_act_pull, B.pull_items.size() * sizeof(WorkItem)));
-  FC_HIP(hipMalloc(&B.d_act_probs, nprob * sizeof(int32_t)));
+  FC_HIP(hipMalloc(&B.d_act_wide, B.wide_items.size() * sizeof(WorkItem)));
   B.act_dofs = -1;   // lists not built yet
   FC_HIP(hipStreamSynchronize(s));
   *out = bt.release();
   return FC_OK;
 }
 
+// Running out of host memory is reported instead of crossing the C boundary.
+template <class F>
+static fc_status no_throw(const char* what, F&& f) {
+  try {
+    return f();
+  } catch (const std::bad_alloc&) {
+    set_error(std::string(what) + ": out of host memory");
+    return FC_E_NOMEM;
+  }
+}
+
+extern "C" fc_status fc_batch_create(int32_t nprob, const fc_problem* problems,
+                                     const fc_precond* preconds, int32_t autotune, void* stream,
+                                     fc_batch* out) {
+  return no_throw("fc_batch_create", [&] {
+    return batch_create_body(nprob, problems, preconds, autotune, stream, out);
+  });
+}
+
 extern "C" fc_status fc_batch_info(fc_batch bt, int64_t* total_dofs, int32_t* n_spmv_classes,
                                    int32_t* n_schwarz_classes, char* report, int64_t report_len) {
   if (!bt) return FC_E_ARG;
   if (total_dofs) *total_dofs = bt->total_dofs;
-  if (n_spmv_classes) *n_spmv_classes = (int32_t)bt->spmv.size();
+  if (n_spmv_classes) *n_spmv_classes = (int32_t)bt->spmv.size() + (bt->sell.empty() ? 0 : 1);
   if (n_schwarz_classes) *n_schwarz_classes = (int32_t)bt->schw.size();
   if (report && report_len > 0) {
     const size_t k = std::min<size_t>(bt->report.size(), (size_t)report_len - 1);
@@ -721,29 +884,23 @@ extern "C" fc_status fc_batch_info(fc_batch bt, int64_t* total_dofs, int32_t* n_
 // Launched lists = the tiles of the problems marked running (synchronous
 // upload into the full-size arrays allocated at creation).
 static fc_status compact_lists(fc_batch_s& B, const std::vector<char>& running) {
-  auto filter = [&](const std::vector<WorkItem>& all, WorkItem* d, int* n) -> fc_status {
-    std::vector<WorkItem> v;
+  auto filter = [&](const auto& all, auto* d, int* n) -> fc_status {
+    std::vector<std::remove_reference_t<decltype(*d)>> v;
     v.reserve(all.size());
-    for (const WorkItem& w : all)
+    for (const auto& w : all)
       if (running[w.prob]) v.push_back(w);
     *n = (int)v.size();
-    if (!v.empty()) FC_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
+    if (!v.empty()) FC_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(*d), hipMemcpyHostToDevice));
     return FC_OK;
   };
+  FC_TRY_B(filter(B.sell, B.d_act_sell, &B.n_act_sell));
   for (auto& c : B.spmv) FC_TRY_B(filter(c.items, c.d_act, &c.n_act));
   for (auto& c : B.schw) FC_TRY_B(filter(c.items, c.d_act, &c.n_act));
   FC_TRY_B(filter(B.pull_items, B.d_act_pull, &B.n_act_pull));
-  std::vector<int32_t> ap;
-  int64_t dofs = 0;
+  FC_TRY_B(filter(B.wide_items, B.d_act_wide, &B.n_act_wide));
+  B.act_dofs = 0;
   for (int k = 0; k < B.nprob; ++k)
-    if (running[k]) {
-      ap.push_back(k);
-      dofs += B.host[k].n_dofs;
-    }
-  B.n_act_probs = (int)ap.size();
-  B.act_dofs = dofs;
-  if (!ap.empty())
-    FC_HIP(hipMemcpy(B.d_act_probs, ap.data(), ap.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    if (running[k]) B.act_dofs += B.host[k].n_dofs;
   return FC_OK;
 }
 
@@ -770,9 +927,8 @@ static fc_status capture_steps(fc_batch_s& B, int chunk, hipStream_t s) {
   return FC_OK;
 }
 
-extern "C" fc_status fc_pcg_solve_batch(fc_batch bt, const double* const* b_dev,
-                                        double* const* x_dev, const fc_solve_opts* opts,
-                                        fc_solve_info* infos, void* stream) {
+static fc_status solve_batch_body(fc_batch bt, const double* const* b_dev, double* const* x_dev,
+                                  const fc_solve_opts* opts, fc_solve_info* infos, void* stream) {
   if (!bt || !b_dev || !x_dev) {
     set_error("fc_pcg_solve_batch: invalid arguments");
     return FC_E_ARG;
@@ -816,14 +972,13 @@ extern "C" fc_status fc_pcg_solve_batch(fc_batch bt, const double* const* b_dev,
   FC_HIP(hipEventRecord(B.ev[1], s));
   const int np = (int)B.pull_items.size();
   // start: r = b, x = 0, z = S r, p = z, scalars
-  hipLaunchKernelGGL(kb_vec<0>, dim3(np), dim3(256), 0, s, B.d_probs, B.d_pull, B.sc, B.r, B.p, B.z);
+  hipLaunchKernelGGL(kb_init, dim3((unsigned)B.wide_items.size()), dim3(256), 0, s, B.d_probs,
+                     B.d_wide, B.r);
   for (auto& c : B.schw)
     FC_HIP(launch_schwarz_class(B, c, c.d_items, (int)c.items.size(), nullptr, s));
   hipLaunchKernelGGL(kb_pull<0>, dim3(np), dim3(256), 0, s, B.d_probs, B.d_pull, np, B.sc, B.r,
                      B.p, B.q, B.z, B.partial);
-  hipLaunchKernelGGL(kb_beta<0>, dim3(B.nprob), dim3(256), 0, s, B.d_probs, B.sc, B.partial, np,
-                     nullptr);
-  hipLaunchKernelGGL(kb_vec<2>, dim3(np), dim3(256), 0, s, B.d_probs, B.d_pull, B.sc, B.r, B.p, B.z);
+  hipLaunchKernelGGL(kb_start, dim3(B.nprob), dim3(256), 0, s, B.d_probs, B.sc, B.partial, np);
   FC_HIP(hipGetLastError());
   const int chunk = o.check_every > 0 ? o.check_every : 16;
   // every problem runs at the start; the lists shrink as problems stop
@@ -839,7 +994,13 @@ extern "C" fc_status fc_pcg_solve_batch(fc_batch bt, const double* const* b_dev,
   const int64_t prog = prog_env ? std::max<int64_t>(0, std::atoll(prog_env)) : 0;
   int64_t launched = 0;
   for (;;) {
-    FC_HIP(hipGraphLaunch(B.exec, s));
+    // no more steps than maxit leaves (a stopped step still dispatches its
+    // grids: 66 us for 16 members)
+    const int64_t left = o.maxit - launched * chunk;
+    if (left > 0 && left < chunk)
+      FC_HIP(enqueue_batch_steps(B, (int)left, s));
+    else
+      FC_HIP(hipGraphLaunch(B.exec, s));
     ++launched;
     FC_HIP(hipMemcpyAsync(B.host_sc, B.sc, B.nprob * sizeof(CgScalars), hipMemcpyDeviceToHost, s));
     FC_HIP(hipStreamSynchronize(s));
@@ -887,6 +1048,13 @@ extern "C" fc_status fc_pcg_solve_batch(fc_batch bt, const double* const* b_dev,
     }
   }
   return worst;
+}
+
+extern "C" fc_status fc_pcg_solve_batch(fc_batch bt, const double* const* b_dev,
+                                        double* const* x_dev, const fc_solve_opts* opts,
+                                        fc_solve_info* infos, void* stream) {
+  return no_throw("fc_pcg_solve_batch",
+                  [&] { return solve_batch_body(bt, b_dev, x_dev, opts, infos, stream); });
 }
 
 extern "C" void fc_batch_destroy(fc_batch bt) { destroy_batch(bt); }

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(1024) void k_cg_alpha(const AlphaIn ai, CgScalars* 
   __shared__ double lds[16];
   if (sc->done) return;
   double alpha;
-  (void)cg_alpha(sc, ai, lds, &alpha);
+  (void)cg_alpha(sc, ai, lds, &alpha, blockIdx.x == 0);
 }
 
 // (p, q) partials of a separate pass over p and q, one per workgroup of a grid
@@ -274,25 +274,6 @@ __global__ __launch_bounds__(256) void k_cg_pull(
   if (threadIdx.x < kN) {
     const int k = threadIdx.x;
     partial[k * gridDim.x + blockIdx.x] = ((lds[0][k] + lds[1][k]) + lds[2][k]) + lds[3][k];
-  }
-}
-
-// Stop test (Eq. 12 or the plain residual) and the scalars of the next step,
-// by one thread.  sc->rz stays: the workgroups of k_cg_beta_p divide by it.
-__device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double zz, double rr) {
-  const double crit = (sc->stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / sc->crit0;
-  sc->zz = zz;
-  sc->rr = rr;
-  sc->crit = crit;
-  if (sc->history) sc->history[sc->iter] = crit;
-  sc->beta = rz / sc->rz;
-  sc->rzn = rz;
-  if (!(crit == crit) || !(rz == rz) || isinf(rz)) {
-    sc->done = 4;
-  } else if (crit <= sc->tol) {
-    sc->done = 1;
-  } else if (sc->iter >= sc->maxit) {
-    sc->done = 2;
   }
 }
 

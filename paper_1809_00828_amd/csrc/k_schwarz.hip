@@ -62,45 +62,15 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
   // list: the workgroups handle only the listed blocks; skip: blocks
   // flagged there are left to another launch
   const int64_t blk = list ? (int64_t)list[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x);
-  const int i = threadIdx.x;
-  const bool act = i < m;
-  int64_t dof = -1;
-  bool stop = false;
   const bool skipped = skip && skip[blk];
   if (skipped && blockIdx.x != 0) return;   // the first workgroup stores alpha
-  // the right-hand side, gathered behind the first loads of the inverse
-  auto gather = [&] {
-    double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
-    const int64_t e = block_elem[blk];
-    double gr = 0.0, gq = 0.0, gs = 1.0;
-    if (act) {
-      dof = block_dof(elem_nodes, e, nn, bd, i);
-      if (dof >= 0) {
-        gr = r[dof];
-        if (q) gq = q[dof];
-        if (isd) gs = isd[dof];
-      }
-    }
-    if (ai.np) stop = !cg_alpha(sc, ai, red, &alpha);
-    if (act) rB[i] = dof >= 0 ? (A)((q ? fma(-alpha, gq, gr) : gr) * gs) : A(0);
-  };
-  const T* Qb = P + blk * block_stride;
-  const double v = kRuns ? sym_block_staged_runs<T, A>(Qb, rB, m, i, tile, gather)
-                         : sym_block_staged_rows<T, A>(Qb, rB, m, i, tile, gather);
-  if (act && !stop && !skipped) y[blk * m + i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
+  schwarz_staged_block<T, kRuns>(
+      P + blk * block_stride, skipped ? nullptr : y + blk * m, m, r, q, isd, sc, ai,
+      blockIdx.x == 0, rB, tile, red,
+      [&](int i) { return block_dof(elem_nodes, block_elem[blk], nn, bd, i); });
 }
 
-// m <= 64: each wave handles floor(64/m) blocks, one lane per output row.
-// kM > 0 (m = kM known at compile time): lane i loads its
-// column of the stored rows (Q_B[k][i] = P_B[i][(i + k) mod m], k = 0 ..
-// m/2; two rows per load, as sym_offset pairs them) into registers before
-// it gathers r_B, so the block's stream is in
-// flight during the gather; the entries P_B[i][(i - k) mod m] =
-// Q_B[k][(i - k) mod m] are then read from the lane that loaded them (a
-// cross-lane read within the wave).  kM = 0: any m, the stored rows read
-// after the gather (sym_row).  kLat: the blocks are the cells of
-// a lattice in order, so a row's unknown follows from the block and row
-// indices and the gather of r_B is issued together with the stored rows.
+// m <= 64 (schwarz_small_tile)
 template <typename T, int kM, bool kLat>
 __global__ __launch_bounds__(256) void k_schwarz_small(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
@@ -110,80 +80,10 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
     const PullLattice lat) {
   __shared__ double rB[4][64], red[16];
   if (sc && sc->done) return;
-  const int m = kM > 0 ? kM : m_arg;
-  double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
-  const int bpw = 64 / m;
-  const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-  const int lb = l / m, i = l % m;
-  const int64_t tile = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t blk = (tile * 4 + w) * bpw + lb;
-  const bool active = lb < bpw && blk < n_blocks;
-  // lanes without a block read block 0 (always present) and store nothing
-  const T* Pb = P + (active ? blk : 0) * block_stride;
-  using A = typename Acc<T>::type;
-  constexpr int kH = kM / 2;
-  T v[kH + 1];
-  int64_t dof = -1;
-  double g_r = 0.0, g_q = 0.0, g_s = 1.0;
-  if constexpr (kLat) {
-    // the gathered entries are loaded first and the stored rows next, all
-    // without branches (a lane without a block reads unknown 0), and only
-    // then combined: the wait for the gather does not wait for the rows
-    // (the lattice is set for scalar problems only: one unknown per node)
-    dof = active ? lattice_cell_node(lat, (int)blk, i) : 0;
-    g_r = r[dof];
-    g_q = (q ? q : r)[dof];
-    g_s = (isd ? isd : r)[dof];
-  }
-  if constexpr (kM > 0) {
-    // stored rows in pairs (sym_offset, m <= 64): one two-wide load each
-    constexpr int kNP = (kH + 1) & ~1;
-    typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
-#pragma unroll
-    for (int k = 0; k < kNP; k += 2) {
-      const t2 t = *reinterpret_cast<const t2*>(Pb + k * kM + 2 * i);
-      v[k] = t.x;
-      v[k + 1] = t.y;
-    }
-    if constexpr (kNP < kH + 1) v[kH] = Pb[kH * kM + i];
-  }
-  if constexpr (!kLat) {
-    if (active) {
-      dof = block_dof(elem_nodes, block_elem[blk], nn, bd, i);
-      if (dof >= 0) {
-        g_r = r[dof];
-        if (q) g_q = q[dof];
-        if (isd) g_s = isd[dof];
-      }
-    }
-  }
-  if (ai.np && !cg_alpha(sc, ai, red, &alpha)) return;
-  const double rv = (q ? fma(-alpha, g_q, g_r) : g_r) * (isd ? g_s : 1.0);
-  if (active) rB[w][l] = rv;
-  __syncthreads();
-  double out;
-  if constexpr (kM > 0) {
-    // every lane takes part in the cross-lane reads; a lane without a block
-    // reads its own group's entries and discards the result
-    const int g0 = (active ? lb : 0) * kM;
-    const double* rb = &rB[w][g0];
-    A acc0 = madd<A>(v[0], rb[i], A(0)), acc1 = 0;
-#pragma unroll
-    for (int k = 1; k <= kH; ++k) {
-      const int ip = i + k < kM ? i + k : i + k - kM;   // (i + k) mod m
-      const int im = i >= k ? i - k : i - k + kM;       // (i - k) mod m
-      const T vr = __shfl(v[k], g0 + im, 64);
-      acc0 = madd<A>(v[k], rb[ip], acc0);
-      if (!((kM & 1) == 0 && k == kH)) acc1 = madd<A>(vr, rb[im], acc1);
-    }
-    out = (double)acc0 + (double)acc1;
-  } else {
-    if (!active) return;
-    const double* rb = &rB[w][lb * m];
-    out = sym_row<T>(Pb, rb, m, i);
-  }
-  if (!active) return;
-  y[blk * m + i] = dof < 0 ? 0.0 : isd ? out * isd[dof] : out;
+  schwarz_small_tile<T, kM, kLat>(
+      P, block_stride, m_arg, r, q, isd, sc, ai, blockIdx.x == 0, y, n_blocks, lat,
+      xcd_remap(blockIdx.x, gridDim.x), rB, red,
+      [&](int64_t blk, int i) { return block_dof(elem_nodes, block_elem[blk], nn, bd, i); });
 }
 
 // Factored low-precision product y_B = D^{-1/2} Lt (Lt^T (D^{-1/2} r_B)) with
@@ -498,21 +398,13 @@ static hipError_t phase1(const fc_precond_s& pc, const T* Q, const double* r, co
                          dim3(256), 0, s, Q, stride, block_nodes(pc), pc.block_elem, pc.nn,    \
                          pc.bdim, pc.m, r, q, isd, sc, ai, pc.y, pc.n_blocks, pc.lat);         \
   } while (0)
+#define FC_SMALL_CASE(KM) \
+  case KM: FC_SMALL_LAUNCH(KM); break;
     switch (pc.m) {
-      case 8: FC_SMALL_LAUNCH(8); break;
-      case 9: FC_SMALL_LAUNCH(9); break;
-      case 16: FC_SMALL_LAUNCH(16); break;
-      case 18: FC_SMALL_LAUNCH(18); break;
-      case 24: FC_SMALL_LAUNCH(24); break;
-      case 25: FC_SMALL_LAUNCH(25); break;
-      case 27: FC_SMALL_LAUNCH(27); break;
-      case 32: FC_SMALL_LAUNCH(32); break;
-      case 36: FC_SMALL_LAUNCH(36); break;
-      case 49: FC_SMALL_LAUNCH(49); break;
-      case 50: FC_SMALL_LAUNCH(50); break;
-      case 64: FC_SMALL_LAUNCH(64); break;
+      FC_SMALL_SIZES(FC_SMALL_CASE)
       default: FC_SMALL_LAUNCH(0); break;
     }
+#undef FC_SMALL_CASE
 #undef FC_SMALL_LAUNCH
   }
   return hipGetLastError();

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell(const SellView A, const doubl
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   double dot = 0.0;
-  if (s < A.n_slices) dot = sell_slice_product<P, kNT>(A, s, l, x, y);
+  if (s < A.n_slices) dot = sell_slice_product<P, kNT>(A, A.slices[s], l, x, y);
   if (!partial) return;
   dot = wave_sum_last(dot);
   if (l == 63) lds[w] = dot;
@@ -292,6 +292,8 @@ static bool lattice_allowed() {
 static bool use_sell(const DeviceBsr& A) {
   return lattice_allowed() && A.lat.dim > 0 && A.bdim == 1 && A.sell_val;
 }
+
+bool spmv_uses_sell(const DeviceBsr& A) { return use_sell(A); }
 
 // Workgroups of the whole-matrix product (one (x, y) partial each when asked).
 static int64_t spmv_blocks(const DeviceBsr& A) {

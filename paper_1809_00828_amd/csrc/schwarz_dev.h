@@ -217,4 +217,136 @@ __device__ __forceinline__ double sym_row(const T* __restrict__ Qb, const double
   return (double)acc0 + (double)acc1;
 }
 
+// One block (m > 64) by a workgroup of 64 ceil(m / 64) threads, its stored rows
+// staged through LDS (kRuns: sym_block_staged_runs).  The right-hand side is
+// gathered, and the step length taken, behind the first loads of the inverse.
+// dof_of(i): unknown of row i (< 0: none).  yb null: nothing is stored.
+template <typename T, bool kRuns, class Dof>
+__device__ __forceinline__ void schwarz_staged_block(
+    const T* __restrict__ Qb, double* __restrict__ yb, int m, const double* __restrict__ r,
+    const double* __restrict__ q, const double* __restrict__ isd, CgScalars* sc,
+    const AlphaIn ai, bool first, typename Acc<T>::type* rB, T* tile, double* red, Dof&& dof_of) {
+  using A = typename Acc<T>::type;
+  const int i = threadIdx.x;
+  const bool act = i < m;
+  int64_t dof = -1;
+  bool stop = false;
+  auto gather = [&] {
+    double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
+    double gr = 0.0, gq = 0.0, gs = 1.0;
+    if (act) {
+      dof = dof_of(i);
+      if (dof >= 0) {
+        gr = r[dof];
+        if (q) gq = q[dof];
+        if (isd) gs = isd[dof];
+      }
+    }
+    if (ai.np) stop = !cg_alpha(sc, ai, red, &alpha, first);
+    if (act) rB[i] = dof >= 0 ? (A)((q ? fma(-alpha, gq, gr) : gr) * gs) : A(0);
+  };
+  const double v = kRuns ? sym_block_staged_runs<T, A>(Qb, rB, m, i, tile, gather)
+                         : sym_block_staged_rows<T, A>(Qb, rB, m, i, tile, gather);
+  if (act && !stop && yb) yb[i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
+}
+
+// m <= 64: each wave handles floor(64/m) blocks, one lane per output row.
+// kM > 0 (m = kM known at compile time): lane i loads its
+// column of the stored rows (Q_B[k][i] = P_B[i][(i + k) mod m], k = 0 ..
+// m/2; two rows per load, as sym_offset pairs them) into registers before
+// it gathers r_B, so the block's stream is in
+// flight during the gather; the entries P_B[i][(i - k) mod m] =
+// Q_B[k][(i - k) mod m] are then read from the lane that loaded them (a
+// cross-lane read within the wave).  kM = 0: any m, the stored rows read
+// after the gather (sym_row).  kLat: the blocks are the cells of
+// a lattice in order, so a row's unknown follows from the block and row
+// indices and the gather of r_B is issued together with the stored rows.  tile: index of the
+// workgroup's 4 floor(64/m) blocks; dof_of(blk, i): unknown of row i (< 0:
+// none).
+template <typename T, int kM, bool kLat, class Dof>
+__device__ __forceinline__ void schwarz_small_tile(
+    const T* __restrict__ P, int64_t block_stride, int m_arg, const double* __restrict__ r,
+    const double* __restrict__ q, const double* __restrict__ isd, CgScalars* sc,
+    const AlphaIn ai, bool first, double* __restrict__ y, int64_t n_blocks,
+    const PullLattice& lat, int64_t tile, double (*rB)[64], double* red, Dof&& dof_of) {
+  const int m = kM > 0 ? kM : m_arg;
+  double alpha = (sc && q && !ai.np) ? sc->alpha : 0.0;
+  const int bpw = 64 / m;
+  const int w = threadIdx.x / 64, l = threadIdx.x % 64;
+  const int lb = l / m, i = l % m;
+  const int64_t blk = (tile * 4 + w) * bpw + lb;
+  const bool active = lb < bpw && blk < n_blocks;
+  // lanes without a block read block 0 (always present) and store nothing
+  const T* Pb = P + (active ? blk : 0) * block_stride;
+  using A = typename Acc<T>::type;
+  constexpr int kH = kM / 2;
+  T v[kH + 1];
+  int64_t dof = -1;
+  double g_r = 0.0, g_q = 0.0, g_s = 1.0;
+  if constexpr (kLat) {
+    // the gathered entries are loaded first and the stored rows next, all
+    // without branches (a lane without a block reads unknown 0), and only
+    // then combined: the wait for the gather does not wait for the rows
+    // (the lattice is set for scalar problems only: one unknown per node)
+    dof = active ? lattice_cell_node(lat, (int)blk, i) : 0;
+    g_r = r[dof];
+    g_q = (q ? q : r)[dof];
+    g_s = (isd ? isd : r)[dof];
+  }
+  if constexpr (kM > 0) {
+    // stored rows in pairs (sym_offset, m <= 64): one two-wide load each
+    constexpr int kNP = (kH + 1) & ~1;
+    typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+#pragma unroll
+    for (int k = 0; k < kNP; k += 2) {
+      const t2 t = *reinterpret_cast<const t2*>(Pb + k * kM + 2 * i);
+      v[k] = t.x;
+      v[k + 1] = t.y;
+    }
+    if constexpr (kNP < kH + 1) v[kH] = Pb[kH * kM + i];
+  }
+  if constexpr (!kLat) {
+    if (active) {
+      dof = dof_of(blk, i);
+      if (dof >= 0) {
+        g_r = r[dof];
+        if (q) g_q = q[dof];
+        if (isd) g_s = isd[dof];
+      }
+    }
+  }
+  if (ai.np && !cg_alpha(sc, ai, red, &alpha, first)) return;
+  const double rv = (q ? fma(-alpha, g_q, g_r) : g_r) * (isd ? g_s : 1.0);
+  if (active) rB[w][l] = rv;
+  __syncthreads();
+  double out;
+  if constexpr (kM > 0) {
+    // every lane takes part in the cross-lane reads; a lane without a block
+    // reads its own group's entries and discards the result
+    const int g0 = (active ? lb : 0) * kM;
+    const double* rb = &rB[w][g0];
+    A acc0 = madd<A>(v[0], rb[i], A(0)), acc1 = 0;
+#pragma unroll
+    for (int k = 1; k <= kH; ++k) {
+      const int ip = i + k < kM ? i + k : i + k - kM;   // (i + k) mod m
+      const int im = i >= k ? i - k : i - k + kM;       // (i - k) mod m
+      const T vr = __shfl(v[k], g0 + im, 64);
+      acc0 = madd<A>(v[k], rb[ip], acc0);
+      if (!((kM & 1) == 0 && k == kH)) acc1 = madd<A>(vr, rb[im], acc1);
+    }
+    out = (double)acc0 + (double)acc1;
+  } else {
+    if (!active) return;
+    const double* rb = &rB[w][lb * m];
+    out = sym_row<T>(Pb, rb, m, i);
+  }
+  if (!active) return;
+  y[blk * m + i] = dof < 0 ? 0.0 : isd ? out * isd[dof] : out;
+}
+
+// List of the block sizes m <= 64 with kernels of their own: scalar and vector
+// problems at p = 1 .. 3 (2-D and 3-D) and p up to 6 (2-D).
+#define FC_SMALL_SIZES(X) \
+  X(8) X(9) X(16) X(18) X(24) X(25) X(27) X(32) X(36) X(49) X(50) X(64)
+
 }  // namespace fc

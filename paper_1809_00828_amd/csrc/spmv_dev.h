@@ -145,12 +145,11 @@ __device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, in
   return acc;
 }
 
-// y = A x on slice s, by one wave.  Returns (x, y) of this lane's row.
+// y = A x on one slice, by one wave.  Returns (x, y) of this lane's row.
 template <int P, bool kNT>
-__device__ __forceinline__ double sell_slice_product(const SellView& A, int64_t s, int l,
+__device__ __forceinline__ double sell_slice_product(const SellView& A, const SellSlice sl, int l,
                                                      const double* __restrict__ x,
                                                      double* __restrict__ y) {
-  const SellSlice sl = A.slices[s];
   const SellRow r = sell_row<P>(sl, l, A);
   const int len1 = sl.cls & 2 ? 2 * P + 1 : P + 1;
   const int npen = len1 * (A.dim == 3 ? (sl.cls & 4 ? 2 * P + 1 : P + 1) : 1);
