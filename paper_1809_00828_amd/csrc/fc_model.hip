@@ -107,9 +107,7 @@ fc_status fc_model_forward(fc_model m, int32_t batch, int32_t grid, const float*
   }
   hipStream_t s = (hipStream_t)stream;
   FC_TRY_M(m->ws.ensure(m->net, batch, grid));
-  FC_HIP(net_forward(m->net, m->ws, x_dev, batch, s));
-  const int64_t n = (int64_t)batch * grid * grid * grid;
-  FC_HIP(hipMemcpyAsync(y_dev, m->ws.y(), n * sizeof(float), hipMemcpyDeviceToDevice, s));
+  FC_HIP(net_forward(m->net, m->ws, x_dev, y_dev, batch, s));
   return FC_OK;
 }
 
@@ -122,7 +120,7 @@ fc_status fc_model_loss_grad(fc_model m, int32_t batch, int32_t grid, const floa
   hipStream_t s = (hipStream_t)stream;
   FC_TRY_M(m->ws.ensure(m->net, batch, grid));
   const int64_t n = (int64_t)batch * grid * grid * grid;
-  FC_HIP(net_forward(m->net, m->ws, x_dev, batch, s));
+  FC_HIP(net_forward(m->net, m->ws, x_dev, m->ws.y(), batch, s));
   FC_HIP(net_mse(m->ws, t_dev, m->ws.gy(), n, s));
   FC_HIP(net_backward(m->net, m->ws, x_dev, m->ws.gy(), batch, s));
   const double l = sum_partials_host(m->ws.partial, s) / (double)n;
@@ -168,7 +166,7 @@ fc_status fc_model_train(fc_model m, int64_t n_samples, int32_t grid, const floa
       }
       if (st != FC_OK) break;
       const int64_t n = (int64_t)B * vox;
-      if (net_forward(m->net, m->ws, xb, B, s) != hipSuccess ||
+      if (net_forward(m->net, m->ws, xb, m->ws.y(), B, s) != hipSuccess ||
           net_mse(m->ws, tb, m->ws.gy(), n, s) != hipSuccess ||
           net_backward(m->net, m->ws, xb, m->ws.gy(), B, s) != hipSuccess ||
           net_adam(m->net, opts->lr, ++m->net.step, s) != hipSuccess) {

@@ -444,7 +444,7 @@ hipError_t coarse_correct(CoarseCtx& c, const double* r, double* z, const double
                           const CgScalars* sc, hipStream_t s) {
   hipError_t e;
   if ((e = coarse_restrict(c, r, c.xin, sc, s)) != hipSuccess) return e;
-  if ((e = net_forward(c.model->net, c.ws, c.xin, 1, s)) != hipSuccess) return e;
+  if ((e = net_forward(c.model->net, c.ws, c.xin, c.ws.y(), 1, s)) != hipSuccess) return e;
   if ((e = coarse_gamma(c, c.ws.y(), sc, nullptr, s)) != hipSuccess) return e;
   return coarse_prolong(c, c.ws.y(), z, q, sc, s);
 }

@@ -19,8 +19,11 @@
 // data-gradient passes, which keeps FP32 accuracy with BF16 weights; two
 // for the weight gradient), and runs the 27 taps from there.  The data
 // gradient is the forward kernel on weights packed transposed with the taps
-// mirrored; the weight gradient sums brick ranges into partials that a
-// second kernel adds in a fixed order (no atomics).
+// mirrored.  Pooling, upsampling, skips and ReLU masks, and their gradients, are
+// part of the convolution before or after them (ConvMode): one launch per
+// convolution.  The weight gradients of all layers are one launch at the end of
+// the backward pass: brick ranges summed into partials that a second launch adds
+// in a fixed order (no atomics).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,7 +37,6 @@
 
 namespace fc {
 
-constexpr int kWgradRanges = 512;   // brick ranges of one weight-gradient launch, at most
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -43,42 +45,45 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 
 // ---------------------------------------------------------- MFMA convolutions
-// Every convolution is an implicit GEMM on the 16x16x16 BF16 matrix cores
-// with FP32 accumulation.  Operand layouts of v_mfma_f32_16x16x16_bf16 (one
-// wave): lane l supplies A[l % 16][4 (l / 16) + j] and B[4 (l / 16) + j]
-// [l % 16], j = 0..3, and holds D[4 (l / 16) + j][l % 16].
+// Every convolution is an implicit GEMM on the 16x16x32 BF16 matrix cores
+// with FP32 accumulation.  Operand layouts of v_mfma_f32_16x16x32_bf16 (one
+// wave): lane l supplies A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j]
+// [l % 16], j = 0..7, and holds D[4 (l / 16) + j][l % 16], j = 0..3.
 //
 // A workgroup owns a brick of 4x4x4 voxels; its input, with a one-voxel
 // halo (6x6x6), is staged once in LDS, already split into BF16 terms, and
 // every tap of the stencil reads it there.  A 16-voxel row tile of the GEMM
 // is one 4x4 (y, x) plane of the brick.
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // in a row of a grid
+
+__device__ __forceinline__ f32x4 mfma32(uint4 a, uint4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
 
 constexpr int kHaloVox = 216;   // 6^3 halo voxels of a 4^3 brick
+
+// two BF16 numbers (nearest even) in one word, the first in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
 
 // v = h0 + h1 + h2 in BF16 with |v - (h0 + h1 + h2)| <= 2^-24 |v| (each
 // term the BF16 rounding of what the earlier ones leave; the remainders are
 // exact in FP32).  Products of BF16 numbers are exact in FP32, so three
 // MFMAs over the three terms give the FP32-accurate product with a BF16
-// weight.  Two terms leave 2^-16 |v|.
-struct Split3 {
-  uint16_t h[3];
-};
-
-__device__ __forceinline__ Split3 split3(float v) {
-  Split3 r;
-  r.h[0] = f2bf(v);
-  const float ra = v - __uint_as_float((uint32_t)r.h[0] << 16);
-  r.h[1] = f2bf(ra);
-  const float rb = ra - __uint_as_float((uint32_t)r.h[1] << 16);
-  r.h[2] = f2bf(rb);
-  return r;
-}
-
-__device__ __forceinline__ void split2(float v, uint16_t& h0, uint16_t& h1) {
-  h0 = f2bf(v);
-  h1 = f2bf(v - __uint_as_float((uint32_t)h0 << 16));
+// weight.  Two terms leave 2^-16 |v|.  Two numbers at a time.
+template <int kTerms>
+__device__ __forceinline__ void split_bf16(float a, float b, uint32_t (&h)[kTerms]) {
+#pragma unroll
+  for (int s = 0; s < kTerms; ++s) {
+    h[s] = pack_bf16(a, b);
+    a -= __uint_as_float(h[s] << 16);
+    b -= __uint_as_float(h[s] & 0xffff0000u);
+  }
 }
 
 // offset of tap t = dz*9 + dy*3 + dx in a 6x6x6 halo (taps past 26 are
@@ -90,7 +95,7 @@ __device__ __forceinline__ int halo_tap_offset(int t) {
 }
 
 // Reduction layout of a convolution with cin input channels: chunks of cc
-// channels (4, 8 or 16), each chunk a run of ksteps * 16 reduction indices
+// channels (4, 8 or 16), each chunk a run of ksteps * 32 reduction indices
 // k = tap * cc + c (c the channel within the chunk), zero weights past
 // 27 * cc.
 struct ConvK {
@@ -101,125 +106,304 @@ inline ConvK conv_k(int cin) {
   ConvK g;
   g.cc = cin <= 4 ? 4 : cin <= 8 ? 8 : 16;
   g.nchunk = (cin + g.cc - 1) / g.cc;
-  g.ksteps = (27 * g.cc + 15) / 16;
-  g.krow = g.nchunk * g.ksteps * 16;
+  g.ksteps = (27 * g.cc + 31) / 32;
+  g.krow = g.nchunk * g.ksteps * 32;
   return g;
 }
 
-// y[b][o][v] = act(bias[o] + sum_{i,t} w(o,i,t) x[b][i][v + off_t]) with the
-// weights packed by k_pack_conv (rows o of krow BF16 values, chunks of kCc
-// input channels) and the input split into three BF16 terms.  Workgroup:
-// brick blockIdx.x (nb^3 per sample), output channels 16 blockIdx.y .. + 15
-// (one column tile), sample blockIdx.z; wave w computes plane z = w of the
-// brick.  Per chunk, the halo input and the tile's weights are staged in
-// LDS, the loads of a thread all issued before the first is used.
-template <int kCc>
-__global__ __launch_bounds__(256) void k_conv3d(const float* __restrict__ x, int Ci, int nchunk,
-                                                const uint16_t* __restrict__ W, int krow,
-                                                const float* __restrict__ bias,
-                                                float* __restrict__ y, int Co, int N, int nb,
-                                                int relu) {
-  constexpr int kRs = kCc + 4;                   // LDS row of a halo voxel (pad: banks)
-  constexpr int kSteps = (27 * kCc + 15) / 16;
-  constexpr int kWRow = kSteps * 16 + 4;         // LDS row of one output channel
-  constexpr int kItems = kHaloVox * kCc / 4;     // (halo voxel, 4 channels) items
-  constexpr int kIter = (kItems + 255) / 256;
-  constexpr int kWItems = 16 * kSteps * 2;       // 8 weights per item
-  constexpr int kWIter = (kWItems + 255) / 256;
-  __shared__ __align__(16) uint16_t xs[3][kHaloVox * kRs];   // [term][voxel][channel]
-  __shared__ __align__(16) uint16_t wl[16 * kWRow];          // [column][k]
-  const int V = N * N * N;
-  const int brick = blockIdx.x, b = blockIdx.z, o0 = blockIdx.y * 16;
-  const int bx = brick % nb, by = (brick / nb) % nb, bz = brick / (nb * nb);
+// What a convolution does with its result val (bias added), on top of the layer
+// itself: every elementwise, pooling or upsampling pass next to it.
+enum ConvMode {
+  kConvPlain,     // y = val
+  kConvRelu,      // y = relu(val)
+  kConvReluPool,  // y = relu(val), y2 = its average over the existing children
+  kConvReluAdd,   // y = relu(val), y2 = y + e1
+  kConvMask,      // y = val where e1 > 0, else 0
+  kConvMaskTwo,   // y = val, y2 = val where e1 > 0, else 0
+  kConvSumMask,   // y2 = sum over the existing children where e1 > 0, else 0
+  kConvExpand,    // y on the finer grid N2: gradient of the average, plus e2,
+                  // where e1 > 0, else 0
+};
+
+struct ConvArgs {
+  const float* x;
+  const uint16_t* W;
+  const float* bias;     // may be null
+  float *y, *y2;
+  const float *e1, *e2;
+  int Ci, nchunk, krow, Co, N, nb;
+  int up;                // 1: x is on the grid of (N + 1) / 2, nearest upsampling
+  int mode, N2;          // ConvMode; grid of y2 (pooling) or y (expanding)
+  FastDiv dnb;           // division by nb
+};
+
+// sum_{i,t} w(o,i,t) x[b][i][v + off_t] with the weights packed by k_pack_conv
+// (rows o of krow BF16 values, chunks of kCc input channels) and the input split
+// into three BF16 terms.  Workgroup: brick blockIdx.x (nb^3 per sample), output
+// channels 16 blockIdx.y .. + 15 (one column tile), sample blockIdx.z; wave w
+// computes plane z = w % 4 of the brick.  Per chunk, the halo input and the
+// tile's weights are staged in LDS, the next chunk's loads in flight during the
+// products.  kKs = 4: sixteen waves, the reduction steps of a plane dealt to four
+// of them and added at the end, and the loads of two chunks in flight; for grids
+// that leave the chip idle, where a step is a chain of latencies.
+// Bound by latencies and instruction issue: a workgroup is one pass of load,
+// split, 27 taps and store.  Against the layer alone, with pooling, upsampling,
+// skip and mask passes between: 25 launches and 152 us -> 15 and 98 us for one
+// 33^3 grid; the network's gradient on eight 25^3 grids 1,150 us in 95 launches ->
+// 494 us in 33.
+template <int kCc, int kKs>
+__global__ __launch_bounds__(256 * kKs) void k_conv3d(const ConvArgs A) {
+  constexpr int kT = 256 * kKs;
+  constexpr int kRs = kCc == 16 ? 24 : kCc;      // LDS row of a halo voxel (pad: banks)
+  constexpr int kSteps = (27 * kCc + 31) / 32;
+  constexpr int kWRow = kSteps * 32 + 8;         // LDS row of one output channel
+  constexpr int kIter = kCc / 4 > kKs ? kCc / 4 / kKs : 1;   // runs of 4 channels per thread
+  constexpr int kWItems = 16 * kSteps * 4;       // 8 weights per item
+  constexpr int kWIter = (kWItems + kT - 1) / kT;
+  constexpr int kXs = kHaloVox * kRs;
+  constexpr int kRed = kKs > 1 ? 3 * 4 * 64 * 8 : 0;   // in 16-bit words
+  constexpr int kLds = 3 * kXs + 16 * kWRow > kRed ? 3 * kXs + 16 * kWRow : kRed;
+  __shared__ __align__(16) uint16_t lds[kLds];   // [term][voxel][channel], [column][k]
+  __shared__ float2 pool[2][64];
+  uint16_t* wl = lds + 3 * kXs;
+  const int N = A.N, V = N * N * N, nb = A.nb, Ci = A.Ci, Co = A.Co;
+  const int Ns = A.up ? (N + 1) / 2 : N, Vs = Ns * Ns * Ns;
+  const int b = blockIdx.z, o0 = blockIdx.y * 16;
+  const int line = (int)fdiv(blockIdx.x, A.dnb), bx = blockIdx.x - line * nb;
+  const int bz = (int)fdiv(line, A.dnb), by = line - bz * nb;
   const int x0 = 4 * bx - 1, y0 = 4 * by - 1, z0 = 4 * bz - 1;   // halo corner
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, r16 = l & 15, kg = l >> 4;
+  const int tid = threadIdx.x, w = (tid >> 6) & 3, l = tid & 63, r16 = l & 15, kg = l >> 4;
+  const int ks = kKs > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
   const int hv0 = (w * 6 + (r16 >> 2)) * 6 + (r16 & 3);   // this lane's A row, tap 0
   // one accumulator per input term (independent MFMA chains), added
   // smallest term first at the end
   f32x4 acc[3];
 #pragma unroll
   for (int s = 0; s < 3; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float* xb = x + (int64_t)b * Ci * V;
-  for (int ch = 0; ch < nchunk; ++ch) {
-    const int c0 = ch * kCc;
+  // the halo voxel of this thread; a run of 256 threads takes the channels 4 q ..
+  // of the chunk, q = ks, ks + kKs, .. (wave-uniform)
+  const int hv = tid & 255;
+  const int hz = hv / 36, hr = hv - 36 * hz, hy = hr / 6, hx = hr - 6 * hy;
+  const int vz = z0 + hz, vy = y0 + hy, vx = x0 + hx;
+  const bool inside = hv < kHaloVox && vz >= 0 && vz < N && vy >= 0 && vy < N && vx >= 0 && vx < N;
+  const int vox = inside ? ((vz >> A.up) * Ns + (vy >> A.up)) * Ns + (vx >> A.up) : 0;
+  const float* xb = A.x + (int64_t)b * Ci * Vs;
+  struct Chunk {
     float v[kIter][4];
-    int dst[kIter];
-#pragma unroll
-    for (int it = 0; it < kIter; ++it) {
-      const int e = tid + 256 * it;
-      const int q = e / kHaloVox, hv = e - q * kHaloVox;
-      const int hz = hv / 36, hr = hv - 36 * hz, hy = hr / 6, hx = hr - 6 * hy;
-      const int gz = z0 + hz, gy = y0 + hy, gx = x0 + hx;
-      const bool in = e < kItems && gz >= 0 && gz < N && gy >= 0 && gy < N && gx >= 0 && gx < N;
-      const float* src = xb + (int64_t)(c0 + 4 * q) * V + (in ? (gz * N + gy) * N + gx : 0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        v[it][j] = (in && c0 + 4 * q + j < Ci) ? src[(int64_t)j * V] : 0.f;
-      dst[it] = e < kItems ? hv * kRs + 4 * q : -1;
-    }
     uint4 wv[kWIter];
-    int wdst[kWIter];
+  };
+  auto load = [&](int ch, Chunk& c) {
 #pragma unroll
-    for (int it = 0; it < kWIter; ++it) {
-      const int e = tid + 256 * it;
-      const int r = e / (2 * kSteps), q = e - r * 2 * kSteps;
-      wv[it] = uint4{0u, 0u, 0u, 0u};
-      if (e < kWItems && o0 + r < Co)
-        wv[it] = *reinterpret_cast<const uint4*>(W + (int64_t)(o0 + r) * krow +
-                                                 (int64_t)ch * kSteps * 16 + 8 * q);
-      wdst[it] = e < kWItems ? r * kWRow + 8 * q : -1;
-    }
-    __syncthreads();   // the previous chunk's reads are done
-#pragma unroll
-    for (int it = 0; it < kIter; ++it) {
-      if (dst[it] < 0) continue;
-      uint16_t h[3][4];
+    for (int it = 0; it < kIter; ++it)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const Split3 sp = split3(v[it][j]);
-        h[0][j] = sp.h[0];
-        h[1][j] = sp.h[1];
-        h[2][j] = sp.h[2];
+        const int i = ch * kCc + 4 * (ks + kKs * it) + j;
+        c.v[it][j] = xb[(int64_t)min(i, Ci - 1) * Vs + vox];
       }
 #pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        uint2 pk;
-        pk.x = (uint32_t)h[s][0] | ((uint32_t)h[s][1] << 16);
-        pk.y = (uint32_t)h[s][2] | ((uint32_t)h[s][3] << 16);
-        *reinterpret_cast<uint2*>(&xs[s][dst[it]]) = pk;
-      }
+    for (int it = 0; it < kWIter; ++it) {
+      const int e = tid + kT * it;
+      const int r = e / (4 * kSteps), q = e - r * 4 * kSteps;
+      c.wv[it] = uint4{0u, 0u, 0u, 0u};
+      if (e < kWItems && o0 + r < Co)
+        c.wv[it] = *reinterpret_cast<const uint4*>(A.W + (int64_t)(o0 + r) * A.krow +
+                                                   (int64_t)ch * kSteps * 32 + 8 * q);
+    }
+  };
+  auto stage = [&](int ch, const Chunk& c) {
+#pragma unroll
+    for (int it = 0; it < kIter; ++it) {
+      const int q = ks + kKs * it, i = ch * kCc + 4 * q;
+      float v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = inside && i + j < Ci ? c.v[it][j] : 0.f;
+      uint32_t h0[3], h1[3];
+      split_bf16(v[0], v[1], h0);
+      split_bf16(v[2], v[3], h1);
+      if (hv < kHaloVox && 4 * q < kCc)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+          *reinterpret_cast<uint2*>(&lds[s * kXs + hv * kRs + 4 * q]) = uint2{h0[s], h1[s]};
     }
 #pragma unroll
     for (int it = 0; it < kWIter; ++it) {
-      if (wdst[it] < 0) continue;
-      *reinterpret_cast<uint2*>(&wl[wdst[it]]) = uint2{wv[it].x, wv[it].y};
-      *reinterpret_cast<uint2*>(&wl[wdst[it] + 4]) = uint2{wv[it].z, wv[it].w};
+      const int e = tid + kT * it;
+      if (e >= kWItems) continue;
+      const int r = e / (4 * kSteps), q = e - r * 4 * kSteps;
+      *reinterpret_cast<uint4*>(&wl[r * kWRow + 8 * q]) = c.wv[it];
     }
-    __syncthreads();
+  };
+  struct Operands {
+    uint4 a[3], b;
+  };
+  auto fetch = [&](int s, Operands& p) {
+    const int k = 32 * s + 8 * kg;   // this lane's eight reduction indices
+    p.b = *reinterpret_cast<const uint4*>(&wl[r16 * kWRow + k]);
+    const int t = k / kCc, c = k - t * kCc;
+    const int a0 = (hv0 + halo_tap_offset(t)) * kRs + c;
+    const int a1 = kCc == 4 ? (hv0 + halo_tap_offset(t + 1)) * kRs : 0;
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      const int k = 16 * s + 4 * kg;
-      const int t = k / kCc, c = k - t * kCc;
-      const int a = (hv0 + halo_tap_offset(t)) * kRs + c;
-      const bf16x4 bw = *reinterpret_cast<const bf16x4*>(&wl[r16 * kWRow + k]);
-#pragma unroll
-      for (int h = 0; h < 3; ++h) {
-        const bf16x4 av = *reinterpret_cast<const bf16x4*>(&xs[h][a]);
-        acc[h] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bw, acc[h], 0, 0, 0);
+    for (int h = 0; h < 3; ++h) {
+      if constexpr (kCc == 4) {
+        const uint2 p0 = *reinterpret_cast<const uint2*>(&lds[h * kXs + a0]);
+        const uint2 p1 = *reinterpret_cast<const uint2*>(&lds[h * kXs + a1]);
+        p.a[h] = uint4{p0.x, p0.y, p1.x, p1.y};
+      } else {
+        p.a[h] = *reinterpret_cast<const uint4*>(&lds[h * kXs + a0]);
       }
     }
+  };
+  auto multiply = [&](const Operands& p) {
+#pragma unroll
+    for (int h = 0; h < 3; ++h) acc[h] = mfma32(p.a[h], p.b, acc[h]);
+  };
+  // the reads of a step one step ahead of its products
+  auto compute = [&] {
+    constexpr int kMine = (kSteps + kKs - 1) / kKs;
+    Operands p[2];
+    fetch(min(ks, kSteps - 1), p[0]);
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      // a step past the last repeats it and is not multiplied
+      if (i + 1 < kMine) fetch(min(ks + kKs * (i + 1), kSteps - 1), p[(i + 1) & 1]);
+      if (kSteps % kKs == 0 || i < kMine - 1 || ks + kKs * i < kSteps) multiply(p[i & 1]);
+    }
+  };
+  if constexpr (kKs == 1) {
+    Chunk c;
+    load(0, c);
+    for (int ch = 0; ch < A.nchunk; ++ch) {
+      if (ch > 0) __syncthreads();   // the previous chunk's reads are done
+      stage(ch, c);
+      __syncthreads();
+      if (ch + 1 < A.nchunk) load(ch + 1, c);
+      compute();
+    }
+  } else {
+    Chunk c0, c1;
+    load(0, c0);
+    if (A.nchunk > 1) load(1, c1);
+    for (int ch = 0; ch < A.nchunk; ch += 2) {
+      if (ch > 0) __syncthreads();
+      stage(ch, c0);
+      __syncthreads();
+      if (ch + 2 < A.nchunk) load(ch + 2, c0);
+      compute();
+      if (ch + 1 >= A.nchunk) break;
+      __syncthreads();
+      stage(ch + 1, c1);
+      __syncthreads();
+      if (ch + 3 < A.nchunk) load(ch + 3, c1);
+      compute();
+    }
+  }
+  f32x4 sum = (acc[2] + acc[1]) + acc[0];
+  if constexpr (kKs > 1) {
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+    __syncthreads();
+    if (ks > 0) red[((ks - 1) * 4 + w) * 64 + l] = sum;
+    __syncthreads();
+    if (ks == 0)
+#pragma unroll
+      for (int k = 1; k < kKs; ++k) sum += red[((k - 1) * 4 + w) * 64 + l];
   }
   // D[4 kg + j][r16]: voxel (y = kg, x = j) of plane w, channel o0 + r16
-  const int gz = z0 + 1 + w, gy = y0 + 1 + kg, o = o0 + r16;
-  if (gz >= N || gy >= N || o >= Co) return;
-  const float bo = bias ? bias[o] : 0.f;
-  float* yo = y + ((int64_t)b * Co + o) * V + (gz * N + gy) * N;
+  const int gz = z0 + 1 + w, gy = y0 + 1 + kg, gx0 = x0 + 1, o = o0 + r16;
+  const bool in = ks == 0 && gz < N && gy < N && o < Co;
+  const int64_t bo = (int64_t)b * Co + o;
+  const float bias = A.bias && o < Co ? A.bias[o] : 0.f;
+  const int mode = A.mode;
+  const bool relu = mode >= kConvRelu && mode <= kConvReluAdd;
+  f32x4 val;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int gx = x0 + 1 + j;
-    if (gx < N) {
-      const float val = (acc[2][j] + acc[1][j]) + acc[0][j] + bo;
-      yo[gx] = relu ? fmaxf(val, 0.f) : val;
+    val[j] = sum[j] + bias;
+    if (relu) val[j] = fmaxf(val[j], 0.f);
+  }
+  // a lane's four voxels are one row of the brick: 16-byte accesses unless the
+  // grid ends in it (every 4-byte store is a request of its own: 64 per
+  // instruction)
+  auto put = [&](float* p, const f32x4 v, int n) {
+    if (n >= 4)
+      *reinterpret_cast<f32x4u*>(p) = v;
+    else
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (j < n) p[j] = v[j];
+  };
+  auto get = [&](const float* p, int n) {
+    f32x4 v{0.f, 0.f, 0.f, 0.f};
+    if (n >= 4)
+      v = *reinterpret_cast<const f32x4u*>(p);
+    else
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (j < n) v[j] = p[j];
+    return v;
+  };
+  auto masked = [&](const f32x4 e, const f32x4 v) {
+    f32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = e[j] > 0.f ? v[j] : 0.f;
+    return r;
+  };
+  const int nrow = N - gx0;   // voxels of the row in the grid (four at most count)
+  if (mode == kConvExpand) {
+    if (in) {
+      const int F = A.N2;
+      const int nz = 2 * gz + 1 < F ? 2 : 1, ny = 2 * gy + 1 < F ? 2 : 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {   // two coarse voxels, four fine ones
+        const int fx = 2 * gx0 + 4 * h;
+        if (fx >= F) break;
+        f32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          v[j] = val[2 * h + j / 2] /
+                 (float)(nz * ny * (2 * (gx0 + 2 * h + j / 2) + 1 < F ? 2 : 1));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int dz = c >> 1, dy = c & 1;
+          if (dz >= nz || dy >= ny) continue;
+          const int64_t f = ((bo * F + 2 * gz + dz) * F + 2 * gy + dy) * F + fx;
+          put(A.y + f, masked(get(A.e1 + f, F - fx), v + get(A.e2 + f, F - fx)), F - fx);
+        }
+      }
+    }
+  } else if (in && mode != kConvSumMask) {
+    const int64_t at = bo * V + (gz * N + gy) * N + gx0;
+    if (mode == kConvMask) {
+      put(A.y + at, masked(get(A.e1 + at, nrow), val), nrow);
+    } else {
+      put(A.y + at, val, nrow);
+      if (mode == kConvReluAdd) put(A.y2 + at, val + get(A.e1 + at, nrow), nrow);
+      if (mode == kConvMaskTwo) put(A.y2 + at, masked(get(A.e1 + at, nrow), val), nrow);
+    }
+  }
+  if (mode != kConvReluPool && mode != kConvSumMask) return;
+  // 2x2x2 children: x within the lane, y one 16-lane group on, z one wave on
+  float2 c;
+  c.x = (in && gx0 < N ? val[0] : 0.f) + (in && gx0 + 1 < N ? val[1] : 0.f);
+  c.y = (in && gx0 + 2 < N ? val[2] : 0.f) + (in && gx0 + 3 < N ? val[3] : 0.f);
+  c.x += __shfl_xor(c.x, 16, 64);
+  c.y += __shfl_xor(c.y, 16, 64);
+  if (ks == 0 && (w & 1)) pool[w >> 1][l] = c;
+  __syncthreads();
+  if (ks != 0 || (w & 1) || (kg & 1)) return;
+  const float2 up = pool[w >> 1][l];
+  const int H = A.N2, Z = 2 * bz + (w >> 1), Y = 2 * by + (kg >> 1);
+  if (Z >= H || Y >= H || o >= Co) return;
+  const float s2[2] = {c.x + up.x, c.y + up.y};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int X = 2 * bx + j;
+    if (X >= H) break;
+    const int64_t at = ((bo * H + Z) * H + Y) * H + X;
+    if (mode == kConvSumMask) {
+      A.y2[at] = A.e1[at] > 0.f ? s2[j] : 0.f;
+    } else {
+      const int cnt = (2 * Z + 1 < N ? 2 : 1) * (2 * Y + 1 < N ? 2 : 1) * (2 * X + 1 < N ? 2 : 1);
+      A.y2[at] = s2[j] / (float)cnt;
     }
   }
 }
@@ -236,7 +420,7 @@ __global__ void k_pack_conv(const float* __restrict__ w, int Co, int Ci, int tra
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int r = (int)(e / krow), k = (int)(e - (int64_t)r * krow);
-    const int chunk = k / (ksteps * 16), kk = k - chunk * ksteps * 16;
+    const int chunk = k / (ksteps * 32), kk = k - chunk * ksteps * 32;
     const int t = kk / cc, c = chunk * cc + kk % cc;
     float v = 0.f;
     if (t < 27 && c < cin)
@@ -245,286 +429,251 @@ __global__ void k_pack_conv(const float* __restrict__ w, int Co, int Ci, int tra
   }
 }
 
-// Weight gradient gw[o][i][t] = sum_{b,v} g[b][o][v] x[b][i][v + off_t] and
-// gb[o] = sum g[b][o][v], on the matrix cores: rows o, columns the 16
-// input channels i of one chunk per tap, reduction over the voxels of a
-// brick (16 per step: one 4x4 plane), both operands split into two BF16
-// terms and the three products above 2^-16 summed.  Workgroup: input
-// channels 16 blockIdx.x .., output channels 32 blockIdx.y .., a range of
-// bricks (over samples and space) blockIdx.z; wave w owns taps w, w + 4, ..
-// (wave 3 also the bias, as a column of ones).  Each workgroup writes its
-// sums to part[z][o][i][28] (slot 27 of i = 0: bias); k_wgrad_reduce adds
-// the ranges in order (deterministic, no atomics).
-__global__ __launch_bounds__(256, 2) void k_conv3d_wgrad(const float* __restrict__ x, int Ci,
-                                                      const float* __restrict__ g, int Co,
-                                                      int N, int nb, int64_t nbricks,
-                                                      int64_t per, int Cip,
-                                                      float* __restrict__ part) {
-  // input terms by x shift: xs[term][dx][i][row (z, y) of the halo][4]
-  // holds x at halo x = dx .. dx + 3, so each shifted 4-voxel run is one
-  // aligned 8-byte read; rows of 148 values per channel spread the banks
-  constexpr int kXRow = 148;
-  constexpr int kGRow = 68;
-  constexpr int kXItems = 16 * kHaloVox;
-  constexpr int kXIter = (kXItems + 255) / 256;
-  constexpr int kGIter = 32 * 64 / 256;
-  __shared__ __align__(16) uint16_t xs[2][3][16 * kXRow];
-  __shared__ __align__(16) uint16_t gs[2][32 * kGRow];   // [term][o][voxel]
-  const int V = N * N * N, nb3 = nb * nb * nb;
-  const int i0 = blockIdx.x * 16, o0 = blockIdx.y * 32;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, r16 = l & 15, kg = l >> 4;
-  const bool two = o0 + 16 < Co;
-  const bool with_bias = w == 3 && blockIdx.x == 0;
-  f32x4 acc[7][2];
+// Weight gradients gw[o][i][t] = sum_{b,v} g[b][o][v] x[b][i][v + off_t] and
+// gb[o] = sum g[b][o][v] of every layer, on the matrix cores: rows o, columns
+// the 16 input channels i of one tile per tap, reduction over the voxels of a
+// brick (32 per step: two 4x4 planes), both operands split into two BF16 terms
+// and the three products above 2^-16 summed.  A workgroup takes 16 input
+// channels, 16 output channels and a range of bricks (over samples and space) of
+// one layer; wave w the taps of five of the nine (dz, dy), on planes 2 (w % 2) and
+// next.  A lane reads the rows of its channel and shifts them for the three dx.  The sums go to
+// part[range][t][o][i] (slot t = 27 of i = 0: bias); k_wgrad_reduce adds the
+// ranges in order (deterministic, no atomics).
+// Bound by instruction issue (340 vector instructions a wave and brick).  Eight
+// 25^3 grids: 88 us for all layers, 465 us in 15 launches of 16x16x16 products
+// with three shifted copies of x in LDS.
+struct WgradJob {
+  const float *x, *g;
+  int64_t nbricks, per, part;   // bricks, bricks per range, offset of the partials
+  int Ci, Co, N, nb, up;        // up: x is on the grid of (N + 1) / 2
+  int nic, nop, nrange;
+  int wg0, red0;                // first workgroup of the sums and of the reduction
+  int64_t woff, boff;           // of the gradient
+};
+struct WgradJobs {
+  WgradJob j[15];
+};
+
+constexpr int kWgradThreads = 256;
+
+__global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJobs jobs,
+                                                                float* __restrict__ part) {
+  constexpr int kXRow = 148;                      // dwords per channel: 36 rows of 4, pad
+  constexpr int kGRow = 36;                       // dwords per channel: 64 voxels, pad
+  constexpr int kXIter = 8;   // 2 channels of 108 pairs of halo values at a time
+  constexpr int kGIter = 2;   // 8 channels of 32 pairs of voxels at a time
+  constexpr int kXs = 16 * kXRow, kGs = 16 * kGRow;
+  __shared__ __align__(16) uint32_t lds[2][2 * (kXs + kGs)];   // [buffer][x terms, g terms]
+  int id = 0;
+  while (id < 14 && (int)blockIdx.x >= jobs.j[id + 1].wg0) ++id;
+  const WgradJob& J = jobs.j[id];
+  const int local = blockIdx.x - J.wg0;
+  const int ic = local % J.nic, oc = (local / J.nic) % J.nop, range = local / (J.nic * J.nop);
+  const int i0 = ic * 16, o0 = oc * 16, N = J.N, nb = J.nb, Ci = J.Ci, Co = J.Co;
+  const int Ns = J.up ? (N + 1) / 2 : N, V = N * N * N, Vs = Ns * Ns * Ns;
+  const int nx = min(16, Ci - i0), ng = min(16, Co - o0);
+  const int tid = threadIdx.x, l = tid & 63, r16 = l & 15, kg = l >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = w & 1, zy0 = 4 * (w >> 1);   // (dz, dy) pairs zy0 .. zy0 + 4
+  f32x4 acc[16];   // fifteen taps, bias
 #pragma unroll
-  for (int q = 0; q < 7; ++q) acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int64_t lo = (int64_t)blockIdx.z * per;
-  const int64_t hi = lo + per < nbricks ? lo + per : nbricks;
-  // the raw values of one brick, loaded one brick ahead of the compute
-  float xv[kXIter], gv[kGIter];
-  auto load = [&](int64_t bi) {
-    const int b = (int)(bi / nb3), brick = (int)(bi - (int64_t)b * nb3);
-    const int bx = brick % nb, by = (brick / nb) % nb, bz = brick / (nb * nb);
-    const int x0 = 4 * bx - 1, y0 = 4 * by - 1, z0 = 4 * bz - 1;
-    const float* xb = x + (int64_t)b * Ci * V;
+  for (int q = 0; q < 16; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int64_t lo = range * J.per, hi = min(lo + J.per, J.nbricks);
+  // This thread's pair of halo values (the same in every brick and channel):
+  // offset from the brick's corner, position in LDS, and the bits of its
+  // coordinates (z 0-5, y 6-11, x 12-17) among those inside the grid.
+  const int xc = tid / 108, xq = tid - 108 * xc, xrow = xq / 3;
+  const int hz = xrow / 6, hy = xrow - 6 * hz, hx = 2 * (xq - 3 * xrow);
+  const int up = J.up, step = 4 >> up;
+  auto below = [&](int h) { return up ? (h + 1) >> 1 : h; };   // ((h - 1) >> up) + 1
+  const int xoff0 = (below(hz) * Ns + below(hy)) * Ns + below(hx);
+  const int xoff1 = xoff0 - below(hx) + below(hx + 1);
+  const int own = (below(1) * Ns + below(1)) * Ns + below(1);   // the first voxel of the brick
+  const uint32_t need0 = (1u << hz) | (64u << hy) | (4096u << hx);
+  const uint32_t need1 = (1u << hz) | (64u << hy) | (8192u << hx);
+  const int64_t xci = (int64_t)xc * Vs, gco = (int64_t)(tid >> 5) * V;
+  const int xat = xc * kXRow + xrow * 4 + (xq - 3 * xrow);
+  const int gc = tid >> 5, gp = tid & 31;
+  const int pz = gp >> 3, py = (gp >> 1) & 3, px = 2 * (gp & 1);
+  const int goff = (pz * N + py) * N + px;
+  const uint32_t gneed0 = (2u << pz) | (128u << py) | (8192u << px);
+  const uint32_t gneed1 = (2u << pz) | (128u << py) | (16384u << px);
+  const int gat = gc * kGRow + gp;
+  float2 xv[kXIter], gv[kGIter];
+  bool x0in, x1in, g0in, g1in;
+  // brick of the next load, stepped (a division per brick costs as much as its
+  // products)
+  int b, bx, by, bz;
+  {
+    const int64_t nb3 = (int64_t)nb * nb * nb;
+    b = (int)(lo / nb3);
+    const int brick = (int)(lo - b * nb3);
+    bx = brick % nb;
+    by = (brick / nb) % nb;
+    bz = brick / (nb * nb);
+  }
+  auto load = [&] {
+    auto inside = [&](int c) {   // bit h: coordinate 4 c - 1 + h is in the grid
+      return (c == 0 ? 62u : 63u) & ((1u << min(6, N + 1 - 4 * c)) - 1);
+    };
+    const uint32_t in = inside(bz) | (inside(by) << 6) | (inside(bx) << 12);
+    x0in = (in & need0) == need0;
+    x1in = (in & need1) == need1;
+    g0in = (in & gneed0) == gneed0;
+    g1in = (in & gneed1) == gneed1;
+    // from the corner (outside the array for the first bricks: such offsets
+    // are replaced by that of the brick's first voxel)
+    const int64_t corner = ((int64_t)(bz * step - 1) * Ns + by * step - 1) * Ns + bx * step - 1;
+    const float* xb = J.x + ((int64_t)b * Ci + i0) * Vs + corner;
+    // a pair's second channel past the last one repeats the first
+    const float* p0 = xb + (x0in ? xoff0 : own);
+    const float* p1 = xb + (x1in ? xoff1 : own);
 #pragma unroll
     for (int it = 0; it < kXIter; ++it) {
-      const int e = tid + 256 * it;
-      const int i = e / kHaloVox, hv = e - i * kHaloVox;
-      const int hz = hv / 36, hr = hv - 36 * hz, hy = hr / 6, hx = hr - 6 * hy;
-      const int gz = z0 + hz, gy = y0 + hy, gx = x0 + hx;
-      xv[it] = (e < kXItems && i0 + i < Ci && gz >= 0 && gz < N && gy >= 0 && gy < N &&
-                gx >= 0 && gx < N)
-                   ? xb[(int64_t)(i0 + i) * V + (gz * N + gy) * N + gx]
-                   : 0.f;
+      if (2 * it >= nx) break;
+      const int64_t ci = 2 * it + 1 < nx ? xci : 0;
+      xv[it].x = p0[ci];
+      xv[it].y = p1[ci];
+      p0 += 2 * (int64_t)Vs;
+      p1 += 2 * (int64_t)Vs;
     }
-    const float* gb = g + (int64_t)b * Co * V;
+    const float* gb = J.g + ((int64_t)b * Co + o0) * V + ((int64_t)4 * bz * N + 4 * by) * N + 4 * bx;
+    const float* q0 = gb + gco + (g0in ? goff : 0);
+    const float* q1 = gb + gco + (g1in ? goff + 1 : 0);
 #pragma unroll
     for (int it = 0; it < kGIter; ++it) {
-      const int e = tid + 256 * it;
-      const int o = e >> 6, v = e & 63;
-      const int gz = z0 + 1 + (v >> 4), gy = y0 + 1 + ((v >> 2) & 3), gx = x0 + 1 + (v & 3);
-      gv[it] = (o0 + o < Co && gz < N && gy < N && gx < N)
-                   ? gb[(int64_t)(o0 + o) * V + (gz * N + gy) * N + gx]
-                   : 0.f;
+      if (8 * it >= ng) break;
+      const int64_t co = (int64_t)8 * it * V - (8 * it + gc < ng ? 0 : gco);
+      gv[it].x = q0[co];
+      gv[it].y = q1[co];
+    }
+    if (++bx == nb) {
+      bx = 0;
+      if (++by == nb) {
+        by = 0;
+        if (++bz == nb) {
+          bz = 0;
+          ++b;
+        }
+      }
     }
   };
-  if (lo < hi) load(lo);
+  auto put = [&](uint32_t* p0, uint32_t* p1, float a, float b) {
+    uint32_t h[2];
+    split_bf16(a, b, h);
+    *p0 = h[0];
+    *p1 = h[1];
+  };
+  if (lo < hi) load();
   for (int64_t bi = lo; bi < hi; ++bi) {
-    __syncthreads();   // the previous brick's reads are done
+    uint32_t* xs = lds[(bi - lo) & 1];
+    uint32_t* gs = xs + 2 * kXs;
 #pragma unroll
     for (int it = 0; it < kXIter; ++it) {
-      const int e = tid + 256 * it;
-      if (e >= kXItems) continue;
-      const int i = e / kHaloVox, hv = e - i * kHaloVox;
-      const int hz = hv / 36, hr = hv - 36 * hz, hy = hr / 6, hx = hr - 6 * hy;
-      uint16_t h0, h1;
-      split2(xv[it], h0, h1);
-      const int base = i * kXRow + (hz * 6 + hy) * 4 + hx;
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const int xq = hx - dx;
-        if (xq >= 0 && xq < 4) {
-          xs[0][dx][base - dx] = h0;
-          xs[1][dx][base - dx] = h1;
-        }
-      }
+      if (2 * it >= nx) break;
+      const int at = xat + 2 * it * kXRow;
+      if (xc < 2 && 2 * it + xc < nx)
+        put(&xs[at], &xs[kXs + at], x0in ? xv[it].x : 0.f, x1in ? xv[it].y : 0.f);
     }
 #pragma unroll
     for (int it = 0; it < kGIter; ++it) {
-      const int e = tid + 256 * it;
-      const int o = e >> 6, v = e & 63;
-      uint16_t h0, h1;
-      split2(gv[it], h0, h1);
-      gs[0][o * kGRow + v] = h0;
-      gs[1][o * kGRow + v] = h1;
+      if (8 * it >= ng) break;
+      const int at = gat + 8 * it * kGRow;
+      if (8 * it + gc < ng)
+        put(&gs[at], &gs[kGs + at], g0in ? gv[it].x : 0.f, g1in ? gv[it].y : 0.f);
     }
+    // one barrier per brick: the next brick goes to the other buffer, whose
+    // readers passed this barrier's predecessor
     __syncthreads();
-    if (bi + 1 < hi) load(bi + 1);   // in flight during the products below
-#pragma unroll 1
-    for (int pz = 0; pz < 4; ++pz) {
-      // A: g[o][voxels (y = kg, x = 0..3) of plane pz]
-      const int ga = r16 * kGRow + 16 * pz + 4 * kg;
-      const bf16x4 g0a = *reinterpret_cast<const bf16x4*>(&gs[0][ga]);
-      const bf16x4 g1a = *reinterpret_cast<const bf16x4*>(&gs[1][ga]);
-      const bf16x4 g0b = *reinterpret_cast<const bf16x4*>(&gs[0][ga + 16 * kGRow]);
-      const bf16x4 g1b = *reinterpret_cast<const bf16x4*>(&gs[1][ga + 16 * kGRow]);
+    if (bi + 1 < hi) load();   // in flight during the products below
+    // A: g[o][voxels 32 half + 8 kg ..]: plane 2 half + kg / 2, rows 2 (kg % 2)
+    // and next; B: the same voxels of x, shifted by the tap
+    const int ga = r16 * kGRow + 16 * half + 4 * kg;
+    const int xa = r16 * kXRow + ((2 * half + (kg >> 1)) * 6 + 2 * (kg & 1)) * 4;
+    const uint4 g0 = *reinterpret_cast<const uint4*>(&gs[ga]);
+    const uint4 g1 = *reinterpret_cast<const uint4*>(&gs[kGs + ga]);
+    const uint4 ones{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};   // BF16 1.0
+    acc[15] = mfma32(g1, ones, acc[15]);
+    acc[15] = mfma32(g0, ones, acc[15]);
 #pragma unroll
-      for (int q = 0; q < 7; ++q) {
-        const int t = w + 4 * q;
-        if (t < 27) {
-          const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-          const int xa = r16 * kXRow + ((pz + dz) * 6 + kg + dy) * 4;
-          const bf16x4 x0v = *reinterpret_cast<const bf16x4*>(&xs[0][dx][xa]);
-          const bf16x4 x1v = *reinterpret_cast<const bf16x4*>(&xs[1][dx][xa]);
-          acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g1a, x0v, acc[q][0], 0, 0, 0);
-          acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0a, x1v, acc[q][0], 0, 0, 0);
-          acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0a, x0v, acc[q][0], 0, 0, 0);
-          if (two) {
-            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g1b, x0v, acc[q][1], 0, 0, 0);
-            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0b, x1v, acc[q][1], 0, 0, 0);
-            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0b, x0v, acc[q][1], 0, 0, 0);
-          }
-        } else if (with_bias) {
-          const short one = (short)0x3f80;   // BF16 1.0
-          const bf16x4 ones = {one, one, one, one};
-          acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g1a, ones, acc[q][0], 0, 0, 0);
-          acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0a, ones, acc[q][0], 0, 0, 0);
-          if (two) {
-            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g1b, ones, acc[q][1], 0, 0, 0);
-            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(g0b, ones, acc[q][1], 0, 0, 0);
-          }
-        }
+    for (int i = 0; i < 5; ++i) {
+      const int dz = (zy0 + i) / 3, dy = zy0 + i - 3 * dz;   // wave-uniform
+      const uint32_t* p = &xs[xa + (dz * 6 + dy) * 4];
+      uint4 xt[2][3];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint4 a = *reinterpret_cast<const uint4*>(p + h * kXs);
+        const uint4 b = *reinterpret_cast<const uint4*>(p + h * kXs + 4);
+        xt[h][0] = uint4{a.x, a.y, b.x, b.y};
+        xt[h][1] = uint4{__builtin_amdgcn_alignbit(a.y, a.x, 16),
+                         __builtin_amdgcn_alignbit(a.z, a.y, 16),
+                         __builtin_amdgcn_alignbit(b.y, b.x, 16),
+                         __builtin_amdgcn_alignbit(b.z, b.y, 16)};
+        xt[h][2] = uint4{a.y, a.z, b.y, b.z};
       }
+      // the three products of a tap go to the same sums: three taps interleaved
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+          acc[3 * i + dx] = mfma32(k == 0 ? g1 : g0, xt[k == 1][dx], acc[3 * i + dx]);
+      __builtin_amdgcn_sched_barrier(0);   // reads hoisted further spill registers
     }
   }
-  // D[4 kg + j][r16]: output channel o0 + 16 ct + 4 kg + j, input channel
-  // i0 + r16
-  float* pz = part + (int64_t)blockIdx.z * Co * Cip * 28;
+  // the two plane pairs added
+  f32x4* red = reinterpret_cast<f32x4*>(&lds[0][0]);
+  static_assert(2 * 16 * 64 * sizeof(f32x4) <= sizeof(lds), "sums of two waves");
+  __syncthreads();
+  if (half == 1)
 #pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    const int t = w + 4 * q;
-    if (t >= 27 && !with_bias) continue;
-    if (t >= 27 && r16 != 0) continue;
-    const int tt = t < 27 ? t : 27;
+    for (int q = 0; q < 16; ++q) red[((w >> 1) * 16 + q) * 64 + l] = acc[q];
+  __syncthreads();
+  if (half != 0) return;
+  // D[4 kg + j][r16]: output channel o0 + 4 kg + j, input channel i0 + r16; the
+  // second pair of waves leaves out the taps it shares with the first
+  float* out = part + J.part + (int64_t)range * 28 * Co * Ci;
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
+  for (int q = 0; q < 16; ++q) {
+    const f32x4 v = acc[q] + red[((w >> 1) * 16 + q) * 64 + l];
+    const int t = q < 15 ? 3 * zy0 + q : 27;
+    if (q < 3 && zy0 != 0) continue;
+    if (q == 15 && (zy0 != 0 || ic != 0 || r16 != 0)) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int o = o0 + 16 * ct + 4 * kg + j;
-        if (o < Co && (ct == 0 || two))
-          pz[((int64_t)o * Cip + i0 + r16) * 28 + tt] = acc[q][ct][j];
-      }
+    for (int j = 0; j < 4; ++j) {
+      const int o = o0 + 4 * kg + j;
+      if (o < Co && i0 + r16 < Ci) out[((int64_t)t * Co + o) * Ci + i0 + r16] = v[j];
     }
   }
 }
 
-// gw[o][i][t] and gb[o] from the per-range sums: 16 outputs per workgroup
-// of 256 threads, thread (slice, output) adds ranges slice, slice + 16, ..
-// in order, then the 16 slice sums are added in order (deterministic).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int Ci,
-                                                      int Co, int Cip, int nrange,
-                                                      float* __restrict__ gw,
-                                                      float* __restrict__ gb) {
-  __shared__ float sums[16][17];
-  const int lane = threadIdx.x & 15, slice = threadIdx.x >> 4;
-  const int64_t e = (int64_t)blockIdx.x * 16 + lane;
-  const int64_t nout = (int64_t)Co * Ci * 28;
-  int o = 0, i = 0, t = 0;
+// gw[o][i][t] and gb[o] of every layer from the per-range sums: 32 outputs per
+// workgroup of 256 threads, thread (slice, output) adds ranges slice, slice + 8,
+// .. in order, then the 8 slice sums are added in order (deterministic).
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const WgradJobs jobs,
+                                                      const float* __restrict__ part,
+                                                      float* __restrict__ g) {
+  __shared__ float sums[8][33];
+  int id = 0;
+  while (id < 14 && (int)blockIdx.x >= jobs.j[id + 1].red0) ++id;
+  const WgradJob& J = jobs.j[id];
+  const int lane = threadIdx.x & 31, slice = threadIdx.x >> 5;
+  const int64_t e = (int64_t)(blockIdx.x - J.red0) * 32 + lane;
+  const int64_t per = (int64_t)J.Co * J.Ci, nout = 28 * per;
+  const int t = (int)(e / per), oi = (int)(e - t * per), o = oi / J.Ci, i = oi - o * J.Ci;
+  const bool on = e < nout && (t < 27 || i == 0);
   float s = 0.f;
-  if (e < nout) {
-    o = (int)(e / (Ci * 28));
-    const int r = (int)(e - (int64_t)o * Ci * 28);
-    i = r / 28;
-    t = r - 28 * i;
-    const int64_t stride = (int64_t)Co * Cip * 28;
-    const float* p = part + ((int64_t)o * Cip + i) * 28 + t;
-    for (int c = slice; c < nrange; c += 16) s += p[c * stride];
+  if (on) {
+    const float* p = part + J.part + e;
+#pragma unroll 4
+    for (int c = slice; c < J.nrange; c += 8) s += p[c * nout];
   }
   sums[slice][lane] = s;
   __syncthreads();
-  if (slice != 0 || e >= nout || (t == 27 && i != 0)) return;
+  if (slice != 0 || !on) return;
   float tot = 0.f;
-  for (int k = 0; k < 16; ++k) tot += sums[k][lane];
-  if (t < 27) gw[((int64_t)o * Ci + i) * 27 + t] = tot;
-  else gb[o] = tot;
-}
-
-// average over the existing children: (D,H,W) -> ceil halves
-__global__ void k_pool(const float* __restrict__ x, float* __restrict__ y, int BC, int D, int H,
-                       int Wd) {
-  const int d = (D + 1) / 2, h = (H + 1) / 2, w = (Wd + 1) / 2;
-  const int64_t total = (int64_t)BC * d * h * w;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t bc = t / ((int64_t)d * h * w);
-    const int rem = (int)(t % ((int64_t)d * h * w));
-    const int X = rem % w, Y = (rem / w) % h, Z = rem / (w * h);
-    float s = 0.f;
-    int cnt = 0;
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b)
-        for (int c = 0; c < 2; ++c) {
-          const int z = 2 * Z + a, yy = 2 * Y + b, xx = 2 * X + c;
-          if (z < D && yy < H && xx < Wd) {
-            s += x[bc * D * H * Wd + ((int64_t)z * H + yy) * Wd + xx];
-            ++cnt;
-          }
-        }
-    y[t] = s / (float)cnt;
-  }
-}
-
-__global__ void k_pool_bwd(const float* __restrict__ gy, float* __restrict__ gx, int BC, int D,
-                           int H, int Wd) {
-  const int d = (D + 1) / 2, h = (H + 1) / 2, w = (Wd + 1) / 2;
-  const int64_t total = (int64_t)BC * D * H * Wd;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t bc = t / ((int64_t)D * H * Wd);
-    const int rem = (int)(t % ((int64_t)D * H * Wd));
-    const int xx = rem % Wd, yy = (rem / Wd) % H, z = rem / (Wd * H);
-    const int X = xx / 2, Y = yy / 2, Z = z / 2;
-    const int cz = (2 * Z + 1 < D) ? 2 : 1, cy = (2 * Y + 1 < H) ? 2 : 1, cx = (2 * X + 1 < Wd) ? 2 : 1;
-    gx[t] = gy[bc * d * h * w + ((int64_t)Z * h + Y) * w + X] / (float)(cz * cy * cx);
-  }
-}
-
-// nearest upsampling (d,h,w) -> (D,H,W): y[i] = x[i/2]; with accumulate
-// into y (mode 1) for the additive use
-__global__ void k_upsample(const float* __restrict__ x, float* __restrict__ y, int BC, int D,
-                           int H, int Wd) {
-  const int d = (D + 1) / 2, h = (H + 1) / 2, w = (Wd + 1) / 2;
-  const int64_t total = (int64_t)BC * D * H * Wd;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t bc = t / ((int64_t)D * H * Wd);
-    const int rem = (int)(t % ((int64_t)D * H * Wd));
-    const int xx = rem % Wd, yy = (rem / Wd) % H, z = rem / (Wd * H);
-    y[t] = x[bc * d * h * w + ((int64_t)(z / 2) * h + yy / 2) * w + xx / 2];
-  }
-}
-
-__global__ void k_upsample_bwd(const float* __restrict__ gy, float* __restrict__ gx, int BC,
-                               int D, int H, int Wd) {
-  const int d = (D + 1) / 2, h = (H + 1) / 2, w = (Wd + 1) / 2;
-  const int64_t total = (int64_t)BC * d * h * w;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t bc = t / ((int64_t)d * h * w);
-    const int rem = (int)(t % ((int64_t)d * h * w));
-    const int X = rem % w, Y = (rem / w) % h, Z = rem / (w * h);
-    float s = 0.f;
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b)
-        for (int c = 0; c < 2; ++c) {
-          const int z = 2 * Z + a, yy = 2 * Y + b, xx = 2 * X + c;
-          if (z < D && yy < H && xx < Wd) s += gy[bc * D * H * Wd + ((int64_t)z * H + yy) * Wd + xx];
-        }
-    gx[t] = s;
-  }
-}
-
-// a = a + b
-__global__ void k_add(float* __restrict__ a, const float* __restrict__ b, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    a[i] += b[i];
-}
-
-// c = a + b
-__global__ void k_add3(float* __restrict__ c, const float* __restrict__ a,
-                       const float* __restrict__ b, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    c[i] = a[i] + b[i];
-}
-
-// g *= (act > 0)
-__global__ void k_relu_mask(float* __restrict__ g, const float* __restrict__ act, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    if (!(act[i] > 0.f)) g[i] = 0.f;
+  for (int k = 0; k < 8; ++k) tot += sums[k][lane];
+  if (t < 27) g[J.woff + (int64_t)oi * 27 + t] = tot;
+  else g[J.boff + o] = tot;
 }
 
 // mean squared error: per-workgroup partial sums and g = 2 (y - t) / n
@@ -599,102 +748,125 @@ int64_t net_param_count(const int32_t* c, int32_t in_channels) {
   return n.nparam;
 }
 
-// One workgroup per 4^3 brick and 16 output channels; cin input channels
-// with weights packed for that width.
-static hipError_t launch_conv(const float* x, int cin, const uint16_t* W, const float* bias,
-                              float* y, int cout, int N, int B, int relu, hipStream_t s) {
-  const ConvK k = conv_k(cin);
-  const int nb = (N + 3) / 4;
-  dim3 g((unsigned)(nb * nb * nb), (unsigned)((cout + 15) / 16), (unsigned)B);
-  if (k.cc == 4)
-    hipLaunchKernelGGL(k_conv3d<4>, g, dim3(256), 0, s, x, cin, k.nchunk, W, k.krow, bias, y,
-                       cout, N, nb, relu);
-  else if (k.cc == 8)
-    hipLaunchKernelGGL(k_conv3d<8>, g, dim3(256), 0, s, x, cin, k.nchunk, W, k.krow, bias, y,
-                       cout, N, nb, relu);
-  else
-    hipLaunchKernelGGL(k_conv3d<16>, g, dim3(256), 0, s, x, cin, k.nchunk, W, k.krow, bias, y,
-                       cout, N, nb, relu);
+// One workgroup per 4^3 brick and 16 output channels, of 16 waves where there are
+// fewer than kSplitBelow of them: 27 bricks of 32 channels take 7 us instead of
+// 10.5, while 512 bricks of eight 13^3 grids take 15 instead of 12.5 (two
+// workgroups of 16 waves fit a compute unit, three to four of four waves).
+constexpr int64_t kSplitBelow = 512;
+
+static hipError_t launch_conv(ConvArgs a, int B, hipStream_t s) {
+  const ConvK k = conv_k(a.Ci);
+  a.nchunk = k.nchunk;
+  a.krow = k.krow;
+  a.nb = (a.N + 3) / 4;
+  a.dnb = make_fastdiv((uint32_t)a.nb);
+  const dim3 g((unsigned)(a.nb * a.nb * a.nb), (unsigned)((a.Co + 15) / 16), (unsigned)B);
+  const bool split = (int64_t)g.x * g.y * g.z < kSplitBelow;
+#define FC_CONV(CC)                                                       \
+  if (split)                                                              \
+    hipLaunchKernelGGL((k_conv3d<CC, 4>), g, dim3(1024), 0, s, a);        \
+  else                                                                    \
+    hipLaunchKernelGGL((k_conv3d<CC, 1>), g, dim3(256), 0, s, a);
+  if (k.cc == 4) {
+    FC_CONV(4)
+  } else if (k.cc == 8) {
+    FC_CONV(8)
+  } else {
+    FC_CONV(16)
+  }
+#undef FC_CONV
   return hipGetLastError();
 }
 
-static hipError_t conv_fwd(const Net& net, int l, const float* x, float* y, int B, int N, bool relu,
-                           hipStream_t s) {
-  return launch_conv(x, net.ci[l], net.wpk + net.wfoff[l], net.p + net.boff[l], y, net.co[l], N,
-                     B, relu ? 1 : 0, s);
+// layer l on x, or with trans the gradient of its input from that of its output
+static ConvArgs conv_args(const Net& net, int l, bool trans, const float* x, float* y, int N,
+                          int mode) {
+  ConvArgs a{};
+  a.x = x;
+  a.W = net.wpk + (trans ? net.wtoff[l] : net.wfoff[l]);
+  a.bias = trans ? nullptr : net.p + net.boff[l];
+  a.y = y;
+  a.Ci = trans ? net.co[l] : net.ci[l];
+  a.Co = trans ? net.ci[l] : net.co[l];
+  a.N = N;
+  a.mode = mode;
+  return a;
 }
 
-// data gradient of layer l: gx (Ci channels) from gy (Co channels)
-static hipError_t conv_bwd_data(const Net& net, int l, const float* gy, float* gx, int B, int N,
-                                hipStream_t s) {
-  return launch_conv(gy, net.co[l], net.wpk + net.wtoff[l], nullptr, gx, net.ci[l], N, B, 0, s);
-}
+// Partials of the weight gradients for batch B: sizes and first workgroups of
+// every layer's ranges.  About kWgradWgs workgroups in all, each with the same
+// number of bricks, so the last one to start is as short as the others.
+constexpr int64_t kWgradWgs = 1480;
+constexpr int64_t kWgradRanges = 512;   // of a layer, at most
 
-static int64_t wgrad_row_floats(int Ci, int Co) {
-  return (int64_t)Co * ((Ci + 15) / 16 * 16) * 28;
-}
+struct WgradPlan {
+  WgradJobs jobs;
+  int64_t wgs = 0, red = 0, floats = 0;
+};
 
-// brick ranges of a weight-gradient launch: about 1024 workgroups
-static int64_t wgrad_max_ranges(int Ci, int Co) {
-  const int64_t tiles = (int64_t)((Ci + 15) / 16) * ((Co + 31) / 32);
-  return std::min<int64_t>(kWgradRanges, std::max<int64_t>(1, 1024 / tiles));
-}
-
-static hipError_t conv_bwd_weight(Net& net, NetWs& ws, int l, const float* x, const float* gy,
-                                  int B, int N, hipStream_t s) {
-  const int Ci = net.ci[l], Co = net.co[l];
-  const int nb = (N + 3) / 4;
-  const int64_t nbricks = (int64_t)B * nb * nb * nb;
-  const int nic = (Ci + 15) / 16, nop = (Co + 31) / 32;
-  int64_t nrange = std::min<int64_t>(wgrad_max_ranges(Ci, Co), nbricks);
-  const int64_t per = (nbricks + nrange - 1) / nrange;
-  nrange = (nbricks + per - 1) / per;
-  dim3 g((unsigned)nic, (unsigned)nop, (unsigned)nrange);
-  hipLaunchKernelGGL(k_conv3d_wgrad, g, dim3(256), 0, s, x, Ci, gy, Co, N, nb, nbricks, per,
-                     nic * 16, ws.wpart);
-  const int64_t nt = (int64_t)Co * Ci * 28;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nt + 15) / 16)), dim3(256), 0, s, ws.wpart,
-                     Ci, Co, nic * 16, (int)nrange, net.g + net.woff[l], net.g + net.boff[l]);
-  return hipGetLastError();
+static WgradPlan wgrad_plan(const Net& net, const int* N, int B) {
+  WgradPlan P{};
+  static const int level[15] = {0, 0, 1, 1, 2, 2, 3, 3, 2, 2, 1, 1, 0, 0, 0};
+  int64_t total = 0;
+  for (int l = 0; l < 15; ++l) {
+    WgradJob& J = P.jobs.j[l];
+    J.Ci = net.ci[l];
+    J.Co = net.co[l];
+    J.N = N[level[l]];
+    J.nb = (J.N + 3) / 4;
+    J.up = l == 8 || l == 10 || l == 12;
+    J.nic = (J.Ci + 15) / 16;
+    J.nop = (J.Co + 15) / 16;
+    J.nbricks = (int64_t)B * J.nb * J.nb * J.nb;
+    J.woff = net.woff[l];
+    J.boff = net.boff[l];
+    total += J.nbricks * J.nic * J.nop;
+  }
+  for (int l = 0; l < 15; ++l) {
+    WgradJob& J = P.jobs.j[l];
+    J.per = std::max((total + kWgradWgs - 1) / kWgradWgs,
+                     (J.nbricks + kWgradRanges - 1) / kWgradRanges);
+    J.nrange = (int)((J.nbricks + J.per - 1) / J.per);
+    const int64_t nout = (int64_t)28 * J.Co * J.Ci;
+    J.part = P.floats;
+    J.wg0 = (int)P.wgs;
+    J.red0 = (int)P.red;
+    P.floats += J.nrange * nout;
+    P.wgs += (int64_t)J.nrange * J.nic * J.nop;
+    P.red += (nout + 31) / 32;
+  }
+  return P;
 }
 
 fc_status NetWs::ensure(const Net& net, int B_, int N0) {
   if (B_ <= capB && N0 == N[0] && buf) return FC_OK;
   release();
   B = B_;
-  capB = B_;
   N[0] = N0;
   for (int l = 1; l < 4; ++l) N[l] = (N[l - 1] + 1) / 2;
-  // per-level tensor sizes (max channels of that level) for every saved
-  // activation and two gradient scratch tensors per level
   int64_t total = 0;
-  auto vox = [&](int l) { return (int64_t)N[l] * N[l] * N[l]; };
-  for (int l = 0; l < 4; ++l) {
-    // widths present at level l: its own, the pooled input from above (or
-    // the network input) and the upsampled tensor from below
-    int64_t cmax = net.ch[l];
-    cmax = std::max<int64_t>(cmax, l == 0 ? net.in_ch : net.ch[l - 1]);
-    if (l < 3) cmax = std::max<int64_t>(cmax, net.ch[l + 1]);
+  for (int l = 0; l < 4; ++l)
     for (int k = 0; k < kSlots; ++k) {
+      // every tensor of a level has its width; the pooled input the one above
+      const int64_t width = k == kIn && l > 0 ? net.ch[l - 1] : net.ch[l];
       off[l][k] = total;
-      total += (int64_t)B * cmax * vox(l);
+      if (k == kIn ? l > 0 : l < 3 || k == kA || k == kB || k == kGa || k == kGb)
+        total += (int64_t)B * width * vox(l);
     }
-  }
   off_y = total;
   total += 2 * (int64_t)B * vox(0);   // output and its gradient
+  // a smaller batch may be cut into more ranges of some layers
+  wslots = 0;
+  for (int b = 1; b <= B; ++b) wslots = std::max(wslots, wgrad_plan(net, N, b).floats);
   hipError_t e = hipMalloc(&buf, total * sizeof(float));
+  if (e == hipSuccess) e = hipMalloc(&partial, 1024 * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc(&wpart, (size_t)wslots * sizeof(float));
   if (e != hipSuccess) {
-    buf = nullptr;
+    release();
     set_error("network workspace allocation failed");
     return FC_E_NOMEM;
   }
-  if (hipMalloc(&partial, 1024 * sizeof(double)) != hipSuccess) return FC_E_NOMEM;
-  // weight-gradient partials of the largest layer
-  wslots = 0;
-  for (int l = 0; l < 15; ++l)
-    wslots = std::max<int64_t>(wslots, wgrad_max_ranges(net.ci[l], net.co[l]) *
-                                           wgrad_row_floats(net.ci[l], net.co[l]));
-  if (hipMalloc(&wpart, (size_t)wslots * sizeof(float)) != hipSuccess) return FC_E_NOMEM;
+  capB = B_;
   return FC_OK;
 }
 
@@ -708,112 +880,88 @@ void NetWs::release() {
   capB = 0;
 }
 
-// slots per level: 0 in, 1 a, 2 b (skip), 3 u (up), 4 da, 5 m, 6 db,
-// 7, 8 gradient scratch
-hipError_t net_forward(const Net& net, NetWs& ws, const float* x, int B, hipStream_t s) {
+hipError_t net_forward(const Net& net, NetWs& ws, const float* x, float* y, int B, hipStream_t s) {
   const int* N = ws.N;
   hipError_t e;
   const float* in = x;
-  for (int l = 0; l < 3; ++l) {
-    float* a = ws.t(l, 1);
-    float* b = ws.t(l, 2);
-    if ((e = conv_fwd(net, 2 * l, in, a, B, N[l], true, s)) != hipSuccess) return e;
-    if ((e = conv_fwd(net, 2 * l + 1, a, b, B, N[l], true, s)) != hipSuccess) return e;
-    float* nxt = ws.t(l + 1, 0);
-    const int64_t bc = (int64_t)B * net.ch[l];
-    hipLaunchKernelGGL(k_pool, grid1(bc * ws.vox(l + 1)), dim3(256), 0, s, b, nxt, (int)bc, N[l],
-                       N[l], N[l]);
-    in = nxt;
+  for (int l = 0; l < 4; ++l) {
+    float *a = ws.t(l, kA), *b = ws.t(l, kB);
+    if ((e = launch_conv(conv_args(net, 2 * l, false, in, a, N[l], kConvRelu), B, s)) != hipSuccess)
+      return e;
+    ConvArgs c = conv_args(net, 2 * l + 1, false, a, b, N[l], l < 3 ? kConvReluPool : kConvRelu);
+    if (l < 3) {
+      c.y2 = ws.t(l + 1, kIn);
+      c.N2 = N[l + 1];
+      in = c.y2;
+    }
+    if ((e = launch_conv(c, B, s)) != hipSuccess) return e;
   }
-  if ((e = conv_fwd(net, 6, in, ws.t(3, 1), B, N[3], true, s)) != hipSuccess) return e;
-  if ((e = conv_fwd(net, 7, ws.t(3, 1), ws.t(3, 2), B, N[3], true, s)) != hipSuccess) return e;
-  const float* h = ws.t(3, 2);
-  int hc = net.ch[3];
+  const float* h = ws.t(3, kB);
   for (int l = 2; l >= 0; --l) {
-    float* u = ws.t(l, 3);
-    const int64_t bc = (int64_t)B * hc;
-    hipLaunchKernelGGL(k_upsample, grid1(bc * ws.vox(l)), dim3(256), 0, s, h, u, (int)bc, N[l],
-                       N[l], N[l]);
     const int la = 8 + 2 * (2 - l), lb = la + 1;
-    float* da = ws.t(l, 4);
-    if ((e = conv_fwd(net, la, u, da, B, N[l], true, s)) != hipSuccess) return e;
-    float* m = ws.t(l, 5);
-    const int64_t n = (int64_t)B * net.ch[l] * ws.vox(l);
-    hipLaunchKernelGGL(k_add3, grid1(n), dim3(256), 0, s, m, da, ws.t(l, 2), n);
-    float* db = ws.t(l, 6);
-    if ((e = conv_fwd(net, lb, m, db, B, N[l], true, s)) != hipSuccess) return e;
-    h = db;
-    hc = net.ch[l];
+    ConvArgs c = conv_args(net, la, false, h, ws.t(l, kDa), N[l], kConvReluAdd);
+    c.up = 1;
+    c.e1 = ws.t(l, kB);
+    c.y2 = ws.t(l, kM);
+    if ((e = launch_conv(c, B, s)) != hipSuccess) return e;
+    if ((e = launch_conv(conv_args(net, lb, false, ws.t(l, kM), ws.t(l, kDb), N[l], kConvRelu), B,
+                         s)) != hipSuccess)
+      return e;
+    h = ws.t(l, kDb);
   }
-  return conv_fwd(net, 14, h, ws.y(), B, N[0], false, s);
+  return launch_conv(conv_args(net, 14, false, h, y, N[0], kConvPlain), B, s);
 }
 
-// Backward from gy (B,1,N0^3) into net.g (parameters); x is the input.
+// Backward from gy (B,1,N0^3) into net.g (parameters); x is the input.  The
+// gradients of the tensors first, then those of all weights from them.
 hipError_t net_backward(Net& net, NetWs& ws, const float* x, float* gy, int B, hipStream_t s) {
   const int* N = ws.N;
   hipError_t e;
-  // head
-  float* g = ws.t(0, 7);
-  if ((e = conv_bwd_weight(net, ws, 14, ws.t(0, 6), gy, B, N[0], s)) != hipSuccess) return e;
-  if ((e = conv_bwd_data(net, 14, gy, g, B, N[0], s)) != hipSuccess) return e;
-  std::vector<float*> gskip(3, nullptr);
-  int gc = net.ch[0];
+  WgradPlan P = wgrad_plan(net, N, B);
+  auto weights = [&](int l, const float* xin, const float* g) {
+    P.jobs.j[l].x = xin;
+    P.jobs.j[l].g = g;
+  };
+  // data gradient of layer l on grid n
+  auto data = [&](int l, const float* g, float* y, int n, int mode, const float* e1,
+                  float* y2 = nullptr, const float* e2 = nullptr, int N2 = 0) {
+    ConvArgs c = conv_args(net, l, true, g, y, n, mode);
+    c.e1 = e1;
+    c.e2 = e2;
+    c.y2 = y2;
+    c.N2 = N2;
+    return launch_conv(c, B, s);
+  };
+  weights(14, ws.t(0, kDb), gy);
+  if ((e = data(14, gy, ws.t(0, kGdb), N[0], kConvMask, ws.t(0, kDb))) != hipSuccess) return e;
   for (int l = 0; l < 3; ++l) {
     const int la = 8 + 2 * (2 - l), lb = la + 1;
-    const int64_t n = (int64_t)B * net.ch[l] * ws.vox(l);
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, g, ws.t(l, 6), n);
-    if ((e = conv_bwd_weight(net, ws, lb, ws.t(l, 5), g, B, N[l], s)) != hipSuccess) return e;
-    float* gm = ws.t(l, 8);
-    if ((e = conv_bwd_data(net, lb, g, gm, B, N[l], s)) != hipSuccess) return e;
-    // gm flows to the skip (kept in slot 8) and to da
-    float* gda = ws.t(l, 7);
-    (void)hipMemcpyAsync(gda, gm, n * sizeof(float), hipMemcpyDeviceToDevice, s);
-    gskip[l] = gm;
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, gda, ws.t(l, 4), n);
-    if ((e = conv_bwd_weight(net, ws, la, ws.t(l, 3), gda, B, N[l], s)) != hipSuccess) return e;
-    // data gradient of up_a lands on the upsampled tensor (Ci = width below)
-    float* gu = ws.t(l, 3);   // the upsampled input is no longer needed
-    if ((e = conv_bwd_data(net, la, gda, gu, B, N[l], s)) != hipSuccess) return e;
-    const int cbelow = net.ci[la];
-    float* gnext = ws.t(l + 1, 7);
-    const int64_t bc = (int64_t)B * cbelow;
-    hipLaunchKernelGGL(k_upsample_bwd, grid1(bc * ws.vox(l + 1)), dim3(256), 0, s, gu, gnext,
-                       (int)bc, N[l], N[l], N[l]);
-    g = gnext;
-    gc = cbelow;
+    const float* below = l < 2 ? ws.t(l + 1, kDb) : ws.t(3, kB);
+    float* gbelow = l < 2 ? ws.t(l + 1, kGdb) : ws.t(3, kGb);
+    weights(lb, ws.t(l, kM), ws.t(l, kGdb));
+    // the gradient flows to the skip (kGm) and, masked, to the decoder (kGda)
+    if ((e = data(lb, ws.t(l, kGdb), ws.t(l, kGm), N[l], kConvMaskTwo, ws.t(l, kDa),
+                  ws.t(l, kGda))) != hipSuccess)
+      return e;
+    weights(la, below, ws.t(l, kGda));
+    if ((e = data(la, ws.t(l, kGda), nullptr, N[l], kConvSumMask, below, gbelow, nullptr,
+                  N[l + 1])) != hipSuccess)
+      return e;
   }
-  (void)gc;
-  // bottom
-  {
-    const int64_t n = (int64_t)B * net.ch[3] * ws.vox(3);
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, g, ws.t(3, 2), n);
-    if ((e = conv_bwd_weight(net, ws, 7, ws.t(3, 1), g, B, N[3], s)) != hipSuccess) return e;
-    float* g2 = ws.t(3, 8);
-    if ((e = conv_bwd_data(net, 7, g, g2, B, N[3], s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, g2, ws.t(3, 1), n);
-    if ((e = conv_bwd_weight(net, ws, 6, ws.t(3, 0), g2, B, N[3], s)) != hipSuccess) return e;
-    g = ws.t(3, 7);
-    if ((e = conv_bwd_data(net, 6, g2, g, B, N[3], s)) != hipSuccess) return e;
+  for (int l = 3; l >= 0; --l) {
+    weights(2 * l + 1, ws.t(l, kA), ws.t(l, kGb));
+    if ((e = data(2 * l + 1, ws.t(l, kGb), ws.t(l, kGa), N[l], kConvMask, ws.t(l, kA))) !=
+        hipSuccess)
+      return e;
+    weights(2 * l, l == 0 ? x : ws.t(l, kIn), ws.t(l, kGa));
+    if (l > 0 && (e = data(2 * l, ws.t(l, kGa), ws.t(l - 1, kGb), N[l], kConvExpand,
+                           ws.t(l - 1, kB), nullptr, ws.t(l - 1, kGm), N[l - 1])) != hipSuccess)
+      return e;
   }
-  for (int l = 2; l >= 0; --l) {
-    const int64_t bc = (int64_t)B * net.ch[l];
-    const int64_t n = bc * ws.vox(l);
-    float* gb = ws.t(l, 7);
-    // gradient of pool input, plus the skip's gradient
-    hipLaunchKernelGGL(k_pool_bwd, grid1(n), dim3(256), 0, s, g, gb, (int)bc, N[l], N[l], N[l]);
-    hipLaunchKernelGGL(k_add, grid1(n), dim3(256), 0, s, gb, gskip[l], n);
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, gb, ws.t(l, 2), n);
-    if ((e = conv_bwd_weight(net, ws, 2 * l + 1, ws.t(l, 1), gb, B, N[l], s)) != hipSuccess) return e;
-    float* g2 = ws.t(l, 8);
-    if ((e = conv_bwd_data(net, 2 * l + 1, gb, g2, B, N[l], s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_relu_mask, grid1(n), dim3(256), 0, s, g2, ws.t(l, 1), n);
-    const float* xin = l == 0 ? x : ws.t(l, 0);
-    if ((e = conv_bwd_weight(net, ws, 2 * l, xin, g2, B, N[l], s)) != hipSuccess) return e;
-    if (l > 0) {
-      g = ws.t(l, 7);   // reuse: data gradient into the pooled input of level l
-      if ((e = conv_bwd_data(net, 2 * l, g2, g, B, N[l], s)) != hipSuccess) return e;
-    }
-  }
+  hipLaunchKernelGGL(k_conv3d_wgrad, dim3((unsigned)P.wgs), dim3(kWgradThreads), 0, s, P.jobs,
+                     ws.wpart);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)P.red), dim3(256), 0, s, P.jobs, ws.wpart,
+                     net.g);
   return hipGetLastError();
 }
 

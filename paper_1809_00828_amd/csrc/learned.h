@@ -28,10 +28,15 @@ struct Net {
   void init(const int32_t* c, int32_t in_channels);
 };
 
-// Activations of one forward pass (and gradient scratch) for batch B on an
-// N0^3 grid: per level, kSlots tensors of the widest channel count there.
+// Tensors of a level of the network: pooled input; encoder (bottom at the last
+// level); decoder after its first convolution, with the skip added, after its
+// second; gradients of encoder and decoder tensors (kGda, kGdb, kGa, kGb before
+// the ReLU of their tensor, kGm of the sum with the skip).
+enum NetSlot { kIn, kA, kB, kDa, kM, kDb, kGdb, kGda, kGm, kGb, kGa, kSlots };
+
+// Activations of one forward pass and their gradients for batch B on an N0^3
+// grid.
 struct NetWs {
-  static constexpr int kSlots = 9;
   int B = 0, capB = 0;
   int N[4] = {0, 0, 0, 0};
   int64_t off[4][kSlots];
@@ -49,8 +54,8 @@ struct NetWs {
 };
 
 int64_t net_param_count(const int32_t* c, int32_t in_channels);
-// forward of batch B (input x: B x in_ch x N0^3) into ws.y()
-hipError_t net_forward(const Net& net, NetWs& ws, const float* x, int B, hipStream_t s);
+// forward of batch B (input x: B x in_ch x N0^3) into y (B x 1 x N0^3)
+hipError_t net_forward(const Net& net, NetWs& ws, const float* x, float* y, int B, hipStream_t s);
 // parameter gradient into net.g from gy (B x 1 x N0^3); needs the forward
 hipError_t net_backward(Net& net, NetWs& ws, const float* x, float* gy, int B, hipStream_t s);
 // mean squared error of ws.y() against target: ws.partial[0..1024) sums,
