@@ -20,7 +20,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libfc.so")
 
-HIP_SOURCES = ["fc_api.hip", "dev_pool.hip", "k_spmv.hip", "k_setup.hip", "k_schwarz.hip", "k_cg.hip",
+HIP_SOURCES = ["fc_api.hip", "dev_pool.hip", "k_tiny.hip", "k_spmv.hip", "k_setup.hip", "k_schwarz.hip", "k_cg.hip",
                "k_batch.hip", "k_learned.hip", "fc_model.hip", "k_coarse.hip"]
 CXX_SOURCES = ["host_assemble.cpp"]
 

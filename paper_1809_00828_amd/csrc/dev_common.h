@@ -11,6 +11,13 @@ namespace fc {
 constexpr int kWave = 64;
 constexpr int kNumXcd = 8;   // MI355X: 8 XCDs, workgroups dispatched round-robin
 
+// v, opaque to the compiler: what is derived from it is computed where it is
+// used and not kept in registers across a loop.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // Map the hardware workgroup id to a logical tile id so that the
 // workgroups that land on one XCD (ids congruent mod 8) process one
 // contiguous range of tiles and share that XCD's L2.  A bijection on

@@ -41,6 +41,7 @@
 #include "learned.h"
 #include "k_setup.h"
 #include "k_spmv.h"
+#include "k_tiny.h"
 
 #define FC_TRY_ST(x)               \
   do {                             \
@@ -745,6 +746,8 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
                                 CoarseCtx* learn = nullptr, int every = 1, int fcg_m = 1) {
   fc_problem_s& pb = *pc.pb;
   const int64_t n = pb.n_dofs;
+  if (precA == 0 && precS == 0 && !tev && !learn && tiny_fits(pc))
+    return launch_tiny_steps(pc, x, w.r, w.p, w.z, w.sc, chunk, s);
   const int np_spmv = precA == 1 ? 0 : spmv_dot_blocks(pb.A);
   for (int it = 0; it < chunk; ++it) {
     hipError_t e;
@@ -882,6 +885,30 @@ static fc_status ensure_graph(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, 
   return FC_OK;
 }
 
+// Steps between two looks at the stop flag (precA = precS = 0 and no correction:
+// a tiny problem tests it in every step and takes more steps a launch).
+static int chunk_of(const fc_precond_s& pc, int check_every, bool plain) {
+  const int chunk = check_every > 0 ? check_every : 16;
+  if (!plain || !tiny_fits(pc)) return chunk;
+  return (int)std::min<int64_t>((int64_t)kTinyChunks * chunk, kTinySteps);
+}
+
+static bool plain_steps(const CoreArgs& a) {
+  return a.precA == 0 && a.precS == 0 && !a.learn && !a.timing;
+}
+
+// Steps of the next chunk: no more than maxit leaves (a step after the stop still
+// dispatches its grids, 7 us).
+static int next_steps(int chunk, int64_t maxit, int64_t launched) {
+  const int64_t left = maxit - launched * chunk;
+  return left > 0 ? (int)std::min<int64_t>(left, chunk) : chunk;
+}
+
+// Whole chunks of several launches are replayed from a graph.
+static bool chunk_in_graph(const fc_precond_s& pc, const CoreArgs& a, int steps) {
+  return steps == chunk_of(pc, a.chunk, false) && !(plain_steps(a) && tiny_fits(pc));
+}
+
 // One PCG run from x = 0 on the solver stream s.
 static fc_status pcg_core(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, CoreResult* res,
                           hipStream_t s) {
@@ -889,7 +916,7 @@ static fc_status pcg_core(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, Core
   const int64_t n = pb.n_dofs;
   FC_HIP(enqueue_start(pc, w, a.b, a.x, a.tol, a.maxit, a.stop, a.history, a.precS, s, a.learn,
                        a.fcg_m));
-  const int chunk = a.chunk > 0 ? a.chunk : 16;
+  const int chunk = chunk_of(pc, a.chunk, plain_steps(a));
   const int64_t max_chunks = (a.maxit + chunk - 1) / chunk + 1;
   int64_t launched = 0;
   if (a.timing) {
@@ -918,9 +945,15 @@ static fc_status pcg_core(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, Core
       if (w.host->done != 0 || launched > max_chunks) break;
     }
   } else {
-    FC_TRY_ST(ensure_graph(pc, w, a, s));
     for (;;) {
-      FC_HIP(hipGraphLaunch(w.exec, s));
+      const int steps = next_steps(chunk, a.maxit, launched);
+      if (chunk_in_graph(pc, a, steps)) {
+        FC_TRY_ST(ensure_graph(pc, w, a, s));
+        FC_HIP(hipGraphLaunch(w.exec, s));
+      } else {
+        FC_HIP(enqueue_steps(pc, w, a.x, steps, a.precA, a.precS, s, nullptr, a.learn, 1,
+                             a.fcg_m));
+      }
       ++launched;
       FC_HIP(hipMemcpyAsync(w.host, w.sc, sizeof(CgScalars), hipMemcpyDeviceToHost, s));
       FC_HIP(hipStreamSynchronize(s));
@@ -1043,7 +1076,9 @@ fc_status pcg_solve(fc_precond_s& pc, const double* b, double* x, const fc_solve
     const int stop = o.mode == FC_MODE_LEARNED ? (int)FC_STOP_RESIDUAL : o.stop;
     CoreArgs a{b, x, o.tol, o.maxit, stop, 0, precS, o.timing, o.check_every, o.history_dev, learn,
                fcg_m};
-    if (!o.timing) FC_TRY_ST(ensure_graph(pc, w, a, s));
+    if (!o.timing &&
+        chunk_in_graph(pc, a, next_steps(chunk_of(pc, a.chunk, plain_steps(a)), a.maxit, 0)))
+      FC_TRY_ST(ensure_graph(pc, w, a, s));
     FC_HIP(hipEventRecord(w.ev[1], s));
     FC_TRY_ST(pcg_core(pc, w, a, &acc, s));
     iters = acc.iters;
@@ -1190,11 +1225,11 @@ fc_status pcg_solve_noalloc(fc_precond_s& pc, const double* b, double* x, const 
   w.partial_len = kPartials;
   w.sc = reinterpret_cast<CgScalars*>(w.partial + kPartials);
   FC_HIP(enqueue_start(pc, w, b, x, o.tol, o.maxit, o.stop, o.history_dev, 0, s));
-  const int chunk = o.check_every > 0 ? o.check_every : 16;
+  const int chunk = chunk_of(pc, o.check_every, true);
   const int64_t max_chunks = (o.maxit + chunk - 1) / chunk + 1;
   CgScalars h{};
   for (int64_t launched = 0;;) {
-    FC_HIP(enqueue_steps(pc, w, x, chunk, 0, 0, s));
+    FC_HIP(enqueue_steps(pc, w, x, next_steps(chunk, o.maxit, launched), 0, 0, s));
     ++launched;
     FC_HIP(hipMemcpyAsync(&h, w.sc, sizeof(CgScalars), hipMemcpyDeviceToHost, s));
     FC_HIP(hipStreamSynchronize(s));

@@ -275,13 +275,6 @@ __device__ __forceinline__ double block_entry(const BlockSrc& S, const BlockRow&
 // 0.71 ms extraction and 1.05 ms packing.
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-// v, opaque to the compiler: what is derived from it is computed where it is
-// used and not kept in registers across a loop.
-__device__ __forceinline__ int opaque(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 template <int K>
 __device__ __forceinline__ double bcast16(double v) {   // lane K of every 16
   return __longlong_as_double(

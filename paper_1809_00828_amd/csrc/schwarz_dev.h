@@ -250,6 +250,40 @@ __device__ __forceinline__ void schwarz_staged_block(
   if (act && !stop && yb) yb[i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
 }
 
+// Column i of the stored rows of a block of kM <= 64, in pairs (sym_offset): one
+// two-wide load each.
+template <typename T, int kM>
+__device__ __forceinline__ void small_rows(const T* __restrict__ Pb, int i, T (&v)[kM / 2 + 1]) {
+  constexpr int kH = kM / 2, kNP = (kH + 1) & ~1;
+  typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+#pragma unroll
+  for (int k = 0; k < kNP; k += 2) {
+    const t2 t = *reinterpret_cast<const t2*>(Pb + k * kM + 2 * i);
+    v[k] = t.x;
+    v[k + 1] = t.y;
+  }
+  if constexpr (kNP < kH + 1) v[kH] = Pb[kH * kM + i];
+}
+
+// Row i of the product from its lane's column v and the right-hand side rb of the
+// block whose columns lie in lanes g0 .. g0 + kM - 1.
+template <typename T, int kM>
+__device__ __forceinline__ double small_product(const T (&v)[kM / 2 + 1], const double* rb, int i,
+                                                int g0) {
+  using A = typename Acc<T>::type;
+  constexpr int kH = kM / 2;
+  A acc0 = madd<A>(v[0], rb[i], A(0)), acc1 = 0;
+#pragma unroll
+  for (int k = 1; k <= kH; ++k) {
+    const int ip = i + k < kM ? i + k : i + k - kM;   // (i + k) mod m
+    const int im = i >= k ? i - k : i - k + kM;       // (i - k) mod m
+    const T vr = __shfl(v[k], g0 + im, 64);
+    acc0 = madd<A>(v[k], rb[ip], acc0);
+    if (!((kM & 1) == 0 && k == kH)) acc1 = madd<A>(vr, rb[im], acc1);
+  }
+  return (double)acc0 + (double)acc1;
+}
+
 // m <= 64: each wave handles floor(64/m) blocks, one lane per output row.
 // kM > 0 (m = kM known at compile time): lane i loads its
 // column of the stored rows (Q_B[k][i] = P_B[i][(i + k) mod m], k = 0 ..
@@ -278,7 +312,6 @@ __device__ __forceinline__ void schwarz_small_tile(
   const bool active = lb < bpw && blk < n_blocks;
   // lanes without a block read block 0 (always present) and store nothing
   const T* Pb = P + (active ? blk : 0) * block_stride;
-  using A = typename Acc<T>::type;
   constexpr int kH = kM / 2;
   T v[kH + 1];
   int64_t dof = -1;
@@ -293,18 +326,7 @@ __device__ __forceinline__ void schwarz_small_tile(
     g_q = (q ? q : r)[dof];
     g_s = (isd ? isd : r)[dof];
   }
-  if constexpr (kM > 0) {
-    // stored rows in pairs (sym_offset, m <= 64): one two-wide load each
-    constexpr int kNP = (kH + 1) & ~1;
-    typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
-#pragma unroll
-    for (int k = 0; k < kNP; k += 2) {
-      const t2 t = *reinterpret_cast<const t2*>(Pb + k * kM + 2 * i);
-      v[k] = t.x;
-      v[k + 1] = t.y;
-    }
-    if constexpr (kNP < kH + 1) v[kH] = Pb[kH * kM + i];
-  }
+  if constexpr (kM > 0) small_rows<T, kM>(Pb, i, v);
   if constexpr (!kLat) {
     if (active) {
       dof = dof_of(blk, i);
@@ -324,17 +346,7 @@ __device__ __forceinline__ void schwarz_small_tile(
     // every lane takes part in the cross-lane reads; a lane without a block
     // reads its own group's entries and discards the result
     const int g0 = (active ? lb : 0) * kM;
-    const double* rb = &rB[w][g0];
-    A acc0 = madd<A>(v[0], rb[i], A(0)), acc1 = 0;
-#pragma unroll
-    for (int k = 1; k <= kH; ++k) {
-      const int ip = i + k < kM ? i + k : i + k - kM;   // (i + k) mod m
-      const int im = i >= k ? i - k : i - k + kM;       // (i - k) mod m
-      const T vr = __shfl(v[k], g0 + im, 64);
-      acc0 = madd<A>(v[k], rb[ip], acc0);
-      if (!((kM & 1) == 0 && k == kH)) acc1 = madd<A>(vr, rb[im], acc1);
-    }
-    out = (double)acc0 + (double)acc1;
+    out = small_product<T, kM>(v, &rB[w][g0], i, g0);
   } else {
     if (!active) return;
     const double* rb = &rB[w][lb * m];
