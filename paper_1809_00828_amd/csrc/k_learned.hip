@@ -482,7 +482,8 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
   // This thread's pair of halo values (the same in every brick and channel):
   // offset from the brick's corner, position in LDS, and the bits of its
   // coordinates (z 0-5, y 6-11, x 12-17) among those inside the grid.
-  const int xc = tid / 108, xq = tid - 108 * xc, xrow = xq / 3;
+  const bool xact = tid < 216;   // the other threads load what thread 0 loads
+  const int xt = xact ? tid : 0, xc = xt / 108, xq = xt - 108 * xc, xrow = xq / 3;
   const int hz = xrow / 6, hy = xrow - 6 * hz, hx = 2 * (xq - 3 * xrow);
   const int up = J.up, step = 4 >> up;
   auto below = [&](int h) { return up ? (h + 1) >> 1 : h; };   // ((h - 1) >> up) + 1
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
     for (int it = 0; it < kXIter; ++it) {
       if (2 * it >= nx) break;
       const int at = xat + 2 * it * kXRow;
-      if (xc < 2 && 2 * it + xc < nx)
+      if (xact && 2 * it + xc < nx)
         put(&xs[at], &xs[kXs + at], x0in ? xv[it].x : 0.f, x1in ? xv[it].y : 0.f);
     }
 #pragma unroll
