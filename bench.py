@@ -612,11 +612,13 @@ def batch_bench(fc, args, count=None, line=True):
     wall = (time.perf_counter() - t0) / steps
     dof_iters = sum(p.n * r["iters"] for p, r in zip(pbs, res))
     # HBM fraction against the summed algorithmic bytes: every member's
-    # iterations times the bytes of one of its iterations (the batch reads
-    # its block columns; symmetric storage of the local inverses)
+    # iterations times the bytes of one of its iterations (members without a
+    # sliced copy read their block columns; symmetric storage of the local
+    # inverses)
     moved = 0
     for p, c, r in zip(pbs, pcs, res):
-        inf = dict(p.info(), lattice_columns=False)
+        inf = p.info()
+        inf["lattice_columns"] = inf["sliced"]
         moved += r["iters"] * iteration_bytes(inf, c.m, c.info()["n_blocks"],
                                               c.m // inf["bsr_dim"])
     gbs = moved / wall / 1e9
@@ -631,7 +633,8 @@ def batch_bench(fc, args, count=None, line=True):
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "bytes_per_solve": moved,
                      "basis": "sum over members of iterations x bytes of one PCG iteration "
-                              "(matrix with block columns, symmetric local inverses, vectors)"},
+                              "(matrix, block columns where they are read, symmetric local "
+                              "inverses, vectors)"},
         "converged": sum(r["status"] == "OK" for r in res),
         "iters_min": min(r["iters"] for r in res), "iters_max": max(r["iters"] for r in res),
         "setup_s": t_setup, "batch_create_autotune_s": t_tune,

@@ -245,21 +245,21 @@ __global__ __launch_bounds__(256) void kb_schwarz_small(
   }
 }
 
-// Blocks of more than 64 rows, one per workgroup (for the batch's m = 125 every
-// thread's own entry of each stored row is 4.5 % faster than 16-byte runs).
+// Blocks of more than 64 rows, one per workgroup.
+template <int kRows, int kMaxM>
 __global__ __launch_bounds__(256) void kb_schwarz_staged(
     const BProb* __restrict__ probs, const WorkItem* __restrict__ items, int n_items,
     CgScalars* __restrict__ sc, const double* __restrict__ rvec, const double* __restrict__ qvec,
     const double* __restrict__ partial) {
-  __shared__ double rB[256], red[16];
-  __shared__ __align__(16) double tile[StageRows<double>::value * 256];
+  __shared__ double rB[kMaxM], red[16];
+  __shared__ __align__(16) double tile[kRows * kMaxM];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   CgScalars* S = sc + it.prob;
   if (S->done) return;
   const BProb& P = probs[it.prob];
   const AlphaIn ai = qvec ? batch_alpha(P, partial, n_items) : AlphaIn{};
   const int64_t blk = it.tile;
-  schwarz_staged_block<double, false>(
+  schwarz_staged_block<double, kRows>(
       P.Q + blk * sym_block_stride_dev(P.m), P.y + blk * P.m, P.m, rvec + P.voff,
       qvec ? qvec + P.voff : nullptr, nullptr, S, ai, it.tile == 0, rB, tile, red,
       [&](int i) { return block_dof(P.elem_nodes, P.block_elem[blk], P.nn, P.bdim, i); });
@@ -552,8 +552,12 @@ static hipError_t launch_schwarz_class(fc_batch_s& bt, const SchwarzClass& c, co
   const int np = (int)bt.pull_items.size();
   dim3 g((unsigned)n), b(c.m > 64 ? 64 * ((c.m + 63) / 64) : 256);
   if (c.m > 64) {
-    hipLaunchKernelGGL(kb_schwarz_staged, g, b, 0, s, bt.d_probs, items, np, bt.sc, bt.r, q,
-                       bt.partial);
+    if (c.m <= 128)
+      hipLaunchKernelGGL((kb_schwarz_staged<4, 128>), g, b, 0, s, bt.d_probs, items, np, bt.sc,
+                         bt.r, q, bt.partial);
+    else
+      hipLaunchKernelGGL((kb_schwarz_staged<8, 192>), g, b, 0, s, bt.d_probs, items, np, bt.sc,
+                         bt.r, q, bt.partial);
     return hipGetLastError();
   }
 #define FC_BSMALL(KM)                                                                         \

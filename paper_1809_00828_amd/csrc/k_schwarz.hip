@@ -40,10 +40,13 @@
 
 namespace fc {
 
-// m > 64, symmetric layout staged through LDS.  kRuns: 16-byte runs of the
-// chunk per thread (sym_block_staged_runs), else every thread's own entry of
-// each stored row (sym_block_staged_rows); launch_staged picks by block size.
-template <typename T, bool kRuns>
+// m > 64, symmetric layout staged through LDS in chunks of kRows stored rows, for
+// blocks of up to kMaxM.  Bound by HBM: 0.21 GB of blocks of 81 in 41 us (5.2 TB/s),
+// of 125 (20^3 cells, p = 4) 95 us with the pull, of 192 4.9 GB in 0.81 ms (6.2
+// TB/s).  With 16 KB of LDS a workgroup and every thread's own entry of
+// each row for m <= 128: 61 and 113 us; FP32 blocks of 192 in chunks of 16 rows 38
+// instead of 33 us.
+template <typename T, int kRows, int kMaxM>
 __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
     const int32_t* __restrict__ block_elem, int nn, int bd, int m,
@@ -51,12 +54,11 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
     CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks,
     const int32_t* __restrict__ list, const int32_t* __restrict__ skip) {
   using A = typename Acc<T>::type;
-  constexpr int kStageRows = StageRows<T>::value;
   // the gathered residual is kept in the accumulation type: an FP32 copy
   // rounds it to FP32 at every use anyway, and half-width entries halve the
   // LDS traffic of the rotated reads
-  __shared__ A rB[256];
-  __shared__ __align__(16) T tile[kStageRows * 256];
+  __shared__ A rB[kMaxM];
+  __shared__ __align__(16) T tile[kRows * kMaxM];
   __shared__ double red[16];
   if (sc && sc->done) return;
   // list: the workgroups handle only the listed blocks; skip: blocks
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
   const int64_t blk = list ? (int64_t)list[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x);
   const bool skipped = skip && skip[blk];
   if (skipped && blockIdx.x != 0) return;   // the first workgroup stores alpha
-  schwarz_staged_block<T, kRuns>(
+  schwarz_staged_block<T, kRows>(
       P + blk * block_stride, skipped ? nullptr : y + blk * m, m, r, q, isd, sc, ai,
       blockIdx.x == 0, rB, tile, red,
       [&](int i) { return block_dof(elem_nodes, block_elem[blk], nn, bd, i); });
@@ -348,27 +350,28 @@ hipError_t launch_inv_sqrt_diag(const fc_problem_s& pb, double* isd, hipStream_t
   return hipGetLastError();
 }
 
-// Loading scheme of the staged product by block size (measured on MI355X):
-// 16-byte runs for m = 192 (32^3-cell p = 3 elasticity, 1.5 % faster than
-// per-thread rows), per-thread rows for m = 125 (4.5 % faster than runs in a
-// 64-member Poisson batch).  One scheme per compiled kernel: a kernel holding
-// both ran the m = 192 products 12 % slower.
-inline bool staged_runs(int m) { return m > 128; }
-
+// Chunks of the staged product by block size (us a product, FP64): 20^3 cells p = 2,
+// m = 81: 43 / 41 / 43.5 in chunks of 4 / 6 / 8 rows; 16^3 cells p = 4, m = 125: 51 /
+// 53 / 53.5; m = 192: 104 in chunks of 4, 6 and 8.  FP32, m = 192: 33.3 / 34.4 / 36.3
+// in chunks of 4 / 8 / 12.
 template <typename T>
 static void launch_staged(const fc_precond_s& pc, const T* Q, int64_t n_launch,
                           const double* r, const double* q, const double* isd,
                           CgScalars* sc, const AlphaIn ai, const int32_t* list,
                           const int32_t* skip, hipStream_t s) {
   const dim3 g((unsigned)n_launch), b(64 * ((pc.m + 63) / 64));
-  if (staged_runs(pc.m))
-    hipLaunchKernelGGL((k_schwarz_sym_staged<T, true>), g, b, 0, s, Q, sym_block_stride(pc.m),
-                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, ai, pc.y,
-                       pc.n_blocks, list, skip);
+#define FC_STAGED(ROWS, MAXM)                                                                \
+  hipLaunchKernelGGL((k_schwarz_sym_staged<T, ROWS, MAXM>), g, b, 0, s, Q,                   \
+                     sym_block_stride(pc.m), block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, \
+                     pc.m, r, q, isd, sc, ai, pc.y, pc.n_blocks, list, skip)
+  constexpr bool k64 = sizeof(T) == 8;
+  if (pc.m <= 96)
+    FC_STAGED((k64 ? 6 : 8), 96);
+  else if (pc.m <= 128)
+    FC_STAGED(4, 128);
   else
-    hipLaunchKernelGGL((k_schwarz_sym_staged<T, false>), g, b, 0, s, Q, sym_block_stride(pc.m),
-                       block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, pc.m, r, q, isd, sc, ai, pc.y,
-                       pc.n_blocks, list, skip);
+    FC_STAGED((k64 ? 8 : 4), 192);
+#undef FC_STAGED
 }
 
 template <typename T>

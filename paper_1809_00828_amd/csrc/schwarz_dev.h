@@ -70,13 +70,6 @@ __device__ __forceinline__ double gather_r(const double* r, const double* q, dou
   return v;
 }
 
-// Rows of the wrapped-diagonal layout staged through LDS per chunk: 16 KB
-// of LDS, 8 rows of FP64 or 16 of FP32.
-template <typename T>
-struct StageRows {
-  static constexpr int value = sizeof(T) == 8 ? 8 : 16;
-};
-
 // Symmetric product of one block (m > 64) by a whole workgroup of
 // 64 ceil(m/64) threads, one output row i per thread (threads with i >= m
 // take part in the loads and barriers only).  A chunk of stored rows is one
@@ -86,14 +79,15 @@ struct StageRows {
 // the rotated one back from LDS, so HBM and L2 see each stored entry exactly
 // once.  The next chunk's loads are issued before the current chunk is
 // summed.  gather() writes the block's right-hand side to rB (m entries, in
-// LDS) once the first chunk's loads are in flight.  tile (16-byte aligned) holds kStageRows * m <= kStageRows * 256 entries,
+// LDS) once the first chunk's loads are in flight.  Chunks of few rows: the less
+// LDS a workgroup holds, the more of them stream at once.  tile (16-byte aligned) holds kStageRows * m entries,
 // as tile[kk * m + j] for stored row k0 + kk.
-template <typename T, typename RB, typename F>
-__device__ __forceinline__ double sym_block_staged_runs(const T* __restrict__ Qb, const RB* rB,
+template <typename T, int kStageRows, typename RB, typename F>
+__device__ __forceinline__ double sym_block_staged(const T* __restrict__ Qb, const RB* rB,
                                                         int m, int i, T* tile, F&& gather) {
   using A = typename Acc<T>::type;
-  constexpr int kStageRows = StageRows<T>::value;
   constexpr int V = 16 / sizeof(T);                // entries per 16-byte piece
+  static_assert(kStageRows % V == 0, "whole pieces per thread");
   constexpr int kPer = kStageRows / V;             // pieces per thread per chunk (m <= threads)
   typedef T tv __attribute__((ext_vector_type(V), aligned(sizeof(T))));
   typedef T tva __attribute__((ext_vector_type(V), aligned(16)));
@@ -151,51 +145,6 @@ __device__ __forceinline__ double sym_block_staged_runs(const T* __restrict__ Qb
   return (double)acc0 + (double)acc1;
 }
 
-// The same with every thread loading its own entry of each stored row of
-// the chunk (8-byte loads) and keeping it in a register; only the rotated
-// entries are read back from LDS (tile[kk * 256 + j]).
-template <typename T, typename RB, typename F>
-__device__ __forceinline__ double sym_block_staged_rows(const T* __restrict__ Qb, const RB* rB,
-                                                        int m, int i, T* tile, F&& gather) {
-  using A = typename Acc<T>::type;
-  constexpr int kStageRows = StageRows<T>::value;
-  const bool act = i < m;
-  const int h = m / 2;
-  const bool even = (m & 1) == 0;
-  A acc0 = 0, acc1 = 0;
-  int ip = i, im = i;
-  for (int k0 = 0; k0 <= h; k0 += kStageRows) {
-    T v[kStageRows];
-#pragma unroll
-    for (int kk = 0; kk < kStageRows; ++kk) {
-      const int k = k0 + kk;
-      const T* src = Qb + (int64_t)k * m + i;
-      v[kk] = (act && k <= h) ? __builtin_nontemporal_load(src) : T(0);
-    }
-    if (k0 == 0) gather();
-    __syncthreads();   // previous chunk's rotated reads are done
-#pragma unroll
-    for (int kk = 0; kk < kStageRows; ++kk) tile[kk * 256 + i] = v[kk];
-    __syncthreads();
-    if (act) {
-#pragma unroll
-      for (int kk = 0; kk < kStageRows; ++kk) {
-        const int k = k0 + kk;
-        if (k > h) break;
-        if (k == 0) {
-          acc0 = madd<A>(v[kk], rB[i], acc0);
-          continue;
-        }
-        ip = (ip + 1 == m) ? 0 : ip + 1;
-        im = (im == 0) ? m - 1 : im - 1;
-        acc0 = madd<A>(v[kk], rB[ip], acc0);
-        if (!(even && k == h)) acc1 = madd<A>(tile[kk * 256 + im], rB[im], acc1);
-      }
-    }
-  }
-  return (double)acc0 + (double)acc1;
-}
-
 // Wrapped-diagonal symmetric product for one block row i (0 <= i < m), in
 // either layout of sym_offset.
 template <typename T>
@@ -218,10 +167,10 @@ __device__ __forceinline__ double sym_row(const T* __restrict__ Qb, const double
 }
 
 // One block (m > 64) by a workgroup of 64 ceil(m / 64) threads, its stored rows
-// staged through LDS (kRuns: sym_block_staged_runs).  The right-hand side is
+// staged through LDS.  The right-hand side is
 // gathered, and the step length taken, behind the first loads of the inverse.
 // dof_of(i): unknown of row i (< 0: none).  yb null: nothing is stored.
-template <typename T, bool kRuns, class Dof>
+template <typename T, int kRows, class Dof>
 __device__ __forceinline__ void schwarz_staged_block(
     const T* __restrict__ Qb, double* __restrict__ yb, int m, const double* __restrict__ r,
     const double* __restrict__ q, const double* __restrict__ isd, CgScalars* sc,
@@ -245,8 +194,7 @@ __device__ __forceinline__ void schwarz_staged_block(
     if (ai.np) stop = !cg_alpha(sc, ai, red, &alpha, first);
     if (act) rB[i] = dof >= 0 ? (A)((q ? fma(-alpha, gq, gr) : gr) * gs) : A(0);
   };
-  const double v = kRuns ? sym_block_staged_runs<T, A>(Qb, rB, m, i, tile, gather)
-                         : sym_block_staged_rows<T, A>(Qb, rB, m, i, tile, gather);
+  const double v = sym_block_staged<T, kRows>(Qb, rB, m, i, tile, gather);
   if (act && !stop && yb) yb[i] = dof < 0 ? 0.0 : isd ? v * isd[dof] : v;
 }
 
