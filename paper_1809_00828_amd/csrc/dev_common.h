@@ -148,6 +148,31 @@ __device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double z
   }
 }
 
+// (r, z) from the pull's np <= kBetaSets partial sets, by every workgroup of 256 in the
+// same order; the first one also sums (z, z) and (r, r), tests for the stop and
+// stores the scalars.
+constexpr int kBetaSets = 1024;
+__device__ __forceinline__ double cg_beta_sum(const double* __restrict__ sets, int np,
+                                              CgScalars* sc, double (*red)[4], bool first) {
+  const int nk = first ? 3 : 1, w = threadIdx.x / kWave;
+  for (int k = 0; k < nk; ++k) {
+    double v[kBetaSets / 256];
+#pragma unroll
+    for (int u = 0; u < kBetaSets / 256; ++u) {
+      const int j = threadIdx.x + 256 * u;
+      v[u] = j < np ? sets[k * np + j] : 0.0;
+    }
+    const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
+    if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
+  }
+  __syncthreads();
+  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+  if (first && threadIdx.x == 0)
+    cg_beta_store(sc, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
+                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
+  return rz;
+}
+
 __device__ __forceinline__ double load_relaxed(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void kb_spmv_sell(const BProb* __restrict__ pr
   const SellItem it = items[s];
   const BProb& B = probs[it.prob];
   if (sc[it.prob].done) return;
-  const double* x = pvec + B.voff;
+  const GatherX x{pvec + B.voff};
   double* y = qvec + B.voff;
   switch (it.p) {
     case 1: (void)sell_slice_product<1, true>(B.sell, it.sl, l, x, y); break;

@@ -280,7 +280,6 @@ __global__ __launch_bounds__(256) void k_cg_pull(
 
 // The pull's partials summed in a fixed order by one workgroup (more than
 // kBetaSets of them), four sets per thread in flight.
-constexpr int kBetaSets = 1024;
 __global__ __launch_bounds__(1024) void k_cg_beta(const double* __restrict__ partial, int np,
                                                   CgScalars* sc) {
   __shared__ double lds[16];
@@ -304,41 +303,23 @@ __global__ __launch_bounds__(1024) void k_cg_beta(const double* __restrict__ par
   if (threadIdx.x == 0) cg_beta_store(sc, rz, zz, rr);
 }
 
-// p = z + beta p with beta from the pull's np <= kBetaSets partials, summed by
-// every workgroup in the same order; the first one also sums (z,z) and (r,r),
-// tests for the stop and stores the scalars.  Two unknowns per thread, loaded
+// p = z + beta p_old (p_old may be p) with beta from the pull's np <= kBetaSets
+// partial sets (cg_beta_sum).  Two unknowns per thread, loaded
 // before the sums.  (A workgroup that still updates p after the first one set
 // the stop flag changes nothing: p is not read again.)
 __global__ __launch_bounds__(256) void k_cg_beta_p(const double* __restrict__ partial, int np,
                                                    const double* __restrict__ z,
-                                                   double* __restrict__ p, int64_t n,
+                                                   const double* p_old, double* p, int64_t n,
                                                    CgScalars* sc) {
   __shared__ double red[3][4];
   if (sc->done) return;
   const double rz_old = sc->rz;
   const int64_t i0 = (int64_t)blockIdx.x * 512 + threadIdx.x, i1 = i0 + 256;
-  const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p[i0] : 0.0;
-  const double z1 = i1 < n ? z[i1] : 0.0, p1 = i1 < n ? p[i1] : 0.0;
-  const int nk = blockIdx.x == 0 ? 3 : 1;
-  const int w = threadIdx.x / kWave;
-  for (int k = 0; k < nk; ++k) {
-    double v[kBetaSets / 256];
-#pragma unroll
-    for (int u = 0; u < kBetaSets / 256; ++u) {
-      const int j = threadIdx.x + 256 * u;
-      v[u] = j < np ? partial[k * np + j] : 0.0;
-    }
-    const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
-    if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
-  }
-  __syncthreads();
-  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-  const double beta = rz / rz_old;
+  const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p_old[i0] : 0.0;
+  const double z1 = i1 < n ? z[i1] : 0.0, p1 = i1 < n ? p_old[i1] : 0.0;
+  const double beta = cg_beta_sum(partial, np, sc, red, blockIdx.x == 0) / rz_old;
   if (i0 < n) p[i0] = fma(beta, p0, z0);
   if (i1 < n) p[i1] = fma(beta, p1, z1);
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    cg_beta_store(sc, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
-                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
 }
 
 // Flexible variant (FCG(1)) for the learned correction z = S r + gamma w:
@@ -621,6 +602,7 @@ static inline unsigned red_grid(int64_t n) {
 // reduction workgroup, or one per SpMV workgroup; two doubles at the end
 // receive the final residual
 constexpr int64_t kPartials = 4 * 4096 + 8;
+constexpr int64_t kDotPartials = 3 * 4096;   // (p, q) partials kept apart from the pull's
 // Workgroups of the fused pull: one round each up to 4,096 of them, then more
 // rounds (each leaves one partial set, which the next kernel sums).
 static inline int pull_rounds(int64_t n) {
@@ -738,6 +720,15 @@ static hipError_t enqueue_resid(SolverWs& w, const double* b, const double* t, h
   return hipGetLastError();
 }
 
+// Stored entries, and entries of the longest row, up to which the p update joins the
+// product: it saves a launch and makes every gather two.  us a step joined / apart: 2-D 40^2 p = 2 (0.1M entries)
+// 14.0 / 15.8, 110^2 p = 3 (2.7M) 21.3 / 22.0, 250^2 p = 2 (4.0M) 29.4 / 30.9; 3-D
+// 10^3 p = 2 (0.6M) 22.2 / 24.0, 20^3 p = 2 (4.3M) 31.0 / 31.5, 60^3 p = 1 (6.1M)
+// 47.4 / 46.9, 30^3 p = 2 (14M) 64 / 61; rows of up to 343, 9^3 p = 3 (2M) 45 / 34,
+// of up to 729, 6^3 p = 4 75 / 60.
+constexpr int64_t kJoinEntries = int64_t(4) << 20;
+constexpr int kJoinRow = 125;
+
 // Enqueue `chunk` PCG steps on stream s (with timing events when tev).
 // precA: 0 = FP64 matrix, 1 = row-mixed FP64/FP32 matrix; precS: 0/1/2 =
 // FP64/FP32/BF16 local inverses.
@@ -749,6 +740,13 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
   if (precA == 0 && precS == 0 && !tev && !learn && tiny_fits(pc))
     return launch_tiny_steps(pc, x, w.r, w.p, w.z, w.sc, chunk, s);
   const int np_spmv = precA == 1 ? 0 : spmv_dot_blocks(pb.A);
+  // small sliced problems: the p update joins the next step's product (tev: apart,
+  // to be timed).  p alternates between two buffers and ends in w.p.
+  const bool join = np_spmv > 0 && spmv_uses_sell(pb.A) && pb.A.nnzb <= kJoinEntries &&
+                    pb.A.max_row <= kJoinRow && !learn && !tev &&
+                    pull_grid(n) <= (unsigned)kBetaSets;
+  double *p = w.p, *p_other = w.t;
+  double* dots = w.partial + (join ? kDotPartials : 0);
   for (int it = 0; it < chunk; ++it) {
     hipError_t e;
     hipEvent_t* tev_it = (tev && it % every == 0) ? tev : nullptr;
@@ -761,11 +759,17 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
                          dim3(kVecThreads), 0, s, w.p, w.p32, n, w.sc);
       e = launch_spmv_mixed(pb.A, w.p, w.p32, w.q, w.sc, s);
     } else {
-      e = launch_spmv_pq(pb.A, w.p, w.q, w.sc, np_spmv ? w.partial : nullptr, s);
+      if (join && it > 0) {
+        e = launch_spmv_beta(pb.A, w.z, p, p_other, w.q, w.sc, dots, w.partial,
+                             (int)pull_grid(n), s);
+        std::swap(p, p_other);
+      } else {
+        e = launch_spmv_pq(pb.A, p, w.q, w.sc, np_spmv ? dots : nullptr, s);
+      }
     }
     if (e != hipSuccess) return e;
     if (tev_it && (e = hipEventRecord(tev[4 * it + 1], s)) != hipSuccess) return e;
-    AlphaIn ai{w.partial, np_spmv};
+    AlphaIn ai{dots, np_spmv};
     if (!np_spmv) {
       ai.np = (int)red_grid(n);
       hipLaunchKernelGGL(k_cg_pq, dim3(red_grid(n)), dim3(red_threads(n)), 0, s, w.p, w.q, n,
@@ -803,14 +807,14 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
       hipLaunchKernelGGL(k_cg_beta_flex, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc,
                          learn->ls);
     } else {
-      if ((e = launch_cg_pull<false>(pc, x, w.r, w.p, w.q, w.z, w.partial, w.sc, s)) !=
-          hipSuccess)
+      if ((e = launch_cg_pull<false>(pc, x, w.r, p, w.q, w.z, w.partial, w.sc, s)) != hipSuccess)
         return e;
+      if (join && it + 1 < chunk) continue;
       if (pg > (unsigned)kBetaSets)
         hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(1024), 0, s, w.partial, (int)pg, w.sc);
       else
         hipLaunchKernelGGL(k_cg_beta_p, dim3((unsigned)((n + 511) / 512)), dim3(256), 0, s,
-                           w.partial, (int)pg, w.z, w.p, n, w.sc);
+                           w.partial, (int)pg, w.z, p, w.p, n, w.sc);
     }
     if (learn ? !ring : pg > (unsigned)kBetaSets)
       hipLaunchKernelGGL(k_cg_p, dim3(nblk(n)), dim3(kVecThreads), 0, s, w.z, w.p, n, w.sc);

@@ -12,6 +12,11 @@ int spmv_dot_blocks(const DeviceBsr& A);
 // spmv_dot_blocks(A)) unless partial is null (skipped when sc->done is set)
 hipError_t launch_spmv_pq(const DeviceBsr& A, const double* p, double* q, CgScalars* sc,
                           double* partial, hipStream_t s);
+// q = A p on the sliced copy with p = z + beta p_old, stored in p_new; beta from the
+// pull's np partial sets, (p, q) partials as above.
+hipError_t launch_spmv_beta(const DeviceBsr& A, const double* z, const double* p_old,
+                            double* p_new, double* q, CgScalars* sc, double* partial,
+                            const double* sets, int np, hipStream_t s);
 // q = A p with the rows A.rows_hi from the FP64 values and p, and the rows
 // A.rows_lo from the FP32 copy and p32 = fl32(p) (skipped when sc->done is
 // set)

@@ -244,12 +244,56 @@ __global__ __launch_bounds__(256) void k_spmv_sell(const SellView A, const doubl
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   double dot = 0.0;
-  if (s < A.n_slices) dot = sell_slice_product<P, kNT>(A, A.slices[s], l, x, y);
+  if (s < A.n_slices) dot = sell_slice_product<P, kNT>(A, A.slices[s], l, GatherX{x}, y);
   if (!partial) return;
   dot = wave_sum_last(dot);
   if (l == 63) lds[w] = dot;
   __syncthreads();
   if (threadIdx.x == 0) partial[blockIdx.x] = ((lds[0] + lds[1]) + lds[2]) + lds[3];
+}
+
+// The same on p = z + beta p_old, with beta from the np <= kBetaSets partial sets of
+// the pull (cg_beta_sum): the p update of a step, its stop test and scalars (by the
+// first workgroup) and the product of the next, in one launch.  p goes to p_new,
+// since neighbours still read p_old.
+template <int P>
+__global__ __launch_bounds__(256) void k_spmv_sell_beta(
+    const SellView A, const double* __restrict__ z, const double* __restrict__ p_old,
+    double* __restrict__ p_new, double* __restrict__ y, double* __restrict__ partial,
+    const double* __restrict__ sets, int np, CgScalars* sc) {
+  __shared__ double red[3][4];
+  if (sc->done) return;
+  const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
+  const double rz_old = sc->rz;
+  const double rz = cg_beta_sum(sets, np, sc, red, blockIdx.x == 0);
+  double dot = 0.0;
+  if (s < A.n_slices)
+    dot = sell_slice_product<P, true>(A, A.slices[s], l, GatherP{z, p_old, rz / rz_old}, y, p_new);
+  dot = wave_sum_last(dot);
+  __syncthreads();   // red is read
+  if (l == 63) red[0][w] = dot;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    partial[blockIdx.x] = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+}
+
+hipError_t launch_spmv_beta(const DeviceBsr& A, const double* z, const double* p_old,
+                            double* p_new, double* q, CgScalars* sc, double* partial,
+                            const double* sets, int np, hipStream_t s) {
+  const SellView v = sell_view(A);
+  const dim3 g((unsigned)((A.n_slices + 3) / 4)), b(256);
+#define FC_SELL(PP)                                                                       \
+  hipLaunchKernelGGL(k_spmv_sell_beta<PP>, g, b, 0, s, v, z, p_old, p_new, q, partial, sets, \
+                     np, sc)
+  switch (A.lat.p) {
+    case 1: FC_SELL(1); break;
+    case 2: FC_SELL(2); break;
+    case 3: FC_SELL(3); break;
+    default: FC_SELL(4); break;
+  }
+#undef FC_SELL
+  return hipGetLastError();
 }
 
 // Launch shape.  G lanes per block row: enough lanes that one pass of U

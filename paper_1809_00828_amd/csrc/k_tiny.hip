@@ -71,7 +71,7 @@ __global__ __launch_bounds__(64 * kTinyWaves) void k_cg_tiny(const TinyArgs T) {
   for (int it = 0; it < T.steps; ++it) {
     double pq[1] = {0.0};
     for (int s = w; s < T.A.n_slices; s += kTinyWaves)
-      pq[0] += sell_slice_product<P, false>(T.A, T.A.slices[s], l, p, q);
+      pq[0] += sell_slice_product<P, false>(T.A, T.A.slices[s], l, GatherX{p}, q);
     const double rz = S.rzn;
     tiny_sums<1>(pq, red_q, w, l);   // q is complete
     const bool ok = pq[0] > 0.0 && rz > 0.0;

@@ -65,6 +65,28 @@ __device__ __forceinline__ SellRow sell_row(const SellSlice sl, int l, const Sel
   return r;
 }
 
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2a8 __attribute__((ext_vector_type(2), aligned(8)));
+
+// The vector a product gathers from: x itself, or p = z + beta p_old, formed as it
+// is read.
+struct GatherX {
+  const double* x;
+  __device__ __forceinline__ double one(int i) const { return x[i]; }
+  __device__ __forceinline__ d2 two(int i) const {
+    return *reinterpret_cast<const d2a8*>(x + i);
+  }
+};
+struct GatherP {
+  const double *z, *p;
+  double beta;
+  __device__ __forceinline__ double one(int i) const { return fma(beta, p[i], z[i]); }
+  __device__ __forceinline__ d2 two(int i) const {
+    const d2 pv = *reinterpret_cast<const d2a8*>(p + i), zv = *reinterpret_cast<const d2a8*>(z + i);
+    return d2{fma(beta, pv.x, zv.x), fma(beta, pv.y, zv.y)};
+  }
+};
+
 // Box entries x-pencil by x-pencil (kx fastest).  Pencils go two per round, all
 // their loads issued before the first FMA: a round's 2K entries are K paired
 // values per lane (one 16-byte load each, 1 KB contiguous per wave; 8 % faster
@@ -74,23 +96,20 @@ __device__ __forceinline__ SellRow sell_row(const SellSlice sl, int l, const Sel
 // The pencil's (y, z) offsets are stepped, not divided out of its index.
 // Two pencils per round: 1 % faster than four and 3 % faster than eight at 64^3
 // cells, p = 2.
-template <int K, bool kNT>
-__device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, int l,
-                                               const double* __restrict__ xb, int len1,
-                                               int npen, int64_t n1) {
-  typedef double d2 __attribute__((ext_vector_type(2)));
-  typedef double d2a8 __attribute__((ext_vector_type(2), aligned(8)));
+template <int K, bool kNT, class X>
+__device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, int l, const X& x,
+                                               int base, int len1, int npen, int n1) {
   double acc = 0.0;
   int qy = 0, qz = 0;   // offsets of pencil q
   for (int q = 0; q < npen; q += 2) {
     const double* vr = vs + (int64_t)128 * K * (q / 2) + 2 * l;
-    const double* xp0 = xb + n1 * (qy + n1 * qz);
+    const int xp0 = base + n1 * (qy + n1 * qz);
     if (++qy == len1) {
       qy = 0;
       ++qz;
     }
     if (q + 1 < npen) {
-      const double* xp1 = xb + n1 * (qy + n1 * qz);
+      const int xp1 = base + n1 * (qy + n1 * qz);
       if (++qy == len1) {
         qy = 0;
         ++qz;
@@ -105,16 +124,15 @@ __device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, in
       }
 #pragma unroll
       for (int kx = 0; kx + 1 < K; kx += 2) {
-        const d2a8 t0 = *reinterpret_cast<const d2a8*>(xp0 + kx);
-        const d2a8 t1 = *reinterpret_cast<const d2a8*>(xp1 + kx);
+        const d2 t0 = x.two(xp0 + kx), t1 = x.two(xp1 + kx);
         b[kx] = t0.x;
         b[kx + 1] = t0.y;
         b[K + kx] = t1.x;
         b[K + kx + 1] = t1.y;
       }
       if (K & 1) {
-        b[K - 1] = xp0[K - 1];
-        b[2 * K - 1] = xp1[K - 1];
+        b[K - 1] = x.one(xp0 + K - 1);
+        b[2 * K - 1] = x.one(xp1 + K - 1);
       }
 #pragma unroll
       for (int e = 0; e < 2 * K; ++e) acc = fma(a[e], b[e], acc);
@@ -133,11 +151,11 @@ __device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, in
       }
 #pragma unroll
       for (int kx = 0; kx + 1 < K; kx += 2) {
-        const d2a8 t0 = *reinterpret_cast<const d2a8*>(xp0 + kx);
+        const d2 t0 = x.two(xp0 + kx);
         b[kx] = t0.x;
         b[kx + 1] = t0.y;
       }
-      if (K & 1) b[K - 1] = xp0[K - 1];
+      if (K & 1) b[K - 1] = x.one(xp0 + K - 1);
 #pragma unroll
       for (int e = 0; e < K; ++e) acc = fma(a[e], b[e], acc);
     }
@@ -145,20 +163,24 @@ __device__ __forceinline__ double sell_pencils(const double* __restrict__ vs, in
   return acc;
 }
 
-// y = A x on one slice, by one wave.  Returns (x, y) of this lane's row.
-template <int P, bool kNT>
+// y = A x on one slice, by one wave.  Returns (x, y) of this lane's row.  p_new (may
+// be null): x of the row is stored there.
+template <int P, bool kNT, class X>
 __device__ __forceinline__ double sell_slice_product(const SellView& A, const SellSlice sl, int l,
-                                                     const double* __restrict__ x,
-                                                     double* __restrict__ y) {
+                                                     const X& x, double* __restrict__ y,
+                                                     double* __restrict__ p_new = nullptr) {
   const SellRow r = sell_row<P>(sl, l, A);
   const int len1 = sl.cls & 2 ? 2 * P + 1 : P + 1;
   const int npen = len1 * (A.dim == 3 ? (sl.cls & 4 ? 2 * P + 1 : P + 1) : 1);
   const double* vs = A.val + sl.off;
-  const double acc = sl.cls & 1 ? sell_pencils<2 * P + 1, kNT>(vs, l, x + r.base, len1, npen, A.n1)
-                                : sell_pencils<P + 1, kNT>(vs, l, x + r.base, len1, npen, A.n1);
+  const double acc = sl.cls & 1
+                         ? sell_pencils<2 * P + 1, kNT>(vs, l, x, r.base, len1, npen, A.n1)
+                         : sell_pencils<P + 1, kNT>(vs, l, x, r.base, len1, npen, A.n1);
   if (!r.valid) return 0.0;
   y[r.row] = acc;
-  return x[r.row] * acc;
+  const double xr = x.one(r.row);
+  if (p_new) p_new[r.row] = xr;
+  return xr * acc;
 }
 
 }  // namespace fc
