@@ -687,7 +687,7 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
     P.m = pc->m;
     P.bdim = pb->bdim;
     P.dbd = make_fastdiv((uint32_t)pb->bdim);
-    if (spmv_uses_sell(pb->A)) P.sell = sell_view(pb->A);
+    if (spmv_has_sell(pb->A)) P.sell = sell_view(pb->A);
     P.lat = pc->lat;
     voff += pb->n_dofs;
     if (P.sell.n_slices == 0) {

@@ -3,7 +3,8 @@
 #include "fc_internal.h"
 
 namespace fc {
-// The FP64 product takes the sliced copy.
+// There is a sliced copy; the FP64 product takes it.
+bool spmv_has_sell(const DeviceBsr& A);
 bool spmv_uses_sell(const DeviceBsr& A);
 // (p, q) partials the product can leave, one per workgroup; 0: it has too many
 // workgroups, and the dot is a pass of its own.

@@ -333,9 +333,21 @@ static bool lattice_allowed() {
   return v;
 }
 
-static bool use_sell(const DeviceBsr& A) {
+bool spmv_has_sell(const DeviceBsr& A) {
   return lattice_allowed() && A.lat.dim > 0 && A.bdim == 1 && A.sell_val;
 }
+
+// One wave walks a slice's rows from end to end, so a matrix of few slices and long
+// rows waits for single waves; the row layout deals a row to 8 to 64 lanes.  us a
+// product, sliced / rows: 3-D p = 2, 381 slices 9.2 / 7.4, 1,076 11.7 / 11.8; p = 3,
+// 107 13.5 / 7.7, 343 18.2 / 9.3, 791 20.5 / 16.4, 1,838 29.4 / 30.2; p = 4, 244 31.6 /
+// 10.4, 1,838 54.5 / 49.5, 3,546 83.5 / 99.8; rows of up to 36 on average never.
+static bool few_long_rows(const DeviceBsr& A) {
+  const double mean = A.n_rows ? double(A.nnzb) / double(A.n_rows) : 0.0;
+  return mean >= 48.0 && (double)A.n_slices < 9.0 * mean;
+}
+
+static bool use_sell(const DeviceBsr& A) { return spmv_has_sell(A) && !few_long_rows(A); }
 
 bool spmv_uses_sell(const DeviceBsr& A) { return use_sell(A); }
 

@@ -156,7 +156,7 @@ static size_t tiny_lds(const fc_precond_s& pc) {
 
 bool tiny_fits(const fc_precond_s& pc) {
   const fc_problem_s& pb = *pc.pb;
-  if (!spmv_uses_sell(pb.A) || pc.lat.dim == 0 || pb.bdim != 1 || pc.n_blocks == 0) return false;
+  if (!spmv_has_sell(pb.A) || pc.lat.dim == 0 || pb.bdim != 1 || pc.n_blocks == 0) return false;
   if (pc.m > 27 || pc.m != pc.nn || pb.n_dofs > 64 * kTinyWaves * kTinyElems) return false;
   const size_t bytes =
       (size_t)pb.A.nnzb * sizeof(double) +

@@ -11,7 +11,8 @@ from tests.gpu_common import require_gpu
 pytestmark = pytest.mark.gpu
 
 CASES = ([(2, n, p) for n, p in ((1, 1), (1, 4), (2, 3), (7, 1), (8, 2), (9, 1), (31, 2), (13, 4))] +
-         [(3, n, p) for n, p in ((1, 1), (1, 4), (2, 2), (4, 1), (5, 3), (7, 2), (6, 4), (17, 1))])
+         [(3, n, p) for n, p in ((1, 1), (1, 4), (2, 2), (4, 1), (5, 3), (7, 2), (6, 4), (17, 1),
+                             (15, 2), (16, 2))])   # either side of the few-long-rows rule
 
 
 @pytest.mark.parametrize("dim,n,p", CASES)
