@@ -114,14 +114,12 @@ void pool_free(void* p) {
   (void)hipFree(p);
 }
 
-std::mutex& capture_mutex() {
-  static std::mutex* mu = new std::mutex();
-  return *mu;
-}
-
+// hipFree waits for the whole device as hipDeviceSynchronize does, which would
+// also break every graph capture in progress on any thread of the process.
 hipError_t device_idle() {
-  std::lock_guard<std::mutex> lock(capture_mutex());
-  return hipDeviceSynchronize();
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, 256);
+  return e == hipSuccess ? hipFree(p) : e;
 }
 
 void pool_problem_created() {

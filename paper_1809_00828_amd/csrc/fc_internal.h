@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -167,9 +166,8 @@ void pool_free(void* p);
 void pool_problem_created();
 void pool_problem_destroyed();
 
-// A synchronisation of the device ends the graph capture of any other thread:
-// device_idle() waits for the captures of this library, which hold the mutex.
-std::mutex& capture_mutex();
+// Waits for all work on the device; graph captures in progress on other threads
+// (and, in relaxed mode, on this one) go on.
 hipError_t device_idle();
 
 // Per-workgroup (p, q) partials a kernel derives the step length from; np = 0:

@@ -918,7 +918,6 @@ static fc_status capture_steps(fc_batch_s& B, int chunk, hipStream_t s) {
     FC_HIP(hipGraphDestroy(B.graph));
     B.graph = nullptr;
   }
-  std::lock_guard<std::mutex> lock(capture_mutex());
   FC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   hipError_t e = enqueue_batch_steps(B, chunk, s);
   hipGraph_t g = nullptr;

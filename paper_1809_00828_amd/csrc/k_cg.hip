@@ -870,7 +870,6 @@ static fc_status ensure_graph(fc_precond_s& pc, SolverWs& w, const CoreArgs& a, 
     w.graph = nullptr;
   }
   w.key_prec = -1;
-  std::lock_guard<std::mutex> lock(capture_mutex());
   FC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   hipError_t e = enqueue_steps(pc, w, a.x, chunk, a.precA, a.precS, s, nullptr, a.learn, 1,
                                a.fcg_m);
