@@ -9,7 +9,11 @@
 // 0.86 ms).  Freed buffers are therefore kept for the next build, at most
 // kPoolBytes of them in the process (the oldest go first) and only while a
 // problem is alive; all are given back when the last problem is destroyed or an
-// allocation fails.
+// allocation fails.  A kept buffer goes to its next user without the driver's
+// wait, so only one that the device has done its work on is kept.  Where the wait
+// for that failed, the buffer goes back to the driver, which waits itself; where
+// that fails too (a capture of the calling thread forbids it), the buffer is
+// parked until a later wait succeeds.
 #include <hip/hip_runtime.h>
 
 #include <deque>
@@ -34,6 +38,8 @@ struct Pool {
   std::unordered_map<void*, Block> out;   // handed out
   std::deque<Block> kept;                 // oldest first
   size_t kept_bytes = 0;
+  std::deque<Block> parked;               // perhaps still in use, oldest first
+  uint64_t parked_gone = 0;               // taken off the front of it so far
   int problems = 0;
 };
 
@@ -43,11 +49,50 @@ Pool& pool() {
   return *p;
 }
 
+void park(Pool& P, const Block& b) {
+  try {
+    P.parked.push_back(b);
+  } catch (const std::bad_alloc&) {   // lost rather than handed out in use
+  }
+}
+
+// (hipFree waits for the device; it fails where it may not wait)
+void give_back(Pool& P, const Block& b) {
+  if (hipFree(b.p) != hipSuccess) {
+    (void)hipGetLastError();
+    park(P, b);
+  }
+}
+
 void drop_oldest(Pool& P) {
   const Block b = P.kept.front();
   P.kept.pop_front();
   P.kept_bytes -= b.bytes;
-  (void)hipFree(b.p);
+  give_back(P, b);
+}
+
+void drop_all(Pool& P) {
+  while (!P.kept.empty()) drop_oldest(P);
+  for (size_t k = P.parked.size(); k > 0; --k) {
+    const Block b = P.parked.front();
+    P.parked.pop_front();
+    ++P.parked_gone;
+    give_back(P, b);
+  }
+}
+
+// b is idle: kept for the next build, or given back.
+void keep(Pool& P, const Block& b) {
+  if (P.problems > 0 && b.bytes <= kPoolBytes) {
+    try {
+      P.kept.push_back(b);
+      P.kept_bytes += b.bytes;
+      while (P.kept_bytes > kPoolBytes) drop_oldest(P);
+      return;
+    } catch (const std::bad_alloc&) {
+    }
+  }
+  give_back(P, b);
 }
 
 }  // namespace
@@ -77,9 +122,9 @@ hipError_t pool_malloc(void** p, size_t bytes) {
     }
     P.out.reserve(P.out.size() + 1);
     e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && !P.kept.empty()) {
+    if (e == hipErrorOutOfMemory && !(P.kept.empty() && P.parked.empty())) {
       (void)hipGetLastError();
-      while (!P.kept.empty()) drop_oldest(P);
+      drop_all(P);
       e = hipMalloc(p, bytes);
     }
     if (e == hipSuccess) P.out.emplace(*p, Block{*p, bytes, dev});
@@ -91,7 +136,7 @@ hipError_t pool_malloc(void** p, size_t bytes) {
   }
 }
 
-void pool_free(void* p) {
+void pool_free(void* p, bool idle) {
   if (!p) return;
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
@@ -102,24 +147,39 @@ void pool_free(void* p) {
   }
   const Block b = it->second;
   P.out.erase(it);
-  if (P.problems > 0 && b.bytes <= kPoolBytes) {
-    try {
-      P.kept.push_back(b);
-      P.kept_bytes += b.bytes;
-      while (P.kept_bytes > kPoolBytes) drop_oldest(P);
-      return;
-    } catch (const std::bad_alloc&) {
-    }
-  }
-  (void)hipFree(p);
+  if (idle) keep(P, b);
+  else give_back(P, b);
 }
 
 // hipFree waits for the whole device as hipDeviceSynchronize does, which would
 // also break every graph capture in progress on any thread of the process.
 hipError_t device_idle() {
+  Pool& P = pool();
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  uint64_t end;   // what is parked from here on may come after the wait
+  {
+    std::lock_guard<std::mutex> lock(P.mu);
+    end = P.parked_gone + P.parked.size();
+  }
   void* p = nullptr;
-  const hipError_t e = hipMalloc(&p, 256);
-  return e == hipSuccess ? hipFree(p) : e;
+  e = hipMalloc(&p, 256);
+  if (e == hipSuccess) e = hipFree(p);
+  std::lock_guard<std::mutex> lock(P.mu);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (p) park(P, Block{p, 256, dev});
+    return e;
+  }
+  for (uint64_t k = P.parked_gone; k < end; ++k) {
+    const Block b = P.parked.front();
+    P.parked.pop_front();
+    ++P.parked_gone;
+    if (b.device == dev) keep(P, b);
+    else park(P, b);
+  }
+  return hipSuccess;
 }
 
 void pool_problem_created() {
@@ -131,8 +191,7 @@ void pool_problem_created() {
 void pool_problem_destroyed() {
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
-  if (--P.problems > 0) return;
-  while (!P.kept.empty()) drop_oldest(P);
+  if (--P.problems == 0) drop_all(P);
 }
 
 }  // namespace fc

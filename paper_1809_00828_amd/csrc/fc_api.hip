@@ -79,8 +79,8 @@ struct Scratch {
     return st;
   }
   ~Scratch() {
-    (void)hipStreamSynchronize(s);
-    for (void* q : p) pool_free(q);
+    const bool idle = hipStreamSynchronize(s) == hipSuccess;
+    for (void* q : p) pool_free(q, idle);
   }
 };
 
@@ -106,14 +106,14 @@ static void free_precond(fc_precond_s* pc) {
   // buffers that are kept for reuse must be idle on every stream
   int dev = 0;
   const bool other = hipGetDevice(&dev) == hipSuccess && dev != pc->device;
-  if (other) (void)hipSetDevice(pc->device);
-  (void)device_idle();
-  solver_ws_destroy(pc->ws);
+  const bool there = !other || hipSetDevice(pc->device) == hipSuccess;
+  const bool idle = there && device_idle() == hipSuccess;
+  solver_ws_destroy(pc->ws, idle);
   coarse_destroy(pc->coarse);
   for (void* p : {(void*)pc->block_elem, (void*)pc->bnodes, (void*)pc->Q, (void*)pc->Q32,
                   (void*)pc->unsafe32, (void*)pc->unsafe_flag32, (void*)pc->Lbf, (void*)pc->isd,
                   (void*)pc->inv_ptr, (void*)pc->inv_idx, (void*)pc->fallback, (void*)pc->y})
-    pool_free(p);
+    pool_free(p, idle);
   if (other) (void)hipSetDevice(dev);
   delete pc;
 }

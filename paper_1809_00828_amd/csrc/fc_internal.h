@@ -160,9 +160,10 @@ inline SellView sell_view(const DeviceBsr& A) {
 }
 
 // Device memory that outlives no problem but is reused from one preconditioner
-// to the next (dev_pool.hip).  pool_free: nothing on the device uses p any more.
+// to the next (dev_pool.hip).  pool_free: idle says that nothing on the device uses
+// p any more; without it p is not kept, or not before device_idle() has succeeded.
 hipError_t pool_malloc(void** p, size_t bytes);
-void pool_free(void* p);
+void pool_free(void* p, bool idle);
 void pool_problem_created();
 void pool_problem_destroyed();
 
@@ -178,7 +179,7 @@ struct AlphaIn {
 };
 
 struct SolverWs;
-void solver_ws_destroy(SolverWs* ws);
+void solver_ws_destroy(SolverWs* ws, bool idle);   // idle: as pool_free
 struct CoarseCtx;
 void coarse_destroy(CoarseCtx* c);
 

@@ -75,14 +75,14 @@ struct SolverWs {
   int ring_cap = 0;
 };
 
-void solver_ws_destroy(SolverWs* w) {
+void solver_ws_destroy(SolverWs* w, bool idle) {
   if (!w) return;
   if (w->exec) (void)hipGraphExecDestroy(w->exec);
   if (w->graph) (void)hipGraphDestroy(w->graph);
   for (void* p : {(void*)w->r, (void*)w->z, (void*)w->p, (void*)w->q, (void*)w->t, (void*)w->d,
                   (void*)w->ro, (void*)w->partial, (void*)w->ring, (void*)w->ring_part,
                   (void*)w->p32, (void*)w->fr, (void*)w->sc})
-    pool_free(p);
+    pool_free(p, idle);
   if (w->host) (void)hipHostFree(w->host);
   for (auto& e : w->ev) if (e) (void)hipEventDestroy(e);
   for (auto& e : w->tev) if (e) (void)hipEventDestroy(e);
@@ -676,8 +676,8 @@ static fc_status ensure_ring(SolverWs& w, int m) {
   }
   w.key_prec = -1;
   FC_HIP(device_idle());
-  pool_free(w.ring);
-  pool_free(w.ring_part);
+  pool_free(w.ring, true);
+  pool_free(w.ring_part, true);
   w.ring = nullptr;
   w.ring_part = nullptr;
   w.ring_cap = 0;
