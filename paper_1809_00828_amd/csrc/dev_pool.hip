@@ -9,7 +9,7 @@
 // 0.86 ms).  Freed buffers are therefore kept for the next build, at most
 // kPoolBytes of them in the process (the oldest go first) and only while a
 // problem is alive; all are given back when the last problem is destroyed or an
-// allocation fails.  A kept buffer goes to its next user without the driver's
+// allocation of the library, of kept memory or not (dev_malloc), fails.  A kept buffer goes to its next user without the driver's
 // wait, so only one that the device has done its work on is kept.  Where the wait
 // for that failed, the buffer goes back to the driver, which waits itself; where
 // that fails too (a capture of the calling thread forbids it), the buffer is
@@ -95,7 +95,26 @@ void keep(Pool& P, const Block& b) {
   give_back(P, b);
 }
 
+hipError_t malloc_or_drop(Pool& P, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && !(P.kept.empty() && P.parked.empty())) {
+    (void)hipGetLastError();
+    drop_all(P);
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 }  // namespace
+
+hipError_t dev_malloc(void** p, size_t bytes) {
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  return malloc_or_drop(P, p, bytes);
+}
 
 hipError_t pool_malloc(void** p, size_t bytes) {
   *p = nullptr;
@@ -121,12 +140,7 @@ hipError_t pool_malloc(void** p, size_t bytes) {
       return hipSuccess;
     }
     P.out.reserve(P.out.size() + 1);
-    e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && !(P.kept.empty() && P.parked.empty())) {
-      (void)hipGetLastError();
-      drop_all(P);
-      e = hipMalloc(p, bytes);
-    }
+    e = malloc_or_drop(P, p, bytes);
     if (e == hipSuccess) P.out.emplace(*p, Block{*p, bytes, dev});
     return e;
   } catch (const std::bad_alloc&) {

@@ -36,7 +36,7 @@ template <bool kPool = false, class T>
 static fc_status dev_alloc(T** p, size_t count) {
   *p = nullptr;
   if (count == 0) return FC_OK;
-  hipError_t e = kPool ? pool_malloc((void**)p, count * sizeof(T)) : hipMalloc(p, count * sizeof(T));
+  hipError_t e = kPool ? pool_malloc((void**)p, count * sizeof(T)) : dev_malloc(p, count * sizeof(T));
   if (e != hipSuccess) {
     set_error(std::string("hipMalloc of ") + std::to_string(count * sizeof(T)) +
               " bytes failed: " + hipGetErrorString(e));

@@ -159,6 +159,14 @@ inline SellView sell_view(const DeviceBsr& A) {
   return v;
 }
 
+// hipMalloc for everything else the library holds: out of memory, the buffers kept
+// for reuse are given back first.
+hipError_t dev_malloc(void** p, size_t bytes);
+template <class T>
+hipError_t dev_malloc(T** p, size_t bytes) {
+  return dev_malloc(reinterpret_cast<void**>(p), bytes);
+}
+
 // Device memory that outlives no problem but is reused from one preconditioner
 // to the next (dev_pool.hip).  pool_free: idle says that nothing on the device uses
 // p any more; without it p is not kept, or not before device_idle() has succeeded.

@@ -71,11 +71,11 @@ fc_status fc_model_create(const int32_t* ch, int32_t in_ch, const float* params,
   Net& net = m->net;
   net.init(ch, in_ch);
   const size_t n = (size_t)net.nparam;
-  FC_HIP(hipMalloc(&net.p, n * sizeof(float)));
-  FC_HIP(hipMalloc(&net.wpk, (size_t)net.nwpk * sizeof(uint16_t)));
-  FC_HIP(hipMalloc(&net.g, n * sizeof(float)));
-  FC_HIP(hipMalloc(&net.m, n * sizeof(float)));
-  FC_HIP(hipMalloc(&net.v, n * sizeof(float)));
+  FC_HIP(dev_malloc(&net.p, n * sizeof(float)));
+  FC_HIP(dev_malloc(&net.wpk, (size_t)net.nwpk * sizeof(uint16_t)));
+  FC_HIP(dev_malloc(&net.g, n * sizeof(float)));
+  FC_HIP(dev_malloc(&net.m, n * sizeof(float)));
+  FC_HIP(dev_malloc(&net.v, n * sizeof(float)));
   FC_HIP(hipMemcpy(net.p, params, n * sizeof(float), hipMemcpyHostToDevice));
   FC_HIP(hipMemset(net.m, 0, n * sizeof(float)));
   FC_HIP(hipMemset(net.v, 0, n * sizeof(float)));
@@ -145,8 +145,8 @@ fc_status fc_model_train(fc_model m, int64_t n_samples, int32_t grid, const floa
   const int in_ch = m->net.in_ch;
   float* xb = nullptr;
   float* tb = nullptr;
-  FC_HIP(hipMalloc(&xb, (size_t)B * in_ch * vox * sizeof(float)));
-  FC_HIP(hipMalloc(&tb, (size_t)B * vox * sizeof(float)));
+  FC_HIP(dev_malloc(&xb, (size_t)B * in_ch * vox * sizeof(float)));
+  FC_HIP(dev_malloc(&tb, (size_t)B * vox * sizeof(float)));
   const int64_t steps_per_epoch = n_samples / B;
   fc_status st = FC_OK;
   for (int ep = 0; ep < opts->epochs && st == FC_OK; ++ep) {

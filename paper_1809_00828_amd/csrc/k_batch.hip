@@ -775,7 +775,7 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
       *d = nullptr;
     }
     if (v.empty()) return FC_OK;
-    FC_HIP(hipMalloc(d, v.size() * sizeof(WorkItem)));
+    FC_HIP(dev_malloc(d, v.size() * sizeof(WorkItem)));
     FC_HIP(hipMemcpy(*d, v.data(), v.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
     return FC_OK;
   };
@@ -784,17 +784,17 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
   FC_TRY_B(upload_items(B.pull_items, &B.d_pull));
   FC_TRY_B(upload_items(B.wide_items, &B.d_wide));
   const int64_t n = B.total_dofs;
-  FC_HIP(hipMalloc(&B.r, n * sizeof(double)));
-  FC_HIP(hipMalloc(&B.z, n * sizeof(double)));
-  FC_HIP(hipMalloc(&B.p, n * sizeof(double)));
-  FC_HIP(hipMalloc(&B.q, n * sizeof(double)));
+  FC_HIP(dev_malloc(&B.r, n * sizeof(double)));
+  FC_HIP(dev_malloc(&B.z, n * sizeof(double)));
+  FC_HIP(dev_malloc(&B.p, n * sizeof(double)));
+  FC_HIP(dev_malloc(&B.q, n * sizeof(double)));
   // three per pull tile, then (p, q) per wide tile
   const int64_t plen = 3 * (int64_t)B.pull_items.size() + (int64_t)B.wide_items.size();
-  FC_HIP(hipMalloc(&B.partial, std::max<int64_t>(plen, 1) * sizeof(double)));
-  FC_HIP(hipMalloc(&B.sc, nprob * sizeof(CgScalars)));
+  FC_HIP(dev_malloc(&B.partial, std::max<int64_t>(plen, 1) * sizeof(double)));
+  FC_HIP(dev_malloc(&B.sc, nprob * sizeof(CgScalars)));
   FC_HIP(hipMemset(B.sc, 0, nprob * sizeof(CgScalars)));
   FC_HIP(hipHostMalloc(&B.host_sc, nprob * sizeof(CgScalars), hipHostMallocDefault));
-  FC_HIP(hipMalloc(&B.d_probs, nprob * sizeof(BProb)));
+  FC_HIP(dev_malloc(&B.d_probs, nprob * sizeof(BProb)));
   FC_HIP(hipMemcpy(B.d_probs, B.host.data(), nprob * sizeof(BProb), hipMemcpyHostToDevice));
   FC_HIP(hipEventRecord(B.ev[0], user));
   FC_HIP(hipStreamWaitEvent(s, B.ev[0], 0));
@@ -840,12 +840,12 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
   }
   B.report = rep.str();
   for (auto& c : B.spmv)
-    if (!c.items.empty()) FC_HIP(hipMalloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
+    if (!c.items.empty()) FC_HIP(dev_malloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
   for (auto& c : B.schw)
-    if (!c.items.empty()) FC_HIP(hipMalloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
-  if (!B.sell.empty()) FC_HIP(hipMalloc(&B.d_act_sell, B.sell.size() * sizeof(SellItem)));
-  FC_HIP(hipMalloc(&B.d_act_pull, B.pull_items.size() * sizeof(WorkItem)));
-  FC_HIP(hipMalloc(&B.d_act_wide, B.wide_items.size() * sizeof(WorkItem)));
+    if (!c.items.empty()) FC_HIP(dev_malloc(&c.d_act, c.items.size() * sizeof(WorkItem)));
+  if (!B.sell.empty()) FC_HIP(dev_malloc(&B.d_act_sell, B.sell.size() * sizeof(SellItem)));
+  FC_HIP(dev_malloc(&B.d_act_pull, B.pull_items.size() * sizeof(WorkItem)));
+  FC_HIP(dev_malloc(&B.d_act_wide, B.wide_items.size() * sizeof(WorkItem)));
   B.act_dofs = -1;   // lists not built yet
   FC_HIP(hipStreamSynchronize(s));
   *out = bt.release();

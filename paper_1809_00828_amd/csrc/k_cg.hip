@@ -1017,7 +1017,7 @@ static fc_status ensure_mixed_matrix(fc_problem_s& pb, hipStream_t s) {
   for (int64_t r = 0; r < nr; ++r) (hi[r] ? rh : rl).push_back((int32_t)r);
   auto up = [&](const std::vector<int32_t>& v, int32_t** d) -> fc_status {
     if (v.empty()) return FC_OK;
-    FC_HIP(hipMalloc(d, v.size() * sizeof(int32_t)));
+    FC_HIP(dev_malloc(d, v.size() * sizeof(int32_t)));
     FC_HIP(hipMemcpyAsync(*d, v.data(), v.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     return FC_OK;
   };
@@ -1025,7 +1025,7 @@ static fc_status ensure_mixed_matrix(fc_problem_s& pb, hipStream_t s) {
   FC_TRY_ST(up(rl, &A.rows_lo));
   A.n_hi = (int64_t)rh.size();
   A.n_lo = (int64_t)rl.size();
-  FC_HIP(hipMalloc(&A.val32, A.nnzb * A.bdim * A.bdim * sizeof(float)));
+  FC_HIP(dev_malloc(&A.val32, A.nnzb * A.bdim * A.bdim * sizeof(float)));
   FC_HIP(launch_cast_matrix(A, s));
   FC_HIP(hipStreamSynchronize(s));   // the host lists must outlive the copies
   return FC_OK;
@@ -1340,7 +1340,7 @@ extern "C" fc_status fc_learned_validate(fc_precond pc, const double* b, double 
   hipStream_t user = (hipStream_t)stream;
   const int64_t n = pc->pb->n_dofs;
   double* x = nullptr;
-  FC_HIP(hipMalloc(&x, n * sizeof(double)));
+  FC_HIP(dev_malloc(&x, n * sizeof(double)));
   fc_solve_opts o{tol, 300000, FC_STOP_RESIDUAL, FC_MODE_F64, 16, 1e-4, nullptr, 0};
   fc_solve_info ip{}, il{};
   pc->coarse->enabled = 1;

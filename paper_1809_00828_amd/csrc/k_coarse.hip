@@ -465,9 +465,9 @@ hipError_t coarse_snapshot(CoarseCtx& c, const double* r, const double* xs, cons
 fc_status coarse_snapshot_projection(CoarseCtx& c, const double* r, float* xin_out,
                                      float* t_out, double tol, int64_t maxit, hipStream_t s) {
   const int64_t nv = c.nvox;
-  if (!c.cg) FC_HIP(hipMalloc(&c.cg, 5 * nv * sizeof(double)));
+  if (!c.cg) FC_HIP(dev_malloc(&c.cg, 5 * nv * sizeof(double)));
   if (!c.cs) {
-    FC_HIP(hipMalloc(&c.cs, sizeof(CoarseCg)));
+    FC_HIP(dev_malloc(&c.cs, sizeof(CoarseCg)));
     FC_HIP(hipMemsetAsync(c.cs, 0, sizeof(CoarseCg), s));
   }
   FC_HIP(coarse_restrict(c, r, xin_out, nullptr, s));
@@ -571,12 +571,12 @@ fc_status coarse_create(fc_precond_s& pc, hipStream_t s, CoarseCtx** out) {
   c->n1 = (int64_t)pb.p * pb.n + 1;
   c->nvox = (int64_t)c->G * c->G * c->G;
   const int64_t nvox = c->nvox;
-  FC_HIP(hipMalloc(&c->Ac, 27 * nvox * sizeof(double)));
-  FC_HIP(hipMalloc(&c->xin, 2 * nvox * sizeof(float)));
-  FC_HIP(hipMalloc(&c->mask, nvox * sizeof(float)));
-  FC_HIP(hipMalloc(&c->rc, nvox * sizeof(double)));
-  FC_HIP(hipMalloc(&c->partial, 2 * kCoarsePartials * sizeof(double)));
-  FC_HIP(hipMalloc(&c->ls, sizeof(LearnScalars)));
+  FC_HIP(dev_malloc(&c->Ac, 27 * nvox * sizeof(double)));
+  FC_HIP(dev_malloc(&c->xin, 2 * nvox * sizeof(float)));
+  FC_HIP(dev_malloc(&c->mask, nvox * sizeof(float)));
+  FC_HIP(dev_malloc(&c->rc, nvox * sizeof(double)));
+  FC_HIP(dev_malloc(&c->partial, 2 * kCoarsePartials * sizeof(double)));
+  FC_HIP(dev_malloc(&c->ls, sizeof(LearnScalars)));
   FC_HIP(hipMemsetAsync(c->ls, 0, sizeof(LearnScalars), s));
   FC_HIP(hipMemsetAsync(c->Ac, 0, 27 * nvox * sizeof(double), s));
   std::vector<float> eta_c, mask;
@@ -588,9 +588,9 @@ fc_status coarse_create(fc_precond_s& pc, hipStream_t s, CoarseCtx** out) {
   double *u = nullptr, *t = nullptr;
   float* yc = nullptr;
   const int64_t nd = pb.n_dofs;
-  FC_HIP(hipMalloc(&u, nd * sizeof(double)));
-  FC_HIP(hipMalloc(&t, nd * sizeof(double)));
-  FC_HIP(hipMalloc(&yc, nvox * sizeof(float)));
+  FC_HIP(dev_malloc(&u, nd * sizeof(double)));
+  FC_HIP(dev_malloc(&t, nd * sizeof(double)));
+  FC_HIP(dev_malloc(&yc, nvox * sizeof(float)));
   const double one = 1.0;
   FC_HIP(hipMemcpyAsync(&c->ls->gamma, &one, sizeof(double), hipMemcpyHostToDevice, s));
   hipError_t e = hipSuccess;

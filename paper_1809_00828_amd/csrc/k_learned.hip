@@ -859,9 +859,9 @@ fc_status NetWs::ensure(const Net& net, int B_, int N0) {
   // a smaller batch may be cut into more ranges of some layers
   wslots = 0;
   for (int b = 1; b <= B; ++b) wslots = std::max(wslots, wgrad_plan(net, N, b).floats);
-  hipError_t e = hipMalloc(&buf, total * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(&partial, 1024 * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&wpart, (size_t)wslots * sizeof(float));
+  hipError_t e = dev_malloc(&buf, total * sizeof(float));
+  if (e == hipSuccess) e = dev_malloc(&partial, 1024 * sizeof(double));
+  if (e == hipSuccess) e = dev_malloc(&wpart, (size_t)wslots * sizeof(float));
   if (e != hipSuccess) {
     release();
     set_error("network workspace allocation failed");

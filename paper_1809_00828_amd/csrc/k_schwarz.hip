@@ -323,7 +323,7 @@ hipError_t schwarz_check_cells(const fc_problem_s& pb, const PullLattice L, bool
                                hipStream_t s) {
   *ok = false;
   unsigned long long* bad = nullptr;
-  hipError_t e = hipMalloc(&bad, sizeof(*bad));
+  hipError_t e = dev_malloc(&bad, sizeof(*bad));
   if (e != hipSuccess) return e;
   unsigned long long hbad = 1;
   e = hipMemsetAsync(bad, 0, sizeof(*bad), s);

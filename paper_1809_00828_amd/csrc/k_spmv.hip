@@ -480,8 +480,8 @@ static hipError_t spmv_build_sell(DeviceBsr& A, hipStream_t s) {
     for (int d = 0; d < lat.dim; ++d) len *= e.sl.cls >> d & 1 ? 2 * p + 1 : p + 1;
     off += len;
   }
-  hipError_t e = hipMalloc(&A.sell_val, (size_t)off * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&A.sell_slices, slices.size() * sizeof(SellSlice));
+  hipError_t e = dev_malloc(&A.sell_val, (size_t)off * sizeof(double));
+  if (e == hipSuccess) e = dev_malloc(&A.sell_slices, slices.size() * sizeof(SellSlice));
   if (e == hipSuccess)
     e = hipMemcpyAsync(A.sell_slices, slices.data(), slices.size() * sizeof(SellSlice),
                        hipMemcpyHostToDevice, s);
@@ -536,7 +536,7 @@ hipError_t spmv_enable_lattice(DeviceBsr& A, int dim, int n1, int p, hipStream_t
   for (int k = 0; k < dim; ++k) nodes *= n1;
   if (nodes != A.n_rows) return hipSuccess;
   unsigned long long* bad = nullptr;
-  hipError_t e = hipMalloc(&bad, sizeof(*bad));
+  hipError_t e = dev_malloc(&bad, sizeof(*bad));
   if (e != hipSuccess) return e;
   unsigned long long hbad = 1;
   const LatticeInfo lat = make_lattice_info(dim, n1, p);

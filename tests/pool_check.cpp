@@ -86,11 +86,25 @@ static void out_of_memory() {
   pool_problem_destroyed();
 }
 
+// .. and for memory that is not itself kept
+static void out_of_memory_elsewhere() {
+  pool_problem_created();
+  const size_t old = stub::budget;
+  stub::budget = stub::used + 10 * kMB;
+  pool_free(get(4 * kMB), true);
+  double* d = nullptr;
+  CHECK(dev_malloc(&d, 9 * kMB) == hipSuccess && d);
+  CHECK(dev_malloc(&d, 9 * kMB) == hipErrorOutOfMemory && !d);
+  stub::budget = old;
+  pool_problem_destroyed();
+}
+
 int main() {
   reuse();
   failed_wait();
   parked_to_the_end();
   out_of_memory();
+  out_of_memory_elsewhere();
   std::printf("failures %d\n", bad);
   return bad ? 1 : 0;
 }
