@@ -196,6 +196,30 @@ hipError_t device_idle() {
   return hipSuccess;
 }
 
+hipError_t own_stream(hipStream_t* s) {
+  constexpr int kDevices = 64;
+  static std::mutex mu;
+  static hipStream_t streams[kDevices] = {};
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!streams[dev]) {
+    const hipError_t c = hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking);
+    if (c != hipSuccess) return c;
+  }
+  *s = streams[dev];
+  return hipSuccess;
+}
+
+hipError_t copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+  hipStream_t s;
+  hipError_t e = own_stream(&s);
+  if (e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, kind, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+
 void pool_problem_created() {
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);

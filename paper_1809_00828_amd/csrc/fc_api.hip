@@ -46,19 +46,10 @@ static fc_status dev_alloc(T** p, size_t count) {
   return FC_OK;
 }
 
-template <class T>
-static fc_status upload(T** p, const T* src, size_t count) {
-  fc_status st = dev_alloc(p, count);
-  if (st != FC_OK || count == 0) return st;
-  FC_HIP(hipMemcpy(*p, src, count * sizeof(T), hipMemcpyHostToDevice));
-  return FC_OK;
-}
-
-// The same from the kept memory, on the caller's stream: a copy on the legacy
-// stream would break the graph capture of a solve in another thread.
-template <class T>
+// src on the device, copied on the caller's stream (kPool: as dev_alloc).
+template <bool kPool = false, class T>
 static fc_status upload(T** p, const T* src, size_t count, hipStream_t s) {
-  fc_status st = dev_alloc<true>(p, count);
+  fc_status st = dev_alloc<kPool>(p, count);
   if (st != FC_OK || count == 0) return st;
   FC_HIP(hipMemcpyAsync(*p, src, count * sizeof(T), hipMemcpyHostToDevice, s));
   FC_HIP(hipStreamSynchronize(s));
@@ -139,11 +130,11 @@ static fc_status upload_system_body(const HostSystem& S, hipStream_t stream, fc_
   int32_t mr = 0;
   for (int64_t i = 0; i < S.n_nodes; ++i) mr = std::max(mr, S.rowptr[i + 1] - S.rowptr[i]);
   pb->A.max_row = mr;
-  FC_TRY(upload(&pb->A.rowptr, S.rowptr.data(), S.rowptr.size()));
-  FC_TRY(upload(&pb->A.col, S.col.data(), S.col.size()));
-  FC_TRY(upload(&pb->A.val, S.val.data(), S.val.size()));
-  FC_TRY(upload(&pb->rhs, S.rhs.data(), S.rhs.size()));
-  FC_TRY(upload(&pb->elem_nodes, S.elem_nodes.data(), S.elem_nodes.size()));
+  FC_TRY(upload(&pb->A.rowptr, S.rowptr.data(), S.rowptr.size(), stream));
+  FC_TRY(upload(&pb->A.col, S.col.data(), S.col.size(), stream));
+  FC_TRY(upload(&pb->A.val, S.val.data(), S.val.size(), stream));
+  FC_TRY(upload(&pb->rhs, S.rhs.data(), S.rhs.size(), stream));
+  FC_TRY(upload(&pb->elem_nodes, S.elem_nodes.data(), S.elem_nodes.size(), stream));
   FC_TRY(dev_alloc(&pb->diag, (size_t)S.n_dofs));
   pb->eta = S.eta;
   pb->elem_nodes_host = S.elem_nodes;
@@ -376,13 +367,13 @@ fc_status fc_get_eta(fc_problem pb, double* eta_host) {
 fc_status fc_export(fc_problem pb, int32_t* rowptr, int32_t* col, double* val, int32_t* elem_dofs) {
   if (!pb) return FC_E_ARG;
   std::vector<int32_t> rp(pb->A.n_rows + 1);
-  FC_HIP(hipMemcpy(rp.data(), pb->A.rowptr, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+  FC_HIP(copy_now(rp.data(), pb->A.rowptr, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
   if (rowptr) std::memcpy(rowptr, rp.data(), rp.size() * sizeof(int32_t));
-  if (col) FC_HIP(hipMemcpy(col, pb->A.col, pb->A.nnzb * sizeof(int32_t), hipMemcpyDeviceToHost));
+  if (col) FC_HIP(copy_now(col, pb->A.col, pb->A.nnzb * sizeof(int32_t), hipMemcpyDeviceToHost));
   if (val) {
     const int bb = pb->bdim * pb->bdim;
     std::vector<double> soa((size_t)pb->A.nnzb * bb);
-    FC_HIP(hipMemcpy(soa.data(), pb->A.val, soa.size() * sizeof(double), hipMemcpyDeviceToHost));
+    FC_HIP(copy_now(soa.data(), pb->A.val, soa.size() * sizeof(double), hipMemcpyDeviceToHost));
     soa_to_rowmajor(rp, soa.data(), pb->bdim, pb->A.n_rows, val);
   }
   if (elem_dofs)
@@ -496,8 +487,8 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     set_error("fc_precond_build: too many block entries for int32 indices");
     return FC_E_UNSUPPORTED;
   }
-  if (patch) FC_TRY(upload(&pc->bnodes, pnodes.data(), pnodes.size(), s));
-  FC_TRY(upload(&pc->block_elem, blocks.data(), blocks.size(), s));
+  if (patch) FC_TRY(upload<true>(&pc->bnodes, pnodes.data(), pnodes.size(), s));
+  FC_TRY(upload<true>(&pc->block_elem, blocks.data(), blocks.size(), s));
   // lattice problem with every cell a block: the pull finds a node's blocks
   // from its lattice indices, and the block products of scalar problems a row's
   // unknown (FC_PULL_LATTICE=0 keeps the node lists and the node-to-block map)
@@ -584,7 +575,7 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
     for (int64_t k = 0; k < nb; ++k)
       if (hf[k]) list.push_back((int32_t)k);
     pc->n_unsafe32 = (int64_t)list.size();
-    if (!list.empty()) FC_TRY(upload(&pc->unsafe32, list.data(), list.size(), s));
+    if (!list.empty()) FC_TRY(upload<true>(&pc->unsafe32, list.data(), list.size(), s));
   }
   // BF16: scaled Cholesky factors (positive semi-definite however rounded)
   const size_t ln = (size_t)nb * ((size_t)m * (m + 1) / 2);
@@ -666,7 +657,7 @@ fc_status fc_get_block_inverse(fc_precond pc, int64_t k, double* out_host) {
   const int64_t per = sym_block_stride(m);
   try {
     std::vector<double> q((size_t)per);
-    FC_HIP(hipMemcpy(q.data(), pc->Q + k * per, per * sizeof(double), hipMemcpyDeviceToHost));
+    FC_HIP(copy_now(q.data(), pc->Q + k * per, per * sizeof(double), hipMemcpyDeviceToHost));
     for (int i = 0; i < m; ++i)
       for (int j = 0; j < m; ++j) out_host[(int64_t)i * m + j] = q[sym_entry(i, j, m)];
   } catch (const std::bad_alloc&) {

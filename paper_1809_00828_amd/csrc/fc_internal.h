@@ -175,6 +175,13 @@ void pool_free(void* p, bool idle);
 void pool_problem_created();
 void pool_problem_destroyed();
 
+// The current device's stream for copies of calls that take none (made once, held
+// until the process ends).  Work on the legacy stream would break every graph
+// capture in progress in the process, and fail itself.
+hipError_t own_stream(hipStream_t* s);
+// Copy on it, done when this returns.  Waits for no other stream.
+hipError_t copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
+
 // Waits for all work on the device; graph captures in progress on other threads
 // (and, in relaxed mode, on this one) go on.
 hipError_t device_idle();

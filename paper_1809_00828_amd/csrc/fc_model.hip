@@ -76,26 +76,32 @@ fc_status fc_model_create(const int32_t* ch, int32_t in_ch, const float* params,
   FC_HIP(dev_malloc(&net.g, n * sizeof(float)));
   FC_HIP(dev_malloc(&net.m, n * sizeof(float)));
   FC_HIP(dev_malloc(&net.v, n * sizeof(float)));
-  FC_HIP(hipMemcpy(net.p, params, n * sizeof(float), hipMemcpyHostToDevice));
-  FC_HIP(hipMemset(net.m, 0, n * sizeof(float)));
-  FC_HIP(hipMemset(net.v, 0, n * sizeof(float)));
-  FC_HIP(net_sync_bf16(net, nullptr));
-  FC_HIP(hipDeviceSynchronize());
+  hipStream_t s;
+  FC_HIP(own_stream(&s));
+  FC_HIP(hipMemcpyAsync(net.p, params, n * sizeof(float), hipMemcpyHostToDevice, s));
+  FC_HIP(hipMemsetAsync(net.m, 0, n * sizeof(float), s));
+  FC_HIP(hipMemsetAsync(net.v, 0, n * sizeof(float), s));
+  FC_HIP(net_sync_bf16(net, s));
+  FC_HIP(hipStreamSynchronize(s));
   *out = m.release();
   return FC_OK;
 }
 
 fc_status fc_model_get_params(fc_model m, float* params) {
   if (!m || !params) return FC_E_ARG;
-  FC_HIP(hipMemcpy(params, m->net.p, m->net.nparam * sizeof(float), hipMemcpyDeviceToHost));
+  FC_HIP(device_idle());   // what still writes them is done
+  FC_HIP(copy_now(params, m->net.p, m->net.nparam * sizeof(float), hipMemcpyDeviceToHost));
   return FC_OK;
 }
 
 fc_status fc_model_set_params(fc_model m, const float* params) {
   if (!m || !params) return FC_E_ARG;
-  FC_HIP(hipMemcpy(m->net.p, params, m->net.nparam * sizeof(float), hipMemcpyHostToDevice));
-  FC_HIP(net_sync_bf16(m->net, nullptr));
-  FC_HIP(hipDeviceSynchronize());
+  hipStream_t s;
+  FC_HIP(own_stream(&s));
+  FC_HIP(device_idle());   // what still reads the old ones is done
+  FC_HIP(hipMemcpyAsync(m->net.p, params, m->net.nparam * sizeof(float), hipMemcpyHostToDevice, s));
+  FC_HIP(net_sync_bf16(m->net, s));
+  FC_HIP(hipStreamSynchronize(s));
   return FC_OK;
 }
 
@@ -125,8 +131,11 @@ fc_status fc_model_loss_grad(fc_model m, int32_t batch, int32_t grid, const floa
   FC_HIP(net_backward(m->net, m->ws, x_dev, m->ws.gy(), batch, s));
   const double l = sum_partials_host(m->ws.partial, s) / (double)n;
   if (loss) *loss = l;
-  if (grad_host)
-    FC_HIP(hipMemcpy(grad_host, m->net.g, m->net.nparam * sizeof(float), hipMemcpyDeviceToHost));
+  if (grad_host) {
+    FC_HIP(hipMemcpyAsync(grad_host, m->net.g, m->net.nparam * sizeof(float),
+                          hipMemcpyDeviceToHost, s));
+    FC_HIP(hipStreamSynchronize(s));
+  }
   return FC_OK;
 }
 

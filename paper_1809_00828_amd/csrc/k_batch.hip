@@ -742,7 +742,9 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
     const SellView& v = B.host[k].sell;
     if (v.n_slices == 0) continue;
     std::vector<SellSlice> sl(v.n_slices);
-    FC_HIP(hipMemcpy(sl.data(), v.slices, sl.size() * sizeof(SellSlice), hipMemcpyDeviceToHost));
+    FC_HIP(hipMemcpyAsync(sl.data(), v.slices, sl.size() * sizeof(SellSlice),
+                          hipMemcpyDeviceToHost, s));
+    FC_HIP(hipStreamSynchronize(s));
     for (const SellSlice& x : sl) B.sell.push_back({x, k, problems[k]->A.lat.p});
   }
   for (size_t c = 0; c < B.spmv.size(); ++c) build_spmv_items(B.spmv[c], (int)c);
@@ -776,7 +778,8 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
     }
     if (v.empty()) return FC_OK;
     FC_HIP(dev_malloc(d, v.size() * sizeof(WorkItem)));
-    FC_HIP(hipMemcpy(*d, v.data(), v.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
+    FC_HIP(hipMemcpyAsync(*d, v.data(), v.size() * sizeof(WorkItem), hipMemcpyHostToDevice, s));
+    FC_HIP(hipStreamSynchronize(s));
     return FC_OK;
   };
   for (auto& c : B.spmv) FC_TRY_B(upload_items(c.items, &c.d_items));
@@ -792,10 +795,11 @@ static fc_status batch_create_body(int32_t nprob, const fc_problem* problems,
   const int64_t plen = 3 * (int64_t)B.pull_items.size() + (int64_t)B.wide_items.size();
   FC_HIP(dev_malloc(&B.partial, std::max<int64_t>(plen, 1) * sizeof(double)));
   FC_HIP(dev_malloc(&B.sc, nprob * sizeof(CgScalars)));
-  FC_HIP(hipMemset(B.sc, 0, nprob * sizeof(CgScalars)));
+  FC_HIP(hipMemsetAsync(B.sc, 0, nprob * sizeof(CgScalars), s));
   FC_HIP(hipHostMalloc(&B.host_sc, nprob * sizeof(CgScalars), hipHostMallocDefault));
   FC_HIP(dev_malloc(&B.d_probs, nprob * sizeof(BProb)));
-  FC_HIP(hipMemcpy(B.d_probs, B.host.data(), nprob * sizeof(BProb), hipMemcpyHostToDevice));
+  FC_HIP(hipMemcpyAsync(B.d_probs, B.host.data(), nprob * sizeof(BProb), hipMemcpyHostToDevice, s));
+  FC_HIP(hipStreamSynchronize(s));
   FC_HIP(hipEventRecord(B.ev[0], user));
   FC_HIP(hipStreamWaitEvent(s, B.ev[0], 0));
 
@@ -894,7 +898,9 @@ static fc_status compact_lists(fc_batch_s& B, const std::vector<char>& running) 
     for (const auto& w : all)
       if (running[w.prob]) v.push_back(w);
     *n = (int)v.size();
-    if (!v.empty()) FC_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(*d), hipMemcpyHostToDevice));
+    if (v.empty()) return FC_OK;
+    FC_HIP(hipMemcpyAsync(d, v.data(), v.size() * sizeof(*d), hipMemcpyHostToDevice, B.stream));
+    FC_HIP(hipStreamSynchronize(B.stream));   // the host list dies here
     return FC_OK;
   };
   FC_TRY_B(filter(B.sell, B.d_act_sell, &B.n_act_sell));

@@ -642,7 +642,8 @@ fc_status fc_learned_attach(fc_precond pc, fc_model m) {
     set_error("fc_learned_attach: NULL preconditioner");
     return FC_E_ARG;
   }
-  hipStream_t s = nullptr;
+  hipStream_t s;
+  FC_HIP(own_stream(&s));
   fc_status st = ensure_coarse(pc, s);
   if (st != FC_OK) return st;
   CoarseCtx& c = *pc->coarse;
@@ -655,14 +656,17 @@ fc_status fc_learned_attach(fc_precond pc, fc_model m) {
   }
   // a captured solver chunk holds the old network buffers
   solver_invalidate_graph(*pc);
-  FC_HIP(hipMemset(c.ls, 0, sizeof(LearnScalars)));
-  FC_HIP(hipDeviceSynchronize());
+  FC_HIP(device_idle());   // what still uses them is done
+  FC_HIP(hipMemsetAsync(c.ls, 0, sizeof(LearnScalars), s));
+  FC_HIP(hipStreamSynchronize(s));
   return FC_OK;
 }
 
 fc_status fc_coarse_grid(fc_precond pc, int32_t* G) {
   if (!pc || !G) return FC_E_ARG;
-  fc_status st = ensure_coarse(pc, nullptr);
+  hipStream_t s;
+  FC_HIP(own_stream(&s));
+  fc_status st = ensure_coarse(pc, s);
   if (st != FC_OK) return st;
   *G = pc->coarse->G;
   return FC_OK;
@@ -670,13 +674,16 @@ fc_status fc_coarse_grid(fc_precond pc, int32_t* G) {
 
 fc_status fc_coarse_channels(fc_precond pc, float* eta_dev, float* mask_dev) {
   if (!pc) return FC_E_ARG;
-  fc_status st = ensure_coarse(pc, nullptr);
+  hipStream_t s;
+  FC_HIP(own_stream(&s));
+  fc_status st = ensure_coarse(pc, s);
   if (st != FC_OK) return st;
   const CoarseCtx& c = *pc->coarse;
+  FC_HIP(device_idle());   // what still uses the caller's buffers is done
   if (eta_dev)
-    FC_HIP(hipMemcpy(eta_dev, c.xin + c.nvox, c.nvox * sizeof(float), hipMemcpyDeviceToDevice));
+    FC_HIP(copy_now(eta_dev, c.xin + c.nvox, c.nvox * sizeof(float), hipMemcpyDeviceToDevice));
   if (mask_dev)
-    FC_HIP(hipMemcpy(mask_dev, c.mask, c.nvox * sizeof(float), hipMemcpyDeviceToDevice));
+    FC_HIP(copy_now(mask_dev, c.mask, c.nvox * sizeof(float), hipMemcpyDeviceToDevice));
   return FC_OK;
 }
 
@@ -722,7 +729,8 @@ fc_status fc_coarse_apply(fc_precond pc, const float* y_dev, double* v_dev, doub
 fc_status fc_learned_stats(fc_precond pc, int64_t* n_apply, int64_t* n_drop) {
   if (!pc || !pc->coarse) return FC_E_ARG;
   LearnScalars h;
-  FC_HIP(hipMemcpy(&h, pc->coarse->ls, sizeof(h), hipMemcpyDeviceToHost));
+  FC_HIP(device_idle());   // what still counts is done
+  FC_HIP(copy_now(&h, pc->coarse->ls, sizeof(h), hipMemcpyDeviceToHost));
   if (n_apply) *n_apply = h.n_apply;
   if (n_drop) *n_drop = h.n_drop;
   return FC_OK;

@@ -8,9 +8,12 @@
 typedef enum {
   hipSuccess = 0,
   hipErrorOutOfMemory = 2,
+  hipErrorInvalidDevice = 101,
   hipErrorStreamCaptureUnsupported = 900
 } hipError_t;
 typedef void* hipStream_t;
+typedef enum { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost, hipMemcpyDeviceToDevice } hipMemcpyKind;
+enum { hipStreamNonBlocking = 1 };
 
 namespace stub {
 inline size_t budget = size_t(1) << 40, used = 0;
@@ -40,3 +43,11 @@ inline hipError_t hipGetDevice(int* d) {
 }
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char* hipGetErrorString(hipError_t) { return ""; }
+inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = nullptr;
+  return hipSuccess;
+}
+inline hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) {
+  return hipSuccess;
+}
+inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }

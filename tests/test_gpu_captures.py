@@ -35,12 +35,68 @@ def solved():
     return pc
 
 
+def problem():
+    p = hs.upload(stream=side)
+    pc = fc.Precond(p, stream=side)
+    assert fc.pcg_solve(p, pc, b, x, tol=1e-9, check_every=4, stream=side)["status"] == "OK"
+    assert (p.export()["val"] == hs.export()["val"]).all()
+    assert pc.block_inverse(0).any()
+
+
+def members():
+    ps = [pb, fc.Problem.setup(fcgen.disk_poisson_2d(2, n=40, p=3))]
+    bs = [torch.ones(p.n, dtype=torch.float64, device="cuda") for p in ps]
+    return ps, [fc.Precond(p) for p in ps], bs, [torch.empty_like(v) for v in bs]
+
+
+def batch(ps, pcs, bs, xs):
+    bt = fc.Batch(ps, pcs, stream=side)
+    for _ in range(2):
+        infos = bt.solve(bs, xs, tol=1e-9, check_every=4, stream=side)
+        assert all(i["status"] == "OK" for i in infos)
+
+
+CH = (4, 4, 4, 4)
+params = fcgen.unet_init(CH, 2, seed=1)
+
+
+def model():
+    return [torch.randn(2, c, 5, 5, 5, device="cuda") for c in (2, 1)]
+
+
+def network(u, t):
+    m = fc.Model(params, CH)
+    m.set_params(2 * params)
+    assert (m.params() == 2 * params).all()
+    assert m.loss_grad(u, t, stream=side)[1].any()
+
+
+def coarse():
+    p = fc.Problem.setup(fcgen.porous_poisson_3d(1, n=4, p=1, n_voids=2, rmin=0.1, rmax=0.15))
+    v = torch.ones(p.n, dtype=torch.float64, device="cuda")
+    return p, fc.Precond(p), v, torch.empty_like(v), torch.empty(27, device="cuda")
+
+
+def learned(p, pc, v, w, eta):
+    m = fc.Model(params, CH)
+    pc.attach(m)
+    pc.coarse_channels(eta, eta)
+    assert fc.pcg_solve(p, pc, v, w, tol=1e-8, mode="learned", stream=side)["status"] == "OK"
+    assert pc.learned_stats()["applied"] > 0
+
+
 ACTIONS = {  # name: (what is there before, the call)
     "destroy_precond": (lambda: [solved()], lambda have: have.clear()),
     "destroy_problem": (lambda: [hs.upload()], lambda have: have.clear()),
     "rebuild": (lambda: [solved()],
                 lambda have: (have.clear(),
                               fc.Precond(pb, stream=side).apply_M(b, z, stream=side))),
+    # a new problem, its first solve (the library's own capture), what it exports
+    "problem": (lambda: None, lambda have: problem()),
+    # members that stop at different steps: the lists are cut down in between
+    "batch": (members, lambda have: batch(*have)),
+    "model": (model, lambda have: network(*have)),
+    "learned": (coarse, lambda have: learned(*have)),
 }
 make, act = ACTIONS[what]
 have = make()
@@ -74,7 +130,8 @@ for k in range(3):
 """
 
 
-@pytest.mark.parametrize("what", ["destroy_precond", "destroy_problem", "rebuild"])
+@pytest.mark.parametrize("what", ["destroy_precond", "destroy_problem", "rebuild", "problem", "batch",
+                                  "model", "learned"])
 @pytest.mark.parametrize("mode", ["thread_local", "relaxed"])
 def test_capture_goes_on(what, mode):
     """thread_local: the call comes from another thread than the capture's;
