@@ -539,7 +539,7 @@ static fc_status precond_build_body(fc_problem pb, const fc_precond_opts* opts, 
   }
   pc->n_eig = (int64_t)sel.size();
   if (!sel.empty()) {
-    const int64_t chunk = std::min<int64_t>(2048, (int64_t)sel.size());
+    const int64_t chunk = jacobi_chunk(m, (int64_t)sel.size());
     Scratch scratch(s);
     double *dense = nullptr, *work = nullptr;
     int32_t* d_sel = nullptr;

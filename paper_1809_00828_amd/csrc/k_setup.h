@@ -10,6 +10,15 @@ hipError_t launch_block_extract(const fc_precond_s& pc, const int32_t* list, int
 // [count][m][m] scratch, work: [count][2][m][m] where jacobi_needs_work
 hipError_t launch_jacobi(fc_precond_s& pc, const int32_t* sel, int64_t count, double* dense,
                          double* work, int32_t* dropped, hipStream_t s);
+// Blocks of a launch of it, of `count`.  Blocks take sweeps of their own number, so
+// every launch ends in a tail: up to m = 64 as many as 256 MB of dense copies hold.
+// Unstabilised inverse, 110,592 blocks of 27: 47.8 ms, 57.7 in launches of 2,048;
+// 13,824 of 8: 0.34 / 0.60.  Above 64 a block fills a compute unit for long enough:
+// 2,048, which at 192 take 0.6 GB of dense copies and 1.2 GB of work.
+inline int64_t jacobi_chunk(int m, int64_t count) {
+  const int64_t most = m <= 64 ? (int64_t(1) << 25) / ((int64_t)m * m) : 2048;
+  return most < count ? most : count;
+}
 // true when the Jacobi eigen path keeps its blocks in global memory
 bool jacobi_needs_work(int m);
 // Certified direct inverses of blocks b0 .. b0 + count - 1 into pc.Q; blocks
