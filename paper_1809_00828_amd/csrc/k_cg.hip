@@ -720,15 +720,6 @@ static hipError_t enqueue_resid(SolverWs& w, const double* b, const double* t, h
   return hipGetLastError();
 }
 
-// Stored entries, and entries of the longest row, up to which the p update joins the
-// product: it saves a launch and makes every gather two.  us a step joined / apart: 2-D 40^2 p = 2 (0.1M entries)
-// 14.0 / 15.8, 110^2 p = 3 (2.7M) 21.3 / 22.0, 250^2 p = 2 (4.0M) 29.4 / 30.9; 3-D
-// 10^3 p = 2 (0.6M) 22.2 / 24.0, 20^3 p = 2 (4.3M) 31.0 / 31.5, 60^3 p = 1 (6.1M)
-// 47.4 / 46.9, 30^3 p = 2 (14M) 64 / 61; rows of up to 343, 9^3 p = 3 (2M) 45 / 34,
-// of up to 729, 6^3 p = 4 75 / 60.
-constexpr int64_t kJoinEntries = int64_t(4) << 20;
-constexpr int kJoinRow = 125;
-
 // Enqueue `chunk` PCG steps on stream s (with timing events when tev).
 // precA: 0 = FP64 matrix, 1 = row-mixed FP64/FP32 matrix; precS: 0/1/2 =
 // FP64/FP32/BF16 local inverses.
@@ -739,12 +730,13 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
   const int64_t n = pb.n_dofs;
   if (precA == 0 && precS == 0 && !tev && !learn && tiny_fits(pc))
     return launch_tiny_steps(pc, x, w.r, w.p, w.z, w.sc, chunk, s);
-  const int np_spmv = precA == 1 ? 0 : spmv_dot_blocks(pb.A);
   // small sliced problems: the p update joins the next step's product (tev: apart,
   // to be timed).  p alternates between two buffers and ends in w.p.
-  const bool join = np_spmv > 0 && spmv_uses_sell(pb.A) && pb.A.nnzb <= kJoinEntries &&
-                    pb.A.max_row <= kJoinRow && !learn && !tev &&
-                    pull_grid(n) <= (unsigned)kBetaSets;
+  const bool may_join = precA == 0 && !learn && spmv_step_joins(pb.A) &&
+                        pull_grid(n) <= (unsigned)kBetaSets;
+  const bool sell = may_join ? spmv_step_uses_sell(pb.A) : spmv_uses_sell(pb.A);
+  const int np_spmv = precA == 1 ? 0 : spmv_dot_blocks(pb.A, sell);
+  const bool join = may_join && sell && np_spmv > 0 && !tev;
   double *p = w.p, *p_other = w.t;
   double* dots = w.partial + (join ? kDotPartials : 0);
   for (int it = 0; it < chunk; ++it) {
@@ -764,7 +756,7 @@ static hipError_t enqueue_steps(fc_precond_s& pc, SolverWs& w, double* x, int ch
                              (int)pull_grid(n), s);
         std::swap(p, p_other);
       } else {
-        e = launch_spmv_pq(pb.A, p, w.q, w.sc, np_spmv ? dots : nullptr, s);
+        e = launch_spmv_pq(pb.A, p, w.q, w.sc, np_spmv ? dots : nullptr, sell, s);
       }
     }
     if (e != hipSuccess) return e;

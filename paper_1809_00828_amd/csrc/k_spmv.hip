@@ -33,6 +33,7 @@
 
 #include "dev_common.h"
 #include "k_spmv.h"
+#include "routes.h"
 #include "spmv_dev.h"
 
 namespace fc {
@@ -337,29 +338,28 @@ bool spmv_has_sell(const DeviceBsr& A) {
   return lattice_allowed() && A.lat.dim > 0 && A.bdim == 1 && A.sell_val;
 }
 
-// One wave walks a slice's rows from end to end, so a matrix of few slices and long
-// rows waits for single waves; the row layout deals a row to 8 to 64 lanes.  us a
-// product, sliced / rows: 3-D p = 2, 381 slices 9.2 / 7.4, 1,076 11.7 / 11.8; p = 3,
-// 107 13.5 / 7.7, 343 18.2 / 9.3, 791 20.5 / 16.4, 1,838 29.4 / 30.2; p = 4, 244 31.6 /
-// 10.4, 1,838 54.5 / 49.5, 3,546 83.5 / 99.8; rows of up to 36 on average never.
-static bool few_long_rows(const DeviceBsr& A) {
-  const double mean = A.n_rows ? double(A.nnzb) / double(A.n_rows) : 0.0;
-  return mean >= 48.0 && (double)A.n_slices < 9.0 * mean;
+bool spmv_uses_sell(const DeviceBsr& A) {
+  return spmv_has_sell(A) && !few_long_rows(A.nnzb, A.n_rows, A.n_slices);
 }
 
-static bool use_sell(const DeviceBsr& A) { return spmv_has_sell(A) && !few_long_rows(A); }
+bool spmv_step_joins(const DeviceBsr& A) {
+  return spmv_has_sell(A) && step_joins(A.nnzb, A.max_row);
+}
 
-bool spmv_uses_sell(const DeviceBsr& A) { return use_sell(A); }
+bool spmv_step_uses_sell(const DeviceBsr& A) {
+  return spmv_step_joins(A) ? !rows_beat_join(A.nnzb, A.n_rows, A.n_slices) : spmv_uses_sell(A);
+}
 
 // Workgroups of the whole-matrix product (one (x, y) partial each when asked).
-static int64_t spmv_blocks(const DeviceBsr& A) {
-  return use_sell(A) ? (A.n_slices + 3) / 4 : num_tiles(A);
+static int64_t spmv_blocks(const DeviceBsr& A, bool sell) {
+  return sell ? (A.n_slices + 3) / 4 : num_tiles(A);
 }
 
 template <int B, typename T, typename XT>
 static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
                                 double* y, hipStream_t s, const CgScalars* sc,
-                                double* partial, const int32_t* rows, int64_t n_list) {
+                                double* partial, const int32_t* rows, int64_t n_list,
+                                bool sell) {
   const int G = group_width(A);
   const int64_t n_rows = rows ? n_list : A.n_rows;
   const int64_t nt = (n_rows + 256 / G - 1) / (256 / G);
@@ -367,9 +367,9 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
   const bool lat = lattice_allowed() && A.lat.dim > 0;
   // the whole scalar matrix with its sliced copy
   if constexpr (B == 1 && sizeof(T) == 8 && sizeof(XT) == 8) {
-    if (use_sell(A) && !rows) {
+    if (sell && !rows) {
       const SellView v = sell_view(A);
-      dim3 g((unsigned)spmv_blocks(A)), b(256);
+      dim3 g((unsigned)spmv_blocks(A, true)), b(256);
       // values streamed non-temporally (3 % faster at 64^3 cells, p = 2;
       // FC_SPMV_SELL_NT=0 reads them through the caches)
       static const bool sell_nt = env_int("FC_SPMV_SELL_NT", 1) != 0;
@@ -419,17 +419,18 @@ static hipError_t spmv_dispatch(const DeviceBsr& A, const T* val, const XT* x,
 template <typename T, typename XT = double>
 static hipError_t spmv_any(const DeviceBsr& A, const T* val, const XT* x, double* y,
                            hipStream_t s, const CgScalars* sc, double* partial,
-                           const int32_t* rows = nullptr, int64_t n_list = 0) {
+                           const int32_t* rows = nullptr, int64_t n_list = 0,
+                           bool sell = false) {
   switch (A.bdim) {
-    case 1: return spmv_dispatch<1, T, XT>(A, val, x, y, s, sc, partial, rows, n_list);
-    case 2: return spmv_dispatch<2, T, XT>(A, val, x, y, s, sc, partial, rows, n_list);
-    case 3: return spmv_dispatch<3, T, XT>(A, val, x, y, s, sc, partial, rows, n_list);
+    case 1: return spmv_dispatch<1, T, XT>(A, val, x, y, s, sc, partial, rows, n_list, sell);
+    case 2: return spmv_dispatch<2, T, XT>(A, val, x, y, s, sc, partial, rows, n_list, sell);
+    case 3: return spmv_dispatch<3, T, XT>(A, val, x, y, s, sc, partial, rows, n_list, sell);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_spmv(const DeviceBsr& A, const double* x, double* y, hipStream_t s) {
-  return spmv_any<double>(A, A.val, x, y, s, nullptr, nullptr);
+  return spmv_any<double>(A, A.val, x, y, s, nullptr, nullptr, nullptr, 0, spmv_uses_sell(A));
 }
 
 // Up to 1,024 workgroups the product leaves one (x, y) partial per workgroup
@@ -437,8 +438,8 @@ hipError_t launch_spmv(const DeviceBsr& A, const double* x, double* y, hipStream
 // more, and the reduction at the end of a workgroup costs more than a pass
 // over both vectors: it holds the workgroup's waves until the slowest row is
 // done (11 % of the product at 32^3 cells, p = 3 elasticity).
-int spmv_dot_blocks(const DeviceBsr& A) {
-  const int64_t nb = spmv_blocks(A);
+int spmv_dot_blocks(const DeviceBsr& A, bool sell) {
+  const int64_t nb = spmv_blocks(A, sell);
   return nb <= 1024 ? (int)nb : 0;
 }
 
@@ -556,8 +557,8 @@ hipError_t spmv_enable_lattice(DeviceBsr& A, int dim, int n1, int p, hipStream_t
 }
 
 hipError_t launch_spmv_pq(const DeviceBsr& A, const double* p, double* q, CgScalars* sc,
-                          double* partial, hipStream_t s) {
-  return spmv_any<double>(A, A.val, p, q, s, sc, partial);
+                          double* partial, bool sell, hipStream_t s) {
+  return spmv_any<double>(A, A.val, p, q, s, sc, partial, nullptr, 0, sell);
 }
 
 hipError_t launch_spmv_mixed(const DeviceBsr& A, const double* p, const float* p32, double* q,

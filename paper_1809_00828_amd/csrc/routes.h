@@ -1,0 +1,40 @@
+// Rules on sizes that pick the product's layout and the way a CG step is launched.
+#pragma once
+#include <cstdint>
+
+namespace fc {
+
+// One wave walks a slice's rows from end to end, so a matrix of few slices and long
+// rows waits for single waves; the row layout deals a row to 8 to 64 lanes.  us a
+// product, sliced / rows: 3-D p = 2, 381 slices 9.2 / 7.4, 1,076 11.7 / 11.8; p = 3,
+// 107 13.5 / 7.7, 343 18.2 / 9.3, 791 20.5 / 16.4, 1,838 29.4 / 30.2; p = 4, 244 31.6 /
+// 10.4, 1,838 54.5 / 49.5, 3,546 83.5 / 99.8; rows of up to 36 on average never.
+inline bool few_long_rows(int64_t nnz, int64_t n_rows, int64_t n_slices) {
+  const double mean = n_rows ? double(nnz) / double(n_rows) : 0.0;
+  return mean >= 48.0 && (double)n_slices < 9.0 * mean;
+}
+
+// Stored entries, and entries of the longest row, up to which the p update of a CG step
+// joins the sliced product of the next: it saves a launch and makes every gather two.
+// us a step joined / apart: 2-D 40^2 p = 2 (0.1M entries) 14.0 / 15.8, 110^2 p = 3
+// (2.7M) 21.3 / 22.0, 250^2 p = 2 (4.0M) 29.4 / 30.9; 3-D 16^3 p = 2 (2.1M) 23.5 / 24.9,
+// 20^3 p = 2 (4.3M) 31.0 / 31.5, 60^3 p = 1 (6.1M) 47.4 / 46.9, 30^3 p = 2 (14M) 64 / 61;
+// rows of up to 343, 9^3 p = 3 (2M) 45 / 34, of up to 729, 6^3 p = 4 75 / 60.
+constexpr int64_t kJoinEntries = int64_t(4) << 20;
+constexpr int kJoinRow = 125;
+inline bool step_joins(int64_t nnz, int32_t max_row) {
+  return nnz <= kJoinEntries && max_row <= kJoinRow;
+}
+
+// Layout of the product in steps whose p update may join the sliced one: few long rows
+// go to the row layout only where its product wins more than the launch saved.  us a
+// step sliced and joined / rows, 3-D p = 2 (slices an entry of the mean row): 5^3 cells
+// (0.5) 18.2 / 20.3, 6^3 18.8 / 20.4, 7^3 19.4 / 20.5, 8^3 (1.4) 19.4 / 21.0, 9^3 (1.9)
+// 19.9 .. 20.6 / 20.4, 10^3 (2.6) 21.6 / 21.5, 11^3 21.6 / 21.3, 12^3 (4.2) 22.0 / 20.6,
+// 14^3 22.8 / 22.0, 15^3 (7.9) 22.5 .. 23.2 / 22.6.
+inline bool rows_beat_join(int64_t nnz, int64_t n_rows, int64_t n_slices) {
+  return few_long_rows(nnz, n_rows, n_slices) &&
+         (double)n_slices * (double)n_rows >= 2.2 * (double)nnz;
+}
+
+}  // namespace fc
