@@ -10,12 +10,13 @@
 #include "dev_common.h"
 #include "k_spmv.h"
 #include "k_tiny.h"
+#include "routes.h"
 #include "schwarz_dev.h"
 #include "spmv_dev.h"
 
 namespace fc {
 
-constexpr int kTinyWaves = 16, kTinyElems = 4;   // unknowns per thread, at most
+constexpr int kTinyWaves = kTinyThreads / 64;
 
 struct TinyArgs {
   SellView A;
@@ -149,19 +150,10 @@ __global__ __launch_bounds__(64 * kTinyWaves) void k_cg_tiny(const TinyArgs T) {
   if (tid == 0) *T.sc = S;
 }
 
-static size_t tiny_lds(const fc_precond_s& pc) {
-  return (4 * (size_t)pc.pb->n_dofs + (size_t)pc.n_blocks * pc.m + 64 * kTinyWaves) *
-         sizeof(double);
-}
-
 bool tiny_fits(const fc_precond_s& pc) {
   const fc_problem_s& pb = *pc.pb;
-  if (!spmv_has_sell(pb.A) || pc.lat.dim == 0 || pb.bdim != 1 || pc.n_blocks == 0) return false;
-  if (pc.m > 27 || pc.m != pc.nn || pb.n_dofs > 64 * kTinyWaves * kTinyElems) return false;
-  const size_t bytes =
-      (size_t)pb.A.nnzb * sizeof(double) +
-      (size_t)pc.n_blocks * sym_block_stride_dev(pc.m) * sizeof(double);
-  return tiny_lds(pc) <= 150 * 1024 && bytes <= kTinyBytes;
+  return spmv_has_sell(pb.A) && pc.lat.dim > 0 && pb.bdim == 1 && pc.n_blocks > 0 &&
+         pc.m == pc.nn && tiny_sizes(pb.A.nnzb, pb.n_dofs, pc.n_blocks, pc.m);
 }
 
 template <int P, int kDim>
@@ -188,7 +180,7 @@ hipError_t launch_tiny_steps(const fc_precond_s& pc, double* x, double* r, doubl
   t.p = p;
   t.z = z;
   t.sc = sc;
-  const size_t lds = tiny_lds(pc);
+  const size_t lds = tiny_lds(t.n, t.n_blocks, pc.m);
   switch (10 * pc.lat.dim + pc.lat.p) {
     case 21: return launch_tiny<1, 2>(t, lds, s);
     case 22: return launch_tiny<2, 2>(t, lds, s);

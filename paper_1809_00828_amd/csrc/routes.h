@@ -1,5 +1,6 @@
 // Rules on sizes that pick the product's layout and the way a CG step is launched.
 #pragma once
+#include <cstddef>
 #include <cstdint>
 
 namespace fc {
@@ -35,6 +36,24 @@ inline bool step_joins(int64_t nnz, int32_t max_row) {
 inline bool rows_beat_join(int64_t nnz, int64_t n_rows, int64_t n_slices) {
   return few_long_rows(nnz, n_rows, n_slices) &&
          (double)n_slices * (double)n_rows >= 2.2 * (double)nnz;
+}
+
+// CG steps in one workgroup (k_tiny.hip).
+// Bytes of matrix and local inverses a step reads, at most.  Measured, in us a step
+// against separate launches: 2-D p = 3, 0.29 MB 7.3 / 15.3, 0.74 MB 13.1 / 15.3;
+// p = 4, 0.45 MB 10.8 / 16.2, 1.0 MB 20.4 / 16.1; 3-D p = 1, 0.72 MB 15.2 / 16.7;
+// p = 2, 0.47 MB 11.9 / 19.5, 0.9 MB 19.6 / 19.8.
+constexpr size_t kTinyBytes = size_t(768) << 10;
+constexpr int kTinyThreads = 1024, kTinyElems = 4;   // unknowns per thread, at most
+// LDS for p, q, r, z, the block outputs and one right-hand side a wave
+inline size_t tiny_lds(int64_t n, int64_t n_blocks, int m) {
+  return (4 * (size_t)n + (size_t)n_blocks * m + kTinyThreads) * sizeof(double);
+}
+inline bool tiny_sizes(int64_t nnz, int64_t n, int64_t n_blocks, int m) {
+  const size_t inverses = (size_t)n_blocks * (m / 2 + 1) * m;
+  return m <= 27 && n <= (int64_t)kTinyThreads * kTinyElems &&
+         tiny_lds(n, n_blocks, m) <= 150 * 1024 &&
+         ((size_t)nnz + inverses) * sizeof(double) <= kTinyBytes;
 }
 
 }  // namespace fc

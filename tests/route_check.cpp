@@ -28,26 +28,33 @@ static void eigen_chunks() {
   }
 }
 
-// rows, stored entries, longest row and slices of n^3 cells at degree p, scalar
-struct Cube {
-  int64_t rows, nnz = 1, slices = 0;
-  int32_t longest = 1;
-  Cube(int64_t n, int64_t p) {
+// n^dim cells at degree p, scalar: rows, stored entries, longest row, slices, cells
+// and unknowns of a cell
+struct Grid {
+  int64_t rows = 1, nnz = 1, slices = 0, cells = 1;
+  int32_t longest = 1, m = 1;
+  Grid(int dim, int64_t n, int64_t p) {
     const int64_t n1 = p * n + 1, nv = n - 1, nn = n1 - nv;
-    rows = n1 * n1 * n1;
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < dim; ++d) {
+      rows *= n1;
       nnz *= nv * (2 * p + 1) + nn * (p + 1);
       longest *= (int32_t)(n > 1 ? 2 * p + 1 : p + 1);
+      cells *= n;
+      m *= (int32_t)(p + 1);
     }
-    for (int c = 0; c < 8; ++c) {
+    for (int c = 0; c < 1 << dim; ++c) {
       int64_t k = 1;
-      for (int d = 0; d < 3; ++d) k *= c >> d & 1 ? nv : nn;
+      for (int d = 0; d < dim; ++d) k *= c >> d & 1 ? nv : nn;
       slices += (k + 63) / 64;
     }
   }
   bool joins() const { return step_joins(nnz, longest); }
   bool few_long() const { return few_long_rows(nnz, rows, slices); }
   bool rows_in_step() const { return joins() ? rows_beat_join(nnz, rows, slices) : few_long(); }
+  bool tiny() const { return tiny_sizes(nnz, rows, cells, m); }
+};
+struct Cube : Grid {
+  Cube(int64_t n, int64_t p) : Grid(3, n, p) {}
 };
 
 // the layout of a step's product, where the launch that the joined p update saves
@@ -62,7 +69,28 @@ static void step_layouts() {
   CHECK(!Cube(14, 3).rows_in_step());
 }
 
+// the sizes of test_gpu_routes.py and test_gpu_tiny.py take the kernels they are there
+// for
+static void tested_sizes() {
+  CHECK(Cube(13, 3).few_long() && !Cube(14, 3).few_long());
+  CHECK(Cube(12, 4).few_long() && !Cube(13, 4).few_long());
+  const int tiny[][3] = {{2, 1, 1}, {2, 7, 1}, {2, 31, 1}, {2, 44, 1}, {2, 1, 2}, {2, 16, 2},
+                         {2, 25, 2}, {2, 5, 3}, {2, 13, 3}, {2, 1, 4}, {2, 9, 4}, {3, 1, 1},
+                         {3, 9, 1}, {3, 1, 2}, {3, 2, 2}, {3, 3, 2}, {3, 4, 2}, {2, 47, 1},
+                         {2, 26, 2}, {2, 16, 3}, {2, 10, 4}, {3, 11, 1}};
+  for (auto& t : tiny) {
+    CHECK(Grid(t[0], t[1], t[2]).tiny());
+    if (!Grid(t[0], t[1], t[2]).tiny()) std::printf("  %d %d %d\n", t[0], t[1], t[2]);
+  }
+  const int more[][3] = {{2, 48, 1}, {2, 27, 2}, {2, 17, 3}, {2, 11, 4}, {3, 12, 1}, {3, 5, 2}};
+  for (auto& t : more) {
+    CHECK(!Grid(t[0], t[1], t[2]).tiny());
+    if (Grid(t[0], t[1], t[2]).tiny()) std::printf("  %d %d %d\n", t[0], t[1], t[2]);
+  }
+}
+
 int main() {
+  tested_sizes();
   eigen_chunks();
   step_layouts();
   std::printf("failures %d\n", bad);
