@@ -102,6 +102,24 @@ __device__ __forceinline__ T block_sum(T v, T* lds /* >= 16 */) {
   return t;
 }
 
+// Whether the run has stopped, for kernels that take neither alpha nor beta (sc may be
+// null), that may take alpha (first: the workgroup that stores the scalars), and that
+// take beta.
+__device__ __forceinline__ bool cg_stopped(const CgScalars* sc) {
+  return sc && (sc->done | sc->halt);
+}
+__device__ __forceinline__ bool alpha_stopped(CgScalars* sc, bool takes, bool first) {
+  if (!takes) return cg_stopped(sc);
+  const int32_t done = sc->done;
+  if (done && first && threadIdx.x == 0) sc->halt = done;
+  return done;
+}
+__device__ __forceinline__ bool beta_stopped(CgScalars* sc, bool first) {
+  const int32_t halt = sc->halt;
+  if (halt && first && threadIdx.x == 0) sc->done = halt;
+  return halt;
+}
+
 // Step length alpha = (r, z) / (p, q) from the (p, q) partials, by every
 // workgroup on its own (a fixed order, so all agree); the first one also
 // counts the step and stores the scalars.  False: breakdown, the step is not
@@ -124,7 +142,7 @@ __device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double
     sc->rz = rz;
     sc->iter += 1;
     if (ok) sc->alpha = *alpha;
-    else sc->done = (pq != pq || rz != rz) ? 4 : 3;
+    else sc->halt = (pq != pq || rz != rz) ? 4 : 3;
   }
   return ok;
 }

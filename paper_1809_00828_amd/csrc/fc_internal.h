@@ -25,7 +25,11 @@ void set_error(const std::string& msg);
 // the host.  Dots are reduced per workgroup into `partial`, which a later
 // kernel sums in a fixed order, so every run is bitwise reproducible.  Kernels
 // of many workgroups derive alpha and beta from the partials themselves; only
-// their first workgroup writes scalars, and none that the same kernel reads.
+// their first workgroup writes scalars, and none that the same kernel reads: the
+// waves of a workgroup that starts late would otherwise part at the stop test.
+// So the stop has two flags.  The kernels that take alpha test `done` and write
+// `halt`, those that take beta test `halt` and write `done`, each passing on what
+// it found set; all others test both.
 struct CgScalars {
   double rz;        // (r, z) of the iterate the step starts from
   double pq;        // (p, A p)
@@ -38,10 +42,11 @@ struct CgScalars {
   int64_t iter;     // products with A done
   int64_t maxit;
   int32_t done;     // 0 running, 1 converged, 2 maxit, 3 breakdown, 4 non-finite
-  int32_t stop;     // FC_STOP_*
+  int32_t halt;     // the same between a step's alpha and its beta
   double rzn;       // (r, z) of the newest iterate (rz of the next step)
   double zn0, rn0;  // ||z_0||, ||r_0||
   double* history;  // optional per-iteration criterion
+  int32_t stop;     // FC_STOP_*
 };
 
 // Tensor-product lattice behind a matrix assembled from a problem

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void kb_spmv(const BProb* __restrict__ probs,
   constexpr int U = B == 1 ? 8 : 2;   // blocks per lane per pass
   const WorkItem it = items[blockIdx.x];
   const BProb& P = probs[it.prob];
-  if (sc[it.prob].done) return;
+  if (cg_stopped(sc + it.prob)) return;
   const int64_t row = (int64_t)it.tile * RPW + threadIdx.x / G;
   const int lane = threadIdx.x % G;
   const double* x = pvec + P.voff;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void kb_spmv_sell(const BProb* __restrict__ pr
   if (s >= n_items) return;
   const SellItem it = items[s];
   const BProb& B = probs[it.prob];
-  if (sc[it.prob].done) return;
+  if (cg_stopped(sc + it.prob)) return;
   const GatherX x{pvec + B.voff};
   double* y = qvec + B.voff;
   switch (it.p) {
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void kb_pq(const BProb* __restrict__ probs,
                                              double* __restrict__ partial) {
   __shared__ double lds[16];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
-  if (sc[it.prob].done) return;
+  if (cg_stopped(sc + it.prob)) return;
   const BProb& P = probs[it.prob];
   const double *p = pvec + P.voff, *q = qvec + P.voff;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(256) void kb_schwarz_small(
   const WorkItem it = items[kM == kMixed ? blockIdx.x
                                          : xcd_remap(blockIdx.x, gridDim.x)];
   CgScalars* S = sc + it.prob;
-  if (S->done) return;
+  if (alpha_stopped(S, qvec != nullptr, it.tile == 0)) return;
   const BProb& P = probs[it.prob];
   if constexpr (kM != kMixed) {
     batch_small<kM, kLat>(P, it, n_items, S, rvec, qvec, partial, rB, red);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void kb_schwarz_staged(
   __shared__ __align__(16) double tile[kRows * kMaxM];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   CgScalars* S = sc + it.prob;
-  if (S->done) return;
+  if (alpha_stopped(S, qvec != nullptr, it.tile == 0)) return;
   const BProb& P = probs[it.prob];
   const AlphaIn ai = qvec ? batch_alpha(P, partial, n_items) : AlphaIn{};
   const int64_t blk = it.tile;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void kb_pull(const BProb* __restrict__ probs,
   __shared__ double lds[4][3];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   const CgScalars& S = sc[it.prob];
-  if (S.done) return;
+  if (cg_stopped(&S)) return;
   const BProb& P = probs[it.prob];
   const double alpha = kMode == 1 ? S.alpha : 0.0;
   const uint32_t n = (uint32_t)P.n_dofs;
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs
   __shared__ double red[3][4];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   CgScalars* S = sc + it.prob;
-  if (S->done) return;
+  if (beta_stopped(S, it.tile == 0)) return;
   const BProb& P = probs[it.prob];
   const double rz_old = S->rz;
   const double* z = zvec + P.voff;

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void k_cg_start_fin(const double* __restrict__
 // inverses, the learned modes).
 __global__ __launch_bounds__(1024) void k_cg_alpha(const AlphaIn ai, CgScalars* sc) {
   __shared__ double lds[16];
-  if (sc->done) return;
+  if (alpha_stopped(sc, true, true)) return;
   double alpha;
   (void)cg_alpha(sc, ai, lds, &alpha, blockIdx.x == 0);
 }
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(1024) void k_cg_pq(const double* __restrict__ p,
                                                 double* __restrict__ partial,
                                                 const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
-  if (sc->done) return;
+  if (cg_stopped(sc)) return;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void k_cg_pull(
   constexpr int kN = kFlex ? 4 : 3;
   constexpr int kE = kPullElems;
   __shared__ double lds[4][kN];
-  if (sc->done) return;
+  if (cg_stopped(sc)) return;
   const double alpha = sc->alpha;
   const uint32_t first = xcd_remap(blockIdx.x, gridDim.x) * (uint32_t)rounds;
   double acc[kN] = {};
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256) void k_cg_pull(
 __global__ __launch_bounds__(1024) void k_cg_beta(const double* __restrict__ partial, int np,
                                                   CgScalars* sc) {
   __shared__ double lds[16];
-  if (sc->done) return;
+  if (beta_stopped(sc, true)) return;
   double t[3] = {0.0, 0.0, 0.0};
   for (int i = threadIdx.x; i < np; i += 4 * blockDim.x) {
     double v[3][4];
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256) void k_cg_beta_p(const double* __restrict__ pa
                                                    const double* p_old, double* p, int64_t n,
                                                    CgScalars* sc) {
   __shared__ double red[3][4];
-  if (sc->done) return;
+  if (beta_stopped(sc, blockIdx.x == 0)) return;
   const double rz_old = sc->rz;
   const int64_t i0 = (int64_t)blockIdx.x * 512 + threadIdx.x, i1 = i0 + 256;
   const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p_old[i0] : 0.0;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(1024) void k_cg_beta_flex(const double* __restrict_
                                                        CgScalars* sc,
                                                        const LearnScalars* __restrict__ ls) {
   __shared__ double lds[16];
-  if (sc->done) return;
+  if (beta_stopped(sc, true)) return;
   double ta = 0.0, tb = 0.0, tc = 0.0, td = 0.0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) {
     ta += partial[i];
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(1024) void k_cg_beta_flex(const double* __restrict_
 
 __global__ __launch_bounds__(256) void k_cg_p(const double* __restrict__ z, double* __restrict__ p,
                                               int64_t n, const CgScalars* sc) {
-  if (sc->done) return;
+  if (cg_stopped(sc)) return;
   const double beta = sc->beta;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = fma(beta, p[i], z[i]);
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(256) void k_fcg_keep_dots(
     int64_t n, int m, double* __restrict__ ring, double* __restrict__ part, FcgRing* fr,
     const CgScalars* __restrict__ sc) {
   __shared__ double red[kMaxFcg][4];
-  if (sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t cnt0 = fr->count;
   const int slot = (int)(cnt0 % m);
   const int cnt = (int)(cnt0 + 1 < m ? cnt0 + 1 : m);
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(1024) void k_fcg_beta(const double* __restrict__ pa
                                                    const LearnScalars* __restrict__ ls) {
   __shared__ double lds[16];
   __shared__ int bad;
-  if (sc->done) return;
+  if (beta_stopped(sc, true)) return;
   if (threadIdx.x == 0) bad = 0;
   double ta = 0.0, tb = 0.0, tc = 0.0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) {
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void k_fcg_dir(const double* __restrict__ z,
                                                  int m, const FcgRing* __restrict__ fr,
                                                  const CgScalars* __restrict__ sc) {
   __shared__ double beta[kMaxFcg];
-  if (sc->done) return;
+  if (cg_stopped(sc)) return;
   const int cnt = (int)(fr->count < m ? fr->count : m);
   for (int j = threadIdx.x; j < cnt; j += blockDim.x) beta[j] = fr->beta[j];
   __syncthreads();
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256) void k_fcg_dir(const double* __restrict__ z,
 // b = fl32(a) (skipped once the stop flag is set)
 __global__ void k_round_f32(const double* __restrict__ a, float* __restrict__ b, int64_t n,
                             const CgScalars* __restrict__ sc) {
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     b[i] = (float)a[i];

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kT) void k_restrict(const double* __restrict__ r, i
                                                  const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
   __shared__ int flag;
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t nvox = (int64_t)G * G * G;
   double ss = 0.0;
   for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < nvox;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kT) void k_coarse_gamma(const float* __restrict__ y
                                                      const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
   __shared__ int flag;
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t nvox = (int64_t)G * G * G;
   double d1 = 0.0, d2 = 0.0;
   for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < nvox;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kT) void k_prolong(const float* __restrict__ y, int
                                                 const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
   __shared__ int flag;
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const double g = ls->gamma;
   const int64_t nv = (int64_t)(n + 1) * (n + 1) * (n + 1);
   double d = 0.0;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
   __shared__ A rB[kMaxM];
   __shared__ __align__(16) T tile[kRows * kMaxM];
   __shared__ double red[16];
-  if (sc && sc->done) return;
+  if (alpha_stopped(sc, ai.np > 0, blockIdx.x == 0)) return;
   // list: the workgroups handle only the listed blocks; skip: blocks
   // flagged there are left to another launch
   const int64_t blk = list ? (int64_t)list[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x);
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void k_schwarz_small(
     CgScalars* sc, const AlphaIn ai, double* __restrict__ y, int64_t n_blocks,
     const PullLattice lat) {
   __shared__ double rB[4][64], red[16];
-  if (sc && sc->done) return;
+  if (alpha_stopped(sc, ai.np > 0, blockIdx.x == 0)) return;
   schwarz_small_tile<T, kM, kLat>(
       P, block_stride, m_arg, r, q, isd, sc, ai, blockIdx.x == 0, y, n_blocks, lat,
       xcd_remap(blockIdx.x, gridDim.x), rB, red,
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void k_schwarz_chol_large(
     const CgScalars* __restrict__ sc, double* __restrict__ y, int64_t n_blocks) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ float rb[256], tb[256];
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
   if (blk >= n_blocks) return;
   const double alpha = (sc && q) ? sc->alpha : 0.0;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void k_schwarz_chol_small(
     const CgScalars* __restrict__ sc, double* __restrict__ y, int64_t n_blocks) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ float rb[4][64], tb[4][64];
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const double alpha = (sc && q) ? sc->alpha : 0.0;
   const int bpw = 64 / m;
   const int w = threadIdx.x / 64, l = threadIdx.x % 64;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void k_schwarz_sym_list(
     int bd, int m, const double* __restrict__ r, const double* __restrict__ q,
     const CgScalars* __restrict__ sc, double* __restrict__ y) {
   __shared__ double rB[256];
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t blk = list[blockIdx.x];
   const double alpha = (sc && q) ? sc->alpha : 0.0;
   const int i = threadIdx.x;

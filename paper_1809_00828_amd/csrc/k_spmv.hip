@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256, 5) void k_spmv_bsr(
   constexpr int BB = B * B;
   constexpr int RPW = 256 / G;   // rows per tile
   __shared__ double lds[16];
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   const int64_t ntiles = (n_rows + RPW - 1) / RPW;
   // XCD-contiguous tile ranges
   const XcdRange xr_ = xcd_range(blockIdx.x, gridDim.x, ntiles);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell(const SellView A, const doubl
                                                    double* __restrict__ partial,
                                                    const CgScalars* __restrict__ sc) {
   __shared__ double lds[4];
-  if (sc && sc->done) return;
+  if (cg_stopped(sc)) return;
   // the slice is wave-uniform, and what depends on it alone stays in scalar
   // registers
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell_beta(
     double* __restrict__ p_new, double* __restrict__ y, double* __restrict__ partial,
     const double* __restrict__ sets, int np, CgScalars* sc) {
   __shared__ double red[3][4];
-  if (sc->done) return;
+  if (beta_stopped(sc, blockIdx.x == 0)) return;
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   const double rz_old = sc->rz;
