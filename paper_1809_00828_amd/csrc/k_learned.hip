@@ -34,6 +34,7 @@
 
 #include "dev_common.h"
 #include "learned.h"
+#include "wgrad_dev.h"
 
 namespace fc {
 
@@ -454,14 +455,12 @@ struct WgradJobs {
   WgradJob j[15];
 };
 
-constexpr int kWgradThreads = 256;
-
 __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJobs jobs,
                                                                 float* __restrict__ part) {
   constexpr int kXRow = 148;                      // dwords per channel: 36 rows of 4, pad
   constexpr int kGRow = 36;                       // dwords per channel: 64 voxels, pad
-  constexpr int kXIter = 8;   // 2 channels of 108 pairs of halo values at a time
-  constexpr int kGIter = 2;   // 8 channels of 32 pairs of voxels at a time
+  constexpr int kXIter = kWgradXIter;
+  constexpr int kGIter = kWgradGIter;
   constexpr int kXs = 16 * kXRow, kGs = 16 * kGRow;
   __shared__ __align__(16) uint32_t lds[2][2 * (kXs + kGs)];   // [buffer][x terms, g terms]
   int id = 0;
@@ -479,27 +478,12 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
 #pragma unroll
   for (int q = 0; q < 16; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int64_t lo = range * J.per, hi = min(lo + J.per, J.nbricks);
-  // This thread's pair of halo values (the same in every brick and channel):
-  // offset from the brick's corner, position in LDS, and the bits of its
-  // coordinates (z 0-5, y 6-11, x 12-17) among those inside the grid.
-  const bool xact = tid < 216;   // the other threads load what thread 0 loads
-  const int xt = xact ? tid : 0, xc = xt / 108, xq = xt - 108 * xc, xrow = xq / 3;
-  const int hz = xrow / 6, hy = xrow - 6 * hz, hx = 2 * (xq - 3 * xrow);
-  const int up = J.up, step = 4 >> up;
-  auto below = [&](int h) { return up ? (h + 1) >> 1 : h; };   // ((h - 1) >> up) + 1
-  const int xoff0 = (below(hz) * Ns + below(hy)) * Ns + below(hx);
-  const int xoff1 = xoff0 - below(hx) + below(hx + 1);
-  const int own = (below(1) * Ns + below(1)) * Ns + below(1);   // the first voxel of the brick
-  const uint32_t need0 = (1u << hz) | (64u << hy) | (4096u << hx);
-  const uint32_t need1 = (1u << hz) | (64u << hy) | (8192u << hx);
-  const int64_t xci = (int64_t)xc * Vs, gco = (int64_t)(tid >> 5) * V;
-  const int xat = xc * kXRow + xrow * 4 + (xq - 3 * xrow);
-  const int gc = tid >> 5, gp = tid & 31;
-  const int pz = gp >> 3, py = (gp >> 1) & 3, px = 2 * (gp & 1);
-  const int goff = (pz * N + py) * N + px;
-  const uint32_t gneed0 = (2u << pz) | (128u << py) | (8192u << px);
-  const uint32_t gneed1 = (2u << pz) | (128u << py) | (16384u << px);
-  const int gat = gc * kGRow + gp;
+  const int up = J.up;
+  const WgradX X = wgrad_x(tid, Ns, up);
+  const WgradG G = wgrad_g(tid, N);
+  const int64_t xci = (int64_t)X.c * Vs, gco = (int64_t)G.c * V;
+  const int xat = X.c * kXRow + X.row * 4 + X.col;
+  const int gat = G.c * kGRow + G.pair;
   float2 xv[kXIter], gv[kGIter];
   bool x0in, x1in, g0in, g1in;
   // brick of the next load, stepped (a division per brick costs as much as its
@@ -514,21 +498,16 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
     bz = brick / (nb * nb);
   }
   auto load = [&] {
-    auto inside = [&](int c) {   // bit h: coordinate 4 c - 1 + h is in the grid
-      return (c == 0 ? 62u : 63u) & ((1u << min(6, N + 1 - 4 * c)) - 1);
-    };
-    const uint32_t in = inside(bz) | (inside(by) << 6) | (inside(bx) << 12);
-    x0in = (in & need0) == need0;
-    x1in = (in & need1) == need1;
-    g0in = (in & gneed0) == gneed0;
-    g1in = (in & gneed1) == gneed1;
-    // from the corner (outside the array for the first bricks: such offsets
-    // are replaced by that of the brick's first voxel)
-    const int64_t corner = ((int64_t)(bz * step - 1) * Ns + by * step - 1) * Ns + bx * step - 1;
+    const uint32_t in = wgrad_inside(bx, by, bz, N);
+    x0in = (in & X.need0) == X.need0;
+    x1in = (in & X.need1) == X.need1;
+    g0in = (in & G.need0) == G.need0;
+    g1in = (in & G.need1) == G.need1;
+    const int64_t corner = wgrad_corner(bx, by, bz, Ns, up);
     const float* xb = J.x + ((int64_t)b * Ci + i0) * Vs + corner;
     // a pair's second channel past the last one repeats the first
-    const float* p0 = xb + (x0in ? xoff0 : own);
-    const float* p1 = xb + (x1in ? xoff1 : own);
+    const float* p0 = xb + (x0in ? X.off0 : X.own);
+    const float* p1 = xb + (x1in ? X.off1 : X.own);
 #pragma unroll
     for (int it = 0; it < kXIter; ++it) {
       if (2 * it >= nx) break;
@@ -539,12 +518,12 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
       p1 += 2 * (int64_t)Vs;
     }
     const float* gb = J.g + ((int64_t)b * Co + o0) * V + ((int64_t)4 * bz * N + 4 * by) * N + 4 * bx;
-    const float* q0 = gb + gco + (g0in ? goff : 0);
-    const float* q1 = gb + gco + (g1in ? goff + 1 : 0);
+    const float* q0 = gb + gco + (g0in ? G.off : 0);
+    const float* q1 = gb + gco + (g1in ? G.off + 1 : 0);
 #pragma unroll
     for (int it = 0; it < kGIter; ++it) {
       if (8 * it >= ng) break;
-      const int64_t co = (int64_t)8 * it * V - (8 * it + gc < ng ? 0 : gco);
+      const int64_t co = (int64_t)8 * it * V - (8 * it + G.c < ng ? 0 : gco);
       gv[it].x = q0[co];
       gv[it].y = q1[co];
     }
@@ -573,14 +552,14 @@ __global__ __launch_bounds__(kWgradThreads, 3) void k_conv3d_wgrad(const WgradJo
     for (int it = 0; it < kXIter; ++it) {
       if (2 * it >= nx) break;
       const int at = xat + 2 * it * kXRow;
-      if (xact && 2 * it + xc < nx)
+      if (X.act && 2 * it + X.c < nx)
         put(&xs[at], &xs[kXs + at], x0in ? xv[it].x : 0.f, x1in ? xv[it].y : 0.f);
     }
 #pragma unroll
     for (int it = 0; it < kGIter; ++it) {
       if (8 * it >= ng) break;
       const int at = gat + 8 * it * kGRow;
-      if (8 * it + gc < ng)
+      if (8 * it + G.c < ng)
         put(&gs[at], &gs[kGs + at], g0in ? gv[it].x : 0.f, g1in ? gv[it].y : 0.f);
     }
     // one barrier per brick: the next brick goes to the other buffer, whose
