@@ -647,15 +647,16 @@ fc_status fc_learned_attach(fc_precond pc, fc_model m) {
   fc_status st = ensure_coarse(pc, s);
   if (st != FC_OK) return st;
   CoarseCtx& c = *pc->coarse;
+  // a captured solver chunk holds the old network buffers
+  solver_invalidate_graph(*pc);
+  c.model = nullptr;   // none attached if the new one's buffers do not fit
   c.ws.release();
-  c.model = m;
-  c.enabled = 1;
   if (m) {
     st = c.ws.ensure(m->net, 1, c.G);
     if (st != FC_OK) return st;
   }
-  // a captured solver chunk holds the old network buffers
-  solver_invalidate_graph(*pc);
+  c.model = m;
+  c.enabled = 1;
   FC_HIP(device_idle());   // what still uses them is done
   FC_HIP(hipMemsetAsync(c.ls, 0, sizeof(LearnScalars), s));
   FC_HIP(hipStreamSynchronize(s));
