@@ -102,8 +102,8 @@ __device__ __forceinline__ T block_sum(T v, T* lds /* >= 16 */) {
   return t;
 }
 
-// Whether the run has stopped, for kernels that take neither alpha nor beta (sc may be
-// null), that may take alpha (first: the workgroup that stores the scalars), and that
+// Whether the run has stopped, for kernels of either place in a step (sc may be null),
+// that may take alpha (first: the workgroup that stores the scalars), and that
 // take beta.
 __device__ __forceinline__ bool cg_stopped(const CgScalars* sc) {
   return sc && (sc->done | sc->halt);
@@ -150,7 +150,8 @@ __device__ __forceinline__ bool cg_alpha(CgScalars* sc, const AlphaIn ai, double
 // Stop test (Eq. 12 or the plain residual) and the scalars of the next step,
 // by one thread.  sc->rz stays: the workgroups that update p divide by it.
 __device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double zz, double rr) {
-  const double crit = (sc->stop == FC_STOP_PRECOND ? sqrt(zz) : sqrt(rr)) / sc->crit0;
+  const bool precond = sc->stop == FC_STOP_PRECOND;
+  const double crit = sqrt(precond ? zz : rr) / (precond ? sc->zn0 : sc->rn0);
   sc->zz = zz;
   sc->rr = rr;
   sc->crit = crit;
@@ -166,19 +167,19 @@ __device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double z
   }
 }
 
-// (r, z) from the pull's np <= kBetaSets partial sets, by every workgroup of 256 in the
-// same order; the first one also sums (z, z) and (r, r), tests for the stop and
-// stores the scalars.
+// (r, z) from the pull's np <= kBetaSets partial sets (value k of set j at k stride + j),
+// by every workgroup of 256 in the same order; the first one also sums (z, z) and (r, r),
+// tests for the stop and stores the scalars.
 constexpr int kBetaSets = 1024;
-__device__ __forceinline__ double cg_beta_sum(const double* __restrict__ sets, int np,
-                                              CgScalars* sc, double (*red)[4], bool first) {
+__device__ __forceinline__ double cg_beta_sum(const double* __restrict__ sets, int64_t stride,
+                                              int np, CgScalars* sc, double (*red)[4], bool first) {
   const int nk = first ? 3 : 1, w = threadIdx.x / kWave;
   for (int k = 0; k < nk; ++k) {
     double v[kBetaSets / 256];
 #pragma unroll
     for (int u = 0; u < kBetaSets / 256; ++u) {
       const int j = threadIdx.x + 256 * u;
-      v[u] = j < np ? sets[k * np + j] : 0.0;
+      v[u] = j < np ? sets[k * stride + j] : 0.0;
     }
     const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
     if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;

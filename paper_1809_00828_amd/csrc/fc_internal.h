@@ -29,14 +29,14 @@ void set_error(const std::string& msg);
 // waves of a workgroup that starts late would otherwise part at the stop test.
 // So the stop has two flags.  The kernels that take alpha test `done` and write
 // `halt`, those that take beta test `halt` and write `done`, each passing on what
-// it found set; all others test both.
+// it found set: the products between beta and alpha test `done`, the pull between
+// alpha and beta `halt`, and what may run in either place both.
 struct CgScalars {
   double rz;        // (r, z) of the iterate the step starts from
   double pq;        // (p, A p)
   double alpha, beta;
   double zz;        // (z, z) of the newest z
   double rr;        // (r, r) of the newest r
-  double crit0;     // ||z_0|| or ||b|| (denominator of the stop test)
   double crit;      // newest relative criterion
   double tol;
   int64_t iter;     // products with A done
@@ -44,10 +44,12 @@ struct CgScalars {
   int32_t done;     // 0 running, 1 converged, 2 maxit, 3 breakdown, 4 non-finite
   int32_t halt;     // the same between a step's alpha and its beta
   double rzn;       // (r, z) of the newest iterate (rz of the next step)
-  double zn0, rn0;  // ||z_0||, ||r_0||
+  double zn0, rn0;  // ||z_0||, ||r_0||: the denominators of the stop test
   double* history;  // optional per-iteration criterion
   int32_t stop;     // FC_STOP_*
+  int32_t pad;
 };
+static_assert(sizeof(CgScalars) == 128, "one cache line each in a batch's array");
 
 // Tensor-product lattice behind a matrix assembled from a problem
 // description (dim = 0 otherwise): the block columns of every row are the

@@ -65,7 +65,7 @@ struct BProb {
   int32_t wide_item0, wide_items, wide_rounds;
 };
 
-constexpr int kPullTiles = 1024, kWideTiles = 256;
+constexpr int kPullTiles = kBetaSets, kWideTiles = 256;
 
 __device__ __forceinline__ AlphaIn batch_alpha(const BProb& P, const double* partial,
                                                int n_items) {
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void kb_spmv(const BProb* __restrict__ probs,
   constexpr int U = B == 1 ? 8 : 2;   // blocks per lane per pass
   const WorkItem it = items[blockIdx.x];
   const BProb& P = probs[it.prob];
-  if (cg_stopped(sc + it.prob)) return;
+  if (sc[it.prob].done) return;
   const int64_t row = (int64_t)it.tile * RPW + threadIdx.x / G;
   const int lane = threadIdx.x % G;
   const double* x = pvec + P.voff;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void kb_spmv_sell(const BProb* __restrict__ pr
   if (s >= n_items) return;
   const SellItem it = items[s];
   const BProb& B = probs[it.prob];
-  if (cg_stopped(sc + it.prob)) return;
+  if (sc[it.prob].done) return;
   const GatherX x{pvec + B.voff};
   double* y = qvec + B.voff;
   switch (it.p) {
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void kb_pq(const BProb* __restrict__ probs,
                                              double* __restrict__ partial) {
   __shared__ double lds[16];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
-  if (cg_stopped(sc + it.prob)) return;
+  if (sc[it.prob].done) return;
   const BProb& P = probs[it.prob];
   const double *p = pvec + P.voff, *q = qvec + P.voff;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void kb_pull(const BProb* __restrict__ probs,
   __shared__ double lds[4][3];
   const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
   const CgScalars& S = sc[it.prob];
-  if (cg_stopped(&S)) return;
+  if (S.halt) return;
   const BProb& P = probs[it.prob];
   const double alpha = kMode == 1 ? S.alpha : 0.0;
   const uint32_t n = (uint32_t)P.n_dofs;
@@ -372,9 +372,9 @@ __global__ __launch_bounds__(256) void kb_start(const BProb* __restrict__ probs,
   S.iter = 0;
   S.zn0 = sqrt(zz);
   S.rn0 = sqrt(rr);
-  S.crit0 = S.stop == FC_STOP_PRECOND ? S.zn0 : S.rn0;
-  S.crit = S.crit0 > 0 ? 1.0 : 0.0;
-  S.done = !(S.crit0 == S.crit0) ? 4 : (S.crit0 == 0.0 ? 1 : 0);
+  const double c0 = S.stop == FC_STOP_PRECOND ? S.zn0 : S.rn0;
+  S.crit = c0 > 0 ? 1.0 : 0.0;
+  S.done = !(c0 == c0) ? 4 : (c0 == 0.0 ? 1 : 0);
 }
 
 // p = z + beta p with beta from the pull's partials, summed by every workgroup
@@ -405,21 +405,8 @@ __global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs
     }
   };
   load(i0);   // the first round's unknowns, before the sums
-  const int nk = it.tile == 0 ? 3 : 1, w = threadIdx.x / kWave;
-  for (int k = 0; k < nk; ++k) {
-    const double* pp = partial + k * (int64_t)n_items + P.pull_item0;
-    double v[kPullTiles / 256];
-#pragma unroll
-    for (int u = 0; u < kPullTiles / 256; ++u) {
-      const int j = threadIdx.x + 256 * u;
-      v[u] = j < P.pull_items ? pp[j] : 0.0;
-    }
-    const double t = wave_sum_last((v[0] + v[1]) + (v[2] + v[3]));
-    if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
-  }
-  __syncthreads();
-  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-  const double beta = rz / rz_old;
+  const double beta = cg_beta_sum(partial + P.pull_item0, n_items, P.pull_items, S, red,
+                                  it.tile == 0) / rz_old;
   for (int t = 0; t < P.wide_rounds; ++t) {
     const int64_t j0 = i0 + 2048 * (int64_t)t;
     if (t > 0) load(j0);
@@ -427,9 +414,6 @@ __global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs
     for (int u = 0; u < 8; ++u)
       if (j0 + 256 * u < P.n_dofs) p[j0 + 256 * u] = fma(beta, pv[u], zv[u]);
   }
-  if (it.tile == 0 && threadIdx.x == 0)
-    cg_beta_store(S, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
-                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
 }
 
 // r = b, x = 0

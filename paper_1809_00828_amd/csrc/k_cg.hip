@@ -157,7 +157,6 @@ __global__ __launch_bounds__(256) void k_cg_start_fin(const double* __restrict__
     sc->zn0 = sqrt(zz);
     sc->rn0 = sqrt(rr);
     const double c0 = sc->stop == FC_STOP_PRECOND ? sc->zn0 : sc->rn0;
-    sc->crit0 = c0;
     sc->crit = c0 > 0.0 ? 1.0 : 0.0;
     if (sc->history) sc->history[0] = sc->crit;
     if (!(c0 == c0) || !(rz == rz)) sc->done = 4;
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(1024) void k_cg_pq(const double* __restrict__ p,
                                                 double* __restrict__ partial,
                                                 const CgScalars* __restrict__ sc) {
   __shared__ double lds[16];
-  if (cg_stopped(sc)) return;
+  if (sc->done) return;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -223,7 +222,7 @@ __global__ __launch_bounds__(256) void k_cg_pull(
   constexpr int kN = kFlex ? 4 : 3;
   constexpr int kE = kPullElems;
   __shared__ double lds[4][kN];
-  if (cg_stopped(sc)) return;
+  if (sc->halt) return;
   const double alpha = sc->alpha;
   const uint32_t first = xcd_remap(blockIdx.x, gridDim.x) * (uint32_t)rounds;
   double acc[kN] = {};
@@ -317,7 +316,7 @@ __global__ __launch_bounds__(256) void k_cg_beta_p(const double* __restrict__ pa
   const int64_t i0 = (int64_t)blockIdx.x * 512 + threadIdx.x, i1 = i0 + 256;
   const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p_old[i0] : 0.0;
   const double z1 = i1 < n ? z[i1] : 0.0, p1 = i1 < n ? p_old[i1] : 0.0;
-  const double beta = cg_beta_sum(partial, np, sc, red, blockIdx.x == 0) / rz_old;
+  const double beta = cg_beta_sum(partial, np, np, sc, red, blockIdx.x == 0) / rz_old;
   if (i0 < n) p[i0] = fma(beta, p0, z0);
   if (i1 < n) p[i1] = fma(beta, p1, z1);
 }
@@ -348,7 +347,7 @@ __global__ __launch_bounds__(1024) void k_cg_beta_flex(const double* __restrict_
       rz += g * ls->yrc;
       zq += g * ls->wq;
     }
-    const double crit = sqrt(rr) / sc->crit0;
+    const double crit = sqrt(rr) / sc->rn0;
     sc->zz = zz;
     sc->rr = rr;
     sc->crit = crit;
@@ -367,7 +366,7 @@ __global__ __launch_bounds__(1024) void k_cg_beta_flex(const double* __restrict_
 
 __global__ __launch_bounds__(256) void k_cg_p(const double* __restrict__ z, double* __restrict__ p,
                                               int64_t n, const CgScalars* sc) {
-  if (cg_stopped(sc)) return;
+  if (sc->done) return;
   const double beta = sc->beta;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = fma(beta, p[i], z[i]);
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(256) void k_fcg_keep_dots(
     int64_t n, int m, double* __restrict__ ring, double* __restrict__ part, FcgRing* fr,
     const CgScalars* __restrict__ sc) {
   __shared__ double red[kMaxFcg][4];
-  if (cg_stopped(sc)) return;
+  if (sc->halt) return;
   const int64_t cnt0 = fr->count;
   const int slot = (int)(cnt0 % m);
   const int cnt = (int)(cnt0 + 1 < m ? cnt0 + 1 : m);
@@ -484,7 +483,7 @@ __global__ __launch_bounds__(1024) void k_fcg_beta(const double* __restrict__ pa
     fr->count = cnt0 + 1;
     const double g = ls->gamma;
     if (g != 0.0) rz += g * ls->yrc;
-    const double crit = sqrt(rr) / sc->crit0;
+    const double crit = sqrt(rr) / sc->rn0;
     sc->zz = zz;
     sc->rr = rr;
     sc->crit = crit;
@@ -507,7 +506,7 @@ __global__ __launch_bounds__(256) void k_fcg_dir(const double* __restrict__ z,
                                                  int m, const FcgRing* __restrict__ fr,
                                                  const CgScalars* __restrict__ sc) {
   __shared__ double beta[kMaxFcg];
-  if (cg_stopped(sc)) return;
+  if (sc->done) return;
   const int cnt = (int)(fr->count < m ? fr->count : m);
   for (int j = threadIdx.x; j < cnt; j += blockDim.x) beta[j] = fr->beta[j];
   __syncthreads();

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256, 5) void k_spmv_bsr(
   constexpr int BB = B * B;
   constexpr int RPW = 256 / G;   // rows per tile
   __shared__ double lds[16];
-  if (cg_stopped(sc)) return;
+  if (sc && sc->done) return;
   const int64_t ntiles = (n_rows + RPW - 1) / RPW;
   // XCD-contiguous tile ranges
   const XcdRange xr_ = xcd_range(blockIdx.x, gridDim.x, ntiles);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell(const SellView A, const doubl
                                                    double* __restrict__ partial,
                                                    const CgScalars* __restrict__ sc) {
   __shared__ double lds[4];
-  if (cg_stopped(sc)) return;
+  if (sc && sc->done) return;
   // the slice is wave-uniform, and what depends on it alone stays in scalar
   // registers
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_spmv_sell_beta(
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   const double rz_old = sc->rz;
-  const double rz = cg_beta_sum(sets, np, sc, red, blockIdx.x == 0);
+  const double rz = cg_beta_sum(sets, np, np, sc, red, blockIdx.x == 0);
   double dot = 0.0;
   if (s < A.n_slices)
     dot = sell_slice_product<P, true>(A, A.slices[s], l, GatherP{z, p_old, rz / rz_old}, y, p_new);
