@@ -168,11 +168,12 @@ __device__ __forceinline__ void cg_beta_store(CgScalars* sc, double rz, double z
 }
 
 // (r, z) from the pull's np <= kBetaSets partial sets (value k of set j at k stride + j),
-// by every workgroup of 256 in the same order; the first one also sums (z, z) and (r, r),
-// tests for the stop and stores the scalars.
+// by every workgroup of 256 in the same order.  The first one also leaves the sums of
+// (z, z) and (r, r) in red: one thread of it then tests for the stop and stores the
+// scalars (cg_beta_finish).
 constexpr int kBetaSets = 1024;
 __device__ __forceinline__ double cg_beta_sum(const double* __restrict__ sets, int64_t stride,
-                                              int np, CgScalars* sc, double (*red)[4], bool first) {
+                                              int np, double (*red)[4], bool first) {
   const int nk = first ? 3 : 1, w = threadIdx.x / kWave;
   for (int k = 0; k < nk; ++k) {
     double v[kBetaSets / 256];
@@ -185,11 +186,11 @@ __device__ __forceinline__ double cg_beta_sum(const double* __restrict__ sets, i
     if (threadIdx.x % kWave == kWave - 1) red[k][w] = t;
   }
   __syncthreads();
-  const double rz = ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
-  if (first && threadIdx.x == 0)
-    cg_beta_store(sc, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
-                  ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
-  return rz;
+  return ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3];
+}
+__device__ __forceinline__ void cg_beta_finish(CgScalars* sc, double rz, double (*red)[4]) {
+  cg_beta_store(sc, rz, ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3],
+                ((red[2][0] + red[2][1]) + red[2][2]) + red[2][3]);
 }
 
 __device__ __forceinline__ double load_relaxed(const double* p) {

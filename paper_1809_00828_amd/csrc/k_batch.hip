@@ -405,8 +405,8 @@ __global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs
     }
   };
   load(i0);   // the first round's unknowns, before the sums
-  const double beta = cg_beta_sum(partial + P.pull_item0, n_items, P.pull_items, S, red,
-                                  it.tile == 0) / rz_old;
+  const double rz = cg_beta_sum(partial + P.pull_item0, n_items, P.pull_items, red, it.tile == 0);
+  const double beta = rz / rz_old;
   for (int t = 0; t < P.wide_rounds; ++t) {
     const int64_t j0 = i0 + 2048 * (int64_t)t;
     if (t > 0) load(j0);
@@ -414,6 +414,7 @@ __global__ __launch_bounds__(256) void kb_beta_p(const BProb* __restrict__ probs
     for (int u = 0; u < 8; ++u)
       if (j0 + 256 * u < P.n_dofs) p[j0 + 256 * u] = fma(beta, pv[u], zv[u]);
   }
+  if (it.tile == 0 && threadIdx.x == 0) cg_beta_finish(S, rz, red);
 }
 
 // r = b, x = 0

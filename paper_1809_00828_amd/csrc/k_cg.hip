@@ -316,9 +316,10 @@ __global__ __launch_bounds__(256) void k_cg_beta_p(const double* __restrict__ pa
   const int64_t i0 = (int64_t)blockIdx.x * 512 + threadIdx.x, i1 = i0 + 256;
   const double z0 = i0 < n ? z[i0] : 0.0, p0 = i0 < n ? p_old[i0] : 0.0;
   const double z1 = i1 < n ? z[i1] : 0.0, p1 = i1 < n ? p_old[i1] : 0.0;
-  const double beta = cg_beta_sum(partial, np, np, sc, red, blockIdx.x == 0) / rz_old;
+  const double rz = cg_beta_sum(partial, np, np, red, blockIdx.x == 0), beta = rz / rz_old;
   if (i0 < n) p[i0] = fma(beta, p0, z0);
   if (i1 < n) p[i1] = fma(beta, p1, z1);
+  if (blockIdx.x == 0 && threadIdx.x == 0) cg_beta_finish(sc, rz, red);
 }
 
 // Flexible variant (FCG(1)) for the learned correction z = S r + gamma w:

@@ -267,7 +267,8 @@ __global__ __launch_bounds__(256) void k_spmv_sell_beta(
   const int l = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int64_t s = xcd_remap(blockIdx.x, gridDim.x) * 4 + w;
   const double rz_old = sc->rz;
-  const double rz = cg_beta_sum(sets, np, np, sc, red, blockIdx.x == 0);
+  const double rz = cg_beta_sum(sets, np, np, red, blockIdx.x == 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) cg_beta_finish(sc, rz, red);
   double dot = 0.0;
   if (s < A.n_slices)
     dot = sell_slice_product<P, true>(A, A.slices[s], l, GatherP{z, p_old, rz / rz_old}, y, p_new);
