@@ -791,8 +791,9 @@ def main():
     if info.get("lattice_columns"):
         # the same product with the 4-byte block columns read from memory
         k_spmv["bytes_per_launch_with_columns"] = spmv_b + info["nnzb"] * 4
-    schw_name = ("k_schwarz_sym_staged<double,%s>" % ("true" if m > 128 else "false")
-                 if m > 64 else "k_schwarz_small<double,sym>")
+    schw_name = ("k_schwarz_sym_staged<double,%s>" % ("6,96" if m <= 96 else "4,128" if m <= 128
+                                                      else "8,192")
+                 if m > 64 else "k_schwarz_small<double,%d>" % m)
     k_schw = {"bound": "hbm", "kernel": schw_name + " (block products)",
               "achieved": gbs_schw, "peak": HBM_PEAK_GBS, "unit": "GB/s",
               "frac": gbs_schw / HBM_PEAK_GBS,

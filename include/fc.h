@@ -208,9 +208,11 @@ fc_status fc_precond_info(fc_precond pc, int64_t* n_blocks,
  * the same in every process), and whether the block columns are computed
  * from the lattice (1: the matrix came from a problem description and its
  * columns were verified to be each row's lattice box, so the column array
- * is not read; 2: as 1, and the scalar rows are also held in the sliced
- * layout, slices of 64 rows of one lattice line with equal boxes, which
- * the whole-matrix product reads) or read (0). */
+ * is not read; 2: as 1, and the scalar rows are also held in slices of 64
+ * rows with boxes of equal shape, gathered across lattice lines.  The FP64
+ * product reads the slices, except that of few long rows: below nine slices
+ * an entry of the mean row, of 48 entries or more, it reads the rows in
+ * their lanes) or read (0). */
 fc_status fc_spmv_info(fc_problem pb, int32_t* group, int32_t* lattice);
 /* FP32 copy (FC_STORE_F32): the diagonally scaled inverse D^1/2 P_B D^1/2
  * (D = diag(A) on the block) rounded to FP32, kept for the blocks where a
@@ -270,6 +272,8 @@ fc_status fc_apply_M(fc_precond pc, const double* r_dev, double* z_dev,
  *                beta = -(z_new, A p)/(p, A p)); always the residual stop
  *                ||r_i|| / ||b||
  *   check_every  iterations between host checks of the device stop flag
+ *                (problems small enough for one workgroup: up to four times
+ *                as many, at most 1,024, since the launch tests it itself)
  *   history_dev  optional device buffer of maxit+1 doubles receiving the
  *                relative stop criterion of every iteration, or NULL
  *   timing       k > 0: launch the steps directly (no captured graph) and
@@ -337,8 +341,8 @@ fc_status fc_pcg_solve(fc_problem pb, fc_precond pc, const double* b_dev,
  * call on one GPU shares that GPU's scratch: calls that overlap on one GPU
  * (two host threads, two streams) race and must be serialised by the
  * caller.  The current device must be the problem's (FC_E_ARG otherwise).
- * Synchronises the stream after every check_every steps (it cannot be
- * captured into a graph).  Returns as fc_pcg_solve. */
+ * Synchronises the stream between the host checks of the stop flag, as
+ * check_every spaces them (it cannot be captured into a graph).  Returns as fc_pcg_solve. */
 fc_status fc_pcg_solve_noalloc(fc_problem pb, fc_precond pc, const double* b_dev,
                                double* x_dev, const fc_solve_opts* opts,
                                fc_solve_info* info, void* stream);

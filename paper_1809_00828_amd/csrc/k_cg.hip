@@ -5,7 +5,9 @@
 //   q = A p;  alpha = (r,z)/(p,q);  x += alpha p;  r -= alpha q;
 //   z = S r;  beta = (r,z)_new/(r,z);  p = z + beta p.
 // One step is four or five kernels up to 1,024 pull workgroups (0.5M
-// unknowns) and six above, all reading their scalars from device memory:
+// unknowns) and six above, all reading their scalars from device memory; three
+// where the p update joins the next step's sliced product (routes.h), and none of
+// their own for problems that one workgroup steps through (k_tiny.hip):
 //   1. SpMV q = A p (k_spmv.hip), with the (p, q) partials of its workgroups
 //      where they are few
 //   2. else (p, q) by workgroup partials in a separate pass over p and q.
@@ -19,7 +21,7 @@
 //      and per-workgroup (r,z), (z,z), (r,r) partials
 //   5. p = z + beta p, every workgroup summing the pull's partials to beta, the
 //      first one also testing for the stop (above 1,024 partials one
-//      workgroup's own launch before it)
+//      workgroup's own launch before it; joined: within 1. of the next step)
 // A launch costs 2.5 to 5 us at any size, and one-workgroup kernels for alpha
 // and beta were two of eight.
 // The reductions stay atomic-free: a same-address atomic per workgroup

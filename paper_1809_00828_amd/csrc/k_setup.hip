@@ -1077,8 +1077,9 @@ bool sweep_reads_lattice(const fc_precond_s& pc) {
   return pc.pb->cells.dim > 0 && pc.pb->A.lat.dim > 0 && !pc.bnodes;
 }
 
-// One instance per block size that the problems at p <= 4 have, and one for
-// every other size up to 16, 32 and 64 (padded with rows of the identity).
+// One instance for each of 9, 24, 25 and 27, and one for every other size up to 8,
+// 16, 32 and 64 (padded with rows of the identity: plane elasticity's 18 and 50
+// among them).
 template <bool kLat>
 static void sweep_small(const BlockSrc& S, const fc_precond_s& pc, int64_t b0, int64_t count,
                         int32_t* need_eig, hipStream_t s) {

@@ -18,15 +18,16 @@
 //
 // Tiles of 256/G rows are dealt out so that the workgroups resident on one
 // XCD (hardware ids congruent mod 8) walk one contiguous range of rows and
-// share that XCD's L2 for x.  The PCG variant leaves one partial (x, y)
-// per workgroup; a one-workgroup kernel of the solver sums them in a fixed
-// order (no atomics).
+// share that XCD's L2 for x.  The PCG variant leaves one partial (x, y) per
+// workgroup, up to 1,024 of them; the workgroups of the block products sum them
+// in a fixed order (no atomics).
 //
 // Matrices assembled from a problem description have lattice rows: the
 // columns and the start of each row follow from the row's lattice indices
 // and are computed, not read.  Scalar ones (degree p <= 4) also keep a
 // sliced copy, 64 rows with boxes of equal shape per slice (spmv_dev.h), for
-// the whole-matrix product (k_spmv_sell below).
+// the whole-matrix product (k_spmv_sell below) unless the rows are few and
+// long (routes.h).
 #include <algorithm>
 #include <cstdlib>
 #include <vector>
