@@ -34,6 +34,7 @@
 #include "dev_common.h"
 #include "k_schwarz.h"
 #include "k_spmv.h"
+#include "routes.h"
 #include "schwarz_dev.h"
 #include "spmv_dev.h"
 
@@ -537,7 +538,10 @@ static hipError_t launch_schwarz_class(fc_batch_s& bt, const SchwarzClass& c, co
   const int np = (int)bt.pull_items.size();
   dim3 g((unsigned)n), b(c.m > 64 ? 64 * ((c.m + 63) / 64) : 256);
   if (c.m > 64) {
-    if (c.m <= 128)
+    if (c.m <= 128 && staged_rows(true, 128, n) == 16)
+      hipLaunchKernelGGL((kb_schwarz_staged<16, 128>), g, b, 0, s, bt.d_probs, items, np, bt.sc,
+                         bt.r, q, bt.partial);
+    else if (c.m <= 128)
       hipLaunchKernelGGL((kb_schwarz_staged<4, 128>), g, b, 0, s, bt.d_probs, items, np, bt.sc,
                          bt.r, q, bt.partial);
     else

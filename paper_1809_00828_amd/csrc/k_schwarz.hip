@@ -36,6 +36,7 @@
 
 #include "dev_common.h"
 #include "k_schwarz.h"
+#include "routes.h"
 #include "schwarz_dev.h"
 
 namespace fc {
@@ -44,8 +45,7 @@ namespace fc {
 // blocks of up to kMaxM.  Bound by HBM: 0.21 GB of blocks of 81 in 41 us (5.2 TB/s),
 // of 125 (20^3 cells, p = 4) 95 us with the pull, of 192 4.9 GB in 0.81 ms (6.2
 // TB/s).  With 16 KB of LDS a workgroup and every thread's own entry of
-// each row for m <= 128: 61 and 113 us; FP32 blocks of 192 in chunks of 16 rows 38
-// instead of 33 us.
+// each row for m <= 128: 61 and 113 us.  Rows a chunk: staged_rows (routes.h).
 template <typename T, int kRows, int kMaxM>
 __global__ __launch_bounds__(256) void k_schwarz_sym_staged(
     const T* __restrict__ P, int64_t block_stride, const int32_t* __restrict__ elem_nodes,
@@ -350,10 +350,6 @@ hipError_t launch_inv_sqrt_diag(const fc_problem_s& pb, double* isd, hipStream_t
   return hipGetLastError();
 }
 
-// Chunks of the staged product by block size (us a product, FP64): 20^3 cells p = 2,
-// m = 81: 43 / 41 / 43.5 in chunks of 4 / 6 / 8 rows; 16^3 cells p = 4, m = 125: 51 /
-// 53 / 53.5; m = 192: 104 in chunks of 4, 6 and 8.  FP32, m = 192: 33.3 / 34.4 / 36.3
-// in chunks of 4 / 8 / 12.
 template <typename T>
 static void launch_staged(const fc_precond_s& pc, const T* Q, int64_t n_launch,
                           const double* r, const double* q, const double* isd,
@@ -364,13 +360,27 @@ static void launch_staged(const fc_precond_s& pc, const T* Q, int64_t n_launch,
   hipLaunchKernelGGL((k_schwarz_sym_staged<T, ROWS, MAXM>), g, b, 0, s, Q,                   \
                      sym_block_stride(pc.m), block_nodes(pc), pc.block_elem, pc.nn, pc.bdim, \
                      pc.m, r, q, isd, sc, ai, pc.y, pc.n_blocks, list, skip)
-  constexpr bool k64 = sizeof(T) == 8;
-  if (pc.m <= 96)
-    FC_STAGED((k64 ? 6 : 8), 96);
-  else if (pc.m <= 128)
-    FC_STAGED(4, 128);
-  else
-    FC_STAGED((k64 ? 8 : 4), 192);
+#define FC_STAGED_ROWS(ROWS, MAXM) \
+  case ROWS: FC_STAGED(ROWS, MAXM); break;
+  const int rows = staged_rows(sizeof(T) == 8, pc.m, n_launch);
+  if constexpr (sizeof(T) == 8) {
+    if (pc.m <= 96) {
+      switch (rows) { FC_STAGED_ROWS(6, 96) FC_STAGED_ROWS(24, 96) }
+    } else if (pc.m <= 128) {
+      switch (rows) { FC_STAGED_ROWS(4, 128) FC_STAGED_ROWS(16, 128) }
+    } else {
+      FC_STAGED(8, 192);
+    }
+  } else {
+    if (pc.m <= 96) {
+      switch (rows) { FC_STAGED_ROWS(8, 96) FC_STAGED_ROWS(24, 96) }
+    } else if (pc.m <= 128) {
+      switch (rows) { FC_STAGED_ROWS(8, 128) FC_STAGED_ROWS(24, 128) }
+    } else {
+      switch (rows) { FC_STAGED_ROWS(4, 192) FC_STAGED_ROWS(12, 192) FC_STAGED_ROWS(24, 192) }
+    }
+  }
+#undef FC_STAGED_ROWS
 #undef FC_STAGED
 }
 

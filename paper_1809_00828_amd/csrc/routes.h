@@ -38,6 +38,22 @@ inline bool rows_beat_join(int64_t nnz, int64_t n_rows, int64_t n_slices) {
          (double)n_slices * (double)n_rows >= 2.2 * (double)nnz;
 }
 
+// Stored rows a chunk of the block products with 64 < m <= 192, n blocks in a launch.
+// A chunk costs two barriers, and the LDS it takes a workgroup less on the compute unit:
+// many rows where the launch does not fill the chip, few where it does.  us a product and
+// pull, FP64 (m / blocks: rows us): 81/216 24 11.9, 6 13.6; 81/1000 24 13.7, 6 14.4;
+// 81/4096 24 37.5, 6 24.6; 98/16 16 13.1, 4 15.7; 125/512 16 16.3, 4 21.3; 125/1331 16 23.1,
+// 4 26.3; 125/4096 16 52.5, 4 48.5; 162/256 8 19.6, 24 18.0; 162/4096 8 78.0, 24 96.5; 192
+// 8 as good as any from 64 to 4,096.  FP32, the product alone: 81/216 24 12.3, 8 14.2;
+// 81/2744 24 24.4, 8 18.8; 125/125 24 14.8, 8 17.2; 125/4096 24 45.2, 8 31.3; 162/256
+// 24 18.5, 12 20.0, 4 27.1; 162/4096 24 71.9, 12 52.0, 4 62.2; 192/216 24 19.0, 4 20.6;
+// 192/2197 24 45.9, 12 38.1, 4 34.6.
+inline int staged_rows(bool f64, int m, int64_t n) {
+  if (f64) return m <= 96 ? (n <= 1024 ? 24 : 6) : m <= 128 ? (n <= 1024 ? 16 : 4) : 8;
+  if (m <= 128) return n <= 1024 ? 24 : 8;
+  return n <= 640 ? 24 : m <= 176 ? 12 : 4;
+}
+
 // CG steps in one workgroup (k_tiny.hip).
 // Bytes of matrix and local inverses a step reads, at most.  Measured, in us a step
 // against separate launches: 2-D p = 3, 0.29 MB 7.3 / 15.3, 0.74 MB 13.1 / 15.3;

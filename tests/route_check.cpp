@@ -89,7 +89,19 @@ static void tested_sizes() {
   }
 }
 
+// chunks of the block products: whole 16-byte pieces, and a tile of at most 20 KB
+static void staged_chunks() {
+  for (int f64 = 0; f64 < 2; ++f64)
+    for (int m = 65; m <= 192; ++m)
+      for (int64_t n : {1, 640, 641, 1024, 1025, 100000}) {
+        const int r = staged_rows(f64, m, n), most = m <= 96 ? 96 : m <= 128 ? 128 : 192;
+        CHECK(r >= 4 && r % (f64 ? 2 : 4) == 0 && r * most * (f64 ? 8 : 4) <= 20 * 1024);
+        CHECK(staged_rows(f64, m, 1) >= r);
+      }
+}
+
 int main() {
+  staged_chunks();
   tested_sizes();
   eigen_chunks();
   step_layouts();
