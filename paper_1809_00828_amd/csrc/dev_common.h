@@ -18,6 +18,14 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// A pointer into device memory that was itself loaded from memory.  The compiler knows
+// that of kernel arguments only and takes flat loads otherwise, whose waits are those of
+// LDS as well.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
 // Map the hardware workgroup id to a logical tile id so that the
 // workgroups that land on one XCD (ids congruent mod 8) process one
 // contiguous range of tiles and share that XCD's L2.  A bijection on

@@ -218,10 +218,11 @@ __device__ __forceinline__ void batch_small(const BProb& P, const WorkItem it, i
                                             const double* partial, double (*rB)[64],
                                             double* red) {
   schwarz_small_tile<double, kM, kLat>(
-      P.Q, sym_block_stride_dev(P.m), P.m, rvec + P.voff, qvec ? qvec + P.voff : nullptr, nullptr,
-      S, qvec ? batch_alpha(P, partial, n_items) : AlphaIn{}, it.tile == 0, P.y, P.n_blocks,
-      P.lat, it.tile, rB, red, [&](int64_t blk, int i) {
-        return block_dof(P.elem_nodes, P.block_elem[blk], P.nn, P.bdim, i);
+      as_global(P.Q), sym_block_stride_dev(P.m), P.m, rvec + P.voff,
+      qvec ? qvec + P.voff : nullptr, nullptr, S,
+      qvec ? batch_alpha(P, partial, n_items) : AlphaIn{}, it.tile == 0, as_global(P.y),
+      P.n_blocks, P.lat, it.tile, rB, red, [&](int64_t blk, int i) {
+        return block_dof(as_global(P.elem_nodes), as_global(P.block_elem)[blk], P.nn, P.bdim, i);
       });
 }
 
@@ -261,9 +262,12 @@ __global__ __launch_bounds__(256) void kb_schwarz_staged(
   const AlphaIn ai = qvec ? batch_alpha(P, partial, n_items) : AlphaIn{};
   const int64_t blk = it.tile;
   schwarz_staged_block<double, kRows>(
-      P.Q + blk * sym_block_stride_dev(P.m), P.y + blk * P.m, P.m, rvec + P.voff,
+      as_global(P.Q) + blk * sym_block_stride_dev(P.m), as_global(P.y) + blk * P.m, P.m,
+      rvec + P.voff,
       qvec ? qvec + P.voff : nullptr, nullptr, S, ai, it.tile == 0, rB, tile, red,
-      [&](int i) { return block_dof(P.elem_nodes, P.block_elem[blk], P.nn, P.bdim, i); });
+      [&](int i) {
+        return block_dof(as_global(P.elem_nodes), as_global(P.block_elem)[blk], P.nn, P.bdim, i);
+      });
 }
 
 // Pull + x, r updates + partial dots (mode 1), or the start (mode 0: z = S r,
