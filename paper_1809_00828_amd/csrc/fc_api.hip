@@ -159,8 +159,10 @@ static fc_status precond_map(fc_precond_s& pc, hipStream_t s) {
   const int64_t n = pc.pb->n_nodes + 1;
   int32_t *work = nullptr, *sums = nullptr, *ptr = nullptr, *idx = nullptr;
   Scratch tmp(s);
-  FC_TRY(tmp.get(0, &work, (size_t)n));
-  FC_TRY(tmp.get(1, &sums, (size_t)map_scan_blocks(n)));
+  if (pc.n_blocks > 0) {
+    FC_TRY(tmp.get(0, &work, (size_t)n));
+    FC_TRY(tmp.get(1, &sums, (size_t)map_scan_blocks(n)));
+  }
   FC_TRY(tmp.get(2, &ptr, (size_t)n));
   FC_TRY(tmp.get(3, &idx, (size_t)std::max<int64_t>(1, pc.n_blocks * pc.nn)));
   FC_HIP(launch_build_map(pc, pc.pb->n_nodes, ptr, idx, work, sums, s));

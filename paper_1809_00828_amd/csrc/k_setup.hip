@@ -998,8 +998,13 @@ hipError_t launch_build_map(const fc_precond_s& pc, int64_t n_nodes, int32_t* pt
   const int64_t n = n_nodes + 1, total = pc.n_blocks * pc.nn;
   const int nruns = (int)map_scan_blocks(n);
   const dim3 b(256), runs((unsigned)nruns);
-  const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 8192)));
-  hipLaunchKernelGGL(k_zero_i32, dim3(1024), b, 0, s, work, n);
+  const dim3 g((unsigned)std::min<int64_t>((total + 255) / 256, 8192));
+  const dim3 gz((unsigned)std::min<int64_t>((n + 255) / 256, 1024));
+  if (total == 0) {   // no block: every node's entries are empty
+    hipLaunchKernelGGL(k_zero_i32, gz, b, 0, s, ptr, n);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_zero_i32, gz, b, 0, s, work, n);
   hipLaunchKernelGGL(k_map_count, g, b, 0, s, block_nodes(pc), pc.block_elem, pc.nn, total, work);
   hipLaunchKernelGGL(k_map_scan<0>, runs, b, 0, s, work, n, sums, nruns, ptr);
   hipLaunchKernelGGL(k_map_scan<1>, dim3(1), b, 0, s, work, n, sums, nruns, ptr);
