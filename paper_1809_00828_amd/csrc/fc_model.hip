@@ -131,11 +131,9 @@ fc_status fc_model_loss_grad(fc_model m, int32_t batch, int32_t grid, const floa
   FC_HIP(net_backward(m->net, m->ws, x_dev, m->ws.gy(), batch, s));
   const double l = sum_partials_host(m->ws.partial, s) / (double)n;
   if (loss) *loss = l;
-  if (grad_host) {
-    FC_HIP(hipMemcpyAsync(grad_host, m->net.g, m->net.nparam * sizeof(float),
-                          hipMemcpyDeviceToHost, s));
-    FC_HIP(hipStreamSynchronize(s));
-  }
+  if (grad_host)   // done when it returns
+    FC_HIP(hipMemcpyWithStream(grad_host, m->net.g, m->net.nparam * sizeof(float),
+                               hipMemcpyDeviceToHost, s));
   return FC_OK;
 }
 
